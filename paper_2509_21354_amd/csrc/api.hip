@@ -400,7 +400,7 @@ static int lstm_gate_common(const kvev_shape *sh, const void *Kbar, const void *
     a.W_ih = w->W_ih; a.W_hh = w->W_hh; a.b_ih = w->b_ih; a.b_hh = w->b_hh; a.w_s = w->w_s; a.b_s = w->b_s;
     a.h = h; a.c = c; a.util = util; a.gate = gate;
     a.L = sh->L; a.BH = sh->B * kv_heads(sh); a.d = sh->d; a.N_cap = sh->N_cap; a.d_g = sh->d_g;
-    a.c0 = chunk_begin; a.c1 = chunk_end;
+    a.c0 = chunk_begin; a.c1 = chunk_end; a.compute_units = device_compute_units();
     hipStream_t st = static_cast<hipStream_t>(stream);
     hipError_t e;
     if (lstm_takes_mfma(sh)) {

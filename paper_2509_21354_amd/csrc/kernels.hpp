@@ -61,6 +61,7 @@ struct LstmArgs {
     int32_t *status;      // workspace: word that a launch sets to 1 when a bounded wait expired (never cleared by the library)
     int prepared;         // 1: the packed weights are already in place (kvev_lstm_prepare), 0: this call packs them first
     int L, BH, d, N_cap, d_g;
+    int compute_units;    // of the device the launch goes to
     int c0, c1;
     int tb;               // steps per workspace block
     int fused;            // 1: the single-kernel form (d_g = 256, 32 sequences per workgroup, no projections in scratch)

@@ -1,89 +1,308 @@
 // Recurrent gate, Eq. 3 of the paper: a standard LSTM cell (gate rows i,f,g,o)
 // over the chunk summaries [Kbar_t ; Vbar_t] with a scalar utility head on h_t.
-// Generic fp32-arithmetic kernel for any storage dtype and any d_g: one
-// workgroup walks one sequence through its steps; the input projection is
-// fused, so no workspace is used.  The bf16 fast path lives in lstm_mfma.hip.
+// fp32-arithmetic kernel for fp32 storage and for gate widths that the
+// matrix-core kernels do not take (lstm_mfma.hip has the bf16 fast path).  No
+// workspace is used: one workgroup walks one sequence through its steps.
+//
+// What bounds it is the chain of dependent steps, so everything that does not
+// depend on h_{t-1} is taken out of the step, and the step itself is spread over
+// a whole workgroup of 16 waves:
+//   * the steps are cut into blocks of up to 16.  The input projections
+//     W_ih x_t + b_ih + b_hh of a block are one 4 d_g x 2d x 16 product on the fp32
+//     matrix instruction (v_mfma_f32_16x16x4_f32: fp32 operands, products and
+//     sums), kept in LDS;
+//   * a group of 16 lanes owns a hidden unit (or several): lane c holds elements
+//     4 c .. 4 c + 3 (mod 64) of that unit's four rows of W_hh and of h, and the
+//     four partial dot products are folded over the 16 lanes by a transposing
+//     reduction that leaves gate q's sum in the lanes with lane % 4 == q, where
+//     its nonlinearity is evaluated; c_t and h_t follow in the same lanes, so a
+//     step has one barrier;
+//   * up to d_g = 128 the four rows stay in registers for the whole call (RES > 0);
+//     wider gates read them from L2 every step, 16 bytes per lane;
+//   * the utility head runs after each block over the block's 16 states.
+// Measured (fp32, d_g = 64, d = 64, 4 sequences x 64 steps): 1346 us with one
+// row of W_ih and W_hh at a time per lane group, dependent loads from L2 in every
+// step; 64 us now (1 us per step, of which the two nonlinearities in a row, expf
+// and tanhf, are about half).  d_g = 256, d = 128, 32 sequences x 64 steps: 11.4 ms
+// -> 0.69 ms, bound by the 1 MiB of W_hh that a workgroup streams per step.
 #include "common.hpp"
 #include "kernels.hpp"
 
 namespace kvev {
 
-template <typename T, int D>
-__global__ __launch_bounds__(256) void lstm_generic_kernel(LstmArgs a)
-{
-    extern __shared__ float smem[];
-    const int dg = a.d_g, G = 4 * dg;
-    float *x = smem;            // [2D]
-    float *h = x + 2 * D;       // [d_g]
-    float *c = h + dg;          // [d_g]
-    float *pre = c + dg;        // [4 d_g]
+constexpr int kGenThreads = 1024, kGenCols = 16;      // (sequence, step) pairs of a block: one column tile of the projection
+constexpr size_t kGenLdsMax = 160 * 1024;
 
-    const int tid = threadIdx.x, grp = tid >> 4, cl = tid & 15;
-    const int s = blockIdx.x, l = s / a.BH;
+// LDS of a block of tb steps of mb sequences: inputs, projections, states (step 0: the state before the block), cell state
+constexpr int gen_hp(int dg) { return (dg + 63) / 64 * 64; }
+constexpr size_t gen_lds(int d, int dg, int mb, int tb)
+{
+    return sizeof(float) * mb * ((size_t)tb * (2 * d + 4) + (size_t)tb * 4 * dg + (size_t)(tb + 1) * gen_hp(dg) + dg);
+}
+// most steps of a block that LDS holds (0: not even one)
+static int gen_tb(int d, int dg, int mb)
+{
+    int tb = kGenCols / mb;
+    while (tb > 0 && gen_lds(d, dg, mb, tb) > kGenLdsMax) --tb;
+    return tb;
+}
+
+template <int CTRL> __device__ __forceinline__ float dpp_move(float v)
+{
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xf, 0xf, true));
+}
+constexpr int kQuadXor1 = 0xB1, kQuadXor2 = 0x4E, kRowShl4 = 0x104, kRowShr4 = 0x114, kRowRor4 = 0x124, kRowRor8 = 0x128;
+
+// The sums over 16 lanes of four values at once: lane q (mod 4) receives the sum of v[gate_of_lane(q)].
+// (every exchange halves the values a lane still carries: 4 -> 2 -> 1, then the four quads are added)
+__device__ __forceinline__ int gate_of_lane(int lane) { return ((lane & 1) << 1) | ((lane >> 1) & 1); }
+__device__ __forceinline__ float fold4(const float (&v)[4], int lane)
+{
+    const bool b0 = lane & 1, b1 = lane & 2;
+    const float r0 = (b0 ? v[2] : v[0]) + dpp_move<kQuadXor1>(b0 ? v[0] : v[2]);
+    const float r1 = (b0 ? v[3] : v[1]) + dpp_move<kQuadXor1>(b0 ? v[1] : v[3]);
+    float q = (b1 ? r1 : r0) + dpp_move<kQuadXor2>(b1 ? r0 : r1);
+    q += dpp_move<kRowRor4>(q);
+    q += dpp_move<kRowRor8>(q);
+    return q;
+}
+
+// The same for 16 values, v[m][gate]: lane 4 m + q receives the sum over the 16 lanes of v[m][gate_of_lane(q)].
+__device__ __forceinline__ float fold16(const float (&v)[4][4], int lane)
+{
+    const bool b0 = lane & 1, b1 = lane & 2, b2 = lane & 4, b3 = lane & 8;
+    float q[4];
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+        const float r0 = (b0 ? v[m][2] : v[m][0]) + dpp_move<kQuadXor1>(b0 ? v[m][0] : v[m][2]);
+        const float r1 = (b0 ? v[m][3] : v[m][1]) + dpp_move<kQuadXor1>(b0 ? v[m][1] : v[m][3]);
+        q[m] = (b1 ? r1 : r0) + dpp_move<kQuadXor2>(b1 ? r0 : r1);
+    }
+    const float p0 = (b3 ? q[2] : q[0]) + dpp_move<kRowRor8>(b3 ? q[0] : q[2]);
+    const float p1 = (b3 ? q[3] : q[1]) + dpp_move<kRowRor8>(b3 ? q[1] : q[3]);
+    const float away = b2 ? p0 : p1;        // what the lane four further on (b2: four back) is short of
+    const float fwd = dpp_move<kRowShl4>(away), back = dpp_move<kRowShr4>(away);
+    return (b2 ? p1 : p0) + (b2 ? back : fwd);
+}
+
+// four consecutive elements of a weight row from element k on, zeros at and past n.  VEC: the row allows one load.
+template <typename T, bool VEC> __device__ __forceinline__ void load4(const T *row, int k, int n, float (&o)[4])
+{
+    if (VEC) {
+        if (k < n) VecLoad<T, 4>::run(row + k, o);
+        else o[0] = o[1] = o[2] = o[3] = 0.f;
+    } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[e] = k + e < n ? Storage<T>::load(row + k + e) : 0.f;
+    }
+}
+
+// MB: sequences of one layer per workgroup.  RES: hidden units per lane group whose rows of W_hh stay in registers, KC
+// chunks of 64 elements each (0: the rows are streamed).  VEC: d_g is a multiple of 4, so every row of W_hh starts where
+// a 4-element load may.
+template <typename T, int D, int MB, int RES, int KC, bool VEC>
+__global__ __launch_bounds__(kGenThreads, RES == 1 && MB == 1 ? 8 : 4) void lstm_generic_kernel(LstmArgs a, int tb)
+{
+    constexpr int XP = 2 * D + 4;       // padded input row: the columns of a block start in different banks
+    static_assert(MB == 1 || MB == 4, "what cell() folds");
+    extern __shared__ __align__(16) float smem[];
+    const int dg = a.d_g, G = 4 * dg, HP = gen_hp(dg);
+    float *x = smem;                                 // [MB * tb][XP]
+    float *pre = x + (size_t)MB * tb * XP;           // [MB * tb][4 d_g]
+    float *hs = pre + (size_t)MB * tb * G;           // [MB][tb + 1][HP]   zeros from d_g on
+    float *cs = hs + (size_t)MB * (tb + 1) * HP;     // [MB][d_g]
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, cl = tid & 15, grp = tid >> 4;
+    const int gpl = (a.BH + MB - 1) / MB;
+    const int l = blockIdx.x / gpl, m0 = (blockIdx.x % gpl) * MB;
+    const int live = min(MB, a.BH - m0);             // (a group never straddles layers; the rest repeat the last sequence)
+    auto seq = [&](int m) __attribute__((always_inline)) { return (size_t)l * a.BH + m0 + min(m, live - 1); };
     const T *W_ih = static_cast<const T *>(a.W_ih) + (size_t)l * G * 2 * D;
     const T *W_hh = static_cast<const T *>(a.W_hh) + (size_t)l * G * dg;
     const T *b_ih = static_cast<const T *>(a.b_ih) + (size_t)l * G;
     const T *b_hh = static_cast<const T *>(a.b_hh) + (size_t)l * G;
     const T *w_s = static_cast<const T *>(a.w_s) + (size_t)l * dg;
     const float b_s = Storage<T>::load(static_cast<const T *>(a.b_s) + l);
+    const int gate = gate_of_lane(cl);
 
     const bool fresh = a.c0 == 0;        // the recurrence starts from a zero state at chunk 0, whatever the buffers hold
-    for (int j = tid; j < dg; j += 256) {
-        h[j] = fresh ? 0.f : a.h[(size_t)s * dg + j];
-        c[j] = fresh ? 0.f : a.c[(size_t)s * dg + j];
+    for (int j = tid; j < MB * (tb + 1) * HP; j += kGenThreads) {
+        const int m = j / ((tb + 1) * HP), e = j % ((tb + 1) * HP);
+        hs[j] = e < dg && !fresh ? a.h[seq(m) * dg + e] : 0.f;
     }
-    for (int t = a.c0; t < a.c1; ++t) {
-        const size_t row = ((size_t)s * a.N_cap + t) * D;
-        for (int e = tid; e < 2 * D; e += 256)
-            x[e] = Storage<T>::load((e < D ? static_cast<const T *>(a.Kbar) : static_cast<const T *>(a.Vbar)) + row + (e % D));
-        __syncthreads();
-        for (int r = grp; r < G; r += 16) {
-            float acc = 0.f;
-            const T *wi = W_ih + (size_t)r * 2 * D;
-            for (int e = cl; e < 2 * D; e += 16) acc = fmaf(Storage<T>::load(wi + e), x[e], acc);
-            const T *wh = W_hh + (size_t)r * dg;
-            for (int j = cl; j < dg; j += 16) acc = fmaf(Storage<T>::load(wh + j), h[j], acc);
-            acc = group16_sum(acc);
-            if (cl == 0) pre[r] = acc + Storage<T>::load(b_ih + r) + Storage<T>::load(b_hh + r);
+    for (int j = tid; j < MB * dg; j += kGenThreads) cs[j] = fresh ? 0.f : a.c[seq(j / dg) * dg + j % dg];
+
+    float w[RES > 0 ? RES : 1][4][KC][4];
+    if constexpr (RES > 0) {
+#pragma unroll
+        for (int i = 0; i < RES; ++i) {
+            const int u = min(grp + kGenThreads / 16 * i, dg - 1);
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+#pragma unroll
+                for (int c = 0; c < KC; ++c) load4<T, VEC>(W_hh + (size_t)(q * dg + u) * dg, 64 * c + 4 * cl, dg, w[i][q][c]);
+        }
+    }
+
+    for (int t0 = a.c0; t0 < a.c1; t0 += tb) {
+        const int nb = min(tb, a.c1 - t0), cols = MB * nb;      // column m * nb + j: step t0 + j of sequence m
+        // ---- the block's inputs ----
+        for (int p = tid; p < cols * (2 * D / 4); p += kGenThreads) {
+            const int col = p / (2 * D / 4), e = (p % (2 * D / 4)) * 4;
+            const size_t row = (seq(col / nb) * a.N_cap + t0 + col % nb) * D;
+            float v[4];
+            VecLoad<T, 4>::run((e < D ? static_cast<const T *>(a.Kbar) + e : static_cast<const T *>(a.Vbar) + (e - D)) + row, v);
+            *reinterpret_cast<float4 *>(x + (size_t)col * XP + e) = make_float4(v[0], v[1], v[2], v[3]);
         }
         __syncthreads();
-        for (int j = tid; j < dg; j += 256) {
-            const float ig = 1.f / (1.f + expf(-pre[j]));
-            const float fg = 1.f / (1.f + expf(-pre[dg + j]));
-            const float gg = tanhf(pre[2 * dg + j]);
-            const float og = 1.f / (1.f + expf(-pre[3 * dg + j]));
-            const float cn = fg * c[j] + ig * gg;
-            c[j] = cn;
-            h[j] = og * tanhf(cn);
+        // ---- their projections: 16 gate rows x 16 columns per wave and turn.  A contraction index may be permuted as
+        // long as both operands agree: lane group g takes elements 16 c + 4 g .. + 3 of chunk c, one per instruction ----
+        for (int r0 = wave * 16; r0 < G; r0 += 16 * (kGenThreads / 64)) {
+            const int g = lane >> 4;
+            const T *wr = W_ih + (size_t)min(r0 + cl, G - 1) * 2 * D + 4 * g;
+            const float *xr = x + (size_t)min(cl, cols - 1) * XP + 4 * g;
+            f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
+            for (int c = 0; c < 2 * D / 16; ++c) {
+                float wv[4];
+                VecLoad<T, 4>::run(wr + 16 * c, wv);
+                const float4 xv = *reinterpret_cast<const float4 *>(xr + 16 * c);
+                acc = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[0], xv.x, acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[1], xv.y, acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[2], xv.z, acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[3], xv.w, acc, 0, 0, 0);
+            }
+            if (cl < cols) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int row = r0 + 4 * g + r;
+                    if (row < G) pre[(size_t)cl * G + row] = acc[r] + Storage<T>::load(b_ih + row) + Storage<T>::load(b_hh + row);
+                }
+            }
         }
         __syncthreads();
-        if (tid < kWave) {
+        // ---- the steps ----
+        // unit u's partial sums are in `part`: the cell update and the new h.  With one sequence the four quads of a lane
+        // group do the same work, with four each quad does that of a sequence of its own.
+        const int mq = MB == 4 ? cl >> 2 : 0;
+        auto cell = [&](int tt, int u, const float (&part)[MB][4]) __attribute__((always_inline)) {
+            float z;
+            if constexpr (MB == 4) z = fold16(part, cl);
+            else z = fold4(part[0], cl);
+            z += pre[(size_t)(mq * nb + tt) * G + gate * dg + u];
+            const float act = gate == 2 ? tanhf(z) : 1.f / (1.f + expf(-z));
+            // lanes 0, 2, 1, 3 of a quad hold i, f, g, o
+            const float ig = dpp_move<0x00>(act), fg = dpp_move<0xAA>(act), gg = dpp_move<0x55>(act), og = dpp_move<0xFF>(act);
+            const float cn = fg * cs[mq * dg + u] + ig * gg;
+            const float hn = og * tanhf(cn);
+            if (MB == 4 ? (cl & 3) == 0 : cl == 0) {     // (lanes with the same values, and all have read the old cell state)
+                cs[mq * dg + u] = cn;
+                hs[(size_t)(mq * (tb + 1) + tt + 1) * HP + u] = hn;
+            }
+        };
+        for (int tt = 0; tt < nb; ++tt) {
+            const float *hp = hs + (size_t)tt * HP + 4 * cl;        // + m * (tb + 1) * HP + 64 * chunk
+            if constexpr (RES > 0) {
+#pragma unroll
+                for (int i = 0; i < RES; ++i) {
+                    const int u = grp + kGenThreads / 16 * i;
+                    if (u < dg) {
+                        float part[MB][4];
+#pragma unroll
+                        for (int m = 0; m < MB; ++m) {
+                            part[m][0] = part[m][1] = part[m][2] = part[m][3] = 0.f;
+#pragma unroll
+                            for (int c = 0; c < KC; ++c) {
+                                float hv[4];
+                                VecLoad<float, 4>::run(hp + (size_t)m * (tb + 1) * HP + 64 * c, hv);
+#pragma unroll
+                                for (int q = 0; q < 4; ++q)
+#pragma unroll
+                                    for (int e = 0; e < 4; ++e) part[m][q] = fmaf(w[i][q][c][e], hv[e], part[m][q]);
+                            }
+                        }
+                        cell(tt, u, part);
+                    }
+                }
+            } else {
+                for (int u = grp; u < dg; u += kGenThreads / 16) {
+                    const T *wr = W_hh + (size_t)u * dg;
+                    float part[MB][4];
+#pragma unroll
+                    for (int m = 0; m < MB; ++m) part[m][0] = part[m][1] = part[m][2] = part[m][3] = 0.f;
+#pragma unroll MB == 1 ? 4 : 2
+                    for (int k = 0; k < dg; k += 64) {
+                        float wv[4][4];
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) load4<T, VEC>(wr + (size_t)q * dg * dg, k + 4 * cl, dg, wv[q]);
+#pragma unroll
+                        for (int m = 0; m < MB; ++m) {
+                            float hv[4];
+                            VecLoad<float, 4>::run(hp + (size_t)m * (tb + 1) * HP + k, hv);
+#pragma unroll
+                            for (int q = 0; q < 4; ++q)
+#pragma unroll
+                                for (int e = 0; e < 4; ++e) part[m][q] = fmaf(wv[q][e], hv[e], part[m][q]);
+                        }
+                    }
+                    cell(tt, u, part);
+                }
+            }
+            __syncthreads();
+        }
+        // ---- the block's scores: a wave per (sequence, step) ----
+        for (int col = wave; col < live * nb; col += kGenThreads / 64) {
+            const int m = col / nb, tt = col % nb;
             float u = 0.f;
-            for (int j = tid; j < dg; j += kWave) u = fmaf(Storage<T>::load(w_s + j), h[j], u);
+            for (int j = lane; j < dg; j += kWave) u = fmaf(Storage<T>::load(w_s + j), hs[(size_t)(m * (tb + 1) + tt + 1) * HP + j], u);
 #pragma unroll
             for (int off = 32; off >= 1; off >>= 1) u += __shfl_xor(u, off);
-            if (tid == 0) {
+            if (lane == 0) {
                 u += b_s;
-                a.util[(size_t)s * a.N_cap + t] = u;
-                a.gate[(size_t)s * a.N_cap + t] = 1.f / (1.f + expf(-u));
+                a.util[seq(m) * a.N_cap + t0 + tt] = u;
+                a.gate[seq(m) * a.N_cap + t0 + tt] = 1.f / (1.f + expf(-u));
             }
+        }
+        // the next block starts from this one's last state (step 0 is read by its first step only)
+        for (int j = tid; j < MB * dg; j += kGenThreads) {
+            float *hm = hs + (size_t)(j / dg) * (tb + 1) * HP + j % dg;
+            hm[0] = hm[(size_t)nb * HP];
         }
     }
     __syncthreads();
-    for (int j = tid; j < dg; j += 256) {
-        a.h[(size_t)s * dg + j] = h[j];
-        a.c[(size_t)s * dg + j] = c[j];
+    for (int j = tid; j < live * dg; j += kGenThreads) {
+        const int m = j / dg, e = j % dg;
+        a.h[seq(m) * dg + e] = hs[(size_t)m * (tb + 1) * HP + e];
+        a.c[seq(m) * dg + e] = cs[j];
     }
+}
+
+template <typename T, int D, int MB, int RES, int KC>
+static hipError_t launch_v(const LstmArgs &a, hipStream_t st)
+{
+    const int tb = gen_tb(D, a.d_g, MB);
+    const size_t lds = gen_lds(D, a.d_g, MB, tb);
+    const auto kernel = a.d_g % 4 == 0 ? lstm_generic_kernel<T, D, MB, RES, KC, true> : lstm_generic_kernel<T, D, MB, RES, KC, false>;
+    if (lds > 64 * 1024) {
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(a.L * ((a.BH + MB - 1) / MB))), dim3(kGenThreads), lds, st, a, tb);
+    return hipGetLastError();
 }
 
 template <typename T, int D>
 static hipError_t launch_t(const LstmArgs &a, hipStream_t st)
 {
-    const size_t S = (size_t)a.L * a.BH;
-    if (S == 0 || a.c1 == a.c0) return hipSuccess;
-    const size_t lds = sizeof(float) * (2 * D + 6 * (size_t)a.d_g);
-    hipLaunchKernelGGL((lstm_generic_kernel<T, D>), dim3((unsigned)S), dim3(256), lds, st, a);
-    return hipGetLastError();
+    if ((size_t)a.L * a.BH == 0 || a.c1 == a.c0) return hipSuccess;
+    // Launches that give every compute unit four sequences put four into a workgroup: W_ih, and W_hh where it is
+    // streamed, are then read once for all of them, and the nonlinearities, which bound a full chip, are evaluated once
+    // instead of in four quads.  (fp32, one against four per workgroup: 2048 sequences x 64
+    // steps at d_g = 64 359 -> 340 us, x 1 step 53 -> 20 us; x 8 steps at d_g = 256 843 -> 324 us.)
+    const bool four = (long long)a.L * ((a.BH + 3) / 4) >= a.compute_units && gen_tb(D, a.d_g, 4) > 0;
+    if (a.d_g <= 64) return four ? launch_v<T, D, 4, 1, 1>(a, st) : launch_v<T, D, 1, 1, 1>(a, st);
+    if (a.d_g <= 128) return four ? launch_v<T, D, 4, 2, 2>(a, st) : launch_v<T, D, 1, 2, 2>(a, st);
+    return four ? launch_v<T, D, 4, 0, 1>(a, st) : launch_v<T, D, 1, 0, 1>(a, st);
 }
 
 hipError_t launch_lstm_generic(const LstmArgs &a, int dtype, hipStream_t st)

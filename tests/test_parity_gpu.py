@@ -265,6 +265,15 @@ LSTM_CASES = [
     _cfg(153, "bf16", d=128, T=1024, C=32, d_g=512, L=1, B=2, H=16),      # one full group of 32 on four workgroups, 32 steps
     _cfg(154, "bf16", d=64, T=256, C=32, d_g=512, L=2, B=5, H=16),        # 80 sequences per layer: the third group of 32 has one block of 16 only
     _cfg(155, "bf16", d=128, T=160, C=32, d_g=512, L=3, B=1, H=16),       # 16 sequences per layer: stays on pairs of workgroups
+    # the fp32-arithmetic kernel: rows of W_hh in registers (up to 64, up to 128 wide) or streamed, widths that are no
+    # multiple of 4 (element-wise loads), blocks of steps that LDS shortens, and four sequences per workgroup (ragged)
+    _cfg(161, "f32", d=64, T=37 * 8, C=8, d_g=64, L=2, B=1, H=2),
+    _cfg(162, "bf16", d=128, T=20 * 8, C=8, d_g=101, L=2, B=1, H=3),
+    _cfg(163, "f32", d=128, T=18 * 8, C=8, d_g=196, L=1, B=1, H=3),
+    _cfg(164, "f32", d=64, T=7 * 8, C=8, d_g=40, L=3, B=18, H=19),
+    _cfg(165, "bf16", d=64, T=6 * 8, C=8, d_g=120, L=3, B=18, H=19),
+    _cfg(166, "f32", d=128, T=5 * 8, C=8, d_g=133, L=3, B=18, H=19),
+    _cfg(167, "f32", d=64, T=6 * 8, C=8, d_g=1500, L=1, B=1, H=2),
 ]
 
 
