@@ -191,6 +191,104 @@ __device__ __forceinline__ float group16_sum(float v)
 
 __device__ __forceinline__ float sigmoidf_(float x) { return 1.0f / (1.0f + __expf(-x)); }
 
+template <int CTRL> __device__ __forceinline__ float dpp_move(float v)
+{
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xf, 0xf, true));
+}
+constexpr int kQuadXor1 = 0xB1, kQuadXor2 = 0x4E, kRowShl4 = 0x104, kRowShr4 = 0x114, kRowRor4 = 0x124, kRowRor8 = 0x128;
+
+// Exchanges between the four rows of 16 lanes of a wave, on the vector unit (v_permlane16_swap, v_permlane32_swap; a
+// shuffle goes through LDS).  swap16: rows 1, 3 of a against rows 0, 2 of b; swap32: the upper half of a against the
+// lower half of b.
+__device__ __forceinline__ void swap16(float &a, float &b)
+{
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    a = __uint_as_float(r[0]); b = __uint_as_float(r[1]);
+}
+__device__ __forceinline__ void swap32(float &a, float &b)
+{
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    a = __uint_as_float(r[0]); b = __uint_as_float(r[1]);
+}
+// over the four lanes that share lane % 16
+__device__ __forceinline__ float rows_sum(float v)
+{
+    float w = v;
+    swap16(v, w);
+    v += w; w = v;
+    swap32(v, w);
+    return v + w;
+}
+__device__ __forceinline__ float rows_max(float v)
+{
+    float w = v;
+    swap16(v, w);
+    v = fmaxf(v, w); w = v;
+    swap32(v, w);
+    return fmaxf(v, w);
+}
+// N values over the four rows at once (op: sum or maximum): afterwards lane row r holds, in v[i], i < N / 4, the result of
+// value rows_value(i, r): an exchange halves the values that a lane still carries.
+template <int N, class F> __device__ __forceinline__ void rows_fold(float (&v)[N], F op)
+{
+    static_assert(N % 4 == 0, "two halvings");
+#pragma unroll
+    for (int i = 0; i < N / 2; ++i) {
+        swap16(v[2 * i], v[2 * i + 1]);
+        v[i] = op(v[2 * i], v[2 * i + 1]);
+    }
+#pragma unroll
+    for (int i = 0; i < N / 4; ++i) {
+        swap32(v[2 * i], v[2 * i + 1]);
+        v[i] = op(v[2 * i], v[2 * i + 1]);
+    }
+}
+__device__ __forceinline__ int rows_value(int i, int row) { return 4 * i + 2 * (row >> 1) + (row & 1); }
+
+// The sums over 16 lanes of four values at once: lane q (mod 4) receives the sum of v[value_of_lane(q)].
+// (every exchange halves the values a lane still carries: 4 -> 2 -> 1, then the four quads are added)
+__device__ __forceinline__ int value_of_lane(int lane) { return ((lane & 1) << 1) | ((lane >> 1) & 1); }
+__device__ __forceinline__ float fold4(const float (&v)[4], int lane)
+{
+    const bool b0 = lane & 1, b1 = lane & 2;
+    const float r0 = (b0 ? v[2] : v[0]) + dpp_move<kQuadXor1>(b0 ? v[0] : v[2]);
+    const float r1 = (b0 ? v[3] : v[1]) + dpp_move<kQuadXor1>(b0 ? v[1] : v[3]);
+    float q = (b1 ? r1 : r0) + dpp_move<kQuadXor2>(b1 ? r0 : r1);
+    q += dpp_move<kRowRor4>(q);
+    q += dpp_move<kRowRor8>(q);
+    return q;
+}
+
+// The same for 16 values, v[m][gate]: lane 4 m + q receives the sum over the 16 lanes of v[m][value_of_lane(q)].
+__device__ __forceinline__ float fold16(const float (&v)[4][4], int lane)
+{
+    const bool b0 = lane & 1, b1 = lane & 2, b2 = lane & 4, b3 = lane & 8;
+    float q[4];
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+        const float r0 = (b0 ? v[m][2] : v[m][0]) + dpp_move<kQuadXor1>(b0 ? v[m][0] : v[m][2]);
+        const float r1 = (b0 ? v[m][3] : v[m][1]) + dpp_move<kQuadXor1>(b0 ? v[m][1] : v[m][3]);
+        q[m] = (b1 ? r1 : r0) + dpp_move<kQuadXor2>(b1 ? r0 : r1);
+    }
+    const float p0 = (b3 ? q[2] : q[0]) + dpp_move<kRowRor8>(b3 ? q[0] : q[2]);
+    const float p1 = (b3 ? q[3] : q[1]) + dpp_move<kRowRor8>(b3 ? q[1] : q[3]);
+    const float away = b2 ? p0 : p1;        // what the lane four further on (b2: four back) is short of
+    const float fwd = dpp_move<kRowShl4>(away), back = dpp_move<kRowShr4>(away);
+    return (b2 ? p1 : p0) + (b2 ? back : fwd);
+}
+
+// four consecutive elements of a weight row from element k on, zeros at and past n.  VEC: the row allows one load.
+template <typename T, bool VEC> __device__ __forceinline__ void load4(const T *row, int k, int n, float (&o)[4])
+{
+    if (VEC) {
+        if (k < n) VecLoad<T, 4>::run(row + k, o);
+        else o[0] = o[1] = o[2] = o[3] = 0.f;
+    } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[e] = k + e < n ? Storage<T>::load(row + k + e) : 0.f;
+    }
+}
+
 // exact (erf) GELU in fp32
 __device__ __forceinline__ float gelu_erf(float x) { return 0.5f * x * (1.0f + erff(x * 0.70710678118654752f)); }
 

@@ -14,16 +14,15 @@
 //   * a group of 16 lanes owns a hidden unit (or several): lane c holds elements
 //     4 c .. 4 c + 3 (mod 64) of that unit's four rows of W_hh and of h, and the
 //     four partial dot products are folded over the 16 lanes by a transposing
-//     reduction that leaves gate q's sum in the lanes with lane % 4 == q, where
-//     its nonlinearity is evaluated; c_t and h_t follow in the same lanes, so a
+//     reduction that leaves one gate's sum in each lane of a quad, where its
+//     nonlinearity is evaluated; c_t and h_t follow in the same lanes, so a
 //     step has one barrier;
 //   * up to d_g = 128 the four rows stay in registers for the whole call (RES > 0);
 //     wider gates read them from L2 every step, 16 bytes per lane;
 //   * the utility head runs after each block over the block's 16 states.
 // Measured (fp32, d_g = 64, d = 64, 4 sequences x 64 steps): 1346 us with one
 // row of W_ih and W_hh at a time per lane group, dependent loads from L2 in every
-// step; 64 us now (1 us per step, of which the two nonlinearities in a row, expf
-// and tanhf, are about half).  d_g = 256, d = 128, 32 sequences x 64 steps: 11.4 ms
+// step; 64 us now (1 us per step, the projections included).  d_g = 256, d = 128, 32 sequences x 64 steps: 11.4 ms
 // -> 0.69 ms, bound by the 1 MiB of W_hh that a workgroup streams per step.
 #include "common.hpp"
 #include "kernels.hpp"
@@ -45,56 +44,6 @@ static int gen_tb(int d, int dg, int mb)
     int tb = kGenCols / mb;
     while (tb > 0 && gen_lds(d, dg, mb, tb) > kGenLdsMax) --tb;
     return tb;
-}
-
-template <int CTRL> __device__ __forceinline__ float dpp_move(float v)
-{
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xf, 0xf, true));
-}
-constexpr int kQuadXor1 = 0xB1, kQuadXor2 = 0x4E, kRowShl4 = 0x104, kRowShr4 = 0x114, kRowRor4 = 0x124, kRowRor8 = 0x128;
-
-// The sums over 16 lanes of four values at once: lane q (mod 4) receives the sum of v[gate_of_lane(q)].
-// (every exchange halves the values a lane still carries: 4 -> 2 -> 1, then the four quads are added)
-__device__ __forceinline__ int gate_of_lane(int lane) { return ((lane & 1) << 1) | ((lane >> 1) & 1); }
-__device__ __forceinline__ float fold4(const float (&v)[4], int lane)
-{
-    const bool b0 = lane & 1, b1 = lane & 2;
-    const float r0 = (b0 ? v[2] : v[0]) + dpp_move<kQuadXor1>(b0 ? v[0] : v[2]);
-    const float r1 = (b0 ? v[3] : v[1]) + dpp_move<kQuadXor1>(b0 ? v[1] : v[3]);
-    float q = (b1 ? r1 : r0) + dpp_move<kQuadXor2>(b1 ? r0 : r1);
-    q += dpp_move<kRowRor4>(q);
-    q += dpp_move<kRowRor8>(q);
-    return q;
-}
-
-// The same for 16 values, v[m][gate]: lane 4 m + q receives the sum over the 16 lanes of v[m][gate_of_lane(q)].
-__device__ __forceinline__ float fold16(const float (&v)[4][4], int lane)
-{
-    const bool b0 = lane & 1, b1 = lane & 2, b2 = lane & 4, b3 = lane & 8;
-    float q[4];
-#pragma unroll
-    for (int m = 0; m < 4; ++m) {
-        const float r0 = (b0 ? v[m][2] : v[m][0]) + dpp_move<kQuadXor1>(b0 ? v[m][0] : v[m][2]);
-        const float r1 = (b0 ? v[m][3] : v[m][1]) + dpp_move<kQuadXor1>(b0 ? v[m][1] : v[m][3]);
-        q[m] = (b1 ? r1 : r0) + dpp_move<kQuadXor2>(b1 ? r0 : r1);
-    }
-    const float p0 = (b3 ? q[2] : q[0]) + dpp_move<kRowRor8>(b3 ? q[0] : q[2]);
-    const float p1 = (b3 ? q[3] : q[1]) + dpp_move<kRowRor8>(b3 ? q[1] : q[3]);
-    const float away = b2 ? p0 : p1;        // what the lane four further on (b2: four back) is short of
-    const float fwd = dpp_move<kRowShl4>(away), back = dpp_move<kRowShr4>(away);
-    return (b2 ? p1 : p0) + (b2 ? back : fwd);
-}
-
-// four consecutive elements of a weight row from element k on, zeros at and past n.  VEC: the row allows one load.
-template <typename T, bool VEC> __device__ __forceinline__ void load4(const T *row, int k, int n, float (&o)[4])
-{
-    if (VEC) {
-        if (k < n) VecLoad<T, 4>::run(row + k, o);
-        else o[0] = o[1] = o[2] = o[3] = 0.f;
-    } else {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) o[e] = k + e < n ? Storage<T>::load(row + k + e) : 0.f;
-    }
 }
 
 // MB: sequences of one layer per workgroup.  RES: hidden units per lane group whose rows of W_hh stay in registers, KC
@@ -123,7 +72,7 @@ __global__ __launch_bounds__(kGenThreads, RES == 1 && MB == 1 ? 8 : 4) void lstm
     const T *b_hh = static_cast<const T *>(a.b_hh) + (size_t)l * G;
     const T *w_s = static_cast<const T *>(a.w_s) + (size_t)l * dg;
     const float b_s = Storage<T>::load(static_cast<const T *>(a.b_s) + l);
-    const int gate = gate_of_lane(cl);
+    const int gate = value_of_lane(cl);
 
     const bool fresh = a.c0 == 0;        // the recurrence starts from a zero state at chunk 0, whatever the buffers hold
     for (int j = tid; j < MB * (tb + 1) * HP; j += kGenThreads) {

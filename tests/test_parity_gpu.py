@@ -205,6 +205,10 @@ POOL_CASES = [
     _cfg(129, "bf16", d=128, T=1026, C=2, d_sum=128, L=1, B=4, H=16),
     _cfg(130, "bf16", d=64, T=2052, C=4, d_sum=64, L=1, B=5, H=13),
     _cfg(128, "bf16", d=64, T=1026, C=2, d_sum=96, L=2, B=2, H=16),       # two layers, three k-steps in the second MLP layer
+    # the fp32-arithmetic kernel with four rows per workgroup (2052 rows, the last group of a layer half empty), and a
+    # hidden width that is no multiple of 4 (element-wise loads of W2)
+    _cfg(123, "f32", d=128, T=345, C=3, d_sum=68, L=2, B=3, H=3),
+    _cfg(124, "bf16", d=64, T=345, C=3, d_sum=50, L=2, B=3, H=3),
 ]
 
 
