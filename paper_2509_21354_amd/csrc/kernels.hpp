@@ -83,6 +83,9 @@ inline int lstm_split(int d_g, int L, int BH, int compute_units, bool quad_allow
     if ((d_g == 256 || d_g == 512) && 2 * g16 <= compute_units) return 2;
     return 0;
 }
+// At d_g = 256, launches that fit the chip with two workgroups per 8 sequences take lstm_rec_oct_kernel (four per 8 where
+// that fits too): 1024 sequences x 64 steps 183 us against 249 us on pairs per 16; above, the pairs remain.
+inline bool lstm_takes_oct(int L, int BH, int compute_units) { return 2ll * L * ((BH + 7) / 8) <= compute_units; }
 inline size_t lstm_split_exch_bytes(int split, int d_g, int L, int BH, int quad_groups)
 {
     if (split == 4) {       // the slots of one launch (quad_groups groups at most), used again by the next
@@ -123,6 +126,7 @@ hipError_t launch_lstm_mfma(const LstmArgs &a, hipStream_t st);          // bf16
 hipError_t launch_lstm_prepare(const LstmArgs &a, hipStream_t st);       // bf16: the packed weights alone
 hipError_t launch_stream_probe(const void *src, size_t tiles, int tile_bytes, void *dst, int write_bytes, int hints, hipStream_t st);   // calibration
 hipError_t launch_lstm_quad(const LstmArgs &a, hipStream_t st);          // bf16, d_g = 512: projection and recurrence of 32 sequences on four workgroups (weights already packed)
+hipError_t launch_lstm_oct(const LstmArgs &a, int t0, int nb, hipStream_t st);   // bf16, d_g = 256: the recurrence on two workgroups per 8 sequences
 hipError_t launch_lstm_fused(const LstmArgs &a, hipStream_t st);         // bf16, d_g = 256: the recurrence with the input projection inside (weights already packed)
 
 }  // namespace kvev

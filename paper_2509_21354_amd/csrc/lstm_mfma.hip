@@ -887,6 +887,11 @@ static hipError_t launch_dg(const LstmArgs &a, hipStream_t st)
             else hipLaunchKernelGGL((lstm_inproj_kernel<DG, 128, kTT>), grid_in, dim3(Geo<DG>::THREADS), lds_in, st, a, t0, nb);
         }
         if constexpr (DG == 256 || DG == 512) {
+            if (DG == 256 && a.split == 2 && lstm_takes_oct(a.L, a.BH, a.compute_units)) {
+                e = launch_lstm_oct(a, t0, nb, st);
+                if (e != hipSuccess) return e;
+                continue;
+            }
             if (a.split == 2) {
                 hipLaunchKernelGGL((lstm_rec_pair_kernel<DG>), dim3(2 * groups), dim3(512), PairGeo<DG>::lds, st, a, t0, nb);
                 continue;

@@ -1,0 +1,337 @@
+// Recurrent gate, Eq. 3 of the paper, bf16 storage, d_g = 256: the sequential half for launches of few sequences, 8
+// sequences on four or two compute units.
+//
+// What bounds such a launch is the chain of one step, and the chip is mostly idle.  As in lstm_rec_pair_kernel
+// (lstm_mfma.hip) the workgroups of a group share the hidden units, keep their rows of W_hh in registers and exchange
+// the new h every step.  What is different, all of it to shorten the step:
+//   * 8 sequences per group instead of 16.  The 16 columns of a matrix instruction hold the two fp16 terms of h for the
+//     8 sequences side by side (column n: sequence n mod 8, hi for n < 8, lo for n >= 8), so one instruction per weight
+//     fragment gives both products; they are added across the columns afterwards, and the two lanes that then hold the
+//     same sums share the four units between them.  Half the matrix work, half the nonlinearities and half the exchange
+//     per group, on compute units that were idle;
+//   * P = 4 workgroups of 4 waves where the launch leaves room for them, else 2 of 8: a wave owns 16 units either way;
+//   * the members of a group sit on one XCD and publish through its L2 (see `near`): an exchange by write-through stores
+//     takes 0.35 us longer;
+//   * 8 bytes per lane carry 4 units of one column, without stamps: |h| <= 1 leaves bit 14 of an fp16 term free (of hi and
+//     of lo), and the first term of every aligned 8-byte word carries a flag there that flips from one use of a slot to
+//     the next.  Two slots by step parity, cleared before the launch: a reader sees the use it waits for, the one before,
+//     or zeros, and one bit tells them apart.  (8 aligned bytes are written and read as one; a slot is rewritten two steps
+//     later, by a workgroup that has seen its partners' h of the step between, whose waves had all read this one: they
+//     publish behind a barrier that follows the reads.);
+//   * the input projections of the next step are requested in this one, into registers of their own.
+// A step: products over the own units | take the partners' h, stage in LDS | barrier | products over the partners' units |
+// cell, publish, own h to LDS | barrier.  Bounded waits, status word and the layout of weights and projections: as the
+// paired kernel.
+// Measured (the whole gate call, weights prepared, 32 sequences x 128 steps): 311 us on pairs per 16 sequences; 217 us with
+// P = 2, 186 us with P = 4 (1.26 us per step; 0.95 us with the exchange taken out); P = 4 with write-through stores 232 us.
+// 512 sequences x 64 steps: 184 -> 125 us, x 8 steps: 40 -> 32.5 us; 1024 x 64 (P = 2): 249 -> 183 us.  Reading the matrix
+// operand straight from the slots, with no staging and one barrier less, measured the same (every wave then reads
+// everything past the L1).
+#include "common.hpp"
+#include "kernels.hpp"
+#include "lstm_common.hpp"
+
+namespace kvev {
+
+namespace {
+constexpr int kDG = 256, kKS = kDG / 32;
+constexpr uint32_t kGroupSlots = 2 * kKS * 1024;             // [parity][member][column 16][own units]
+static_assert(2 * (kGroupSlots + 64) <= kLstmPairExchBytes256, "two groups of 8 and their members' XCDs fit the scratch planned for one of 16");
+constexpr int kHwRegXccId = 20 | (3 << 11);                  // hardware register XCC_ID, bits 0 .. 3
+}
+
+// P workgroups per group, each with 256 / P hidden units: a wave per 16 of them
+template <int P>
+__global__ __launch_bounds__(1024 / P) void lstm_rec_oct_kernel(LstmArgs a, int t0, int nb)
+{
+    using G = Geo<kDG>;
+    constexpr int kNW = 16 / P, kKH = kKS / P, kKP = kKS - kKH;      // waves; k-steps over own units, over the partners'
+    constexpr int kOwn = kDG / P, kOP = kOwn + 8, kPP = kDG - kOwn + 8;     // own units; row pitches in LDS
+    constexpr uint32_t kSlot = 16 * kOwn * sizeof(f16_t);            // one member's h of one step: [column 16][own units]
+    constexpr int kLR = kOwn / 4, kRows = 64 / kLR;                  // receiving: lanes per row, rows per wave
+    __shared__ __align__(16) f16_t s_h[16 * kOP];            // own units of h, row = column of the operand
+    __shared__ __align__(16) f16_t s_p[16 * kPP];            // the partners' units
+    __shared__ float s_up[2][kNW][8], s_up2[16];             // shares of the utility logit: own units (by step parity), partners' by column
+    __shared__ int s_fail;
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n = lane & 15, g4 = lane >> 4, sn = n & 7, hn2 = n >> 3;
+    // The members of a group are 8 apart in the launch order.  Workgroup ids go round-robin over the 8 XCDs, so they are
+    // neighbours in the queue of one XCD: a running member's partner is next in line there.  (Nothing but speed depends
+    // on it: see `near`.)
+    const int gpl = (a.BH + 7) / 8, ngroups = a.L * gpl;
+    const int member = (blockIdx.x / 8) % P, gid = blockIdx.x / (8 * P) * 8 + blockIdx.x % 8;
+    if (gid >= ngroups) return;
+    const int l = gid / gpl, grp = gid % gpl;
+    const bool live = grp * 8 + sn < a.BH;
+    const size_t s = (size_t)l * a.BH + min(grp * 8 + sn, a.BH - 1);
+    // the partners follow cyclically: k-step i < kKP of theirs belongs to member + 1 + i / kKH (mod P)
+    auto par_of = [&](int i) __attribute__((always_inline)) { return (member + 1 + i / kKH) % P; };
+    const int tile = member * kNW + wave;                    // unit tile (16 units) of this wave
+    const int unit0 = tile * 16 + 4 * g4 + 2 * hn2;          // this lane's two cells: units unit0, unit0 + 1 of sequence s
+
+    const bf16_t *w_s = static_cast<const bf16_t *>(a.w_s) + (size_t)l * kDG;
+    const float b_s = bf16_to_f32(static_cast<const bf16_t *>(a.b_s)[l]);
+    const float inv_scale = ldexpf(1.f, -whh_scale_exp(whh_layer_max(a.whh_max_bits, l)));
+    if (tid == 0) s_fail = 0;
+
+    // ---- all weights of the wave: 8 k-steps x 4 gates, own units first ----
+    const uint32_t lane16 = lane * 16;
+    const __amdgpu_buffer_rsrc_t w_rsrc = make_rsrc(
+        reinterpret_cast<const unsigned char *>(a.whh_packed + (((size_t)l * G::NW + tile / G::UT) * G::ITEMS + (tile % G::UT) * kKS) * 4 * 64),
+        kKS * 4096);
+    f16x8_t w[kKS][4];
+#pragma unroll
+    for (int i = 0; i < kKS; ++i)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            w[i][q] = buffer_load16<f16x8_t>(w_rsrc, lane16 + q * 1024, (uint32_t)((i < kKH ? member * kKH + i : par_of(i - kKH) * kKH + (i - kKH) % kKH) * 4096));
+
+    // ---- the input projections: written in fragments of 16 sequences, this lane reads its two units of its sequence ----
+    const int gpl16 = (a.BH + 15) / 16, gid16 = l * gpl16 + grp / 2;
+    const unsigned char *xbase = reinterpret_cast<const unsigned char *>(
+        reinterpret_cast<const f32x4_t *>(a.xproj) + xp_block<kDG>(gid16, a.tb, 0, tile / G::UT, tile % G::UT, 0) * 64);
+    const __amdgpu_buffer_rsrc_t x_rsrc = make_rsrc(xbase, (uint32_t)nb * G::NW * G::UT * 4096 - (uint32_t)tile * 4096);
+    const uint32_t xoff = (uint32_t)((g4 * 16 + (grp & 1) * 8 + sn) * 16 + hn2 * 8);
+    // (two sets by step parity: a set in flight across the step boundary is not copied, which would wait for it)
+    float xin[2][4][2];
+    auto fetch_x = [&](int tt, float (&x)[4][2]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const u32x2_t v = __builtin_amdgcn_raw_buffer_load_b64(x_rsrc, (int)(xoff + q * 1024), (int)((uint32_t)tt * G::NW * G::UT * 4096), 2);
+            x[q][0] = __uint_as_float(v[0]);
+            x[q][1] = __uint_as_float(v[1]);
+        }
+    };
+    fetch_x(0, xin[0]);
+
+    // Members on one XCD publish with plain stores, which meet the partners' device-scope loads in the L2 that they share
+    // (an L2 cannot pass over its own dirty line); others write through.  Each tells its XCD before the first step.
+    const __amdgpu_buffer_rsrc_t e_rsrc = make_rsrc(a.exch + (size_t)gid * kGroupSlots, kGroupSlots);
+    uint32_t *const where = reinterpret_cast<uint32_t *>(a.exch + (size_t)ngroups * kGroupSlots) + (size_t)gid * 16;
+    const uint32_t xcd = 1u + __builtin_amdgcn_s_getreg(kHwRegXccId);
+    if (tid == 0) __hip_atomic_store(where + member, xcd, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    // a look at the partners' slots of parity `par`: this wave takes rows wave * kRows .. of each, 8 bytes per lane
+    const int rrow = wave * kRows + lane / kLR, rcol = lane % kLR;       // column of the operand; 4 units from 4 rcol on
+    auto ask = [&](int par, u32x2_t (&v)[P - 1]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int p = 0; p < P - 1; ++p)
+            v[p] = __builtin_amdgcn_raw_buffer_load_b64(e_rsrc, lane * 8, (int)((par * P + (member + 1 + p) % P) * kSlot + wave * 512), 16);
+    };
+
+    // h of step t0 - 1, split into two fp16 terms: (hi, lo) pairs of two neighbouring units
+    auto split2 = [](float h0, float h1, uint32_t &hi, uint32_t &lo) __attribute__((always_inline)) {
+        typedef _Float16 f16x2_t __attribute__((ext_vector_type(2)));
+        const f16x2_t h = {(f16_t)h0, (f16_t)h1};
+        const f16x2_t r = {(f16_t)(h0 - (float)h[0]), (f16_t)(h1 - (float)h[1])};
+        hi = __builtin_bit_cast(uint32_t, h);
+        lo = __builtin_bit_cast(uint32_t, r);
+    };
+    // the lanes of a sequence trade pairs: lane n < 8 leaves with hi of units 4 g4 .. + 3, lane n + 8 with lo of them
+    auto gather = [&](uint32_t hi, uint32_t lo) __attribute__((always_inline)) {
+        const uint32_t other = __float_as_uint(dpp_move<kRowRor8>(__uint_as_float(hn2 ? hi : lo)));
+        return hn2 ? u32x2_t{other, lo} : u32x2_t{hi, other};
+    };
+    f16_t *const h_wr = s_h + (size_t)n * kOP + wave * 16 + 4 * g4;
+    const f16_t *const h_rd = s_h + (size_t)n * kOP + g4 * 8, *const p_rd = s_p + (size_t)n * kPP + g4 * 8;     // + j * 32
+    f16_t *const p_wr = s_p + (size_t)rrow * kPP + 4 * rcol;          // + p * kOwn
+
+    float c_reg[2], ws_own[2];
+#pragma unroll
+    for (int p = 0; p < P; ++p) {        // own units, then the partners'
+        float hv[2];
+#pragma unroll
+        for (int r = 0; r < 2; ++r) {
+            const int u = (member + p) % P * kOwn + unit0 - member * kOwn + r;
+            // (chunk 0 starts the recurrence from a zero state, whatever the buffers hold)
+            hv[r] = live && t0 > 0 ? a.h[s * kDG + u] : 0.f;
+            if (p == 0) {
+                c_reg[r] = live && t0 > 0 ? a.c[s * kDG + u] : 0.f;
+                ws_own[r] = bf16_to_f32(w_s[u]);
+            }
+        }
+        uint32_t hi, lo;
+        split2(hv[0], hv[1], hi, lo);
+        f16_t *dst = p == 0 ? h_wr : s_p + (size_t)n * kPP + (p - 1) * kOwn + wave * 16 + 4 * g4;
+        *reinterpret_cast<u32x2_t *>(dst) = gather(hi, lo);
+    }
+    float ws_par[P - 1][4];          // of the units that this lane receives
+#pragma unroll
+    for (int p = 0; p < P - 1; ++p)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) ws_par[p][e] = bf16_to_f32(w_s[(member + 1 + p) % P * kOwn + 4 * rcol + e]);
+    bool near = true;
+    for (int p = 1; p < P; ++p) {        // (a member that stays silent is taken to be elsewhere: the steps' waits deal with it)
+        uint32_t x = 0;
+        for (int spin = 0; x == 0 && spin < a.pair_spin_limit; ++spin)
+            x = __hip_atomic_load(where + (member + p) % P, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        near = near && x == xcd;
+    }
+    __syncthreads();
+
+    // the logit of a step from the shares of all members, by wave 0 of member 0 where it would otherwise wait
+    auto write_util = [&](int step) __attribute__((always_inline)) {
+        float u = s_up2[sn] + s_up2[sn + 8];             // products with hi and with lo
+#pragma unroll
+        for (int w_ = 0; w_ < kNW; ++w_) u += s_up[step & 1][w_][sn];
+        u += b_s;
+        if (live && lane < 8) {
+            a.util[s * a.N_cap + t0 + step] = u;
+            a.gate[s * a.N_cap + t0 + step] = sigmoid_hw(u);
+        }
+    };
+    constexpr uint32_t kFlag = 0x4000u;
+    // The partners' h of step tt - 1 into LDS, from a look asked for earlier; more looks follow if it is not there yet.
+    // Member 0 also sums up this wave's rows for the utility.
+    auto receive = [&](int tt, u32x2_t (&v)[P - 1]) __attribute__((always_inline)) {
+        typedef _Float16 f16x4_t __attribute__((ext_vector_type(4)));
+        const int par = (tt - 1) & 1;
+        const uint32_t flag = ((tt - 1) >> 1) & 1 ? 0u : kFlag;
+        auto complete = [&]() __attribute__((always_inline)) {
+            uint32_t off = 0;
+#pragma unroll
+            for (int p = 0; p < P - 1; ++p) off |= v[p][0] ^ flag;
+            return __all((off & kFlag) == 0) != 0;
+        };
+        bool got = complete();
+        for (int spin = 0; !got && spin < a.pair_spin_limit; ++spin) {
+            asm volatile("" ::: "memory");
+            if ((spin & 255) == 255 && s_fail) break;
+            ask(par, v);
+            got = complete();
+        }
+        if (!got) s_fail = 1;
+        float u = 0.f;
+#pragma unroll
+        for (int p = 0; p < P - 1; ++p) {
+            uint32_t x = v[p][0] & ~kFlag;
+            // a NaN without its flag bit reads as a magnitude above 1 (exponent 15, a mantissa), which no |h| <= 1 has
+            if ((x & 0x7fffu) > 0x3c00u) x |= kFlag;
+            const u32x2_t o = {x, v[p][1]};
+            *reinterpret_cast<u32x2_t *>(p_wr + p * kOwn) = o;
+            const f16x4_t h4 = __builtin_bit_cast(f16x4_t, o);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) u = fmaf(ws_par[p][e], (float)h4[e], u);
+        }
+        return u;
+    };
+    // ... whose sums over a row's lanes are not waited for by the products
+    auto share = [&](float u) __attribute__((always_inline)) {
+        u += dpp_move<kQuadXor1>(u);
+        u += dpp_move<kQuadXor2>(u);
+        u += dpp_move<kRowRor4>(u);
+        u += dpp_move<kRowRor8>(u);
+        if (kLR == 32) {
+            float w_ = u;
+            swap16(u, w_);
+            u += w_;
+        }
+        if (rcol == 0) s_up2[rrow] = u;
+    };
+
+    bool failed = false;
+    u32x2_t look[P - 1];
+    // one step; false: a wait in it expired in some wave of the workgroup
+    auto step = [&](int tt, auto cur_tag) __attribute__((always_inline)) {
+        constexpr int cur = decltype(cur_tag)::value, nxt = cur ^ 1;
+        f32x4_t acc[4];
+        auto products = [&](const f16_t *rd, auto first_tag, auto count_tag) __attribute__((always_inline)) {
+            constexpr int first = decltype(first_tag)::value, count = decltype(count_tag)::value;
+            f16x8_t hb[count];
+#pragma unroll
+            for (int j = 0; j < count; ++j) hb[j] = *reinterpret_cast<const f16x8_t *>(rd + j * 32);
+#pragma unroll
+            for (int j = 0; j < count; ++j)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const f32x4_t zero = {0.f, 0.f, 0.f, 0.f};
+                    acc[q] = __builtin_amdgcn_mfma_f32_16x16x32_f16(w[first + j][q], hb[j], first + j == 0 ? zero : acc[q], 0, 0, 0);
+                }
+        };
+        products(h_rd, std::integral_constant<int, 0>{}, std::integral_constant<int, kKH>{});
+        if (tt > 0) ask(nxt, look);      // (earlier it finds the slots not yet written)
+        __builtin_amdgcn_sched_barrier(0);
+        if (tt > 1 && member == 0 && wave == 0) write_util(tt - 2);
+        float ushare = 0.f;
+        if (tt > 0) ushare = receive(tt, look);
+        lds_barrier();
+        if (s_fail) return false;
+        products(p_rd, std::integral_constant<int, kKH>{}, std::integral_constant<int, kKP>{});
+        if (tt > 0 && member == 0) share(ushare);
+
+        // ---- hi + lo products of this lane's two units, the cell, the new h ----
+        float z[4][2];
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int r = 0; r < 2; ++r) {
+                const float keep = hn2 ? acc[q][2 + r] : acc[q][r], send = hn2 ? acc[q][r] : acc[q][2 + r];
+                z[q][r] = fmaf(keep + dpp_move<kRowRor8>(send), inv_scale, xin[cur][q][r]);
+            }
+        fetch_x(min(tt + 1, nb - 1), xin[nxt]);
+        float hv[2], upart = 0.f;
+#pragma unroll
+        for (int r = 0; r < 2; ++r) {
+            const float ig = sigmoid_hw(z[0][r]), fg = sigmoid_hw(z[1][r]), gg = tanh_hw(z[2][r]), og = sigmoid_hw(z[3][r]);
+            const float cn = fmaf(fg, c_reg[r], ig * gg);
+            c_reg[r] = cn;
+            float hn = og * tanh_hw(cn);
+            asm volatile("" : "+v"(hn));     // opaque to the optimiser: hn is the rounded product from here on
+            hv[r] = hn;
+            upart = fmaf(ws_own[r], hn, upart);
+        }
+        uint32_t hi, lo;
+        split2(hv[0], hv[1], hi, lo);
+        const u32x2_t mine = gather(hi, lo);
+        // to the partner first (the long way), then to this workgroup's own waves
+        if (member != a.pair_mute) {
+            const uint32_t flag = (tt >> 1) & 1 ? 0u : kFlag;
+            const u32x2_t out = {(mine[0] & ~kFlag) | flag, mine[1]};
+            const int voff = n * kOwn * 2 + wave * 32 + g4 * 8, soff = (int)((cur * P + member) * kSlot);
+            if (near) __builtin_amdgcn_raw_buffer_store_b64(out, e_rsrc, voff, soff, 0);
+            else __builtin_amdgcn_raw_buffer_store_b64(out, e_rsrc, voff, soff, 16);
+        }
+        *reinterpret_cast<u32x2_t *>(h_wr) = mine;
+        upart = rows_sum(upart);
+        upart += dpp_move<kRowRor8>(upart);
+        if (lane < 8) s_up[cur][wave][lane] = upart;
+        if (tt == nb - 1 && live) *reinterpret_cast<float2 *>(a.h + s * kDG + unit0) = make_float2(hv[0], hv[1]);
+        lds_barrier();
+        return true;
+    };
+    for (int tt = 0; tt < nb && !failed; tt += 2) {
+        failed = !step(tt, std::integral_constant<int, 0>{});
+        if (tt + 1 < nb && !failed) failed = !step(tt + 1, std::integral_constant<int, 1>{});
+    }
+    if (!failed) {      // the last step's logit needs the partners' last h
+        if (nb > 1 && member == 0 && wave == 0) write_util(nb - 2);
+        lds_barrier();
+        ask((nb - 1) & 1, look);
+        share(receive(nb, look));
+        lds_barrier();
+        failed = s_fail != 0;
+        if (!failed && member == 0 && wave == 0) write_util(nb - 1);
+    }
+    if (live) {
+#pragma unroll
+        for (int r = 0; r < 2; ++r) a.c[s * kDG + unit0 + r] = failed ? __builtin_nanf("") : c_reg[r];
+    }
+    if (failed && tid == 0) __hip_atomic_store(a.status, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // sticky: the caller's to clear
+    if (failed && tid < 8 && live) {
+        for (int t = 0; t < nb; ++t) {
+            a.util[s * a.N_cap + t0 + t] = __builtin_nanf("");
+            a.gate[s * a.N_cap + t0 + t] = __builtin_nanf("");
+        }
+    }
+}
+
+hipError_t launch_lstm_oct(const LstmArgs &a, int t0, int nb, hipStream_t st)
+{
+    const int groups = a.L * ((a.BH + 7) / 8);
+    const unsigned wgs = (unsigned)((groups + 7) / 8 * 8);
+    if (4 * groups <= a.compute_units) hipLaunchKernelGGL((lstm_rec_oct_kernel<4>), dim3(4 * wgs), dim3(256), 0, st, a, t0, nb);
+    else hipLaunchKernelGGL((lstm_rec_oct_kernel<2>), dim3(2 * wgs), dim3(512), 0, st, a, t0, nb);
+    return hipGetLastError();
+}
+
+}  // namespace kvev

@@ -323,7 +323,7 @@ def test_lstm_gate(cfg):
 
 NAN_CASES = [
     (_cfg(157, "bf16", d=128, T=256, C=32, d_g=512, L=1, B=1, H=40), 0),     # four workgroups per 32 sequences: h travels with a flag in a bit of its hi terms
-    (_cfg(158, "bf16", d=64, T=256, C=32, d_g=256, L=1, B=1, H=20), 0),      # pairs of workgroups
+    (_cfg(158, "bf16", d=64, T=256, C=32, d_g=256, L=1, B=1, H=20), 0),      # four workgroups per 8 sequences: a flag in a bit of hi and lo terms
     (_cfg(159, "bf16", d=128, T=256, C=32, d_g=256, L=1, B=1, H=40), 1),     # the single-kernel form
     (_cfg(160, "bf16", d=128, T=256, C=32, d_g=512, L=1, B=1, H=9), 0),      # pairs at d_g = 512
 ]
@@ -450,6 +450,45 @@ def test_lstm_gate_single_kernel_form(cfg):
     assert (util[..., N:] == 9.0).all() and (gate[..., N:] == 9.0).all()
     for x, y in zip(outs[0], outs[1]):
         assert torch.equal(x, y)
+
+
+OCT_CASES = [
+    _cfg(171, "bf16", d=128, T=23 * 32, C=32, d_g=256, L=3, B=1, H=13),     # four workgroups per 8 sequences, 13 per layer: ragged
+    _cfg(172, "bf16", d=64, T=9 * 32, C=32, d_g=256, L=13, B=1, H=37),      # 65 groups: two workgroups per 8 sequences
+    _cfg(173, "bf16", d=128, T=1 * 32, C=32, d_g=256, L=1, B=1, H=1),       # one sequence, one step
+    _cfg(174, "bf16", d=128, T=2 * 32, C=32, d_g=256, L=2, B=2, H=8),       # two steps: every slot used once
+]
+
+
+@pytest.mark.parametrize("cfg", OCT_CASES, ids=lambda c: c.name)
+def test_lstm_gate_eight_sequences_per_group(cfg):
+    """The form of the gate that small launches take at d_g = 256: groups of 8 sequences on two or four workgroups.  One
+    call, then the same range cut into calls that carry the state (with scratch for two steps per launch, so that the
+    exchange slots start anew inside a call): the same bits."""
+    N = cfg.T // cfg.C
+    w = synth.make_weights(cfg, "cpu")
+    Kbar, Vbar = _summaries(cfg, N)
+    sh = kb.make_shape(cfg, N_cap=N)
+    lead = (cfg.L, cfg.B, cfg.H)
+    gw = dev(w)
+    Kb, Vb = Kbar.cuda(), Vbar.cuda()
+    outs = []
+    for cuts, steps in (([(0, N)], N), ([(0, min(1, N)), (min(1, N), min(N, 6)), (min(N, 6), N)], 2)):
+        ws = kb.alloc_workspace(kb.workspace_bytes(kb.OP_LSTM_GATE, sh, steps))
+        h = torch.full(lead + (cfg.d_g,), 7.0, device="cuda")
+        c = torch.full_like(h, float("nan"))
+        util = torch.full(lead + (N,), 9.0, device="cuda")
+        gate = torch.full_like(util, 9.0)
+        for a, b in cuts:
+            kb.kvev_lstm_gate(sh, Kb, Vb, kb.lstm_weights(gw), a, b, h, c, util, gate, ws)
+        torch.cuda.synchronize()
+        assert int(ws[:4].view(torch.int32).item()) == 0
+        outs.append((h, c, util, gate))
+    for x, y in zip(*outs):
+        assert torch.equal(x, y)
+    rh, rc, ru, rg = orc.lstm_gate(Kbar, Vbar, kb.lstm_weights(w), 0, N)
+    for got, ref, tol in zip(outs[0], (rh, rc, ru, rg), (SCORE_TOL, 2 * SCORE_TOL, SCORE_TOL, SCORE_TOL)):
+        assert np.abs(got.cpu().numpy() - ref).max() <= tol
 
 
 WAIT_CASES = [
