@@ -62,8 +62,11 @@ static int env_int(const char *name, int dflt)
 }
 // Tuning knobs (environment, read once; unset = the rule below): workgroups wanted per launch and the smallest
 // run of raw rows worth a workgroup.  The rule: with fewer key-value units than compute units the launch is filled
-// with up to one 16-wave workgroup per compute unit and runs down to 64 rows (one batch of a 4-wave workgroup);
-// with more, four 4-wave workgroups per compute unit and runs of at least 512 rows.
+// with up to one workgroup per compute unit; a run is at least 64 rows (one batch of a 4-wave workgroup) while there
+// are fewer than 64 units, 1024 rows above: from 64 units on the merge of a split costs more than it saves on a short
+// cache (64 x 283 rows: 8.2 us in 4 runs, 7.4 us in one; 128 x 1000 rows: 17.4 us in 2 runs, 15.8 us in one; 48 x 283
+// rows: 6.6 us in 5 runs, 6.9 us in one).  With more units than compute units, four 4-wave workgroups per compute unit
+// and runs of at least 512 rows.
 static const int g_attn_target_blocks = env_int("KVEV_ATTN_TARGET_BLOCKS", -1);
 static const int g_attn_min_rows = env_int("KVEV_ATTN_MIN_ROWS", -1);
 // large pooling launches write their summaries once per 2^shift ticks of the 100 MHz real-time counter: 8192 ticks
@@ -85,7 +88,7 @@ static AttnPlan plan_attn(const kvev_shape *sh, int Tq, int n_rows)
     const int64_t sq = (int64_t)sh->L * sh->B * sh->H * (Tq > 0 ? Tq : 1);
     const bool few = units < 256;
     const int target = g_attn_target_blocks > 0 ? g_attn_target_blocks : few ? 256 : 1024;
-    const int min_rows = g_attn_min_rows > 0 ? g_attn_min_rows : few ? 64 : 512;
+    const int min_rows = g_attn_min_rows > 0 ? g_attn_min_rows : units < 64 ? 64 : few ? 1024 : 512;
     int64_t want = (target + units - 1) / units;
     int64_t most = (n_rows + min_rows - 1) / min_rows;
     if (want > most) want = most;

@@ -277,6 +277,22 @@ __device__ __forceinline__ float fold16(const float (&v)[4][4], int lane)
     return (b2 ? p1 : p0) + (b2 ? back : fwd);
 }
 
+// The same for 8 values, v[m][value]: lane 8 m + q (mod 4 in q) receives the sum over the 16 lanes of v[m][value_of_lane(q)].
+__device__ __forceinline__ float fold8(const float (&v)[2][4], int lane)
+{
+    const bool b0 = lane & 1, b1 = lane & 2, b2 = lane & 4, b3 = lane & 8;
+    float q[2];
+#pragma unroll
+    for (int m = 0; m < 2; ++m) {
+        const float r0 = (b0 ? v[m][2] : v[m][0]) + dpp_move<kQuadXor1>(b0 ? v[m][0] : v[m][2]);
+        const float r1 = (b0 ? v[m][3] : v[m][1]) + dpp_move<kQuadXor1>(b0 ? v[m][1] : v[m][3]);
+        q[m] = (b1 ? r1 : r0) + dpp_move<kQuadXor2>(b1 ? r0 : r1);
+    }
+    const float p = (b3 ? q[1] : q[0]) + dpp_move<kRowRor8>(b3 ? q[0] : q[1]);
+    const float fwd = dpp_move<kRowShl4>(p), back = dpp_move<kRowShr4>(p);
+    return p + (b2 ? back : fwd);
+}
+
 // four consecutive elements of a weight row from element k on, zeros at and past n.  VEC: the row allows one load.
 template <typename T, bool VEC> __device__ __forceinline__ void load4(const T *row, int k, int n, float (&o)[4])
 {

@@ -36,6 +36,11 @@ ATTN_CASES = [
     _cfg(107, "bf16", d=64, T=333, Tq=130, L=1, B=1, H=3),
     _cfg(108, "bf16", d=128, T=64, Tq=64, L=2, B=1, H=1),         # exactly one tile each way
     _cfg(109, "f32", d=64, T=200, Tq=40, L=1, B=1, H=2),          # fp32 storage: many queries on the streaming kernel
+    # 64 units with runs above 320 rows: workgroups of 16 waves, and of 8 where two batches of rows need the registers
+    _cfg(175, "bf16", d=128, T=509, Tq=1, L=1, B=2, H=32),
+    _cfg(176, "bf16", d=128, T=333, Tq=2, L=1, B=2, H=32),
+    _cfg(177, "f32", d=64, T=341, Tq=4, L=1, B=2, H=32),
+    _cfg(178, "f32", d=128, T=400, Tq=1, L=1, B=2, H=32),
 ]
 
 
