@@ -118,16 +118,18 @@ class RowsFrom:
 
 
 def _ptr(t):
+    """A tensor's address as ctypes takes it for a void pointer (an int; no object is built per argument)."""
     if t is None:
         return None
     if isinstance(t, RowsFrom):
-        return ctypes.c_void_p(t.ptr)
+        return t.ptr
     assert t.is_contiguous(), "kvev takes contiguous tensors"
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    # the raw handle of torch's current stream, without building a Stream object around it
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def make_shape(cfg=None, **kw) -> Shape:
