@@ -149,6 +149,8 @@ __global__ __launch_bounds__(256) void fill_zero_kernel(uint4 *p, size_t n16)
     if (i < n16) p[i] = make_uint4(0u, 0u, 0u, 0u);
 }
 
+static int device_compute_units();
+
 static int attention_common(const kvev_shape *sh, const void *Q, int Tq, const void *K, const void *V,
                             const void *Kbar, const void *Vbar, const int32_t *idx, const int32_t *count,
                             int k_cap, int gated, int causal, void *O, void *ws, size_t ws_bytes,
@@ -199,7 +201,7 @@ static int attention_common(const kvev_shape *sh, const void *Q, int Tq, const v
     a.G = sh->H / kv_heads(sh); a.Hkv = kv_heads(sh); a.causal = causal;
     a.T = sh->T; a.T_cap = sh->T_cap; a.N_cap = compact ? k_cap : sh->N_cap; a.k_cap = k_cap;
     a.win0 = win0; a.ring_first = ring_first; a.gated = gated ? 1 : 0;
-    a.nsplit = p.nsplit; a.rows_per_split = p.rows_per_split;
+    a.nsplit = p.nsplit; a.rows_per_split = p.rows_per_split; a.compute_units = device_compute_units();
     // rows that no cache can hold until the next call are read with the streaming hint (256 MB: the memory-side cache)
     a.stream = (size_t)a.S * (size_t)n_rows * sh->d * 2 * (sh->dtype == KVEV_F32 ? 4 : 2) > g_stream_bytes.load(std::memory_order_relaxed) ? 1 : 0;
     a.scale_log2e = (float)(1.4426950408889634 / sqrt((double)sh->d));

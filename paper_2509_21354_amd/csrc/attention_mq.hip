@@ -20,7 +20,7 @@
 //                 give a lane its 8 keys in the order the C layout holds them (the
 //                 contraction index may be permuted freely as long as A and B agree).
 // Online softmax state (m, l) is per query = per lane, shared by 4 lanes through
-// two shuffles; the running output is rescaled only when some maximum moved.
+// two exchanges; the running output is rescaled only when some maximum moved.
 // Query tiles of one sequence sit in neighbouring workgroups of the same XCD, so
 // the second one finds the cache rows in that XCD's L2.
 #include "common.hpp"
@@ -32,8 +32,12 @@ constexpr float kNegBigMq = -1.0e30f;
 typedef short v4i16_t __attribute__((ext_vector_type(4)));
 typedef v4i16_t __attribute__((address_space(3))) lds_v4i16_t;
 
-template <int D, int QS, int NWV = 4>
-__global__ __launch_bounds__(64 * NWV, NWV == 4 ? 2 : 1) void attn_mq_kernel(AttnArgs a, int qtiles, int nblocks)
+// The two kernels below are this body under two register budgets: launches of at most one workgroup per compute unit are
+// latency chains, and the scheduler spends registers on them that would cost a full chip its occupancy (32 sequences x 197
+// queries x 312 rows: 11.6 us with the budget of a full chip, 10.1 us with that of two waves per SIMD; 2048 x 256 queries
+// the other way round: 307 and 358 us).
+template <int D, int QS, int NWV>
+__device__ __forceinline__ void attn_mq_body(const AttnArgs &a, int qtiles, int nblocks)
 {
     constexpr int BN = 64, RP = D + 8, KS = D / 32, DT = D / 16, BM = 16 * NWV * QS, NT = 64 * NWV;
     // V rows are padded by 32 bytes: the transposing load has 16 lanes read 8 bytes each from 4 consecutive
@@ -168,8 +172,7 @@ __global__ __launch_bounds__(64 * NWV, NWV == 4 ? 2 : 1) void attn_mq_kernel(Att
             for (int kt = 0; kt < 4; ++kt)
 #pragma unroll
                 for (int r = 0; r < 4; ++r) mx = fmaxf(mx, st[u][kt][r]);
-            mx = fmaxf(mx, __shfl_xor(mx, 16));
-            mx = fmaxf(mx, __shfl_xor(mx, 32));
+            mx = rows_max(mx);
             const float m_new = fmaxf(m[u], mx);
             if (__any(m_new > m[u])) {
                 const float alpha = __builtin_amdgcn_exp2f((m[u] - m_new) * c);
@@ -214,9 +217,7 @@ __global__ __launch_bounds__(64 * NWV, NWV == 4 ? 2 : 1) void attn_mq_kernel(Att
 
 #pragma unroll
     for (int u = 0; u < QS; ++u) {
-        float l = lsum[u];
-        l += __shfl_xor(l, 16);
-        l += __shfl_xor(l, 32);
+        const float l = rows_sum(lsum[u]);
         if (qrow[u] < R) {
             const float inv = l > 0.f ? 1.0f / l : 0.f;
             bf16_t *Op = static_cast<bf16_t *>(a.O) + orow[u] * D + 4 * g;
@@ -231,11 +232,22 @@ __global__ __launch_bounds__(64 * NWV, NWV == 4 ? 2 : 1) void attn_mq_kernel(Att
     }
 }
 
+template <int D, int QS, int NWV>
+__global__ __launch_bounds__(64 * NWV, NWV == 4 ? 2 : 1) void attn_mq_kernel(AttnArgs a, int qtiles, int nblocks)
+{
+    attn_mq_body<D, QS, NWV>(a, qtiles, nblocks);
+}
+template <int D>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_mq_small_kernel(AttnArgs a, int qtiles, int nblocks)
+{
+    attn_mq_body<D, 1, 4>(a, qtiles, nblocks);
+}
+
 #undef KVEV_MQ_FETCH
 #undef KVEV_MQ_FETCH_RAW
 #undef KVEV_MQ_FETCH_ANY
 
-template <int D, int QS, int NWV = 4>
+template <int D, int QS, int NWV>
 static hipError_t launch_mq_t(const AttnArgs &a, hipStream_t st)
 {
     const int qtiles = (a.G * a.Tq + 16 * NWV * QS - 1) / (16 * NWV * QS);
@@ -245,16 +257,30 @@ static hipError_t launch_mq_t(const AttnArgs &a, hipStream_t st)
     return hipGetLastError();
 }
 
-hipError_t launch_attn_mq(const AttnArgs &a, hipStream_t st)
+template <int D>
+static hipError_t launch_mq_d(const AttnArgs &a, hipStream_t st)
 {
+    const int64_t R = (int64_t)a.G * a.Tq, cus = a.compute_units;
+    // Launches that leave compute units idle with 128 or 256 queries per workgroup take smaller query tiles: 64 queries
+    // while those are at most one workgroup per compute unit (64 sequences x 256 queries x 2048 rows: 41 us, 54 us with
+    // 128 queries, 72 us with 256), then 128 (128 x 256 x 2048: 59 us, 61 us with 64, 74 us with 256).
+    const int64_t tiles64 = a.S * ((R + 63) / 64), tiles128 = a.S * ((R + 127) / 128);
+    if (tiles64 > 0 && tiles64 <= cus) {
+        hipLaunchKernelGGL((attn_mq_small_kernel<D>), dim3((unsigned)tiles64), dim3(256), 0, st, a, (int)((R + 63) / 64), (int)tiles64);
+        return hipGetLastError();
+    }
     // 128 queries per workgroup halve the LDS traffic per flop; frames shorter than
     // that would leave half the waves idle.  Frames of more than 128 queries take workgroups of 8 waves (256 queries):
     // a tile of K and V is then fetched and staged once for all of them, instead of by two workgroups that meet in L2
     // (dense launch at 256 queries and 32768 rows: 11.0 -> 10.0 ms; 10 tiles per workgroup: 290 -> 287 us).
-    const bool wide = a.G * a.Tq > 64;
-    if (a.G * a.Tq > 128) return a.d == 64 ? launch_mq_t<64, 2, 8>(a, st) : launch_mq_t<128, 2, 8>(a, st);
-    if (a.d == 64) return wide ? launch_mq_t<64, 2>(a, st) : launch_mq_t<64, 1>(a, st);
-    return wide ? launch_mq_t<128, 2>(a, st) : launch_mq_t<128, 1>(a, st);
+    if (R <= 64) return launch_mq_t<D, 1, 4>(a, st);
+    if (R <= 128 || tiles128 <= cus) return launch_mq_t<D, 2, 4>(a, st);
+    return launch_mq_t<D, 2, 8>(a, st);
+}
+
+hipError_t launch_attn_mq(const AttnArgs &a, hipStream_t st)
+{
+    return a.d == 64 ? launch_mq_d<64>(a, st) : launch_mq_d<128>(a, st);
 }
 
 }  // namespace kvev

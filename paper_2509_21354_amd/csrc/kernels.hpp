@@ -23,6 +23,7 @@ struct AttnArgs {
     int ring_first;       // compact form: the window buffer is a ring, its token t sits in row (ring_first + t) mod T_cap; else 0
     int gated;            // 1: kept summaries precede the raw rows
     int nsplit, rows_per_split;
+    int compute_units;    // of the device the launch goes to
     int stream;           // 1: the launch reads more than the memory-side cache holds: single-query loads carry the non-temporal hint
     float scale_log2e;    // log2(e) / sqrt(d)
 };

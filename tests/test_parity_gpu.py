@@ -72,8 +72,13 @@ GATED_CASES = [
     _cfg(117, "bf16", d=128, T=2048, C=32, W=256, k=19, Tq=70, L=1, B=2, H=2),   # matrix-core path, gather + window
     _cfg(118, "bf16", d=64, T=700, C=16, W=50, k=300, Tq=16, L=1, B=1, H=3),     # k > N_cand, ragged window
     _cfg(119, "bf16", d=128, T=100, C=32, W=256, k=4, Tq=33, L=1, B=1, H=2),     # no candidate: raw tokens only
-    _cfg(120, "bf16", d=128, T=1500, C=32, W=192, k=21, Tq=200, L=1, B=1, H=3),  # 8-wave workgroups (more than 128 queries)
-    _cfg(121, "bf16", d=64, T=800, C=16, W=70, k=11, Tq=257, L=1, B=1, H=2),     # ... two of them, the second with one query
+    _cfg(120, "bf16", d=128, T=1500, C=32, W=192, k=21, Tq=200, L=1, B=1, H=3),  # more than 128 queries of few sequences: tiles of 64
+    _cfg(121, "bf16", d=64, T=800, C=16, W=70, k=11, Tq=257, L=1, B=1, H=2),     # ... five of them, the last with one query
+    # enough sequences for the query tiles of a full chip: 256, 128 and 64 queries per workgroup
+    _cfg(179, "bf16", d=128, T=200, C=16, W=60, k=5, Tq=200, L=1, B=5, H=26),
+    _cfg(185, "bf16", d=64, T=150, C=16, W=40, k=4, Tq=257, L=1, B=5, H=26),
+    _cfg(186, "bf16", d=128, T=150, C=16, W=40, k=4, Tq=100, L=1, B=5, H=26),
+    _cfg(187, "bf16", d=64, T=100, C=16, W=30, k=3, Tq=17, L=1, B=9, H=32),
 ]
 
 
