@@ -33,6 +33,27 @@ __device__ __forceinline__ void split3_pair(float x0, float x1, uint32_t &hi, ui
     lo = pack_bf16x2(r0 - __uint_as_float(mid << 16), r1 - __uint_as_float(mid & 0xFFFF0000u));
 }
 
+// N partial values per lane (N = 4 or 8) over the four lane rows: afterwards lane row r holds, in v[0], v[1], the results
+// of values 2 r, 2 r + 1 (N = 8) or 2 (r mod 2), 2 (r mod 2) + 1 (N = 4).  op(op(row 0, row 1), op(row 2, row 3)).
+template <int N, class F> __device__ __forceinline__ void rows_fold2(float (&v)[N], F op)
+{
+    static_assert(N == 4 || N == 8, "elements of a lane");
+    float t[N / 2];
+#pragma unroll
+    for (int i = 0; i < N / 2; ++i) {
+        const int lo = i / 2 * 4 + i % 2;
+        float x = v[lo], y = v[lo + 2];
+        swap16(x, y);
+        t[i] = op(x, y);
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        float x = t[i], y = N == 8 ? t[2 + i] : t[i];
+        swap32(x, y);
+        v[i] = op(x, y);
+    }
+}
+
 // NW waves per workgroup: 4 when the launch fills the chip several times over, 16 (one tile row per wave) when
 // there are few tiles, so that a compute unit still has enough loads in flight.
 //
@@ -219,31 +240,26 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 3 : 1) void pool_mfma_kernel(Poo
                     consume(j0, I0{}, I8{});
                 }
             }
+            // over the 4 lane rows, all on the vector unit: a lane is left with 2 neighbouring elements of K and of V, and all
+            // lanes take part in the division and the split.  (Shuffles, 32 per tile row, go through LDS and left 3/4 of the
+            // lanes idle after them: 8 layers x 256 sequences x 256 chunks of 32 1553 -> 1417 us, chunks of 16 1166 -> 1018
+            // us, the mean alone 1453 -> 1411 us; the same bits.)
             const float cf = is_max ? 1.f : (float)a.C;
-#pragma unroll
-            for (int e = 0; e < EPL; ++e) {
-                if (is_max) {
-                    sk[e] = fmaxf(sk[e], __shfl_xor(sk[e], 16)); sk[e] = fmaxf(sk[e], __shfl_xor(sk[e], 32));
-                    sv[e] = fmaxf(sv[e], __shfl_xor(sv[e], 16)); sv[e] = fmaxf(sv[e], __shfl_xor(sv[e], 32));
-                } else {
-                    sk[e] += __shfl_xor(sk[e], 16); sk[e] += __shfl_xor(sk[e], 32);
-                    sv[e] += __shfl_xor(sv[e], 16); sv[e] += __shfl_xor(sv[e], 32);
-                }
-            }
-            if (g4 == 0) {
-#pragma unroll
-                for (int e = 0; e < EPL; e += 2) {
+            auto reduce = [&](float (&v)[EPL], int kv) __attribute__((always_inline)) {
+                if (is_max) rows_fold2(v, [](float x, float y) __attribute__((always_inline)) { return fmaxf(x, y); });
+                else rows_fold2(v, [](float x, float y) __attribute__((always_inline)) { return x + y; });
+                if (EPL == 8 || g4 < 2) {                // (at d = 64 two lane rows hold the same)
                     uint32_t hi, mid, lo;
-                    split3_pair(sk[e] / cf, sk[e + 1] / cf, hi, mid, lo);
-                    *reinterpret_cast<uint32_t *>(xm + ((0 * 2 + 0) * 16 + rt) * XP + n * EPL + e) = hi;
-                    *reinterpret_cast<uint32_t *>(xm + ((1 * 2 + 0) * 16 + rt) * XP + n * EPL + e) = mid;
-                    *reinterpret_cast<uint32_t *>(xm + ((2 * 2 + 0) * 16 + rt) * XP + n * EPL + e) = lo;
-                    split3_pair(sv[e] / cf, sv[e + 1] / cf, hi, mid, lo);
-                    *reinterpret_cast<uint32_t *>(xm + ((0 * 2 + 1) * 16 + rt) * XP + n * EPL + e) = hi;
-                    *reinterpret_cast<uint32_t *>(xm + ((1 * 2 + 1) * 16 + rt) * XP + n * EPL + e) = mid;
-                    *reinterpret_cast<uint32_t *>(xm + ((2 * 2 + 1) * 16 + rt) * XP + n * EPL + e) = lo;
+                    split3_pair(v[0] / cf, v[1] / cf, hi, mid, lo);
+                    bf16_t *dst = xm + (kv * 16 + rt) * XP + n * EPL + 2 * g4;
+                    *reinterpret_cast<uint32_t *>(dst + (size_t)0 * 2 * 16 * XP) = hi;
+                    *reinterpret_cast<uint32_t *>(dst + (size_t)1 * 2 * 16 * XP) = mid;
+                    *reinterpret_cast<uint32_t *>(dst + (size_t)2 * 2 * 16 * XP) = lo;
                 }
-            }
+            };
+            reduce(sk, 0);
+            __builtin_amdgcn_sched_barrier(0);       // (one side after the other: the registers are all taken)
+            reduce(sv, 1);
         }
         __syncthreads();
 
