@@ -12,12 +12,12 @@
 //   * P = 4 workgroups of 4 waves where the launch leaves room for them, else 2 of 8: a wave owns 16 units either way;
 //   * the members of a group sit on one XCD and publish through its L2 (see `near`): an exchange by write-through stores
 //     takes 0.35 us longer;
-//   * 8 bytes per lane carry 4 units of one column, without stamps: |h| <= 1 leaves bit 14 of an fp16 term free (of hi and
-//     of lo), and the first term of every aligned 8-byte word carries a flag there that flips from one use of a slot to
-//     the next.  Two slots by step parity, cleared before the launch: a reader sees the use it waits for, the one before,
-//     or zeros, and one bit tells them apart.  (8 aligned bytes are written and read as one; a slot is rewritten two steps
-//     later, by a workgroup that has seen its partners' h of the step between, whose waves had all read this one: they
-//     publish behind a barrier that follows the reads.);
+//   * 16 bytes per lane carry 4 units of one column as {payload, stamp, payload, stamp} (stamp = step + 1 within the
+//     launch; 8 aligned bytes are written and read as one).  Two slots by step parity, cleared before the launch: a slot
+//     is rewritten two steps later, by a workgroup that has seen its partners' h of the step between, whose waves had all
+//     read this one: they publish behind a barrier that follows the reads.  A whole stamp and not a flag bit that flips
+//     from use to use: plain stores leave memory behind the L2 any number of steps old, and a load that an eviction
+//     sends there must not take such a value for the one it waits for;
 //   * the input projections of the next step are requested in this one, into registers of their own.
 // A step: products over the own units | take the partners' h, stage in LDS | barrier | products over the partners' units |
 // cell, publish, own h to LDS | barrier.  Bounded waits, status word and the layout of weights and projections: as the
@@ -35,9 +35,8 @@ namespace kvev {
 
 namespace {
 constexpr int kDG = 256, kKS = kDG / 32;
-constexpr uint32_t kGroupSlots = 2 * kKS * 1024;             // [parity][member][column 16][own units]
-static_assert(2 * (kGroupSlots + 64) <= kLstmPairExchBytes256, "two groups of 8 and their members' XCDs fit the scratch planned for one of 16");
-constexpr int kHwRegXccId = 20 | (3 << 11);                  // hardware register XCC_ID, bits 0 .. 3
+constexpr uint32_t kGroupSlots = 2 * kDG * 16 * 4;           // [parity][member][column 16][own units], 4 bytes per unit
+static_assert(2 * kGroupSlots <= kLstmPairExchBytes256, "two groups of 8 fit the scratch planned for one of 16");
 }
 
 // P workgroups per group, each with 256 / P hidden units: a wave per 16 of them
@@ -47,7 +46,7 @@ __global__ __launch_bounds__(1024 / P) void lstm_rec_oct_kernel(LstmArgs a, int 
     using G = Geo<kDG>;
     constexpr int kNW = 16 / P, kKH = kKS / P, kKP = kKS - kKH;      // waves; k-steps over own units, over the partners'
     constexpr int kOwn = kDG / P, kOP = kOwn + 8, kPP = kDG - kOwn + 8;     // own units; row pitches in LDS
-    constexpr uint32_t kSlot = 16 * kOwn * sizeof(f16_t);            // one member's h of one step: [column 16][own units]
+    constexpr uint32_t kSlot = 16 * kOwn * 4;                        // one member's h of one step: [column 16][own units]
     constexpr int kLR = kOwn / 4, kRows = 64 / kLR;                  // receiving: lanes per row, rows per wave
     __shared__ __align__(16) f16_t s_h[16 * kOP];            // own units of h, row = column of the operand
     __shared__ __align__(16) f16_t s_p[16 * kPP];            // the partners' units
@@ -105,18 +104,19 @@ __global__ __launch_bounds__(1024 / P) void lstm_rec_oct_kernel(LstmArgs a, int 
     };
     fetch_x(0, xin[0]);
 
-    // Members on one XCD publish with plain stores, which meet the partners' device-scope loads in the L2 that they share
-    // (an L2 cannot pass over its own dirty line); others write through.  Each tells its XCD before the first step.
+    // Members on one XCD publish with plain stores, which meet the partners' device-scope loads in the L2 that they share;
+    // others write through.  Each tells its XCD (plus 1) in the first word of its slot of parity 1, which stays its own
+    // until it publishes step 1, after its partners have read this: to the exchange it is a payload without a stamp.
     const __amdgpu_buffer_rsrc_t e_rsrc = make_rsrc(a.exch + (size_t)gid * kGroupSlots, kGroupSlots);
-    uint32_t *const where = reinterpret_cast<uint32_t *>(a.exch + (size_t)ngroups * kGroupSlots) + (size_t)gid * 16;
+    auto tell_word = [&](int m) { return reinterpret_cast<uint32_t *>(a.exch + (size_t)gid * kGroupSlots + (size_t)(P + m) * kSlot); };
     const uint32_t xcd = 1u + __builtin_amdgcn_s_getreg(kHwRegXccId);
-    if (tid == 0) __hip_atomic_store(where + member, xcd, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    // a look at the partners' slots of parity `par`: this wave takes rows wave * kRows .. of each, 8 bytes per lane
+    if (tid == 0) __hip_atomic_store(tell_word(member), xcd, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    // a look at the partners' slots of parity `par`: this wave takes rows wave * kRows .. of each, 16 bytes per lane
     const int rrow = wave * kRows + lane / kLR, rcol = lane % kLR;       // column of the operand; 4 units from 4 rcol on
-    auto ask = [&](int par, u32x2_t (&v)[P - 1]) __attribute__((always_inline)) {
+    auto ask = [&](int par, u32x4_t (&v)[P - 1]) __attribute__((always_inline)) {
 #pragma unroll
         for (int p = 0; p < P - 1; ++p)
-            v[p] = __builtin_amdgcn_raw_buffer_load_b64(e_rsrc, lane * 8, (int)((par * P + (member + 1 + p) % P) * kSlot + wave * 512), 16);
+            v[p] = __builtin_amdgcn_raw_buffer_load_b128(e_rsrc, (int)lane16, (int)((par * P + (member + 1 + p) % P) * kSlot + wave * 1024), 16);
     };
 
     // h of step t0 - 1, split into two fp16 terms: (hi, lo) pairs of two neighbouring units
@@ -164,7 +164,7 @@ __global__ __launch_bounds__(1024 / P) void lstm_rec_oct_kernel(LstmArgs a, int 
     for (int p = 1; p < P; ++p) {        // (a member that stays silent is taken to be elsewhere: the steps' waits deal with it)
         uint32_t x = 0;
         for (int spin = 0; x == 0 && spin < a.pair_spin_limit; ++spin)
-            x = __hip_atomic_load(where + (member + p) % P, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            x = __hip_atomic_load(tell_word((member + p) % P), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         near = near && x == xcd;
     }
     __syncthreads();
@@ -180,18 +180,16 @@ __global__ __launch_bounds__(1024 / P) void lstm_rec_oct_kernel(LstmArgs a, int 
             a.gate[s * a.N_cap + t0 + step] = sigmoid_hw(u);
         }
     };
-    constexpr uint32_t kFlag = 0x4000u;
     // The partners' h of step tt - 1 into LDS, from a look asked for earlier; more looks follow if it is not there yet.
     // Member 0 also sums up this wave's rows for the utility.
-    auto receive = [&](int tt, u32x2_t (&v)[P - 1]) __attribute__((always_inline)) {
+    auto receive = [&](int tt, u32x4_t (&v)[P - 1]) __attribute__((always_inline)) {
         typedef _Float16 f16x4_t __attribute__((ext_vector_type(4)));
         const int par = (tt - 1) & 1;
-        const uint32_t flag = ((tt - 1) >> 1) & 1 ? 0u : kFlag;
         auto complete = [&]() __attribute__((always_inline)) {
-            uint32_t off = 0;
+            bool ok = true;
 #pragma unroll
-            for (int p = 0; p < P - 1; ++p) off |= v[p][0] ^ flag;
-            return __all((off & kFlag) == 0) != 0;
+            for (int p = 0; p < P - 1; ++p) ok = ok && v[p][1] == (uint32_t)tt && v[p][3] == (uint32_t)tt;
+            return __all(ok) != 0;
         };
         bool got = complete();
         for (int spin = 0; !got && spin < a.pair_spin_limit; ++spin) {
@@ -204,10 +202,7 @@ __global__ __launch_bounds__(1024 / P) void lstm_rec_oct_kernel(LstmArgs a, int 
         float u = 0.f;
 #pragma unroll
         for (int p = 0; p < P - 1; ++p) {
-            uint32_t x = v[p][0] & ~kFlag;
-            // a NaN without its flag bit reads as a magnitude above 1 (exponent 15, a mantissa), which no |h| <= 1 has
-            if ((x & 0x7fffu) > 0x3c00u) x |= kFlag;
-            const u32x2_t o = {x, v[p][1]};
+            const u32x2_t o = {v[p][0], v[p][2]};
             *reinterpret_cast<u32x2_t *>(p_wr + p * kOwn) = o;
             const f16x4_t h4 = __builtin_bit_cast(f16x4_t, o);
 #pragma unroll
@@ -230,7 +225,7 @@ __global__ __launch_bounds__(1024 / P) void lstm_rec_oct_kernel(LstmArgs a, int 
     };
 
     bool failed = false;
-    u32x2_t look[P - 1];
+    u32x4_t look[P - 1];
     // one step; false: a wait in it expired in some wave of the workgroup
     auto step = [&](int tt, auto cur_tag) __attribute__((always_inline)) {
         constexpr int cur = decltype(cur_tag)::value, nxt = cur ^ 1;
@@ -285,11 +280,11 @@ __global__ __launch_bounds__(1024 / P) void lstm_rec_oct_kernel(LstmArgs a, int 
         const u32x2_t mine = gather(hi, lo);
         // to the partner first (the long way), then to this workgroup's own waves
         if (member != a.pair_mute) {
-            const uint32_t flag = (tt >> 1) & 1 ? 0u : kFlag;
-            const u32x2_t out = {(mine[0] & ~kFlag) | flag, mine[1]};
-            const int voff = n * kOwn * 2 + wave * 32 + g4 * 8, soff = (int)((cur * P + member) * kSlot);
-            if (near) __builtin_amdgcn_raw_buffer_store_b64(out, e_rsrc, voff, soff, 0);
-            else __builtin_amdgcn_raw_buffer_store_b64(out, e_rsrc, voff, soff, 16);
+            const uint32_t stamp = (uint32_t)tt + 1;
+            const u32x4_t out = {mine[0], stamp, mine[1], stamp};
+            const int voff = n * kOwn * 4 + wave * 64 + g4 * 16, soff = (int)((cur * P + member) * kSlot);
+            if (near) __builtin_amdgcn_raw_buffer_store_b128(out, e_rsrc, voff, soff, 0);
+            else __builtin_amdgcn_raw_buffer_store_b128(out, e_rsrc, voff, soff, 16);
         }
         *reinterpret_cast<u32x2_t *>(h_wr) = mine;
         upart = rows_sum(upart);
