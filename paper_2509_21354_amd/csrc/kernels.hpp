@@ -85,7 +85,7 @@ inline int lstm_split(int d_g, int L, int BH, int compute_units, bool quad_allow
     return 0;
 }
 // At d_g = 256, launches that fit the chip with two workgroups per 8 sequences take lstm_rec_oct_kernel (four per 8 where
-// that fits too): 1024 sequences x 64 steps 183 us against 249 us on pairs per 16; above, the pairs remain.
+// that fits too): 1024 sequences x 64 steps 224 us against 245 us on pairs per 16; above, the pairs remain.
 inline bool lstm_takes_oct(int L, int BH, int compute_units) { return 2ll * L * ((BH + 7) / 8) <= compute_units; }
 inline size_t lstm_split_exch_bytes(int split, int d_g, int L, int BH, int quad_groups)
 {

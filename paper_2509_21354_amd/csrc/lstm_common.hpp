@@ -63,8 +63,6 @@ __device__ __forceinline__ void lds_barrier()
     asm volatile("" ::: "memory");
 }
 
-constexpr int kHwRegXccId = 20 | (3 << 11);      // operand of s_getreg: hardware register XCC_ID, bits 0 .. 3
-
 constexpr int kScaleBlocks = 32;   // partial maxima of |W_hh| per layer (one per preparation workgroup)
 
 // The power of two s that lifts max |W_hh| of a layer into [2^14, 2^15), from the

@@ -10,23 +10,20 @@
 //     same sums share the four units between them.  Half the matrix work, half the nonlinearities and half the exchange
 //     per group, on compute units that were idle;
 //   * P = 4 workgroups of 4 waves where the launch leaves room for them, else 2 of 8: a wave owns 16 units either way;
-//   * the members of a group sit on one XCD and publish through its L2 (see `near`): an exchange by write-through stores
-//     takes 0.35 us longer;
 //   * 16 bytes per lane carry 4 units of one column as {payload, stamp, payload, stamp} (stamp = step + 1 within the
 //     launch; 8 aligned bytes are written and read as one).  Two slots by step parity, cleared before the launch: a slot
 //     is rewritten two steps later, by a workgroup that has seen its partners' h of the step between, whose waves had all
-//     read this one: they publish behind a barrier that follows the reads.  A whole stamp and not a flag bit that flips
-//     from use to use: plain stores leave memory behind the L2 any number of steps old, and a load that an eviction
-//     sends there must not take such a value for the one it waits for;
+//     read this one: they publish behind a barrier that follows the reads.  Stores write through and loads look past the
+//     caches of one XCD (device scope): the members sit on different ones;
 //   * the input projections of the next step are requested in this one, into registers of their own.
 // A step: products over the own units | take the partners' h, stage in LDS | barrier | products over the partners' units |
 // cell, publish, own h to LDS | barrier.  Bounded waits, status word and the layout of weights and projections: as the
 // paired kernel.
-// Measured (the whole gate call, weights prepared, 32 sequences x 128 steps): 311 us on pairs per 16 sequences; 217 us with
-// P = 2, 186 us with P = 4 (1.26 us per step; 0.95 us with the exchange taken out); P = 4 with write-through stores 232 us.
-// 512 sequences x 64 steps: 184 -> 125 us, x 8 steps: 40 -> 32.5 us; 1024 x 64 (P = 2): 249 -> 183 us.  Reading the matrix
-// operand straight from the slots, with no staging and one barrier less, measured the same (every wave then reads
-// everything past the L1).
+// Measured (the whole gate call, weights prepared, 32 sequences x 128 steps): 304 us on pairs per 16 sequences, 249 us here
+// (P = 4; about 0.95 us of a step are its own work, the rest is the exchange).  512 sequences x 64 steps: 183 -> 160 us,
+// x 8 steps: 40.6 -> 35.6 us; 1024 x 64 (P = 2): 245 -> 224 us.  Members on one XCD that exchange by plain stores through
+// its L2 took 185 us, but publications of that kind were lost under cache pressure (seen in lstm_quad.hip; cause not
+// shown), so all stores write through.
 #include "common.hpp"
 #include "kernels.hpp"
 #include "lstm_common.hpp"
@@ -55,12 +52,9 @@ __global__ __launch_bounds__(1024 / P) void lstm_rec_oct_kernel(LstmArgs a, int 
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n = lane & 15, g4 = lane >> 4, sn = n & 7, hn2 = n >> 3;
-    // The members of a group are 8 apart in the launch order.  Workgroup ids go round-robin over the 8 XCDs, so they are
-    // neighbours in the queue of one XCD: a running member's partner is next in line there.  (Nothing but speed depends
-    // on it: see `near`.)
-    const int gpl = (a.BH + 7) / 8, ngroups = a.L * gpl;
-    const int member = (blockIdx.x / 8) % P, gid = blockIdx.x / (8 * P) * 8 + blockIdx.x % 8;
-    if (gid >= ngroups) return;
+    // The members of a group are neighbours in launch order: where one runs, the others run or are next.
+    const int gpl = (a.BH + 7) / 8;
+    const int member = blockIdx.x % P, gid = blockIdx.x / P;
     const int l = gid / gpl, grp = gid % gpl;
     const bool live = grp * 8 + sn < a.BH;
     const size_t s = (size_t)l * a.BH + min(grp * 8 + sn, a.BH - 1);
@@ -104,13 +98,7 @@ __global__ __launch_bounds__(1024 / P) void lstm_rec_oct_kernel(LstmArgs a, int 
     };
     fetch_x(0, xin[0]);
 
-    // Members on one XCD publish with plain stores, which meet the partners' device-scope loads in the L2 that they share;
-    // others write through.  Each tells its XCD (plus 1) in the first word of its slot of parity 1, which stays its own
-    // until it publishes step 1, after its partners have read this: to the exchange it is a payload without a stamp.
     const __amdgpu_buffer_rsrc_t e_rsrc = make_rsrc(a.exch + (size_t)gid * kGroupSlots, kGroupSlots);
-    auto tell_word = [&](int m) { return reinterpret_cast<uint32_t *>(a.exch + (size_t)gid * kGroupSlots + (size_t)(P + m) * kSlot); };
-    const uint32_t xcd = 1u + __builtin_amdgcn_s_getreg(kHwRegXccId);
-    if (tid == 0) __hip_atomic_store(tell_word(member), xcd, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     // a look at the partners' slots of parity `par`: this wave takes rows wave * kRows .. of each, 16 bytes per lane
     const int rrow = wave * kRows + lane / kLR, rcol = lane % kLR;       // column of the operand; 4 units from 4 rcol on
     auto ask = [&](int par, u32x4_t (&v)[P - 1]) __attribute__((always_inline)) {
@@ -160,13 +148,6 @@ __global__ __launch_bounds__(1024 / P) void lstm_rec_oct_kernel(LstmArgs a, int 
     for (int p = 0; p < P - 1; ++p)
 #pragma unroll
         for (int e = 0; e < 4; ++e) ws_par[p][e] = bf16_to_f32(w_s[(member + 1 + p) % P * kOwn + 4 * rcol + e]);
-    bool near = true;
-    for (int p = 1; p < P; ++p) {        // (a member that stays silent is taken to be elsewhere: the steps' waits deal with it)
-        uint32_t x = 0;
-        for (int spin = 0; x == 0 && spin < a.pair_spin_limit; ++spin)
-            x = __hip_atomic_load(tell_word((member + p) % P), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        near = near && x == xcd;
-    }
     __syncthreads();
 
     // the logit of a step from the shares of all members, by wave 0 of member 0 where it would otherwise wait
@@ -282,9 +263,7 @@ __global__ __launch_bounds__(1024 / P) void lstm_rec_oct_kernel(LstmArgs a, int 
         if (member != a.pair_mute) {
             const uint32_t stamp = (uint32_t)tt + 1;
             const u32x4_t out = {mine[0], stamp, mine[1], stamp};
-            const int voff = n * kOwn * 4 + wave * 64 + g4 * 16, soff = (int)((cur * P + member) * kSlot);
-            if (near) __builtin_amdgcn_raw_buffer_store_b128(out, e_rsrc, voff, soff, 0);
-            else __builtin_amdgcn_raw_buffer_store_b128(out, e_rsrc, voff, soff, 16);
+            __builtin_amdgcn_raw_buffer_store_b128(out, e_rsrc, n * kOwn * 4 + wave * 64 + g4 * 16, (int)((cur * P + member) * kSlot), 16);
         }
         *reinterpret_cast<u32x2_t *>(h_wr) = mine;
         upart = rows_sum(upart);
@@ -323,9 +302,8 @@ __global__ __launch_bounds__(1024 / P) void lstm_rec_oct_kernel(LstmArgs a, int 
 hipError_t launch_lstm_oct(const LstmArgs &a, int t0, int nb, hipStream_t st)
 {
     const int groups = a.L * ((a.BH + 7) / 8);
-    const unsigned wgs = (unsigned)((groups + 7) / 8 * 8);
-    if (4 * groups <= a.compute_units) hipLaunchKernelGGL((lstm_rec_oct_kernel<4>), dim3(4 * wgs), dim3(256), 0, st, a, t0, nb);
-    else hipLaunchKernelGGL((lstm_rec_oct_kernel<2>), dim3(2 * wgs), dim3(512), 0, st, a, t0, nb);
+    if (4 * groups <= a.compute_units) hipLaunchKernelGGL((lstm_rec_oct_kernel<4>), dim3(4 * groups), dim3(256), 0, st, a, t0, nb);
+    else hipLaunchKernelGGL((lstm_rec_oct_kernel<2>), dim3(2 * groups), dim3(512), 0, st, a, t0, nb);
     return hipGetLastError();
 }
 
