@@ -87,6 +87,10 @@ def roof(name, kernel, cost, us, bound, workload=None):
     return r
 
 
+def oct_groups(cfg):
+    return cfg.L * ((cfg.B * cfg.kv_heads + 7) // 8)
+
+
 def rec_kernel_name(cfg):
     groups = cfg.L * ((cfg.B * cfg.kv_heads + 15) // 16)
     if cfg.d_g == 256 and groups >= 257:
@@ -94,6 +98,8 @@ def rec_kernel_name(cfg):
     bh = cfg.B * cfg.kv_heads
     if cfg.d_g == 512 and bh > 16:      # (more groups than fit at once: several launches of the same kernel)
         return f"lstm_quad_kernel<{cfg.d}>"
+    if cfg.d_g == 256 and oct_groups(cfg) <= 128:
+        return f"lstm_rec_oct_kernel<{4 if oct_groups(cfg) <= 64 else 2}>"
     paired = cfg.d_g in (256, 512) and groups <= 128
     return f"lstm_rec_pair_kernel<{cfg.d_g}>" if paired else f"lstm_rec_kernel<{cfg.d_g}>"
 
@@ -101,19 +107,24 @@ def rec_kernel_name(cfg):
 def recurrence_occupancy(cfg, gate_us):
     """The recurrence is N dependent steps on the compute units its sequences occupy, so for small launches its
     share of the whole chip's MFMA peak says little.  This is the local figure: clocks the matrix pipe of an
-    occupied SIMD needs for one step (two fp16 terms per weight fragment, 16 clocks per 16x16x32 instruction,
+    occupied SIMD needs for one step (two fp16 terms per weight fragment, one where they share an instruction, 16 clocks per 16x16x32 instruction,
     2.4 GHz) over the measured time per step (the whole gate call, so a lower bound on the recurrence kernel's own
     utilisation; profiles/mfma_counters.md has the counter-based figure)."""
     groups = cfg.L * ((cfg.B * cfg.kv_heads + 15) // 16)
     paired = rec_kernel_name(cfg).startswith("lstm_rec_pair")
     fused = rec_kernel_name(cfg).startswith("lstm_fused")
     quad = rec_kernel_name(cfg).startswith("lstm_quad")
+    octs = rec_kernel_name(cfg).startswith("lstm_rec_oct")
+    members, seqs = 4 if quad else 2 if paired else 1, 32 if fused or quad else 16
     if fused or quad:              # 32 sequences per workgroup (or four of them), the input projection's MFMAs inside the step
-        members = 4 if quad else 1
         wgs = members * cfg.L * ((cfg.B * cfg.kv_heads + 31) // 32)
         cus, rounds = min(256, wgs), -(-wgs // 256)
         mfma_per_group_step = 2 * (2 * (4 * cfg.d_g // 16) * (cfg.d_g // 32) + (4 * cfg.d_g // 16) * (2 * cfg.d // 32))
         per_simd = mfma_per_group_step / members / 4 * rounds
+    elif octs:      # 8 sequences on 4 or 2 workgroups, both terms of h in one instruction
+        members, seqs = 4 if oct_groups(cfg) <= 64 else 2, 8
+        cus = members * oct_groups(cfg)
+        per_simd = (4 * cfg.d_g // 16) * (cfg.d_g // 32) / members / 4
     else:
         cus = min(256, groups * (2 if paired else 1))
         rounds = -(-groups * (2 if paired else 1) // 256)
@@ -122,7 +133,7 @@ def recurrence_occupancy(cfg, gate_us):
     us_step = gate_us / cfg.N
     busy_us = per_simd * 16 / 2400.0
     return {"dependent_steps": cfg.N, "us_per_step": round(us_step, 3), "compute_units_occupied": cus,
-            "workgroups_per_sequence_group": 4 if quad else 2 if paired else 1, "sequences_per_group": 32 if fused or quad else 16,
+            "workgroups_per_sequence_group": members, "sequences_per_group": seqs,
             "mfma_pipe_us_per_step_per_simd": round(busy_us, 3), "mfma_pipe_busy_frac_of_occupied_simds": round(busy_us / us_step, 3)}
 
 
