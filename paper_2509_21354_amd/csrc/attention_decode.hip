@@ -314,7 +314,9 @@ __global__ __launch_bounds__(64 * NW) void attn_decode_kernel(AttnArgs a)
     // partial stores are acknowledged, then draws its ticket; the workgroup that draws number nsplit - 1 therefore
     // knows that all partials are in memory.  The merge walks the splits in their own order, whoever arrived last.
     __shared__ int s_last;
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");       // this thread's stores have completed
+    // The wait is spelled out: neither relaxed device-scope stores nor a workgroup-scope release make the compiler wait for
+    // vector stores, and the ticket is drawn by one wave for all of them.
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");              // this wave's stores have completed
     __syncthreads();
     int32_t *ticket = a.tickets + ((size_t)s * qgroups + qg);
     if (tid == 0)
