@@ -775,8 +775,10 @@ __global__ __launch_bounds__(512) void lstm_rec_pair_kernel(LstmArgs a, int t0, 
         for (int ut = 0; ut < UT; ++ut) {
             *reinterpret_cast<f16x4_t *>(h_own + (size_t)(nxt * 2 + 0) * 16 * HP + ut * 16) = hi[ut];
             *reinterpret_cast<f16x4_t *>(h_own + (size_t)(nxt * 2 + 1) * 16 * HP + ut * 16) = lo[ut];
-            if (tt == nb - 1 && live)
-                *reinterpret_cast<float4 *>(a.h + s * DG + (tile0 + ut) * 16 + 4 * g4) = make_float4(hv[ut][0], hv[ut][1], hv[ut][2], hv[ut][3]);
+            if (tt == nb - 1) {      // nobody reads the last step's h as an operand: its fp32 bits wait here for the end
+                *reinterpret_cast<f16x4_t *>(h_own + (size_t)(nxt * 2 + 0) * 16 * HP + ut * 16) = __builtin_bit_cast(f16x4_t, make_float2(hv[ut][0], hv[ut][1]));
+                *reinterpret_cast<f16x4_t *>(h_own + (size_t)(nxt * 2 + 1) * 16 * HP + ut * 16) = __builtin_bit_cast(f16x4_t, make_float2(hv[ut][2], hv[ut][3]));
+            }
         }
         s_up[cur][wave][lane] = upart;
         if (tt > 0) write_util(nxt, tt - 1);       // both halves of step tt - 1 have been in LDS since this step's first barrier
@@ -789,6 +791,18 @@ __global__ __launch_bounds__(512) void lstm_rec_pair_kernel(LstmArgs a, int t0, 
         lds_barrier();
         failed = s_fail != 0;
         if (!failed) write_util((nb - 1) & 1, nb - 1);
+    }
+    // The state leaves the kernel as fp32, and not before this point: a member reads the partner's half of a.h when it
+    // starts, and only the partner's publication, received above, says that it has done so (a launch of one step receives
+    // nothing before its last one).
+    if (!failed && live) {
+#pragma unroll
+        for (int ut = 0; ut < UT; ++ut) {
+            const f16_t *last = h_own + (size_t)((nb & 1) * 2) * 16 * HP + ut * 16;
+            const float2 h01 = __builtin_bit_cast(float2, *reinterpret_cast<const f16x4_t *>(last));
+            const float2 h23 = __builtin_bit_cast(float2, *reinterpret_cast<const f16x4_t *>(last + (size_t)16 * HP));
+            *reinterpret_cast<float4 *>(a.h + s * DG + (tile0 + ut) * 16 + 4 * g4) = make_float4(h01.x, h01.y, h23.x, h23.y);
+        }
     }
     if (live) {
 #pragma unroll

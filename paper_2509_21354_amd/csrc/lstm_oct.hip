@@ -269,7 +269,7 @@ __global__ __launch_bounds__(1024 / P) void lstm_rec_oct_kernel(LstmArgs a, int 
         upart = rows_sum(upart);
         upart += dpp_move<kRowRor8>(upart);
         if (lane < 8) s_up[cur][wave][lane] = upart;
-        if (tt == nb - 1 && live) *reinterpret_cast<float2 *>(a.h + s * kDG + unit0) = make_float2(hv[0], hv[1]);
+        if (tt == nb - 1) *reinterpret_cast<u32x2_t *>(h_wr) = u32x2_t{__float_as_uint(hv[0]), __float_as_uint(hv[1])};     // nobody reads it as an operand: see the end
         lds_barrier();
         return true;
     };
@@ -285,6 +285,13 @@ __global__ __launch_bounds__(1024 / P) void lstm_rec_oct_kernel(LstmArgs a, int 
         lds_barrier();
         failed = s_fail != 0;
         if (!failed && member == 0 && wave == 0) write_util(nb - 1);
+    }
+    // The state leaves the kernel as fp32, and not before this point: a member reads the partners' units of a.h when it
+    // starts, and only their publications, received above, say that they have all done so (a launch of one step receives
+    // nothing before its last one).
+    if (!failed && live) {
+        const u32x2_t hb = *reinterpret_cast<const u32x2_t *>(h_wr);      // (as the last step left it in LDS)
+        *reinterpret_cast<float2 *>(a.h + s * kDG + unit0) = make_float2(__uint_as_float(hb[0]), __uint_as_float(hb[1]));
     }
     if (live) {
 #pragma unroll

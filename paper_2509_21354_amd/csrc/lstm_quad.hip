@@ -404,8 +404,8 @@ __global__ __launch_bounds__(512) void lstm_quad_kernel(LstmArgs a, int t0, int 
             if (member != a.pair_mute)         // device scope: the store writes through to where the partners' loads look
                 __builtin_amdgcn_raw_buffer_store_b128(line, e_rsrc, (int)lane16, (int)off, 16);
             put_h(0, sb, hi, lo);
-            if (tt == nb - 1 && live[sb])        // the state leaves the kernel as fp32
-                *reinterpret_cast<float4 *>(a.h + sq[sb] * DG + tile * 16 + 4 * g4) = make_float4(hv[0], hv[1], hv[2], hv[3]);
+            if (tt == nb - 1)        // nobody reads the last step's h as an operand: its fp32 bits wait here for the end
+                put_h(0, sb, __builtin_bit_cast(f16x4_t, make_float2(hv[0], hv[1])), __builtin_bit_cast(f16x4_t, make_float2(hv[2], hv[3])));
             s_up[((cur * NW + wave) * SB + sb) * 64 + lane] = upart;
         }
         if (tt > 0) write_util(nxt, tt - 1);       // all quarters of step tt - 1 have been in LDS since this step's first barrier
@@ -420,6 +420,18 @@ __global__ __launch_bounds__(512) void lstm_quad_kernel(LstmArgs a, int t0, int 
         lds_barrier();
         failed = s_fail != 0;
         if (!failed) write_util((nb - 1) & 1, nb - 1);
+    }
+    // The state leaves the kernel as fp32, and not before this point: a member reads the partners' quarters of a.h when it
+    // starts, and only their publications, received above, say that they have all done so (a launch of one step receives
+    // nothing before its last one).
+    if (!failed) {
+#pragma unroll
+        for (int sb = 0; sb < SB; ++sb)
+            if (live[sb]) {
+                const float2 lo2 = __builtin_bit_cast(float2, *reinterpret_cast<const f16x4_t *>(h_wr[0] + ((size_t)0 * SEQ + sb * 16) * HP));
+                const float2 hi2 = __builtin_bit_cast(float2, *reinterpret_cast<const f16x4_t *>(h_wr[0] + ((size_t)1 * SEQ + sb * 16) * HP));
+                *reinterpret_cast<float4 *>(a.h + sq[sb] * DG + tile * 16 + 4 * g4) = make_float4(lo2.x, lo2.y, hi2.x, hi2.y);
+            }
     }
 #pragma unroll
     for (int sb = 0; sb < SB; ++sb)

@@ -501,6 +501,111 @@ def test_lstm_gate_eight_sequences_per_group(cfg):
         assert np.abs(got.cpu().numpy() - ref).max() <= tol
 
 
+def gate_form(cfg):
+    """Which workgroups share a group of sequences in the gate (bf16): (members, sequences per group), by the rule of the
+    library's dispatch at this device's compute units.  (1, ..) stands for every form on one workgroup."""
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    bh = cfg.B * cfg.kv_heads
+    groups8, groups16 = cfg.L * ((bh + 7) // 8), cfg.L * ((bh + 15) // 16)
+    if cfg.d_g == 512 and bh > 16:
+        return 4, 32
+    if cfg.d_g == 256 and 4 * groups8 <= cus:
+        return 4, 8
+    if cfg.d_g == 256 and 2 * groups8 <= cus:
+        return 2, 8
+    return (2, 16) if cfg.d_g in (256, 512) and 2 * groups16 <= cus else (1, 16)
+
+
+# one case per form in which workgroups hand each other h
+SHARED_CASES = [
+    (_cfg(251, "bf16", d=128, T=6 * 32, C=32, d_g=256, L=4, B=1, H=125), (4, 8)),       # 64 groups: a workgroup per compute unit
+    (_cfg(252, "bf16", d=64, T=6 * 32, C=32, d_g=256, L=13, B=1, H=37), (2, 8)),
+    (_cfg(253, "bf16", d=128, T=6 * 32, C=32, d_g=256, L=13, B=5, H=15), (2, 16)),      # 65 groups, 75 sequences per layer: the last one ragged
+    (_cfg(254, "bf16", d=64, T=6 * 32, C=32, d_g=512, L=9, B=1, H=13), (2, 16)),
+    (_cfg(255, "bf16", d=128, T=6 * 32, C=32, d_g=512, L=2, B=5, H=16), (4, 32)),
+]
+
+
+@pytest.mark.parametrize("cfg,form", SHARED_CASES, ids=lambda c: getattr(c, "name", str(c)))
+def test_lstm_gate_one_step_per_call(cfg, form):
+    """A range walked one step per call: every launch reads the carried h of all members' units and replaces it, and
+    receives nothing before its only step.  The same bits as one call, and the oracle's."""
+    assert gate_form(cfg) == form
+    N = cfg.T // cfg.C
+    w = synth.make_weights(cfg, "cpu")
+    Kbar, Vbar = _summaries(cfg, N)
+    sh = kb.make_shape(cfg, N_cap=N)
+    lead = (cfg.L, cfg.B, cfg.H)
+    gw = dev(w)
+    Kb, Vb = Kbar.cuda(), Vbar.cuda()
+    outs = []
+    for cuts in ([(0, N)], [(t, t + 1) for t in range(N)]):
+        ws = kb.alloc_workspace(kb.workspace_bytes(kb.OP_LSTM_GATE, sh, N))
+        h = torch.full(lead + (cfg.d_g,), 7.0, device="cuda")
+        c = torch.full_like(h, float("nan"))
+        util = torch.full(lead + (N,), 9.0, device="cuda")
+        gate = torch.full_like(util, 9.0)
+        for a, b in cuts:
+            kb.kvev_lstm_gate(sh, Kb, Vb, kb.lstm_weights(gw), a, b, h, c, util, gate, ws)
+        torch.cuda.synchronize()
+        assert int(ws[:4].view(torch.int32).item()) == 0
+        outs.append((h, c, util, gate))
+    for x, y in zip(*outs):
+        assert torch.equal(x, y)
+    rh, rc, ru, rg = orc.lstm_gate(Kbar, Vbar, kb.lstm_weights(w), 0, N)
+    for got, ref, tol in zip(outs[1], (rh, rc, ru, rg), (SCORE_TOL, 2 * SCORE_TOL, SCORE_TOL, SCORE_TOL)):
+        assert np.abs(got.cpu().numpy() - ref).max() <= tol
+
+
+@pytest.mark.parametrize("cfg,form", SHARED_CASES, ids=lambda c: getattr(c, "name", str(c)))
+def test_lstm_gate_replaces_h_only_after_hearing_from_all_members(cfg, form):
+    """The members of a group read each other's units of the carried h when they start, and only a member's publication
+    says that it has.  So no member may replace its units before it has heard from all others: with one member's
+    publications withheld in a call of one step, the others must leave theirs as they were.  (The silent member hears
+    from everybody and completes.)"""
+    assert gate_form(cfg) == form
+    N, t = 3, 2
+    members, width = form[0], cfg.d_g // form[0]
+    w = synth.make_weights(cfg, "cpu")
+    Kbar, Vbar = _summaries(cfg, N)
+    sh = kb.make_shape(cfg, N_cap=N, T=N * cfg.C)
+    lead = (cfg.L, cfg.B, cfg.H)
+    gw = dev(w)
+    Kb, Vb = Kbar.cuda(), Vbar.cuda()
+    ws = kb.alloc_workspace(kb.workspace_bytes(kb.OP_LSTM_GATE, sh, N))
+    h0 = torch.zeros(lead + (cfg.d_g,), device="cuda")
+    c0 = torch.zeros_like(h0)
+    util = torch.zeros(lead + (N,), device="cuda")
+    gate = torch.zeros_like(util)
+    kb.kvev_lstm_gate(sh, Kb, Vb, kb.lstm_weights(gw), 0, t, h0, c0, util, gate, ws)
+    torch.cuda.synchronize()
+
+    def step():
+        h, c = h0.clone(), c0.clone()
+        kb.kvev_lstm_gate(sh, Kb, Vb, kb.lstm_weights(gw), t, t + 1, h, c, util, gate, ws)
+        torch.cuda.synchronize()
+        return h, c, int(ws[:4].view(torch.int32).item())
+
+    good_h, good_c, status = step()
+    assert status == 0
+    for mute in (0, 1):
+        kb.kvev_debug_pair_wait(4096, mute)
+        try:
+            h, c, status = step()
+        finally:
+            kb.kvev_debug_pair_wait()
+        assert status == 1
+        ws[:4].zero_()
+        for m in range(members):
+            u = slice(m * width, (m + 1) * width)
+            if m == mute:
+                assert torch.equal(c[..., u], good_c[..., u]) and torch.equal(h[..., u], good_h[..., u])
+            else:
+                assert torch.isnan(c[..., u]).all() and torch.equal(h[..., u], h0[..., u])
+    h, c, status = step()
+    assert status == 0 and torch.equal(h, good_h) and torch.equal(c, good_c)
+
+
 WAIT_CASES = [
     _cfg(151, "bf16", d=64, T=320, C=32, d_g=256, L=1, B=1, H=5),         # a pair of workgroups
     _cfg(156, "bf16", d=64, T=320, C=32, d_g=512, L=1, B=1, H=20),        # four workgroups per 32 sequences
