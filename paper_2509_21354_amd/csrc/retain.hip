@@ -15,9 +15,12 @@
 // in batches of destination slots: every source of a batch is read into
 // registers before the batch is written, and a batch only overwrites slots
 // below the sources that later batches still need.
-// Measured (from graphs): 512 sequences, 240 new chunks into a store of 64: 24.2 ->
-// 10.4 us, 8 new ones: 9.0 -> 6.4 us; 64 sequences, 1000 into 128: 154 -> 18 us (the
-// ranks were found by counting, and rows moved 32 at a time, also those that stay).
+// Measured (from graphs; ranks by counting and 32 rows per pass, also those that stay -> now): 512 sequences, 240 new
+// chunks into a store of 64: 13.9 -> 10.6 us, 8 new ones into a full store: 8.6 -> 6.9 us; 64 sequences, 1000 into 128:
+// 111 -> 13.7 us; 8192 sequences (bound by HBM), 248 into 64: 121 -> 119 us, 8 into a full store: 92 -> 80 us; 2048
+// sequences, 1000 into 256: 310 -> 124 us.  The bound of 8 waves per SIMD keeps the scheduler from holding the search
+// and all the row addresses in registers at once: without it the kernel takes 124 registers (244 for more than 512
+// candidates) and those three take 136, 94 and 171 us.
 #include "common.hpp"
 #include "kernels.hpp"
 #include "topk.hpp"
@@ -30,7 +33,7 @@ constexpr int kRetainPieces = 4;      // 16-byte pieces per thread, tensor and p
 
 // KPL, NW: see topk.hpp.  NW = 1: every wave finds the best k by itself (up to 1024 candidates), which costs no barrier.
 template <int KPL, int NW>
-__global__ __launch_bounds__(256) void retain_kernel(RetainArgs a)
+__global__ __launch_bounds__(256, 8) void retain_kernel(RetainArgs a)
 {
     static_assert(NW == 1 || NW == 4, "one wave each, or the workgroup");
     using Top = TopK<KPL, NW>;
@@ -88,25 +91,24 @@ __global__ __launch_bounds__(256) void retain_kernel(RetainArgs a)
     const unsigned char *Vn = static_cast<const unsigned char *>(a.Vn) + (size_t)s * a.n_new_cap * a.row_bytes;
     for (int p0 = 0; p0 < kept; p0 += batch) {
         piece_t rk[kRetainPieces], rv[kRetainPieces];
-        size_t to[kRetainPieces];
+        uint32_t to[kRetainPieces];          // (byte offset in a store of at most 4000 rows)
         const int pieces = min(batch, kept - p0) << vec_shift;
 #pragma unroll
         for (int i = 0; i < kRetainPieces; ++i) {
             const int e = tid + 256 * i, p = p0 + (e >> vec_shift), off = (e & ((1 << vec_shift) - 1)) * 16;
             const int c = e < pieces ? s_src[p] : p;
-            to[i] = ~(size_t)0;
+            to[i] = ~0u;
             if (e < pieces && (c != p || c >= cnt)) {           // (slot p < cnt with c == p: an old row that stays)
-                to[i] = (size_t)p * a.row_bytes + off;
-                const unsigned char *sk = c < cnt ? Kc + (size_t)c * a.row_bytes : Kn + (size_t)(c - cnt) * a.row_bytes;
-                const unsigned char *sv = c < cnt ? Vc + (size_t)c * a.row_bytes : Vn + (size_t)(c - cnt) * a.row_bytes;
-                rk[i] = *reinterpret_cast<const piece_t *>(sk + off);
-                rv[i] = *reinterpret_cast<const piece_t *>(sv + off);
+                to[i] = (uint32_t)(p * a.row_bytes + off);
+                const uint32_t from = (uint32_t)((c < cnt ? c : c - cnt) * a.row_bytes + off);
+                rk[i] = *reinterpret_cast<const piece_t *>((c < cnt ? Kc : Kn) + from);
+                rv[i] = *reinterpret_cast<const piece_t *>((c < cnt ? Vc : Vn) + from);
             }
         }
         __syncthreads();
 #pragma unroll
         for (int i = 0; i < kRetainPieces; ++i) {
-            if (to[i] != ~(size_t)0) {
+            if (to[i] != ~0u) {
                 *reinterpret_cast<piece_t *>(Kc + to[i]) = rk[i];
                 *reinterpret_cast<piece_t *>(Vc + to[i]) = rv[i];
             }
