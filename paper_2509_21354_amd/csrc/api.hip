@@ -53,7 +53,9 @@ static int n_cand_of(const kvev_shape *sh) { return (sh->T > sh->W ? sh->T - sh-
 // workgroup's own start-up: one or two rounds of row loads.
 // Scratch: one ticket (int32) per (key-value sequence, query group), padded to
 // 256 bytes, then the split partials.
-struct AttnPlan { int nsplit, rows_per_split; size_t ticket_bytes, ws_bytes; };
+// ws_reported: what covers ws_bytes of this and of every smaller number of raw rows, so that a caller who sized its
+// scratch at capacity can use it at any length (runs are rounded to 16 rows, so fewer may be needed for more rows).
+struct AttnPlan { int nsplit, rows_per_split; size_t ticket_bytes, ws_bytes, ws_reported; };
 
 static int env_int(const char *name, int dflt)
 {
@@ -89,18 +91,20 @@ static AttnPlan plan_attn(const kvev_shape *sh, int Tq, int n_rows)
     const bool few = units < 256;
     const int target = g_attn_target_blocks > 0 ? g_attn_target_blocks : few ? 256 : 1024;
     const int min_rows = g_attn_min_rows > 0 ? g_attn_min_rows : units < 64 ? 64 : few ? 1024 : 512;
-    int64_t want = (target + units - 1) / units;
-    int64_t most = (n_rows + min_rows - 1) / min_rows;
-    if (want > most) want = most;
-    if (want > KVEV_ATTN_MAX_SPLIT) want = KVEV_ATTN_MAX_SPLIT;
-    if (want < 1) want = 1;
+    auto runs = [&](int64_t rows) {
+        const int64_t n = std::min((target + units - 1) / units, (rows + min_rows - 1) / min_rows);
+        return std::max<int64_t>(std::min<int64_t>(n, KVEV_ATTN_MAX_SPLIT), 1);
+    };
+    const int64_t want = runs(n_rows);
     int rps = (int)((n_rows + want - 1) / want);
     rps = (rps + 15) / 16 * 16;
     if (rps < 16) rps = 16;
     p.rows_per_split = rps;
     p.nsplit = n_rows > 0 ? (n_rows + rps - 1) / rps : 1;
     p.ticket_bytes = ((size_t)units * sizeof(int32_t) + 255) / 256 * 256;
-    p.ws_bytes = p.nsplit > 1 ? p.ticket_bytes + (size_t)sq * p.nsplit * (sh->d + 2) * sizeof(float) : 0;
+    auto scratch = [&](int64_t n) { return n > 1 ? p.ticket_bytes + (size_t)sq * n * (sh->d + 2) * sizeof(float) : (size_t)0; };
+    p.ws_bytes = scratch(p.nsplit);
+    p.ws_reported = scratch(want);
     return p;
 }
 
@@ -177,7 +181,7 @@ static int attention_common(const kvev_shape *sh, const void *Q, int Tq, const v
     if (causal && Tq > sh->T - win0) return KVEV_ERR_INVALID_ARG;      // the frame must lie inside the raw rows
     // a frame of queries on bf16 storage goes to the matrix-core kernel (no split, no scratch)
     const bool mq = attn_takes_mq(sh, Tq);
-    const AttnPlan p = mq ? AttnPlan{1, n_rows, 0, 0} : plan_attn(sh, Tq, sh->T - win0);     // (split by the raw rows)
+    const AttnPlan p = mq ? AttnPlan{1, n_rows, 0, 0, 0} : plan_attn(sh, Tq, sh->T - win0);     // (split by the raw rows)
     if (static_ws) {
         // the library's own array stands in for the caller's scratch; its tickets are cleared on every call, so
         // nothing is assumed about what the call before left there
@@ -608,13 +612,13 @@ size_t kvev_workspace_bytes(int op, const kvev_shape *sh, int n, int k_cap)
         const int ncand = n_cand_of(sh);
         const int kmax = k_cap < ncand ? k_cap : ncand;
         (void)kmax;
-        return attn_takes_mq(sh, n) ? 0 : plan_attn(sh, n, sh->T - ncand * sh->C).ws_bytes;
+        return attn_takes_mq(sh, n) ? 0 : plan_attn(sh, n, sh->T - ncand * sh->C).ws_reported;
     }
     case KVEV_OP_DENSE_ATTENTION:
-        return attn_takes_mq(sh, n) ? 0 : plan_attn(sh, n, sh->T).ws_bytes;
+        return attn_takes_mq(sh, n) ? 0 : plan_attn(sh, n, sh->T).ws_reported;
     case KVEV_OP_COMPACT_ATTENTION:
         if (k_cap < 0) return 0;
-        return attn_takes_mq(sh, n) ? 0 : plan_attn(sh, n, sh->T).ws_bytes;
+        return attn_takes_mq(sh, n) ? 0 : plan_attn(sh, n, sh->T).ws_reported;
     default:
         return 0;
     }

@@ -156,6 +156,15 @@ def test_pointer_range_and_mode_validation():
     assert L.kvev_select(r, None, FAKE, kb.SELECT_THRESHOLD, 0, float("nan"), 120, FAKE, FAKE, None) == kb.ERR_INVALID_ARG
 
 
+@pytest.mark.parametrize("H", [1, 3, 16, 32, 63, 64, 72, 96, 128, 129, 200, 255, 256, 400])
+@pytest.mark.parametrize("dtype,d", [(kb.BF16, 128), (kb.BF16, 64), (kb.F32, 128)])
+def test_attention_scratch_never_shrinks_with_the_rows(H, dtype, d):
+    """A cache grows, its scratch is sized once, at capacity: what the query reports covers every shorter length."""
+    need = [kb.workspace_bytes(kb.OP_DENSE_ATTENTION, kb.make_shape(L=1, B=1, H=H, d=d, T=T, T_cap=5000, C=32, N_cap=200, W=64, d_sum=64,
+                                                                    d_g=64, dtype=dtype), 1) for T in range(1, 5000, 7)]
+    assert all(a <= b for a, b in zip(need, need[1:]))
+
+
 def test_workspace_query():
     L_ = kb.lib()
     sh = _shape()

@@ -62,6 +62,23 @@ def test_dense_attention(cfg):
     assert torch.equal(O.view(torch.uint8), O2.view(torch.uint8))
 
 
+@pytest.mark.parametrize("H,dtype", [(64, "bf16"), (96, "f32"), (16, "bf16")])
+def test_attention_scratch_sized_at_capacity(H, dtype):
+    """Scratch sized for a cache's capacity serves every shorter length: the runs that a launch is cut into do not grow
+    with the rows everywhere."""
+    T_cap = 1500
+    cfg = _cfg(261, dtype, d=128, T=T_cap, L=1, B=1, H=H)
+    t = synth.make_qkv(cfg, "cpu")
+    g = dev(t)
+    ws = kb.alloc_workspace(kb.workspace_bytes(kb.OP_DENSE_ATTENTION, kb.make_shape(cfg), 1))
+    for T in (1500, 1024, 1000, 700, 513, 100):
+        sh = kb.make_shape(cfg, T=T, T_cap=T_cap, N_cap=T_cap // cfg.C)
+        O = torch.full_like(g["Q"], 7.0)
+        kb.kvev_dense_attention(sh, g["Q"], 1, g["K"], g["V"], O, ws)
+        torch.cuda.synchronize()
+        assert_close_storage(O, orc.dense_attention(t["Q"], t["K"], t["V"], T), dtype, f"dense O, {T} rows")
+
+
 GATED_CASES = [
     _cfg(111, "f32", d=64, T=1024, C=16, W=64, k=16),
     _cfg(112, "bf16", d=128, T=1000, C=32, W=100, k=9, Tq=2),    # T, W not multiples of C
