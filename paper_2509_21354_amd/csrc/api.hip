@@ -54,7 +54,7 @@ static int n_cand_of(const kvev_shape *sh) { return (sh->T > sh->W ? sh->T - sh-
 // Scratch: one ticket (int32) per (key-value sequence, query group), padded to
 // 256 bytes, then the split partials.
 // ws_reported: what covers ws_bytes of this and of every smaller number of raw rows, so that a caller who sized its
-// scratch at capacity can use it at any length (runs are rounded to 16 rows, so fewer may be needed for more rows).
+// scratch at capacity can use it at any length (runs are rounded to 16 rows, and long runs can be fewer than short ones).
 struct AttnPlan { int nsplit, rows_per_split; size_t ticket_bytes, ws_bytes, ws_reported; };
 
 static int env_int(const char *name, int dflt)
@@ -64,11 +64,23 @@ static int env_int(const char *name, int dflt)
 }
 // Tuning knobs (environment, read once; unset = the rule below): workgroups wanted per launch and the smallest
 // run of raw rows worth a workgroup.  The rule: with fewer key-value units than compute units the launch is filled
-// with up to one workgroup per compute unit; a run is at least 64 rows (one batch of a 4-wave workgroup) while there
-// are fewer than 64 units, 1024 rows above: from 64 units on the merge of a split costs more than it saves on a short
-// cache (64 x 283 rows: 8.2 us in 4 runs, 7.4 us in one; 128 x 1000 rows: 17.4 us in 2 runs, 15.8 us in one; 48 x 283
-// rows: 6.6 us in 5 runs, 6.9 us in one).  With more units than compute units, four 4-wave workgroups per compute unit
-// and runs of at least 512 rows.
+// with up to one workgroup per compute unit.
+//   * Fewer than 64 units: runs of at least 64 rows (one batch of a 4-wave workgroup; 48 units x 283 rows: 6.6 us in 5
+//     runs, 6.9 us in one).
+//   * From 64 units on the merge of a split costs more than it saves on a short cache, and the more units share the
+//     memory, the longer a run pays to be: up to 1024 rows in one run (64 units x 283 rows, bf16, d = 128: 8.5 us in 4
+//     runs, 7.8 us in one; 128 x 700: 16.2 us in 2, 15.2 us in one; 240 x 1000: 29.7 us in 2, 28.3 us in one), then runs
+//     of at least 1024.
+//   * But up to 128 units, when a unit has more than kSplitRows rows and they take more than kSplitBytes times the number
+//     of units, as many runs as the compute units take at once: one workgroup per unit then leaves too much of the chip
+//     idle for too long (one run against 2 to 4: bf16 64 x 620 rows 10.5 and 9.8 us, 64 x 1000 14.8 and 11.7 us, 72 x 850
+//     14.4 and 12.0 us, 96 x 1000 18.7 and 16.5 us; fp32 64 x 1000 24.8 and 16.9 us, 96 x 610 17.4 and 15.6 us, 128 x 650
+//     24.4 and 21.5 us.  Short of either border one run is the faster or about the same: bf16 96 x 700 12.4 and 13.8 us,
+//     112 x 700 14.0 and 15.2 us, 64 x 512 9.5 and 9.3 us; fp32 64 x 350 9.3 and 10.3 us.  One run more than fits at once:
+//     fp32 72 x 601 14.6 us, 13.7 us with as many as fit).  Above 1024 rows the runs of at least 1024 are as good or
+//     better (64 x 1500: 14.8 us in 2 runs, 15.6 us in 4).
+// With more units than compute units, four 4-wave workgroups per compute unit and runs of at least 512 rows.
+constexpr int64_t kSplitRows = 600, kSplitBytes = 4864;
 static const int g_attn_target_blocks = env_int("KVEV_ATTN_TARGET_BLOCKS", -1);
 static const int g_attn_min_rows = env_int("KVEV_ATTN_MIN_ROWS", -1);
 // large pooling launches write their summaries once per 2^shift ticks of the 100 MHz real-time counter: 8192 ticks
@@ -90,9 +102,11 @@ static AttnPlan plan_attn(const kvev_shape *sh, int Tq, int n_rows)
     const int64_t sq = (int64_t)sh->L * sh->B * sh->H * (Tq > 0 ? Tq : 1);
     const bool few = units < 256;
     const int target = g_attn_target_blocks > 0 ? g_attn_target_blocks : few ? 256 : 1024;
-    const int min_rows = g_attn_min_rows > 0 ? g_attn_min_rows : units < 64 ? 64 : few ? 1024 : 512;
+    const int64_t row_bytes = (int64_t)sh->d * 2 * (sh->dtype == KVEV_F32 ? 4 : 2);
     auto runs = [&](int64_t rows) {
-        const int64_t n = std::min((target + units - 1) / units, (rows + min_rows - 1) / min_rows);
+        const bool large = g_attn_min_rows <= 0 && units >= 64 && units <= 128 && rows > kSplitRows && rows <= 1024 && rows * row_bytes > units * kSplitBytes;
+        const int64_t min_rows = g_attn_min_rows > 0 ? g_attn_min_rows : units < 64 || large ? 64 : few ? 1024 : 512;
+        const int64_t n = std::min(large ? target / units : (target + units - 1) / units, (rows + min_rows - 1) / min_rows);
         return std::max<int64_t>(std::min<int64_t>(n, KVEV_ATTN_MAX_SPLIT), 1);
     };
     const int64_t want = runs(n_rows);
@@ -104,7 +118,7 @@ static AttnPlan plan_attn(const kvev_shape *sh, int Tq, int n_rows)
     p.ticket_bytes = ((size_t)units * sizeof(int32_t) + 255) / 256 * 256;
     auto scratch = [&](int64_t n) { return n > 1 ? p.ticket_bytes + (size_t)sq * n * (sh->d + 2) * sizeof(float) : (size_t)0; };
     p.ws_bytes = scratch(p.nsplit);
-    p.ws_reported = scratch(want);
+    p.ws_reported = scratch(std::max(want, runs(std::min(n_rows, 1024))));
     return p;
 }
 

@@ -41,6 +41,12 @@ ATTN_CASES = [
     _cfg(176, "bf16", d=128, T=333, Tq=2, L=1, B=2, H=32),
     _cfg(177, "f32", d=64, T=341, Tq=4, L=1, B=2, H=32),
     _cfg(178, "f32", d=128, T=400, Tq=1, L=1, B=2, H=32),
+    # from 64 units on: one run, short runs, long runs, at both sides of the borders
+    _cfg(256, "f32", d=128, T=600, Tq=1, L=1, B=2, H=36),
+    _cfg(257, "f32", d=128, T=601, Tq=1, L=1, B=2, H=36),
+    _cfg(258, "bf16", d=128, T=1024, Tq=1, L=1, B=2, H=32),
+    _cfg(259, "bf16", d=128, T=1025, Tq=1, L=1, B=2, H=32),
+    _cfg(260, "bf16", d=64, T=1025, Tq=1, L=1, B=3, H=43),        # 129 units
 ]
 
 
@@ -65,7 +71,7 @@ def test_dense_attention(cfg):
 @pytest.mark.parametrize("H,dtype", [(64, "bf16"), (96, "f32"), (16, "bf16")])
 def test_attention_scratch_sized_at_capacity(H, dtype):
     """Scratch sized for a cache's capacity serves every shorter length: the runs that a launch is cut into do not grow
-    with the rows everywhere."""
+    with the rows everywhere (rounding; long runs instead of short ones)."""
     T_cap = 1500
     cfg = _cfg(261, dtype, d=128, T=T_cap, L=1, B=1, H=H)
     t = synth.make_qkv(cfg, "cpu")
