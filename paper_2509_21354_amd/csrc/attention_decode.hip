@@ -89,7 +89,7 @@ __global__ __launch_bounds__(64 * NW) void attn_decode_kernel(AttnArgs a)
     constexpr int EPL = D / 16, GROUPS = 4 * NW;     // elements per lane; 16-lane row groups per workgroup
     constexpr int W = 16 / (int)sizeof(T) < EPL ? 16 / (int)sizeof(T) : EPL, NL = EPL / W;     // NL loads of W elements
     const int tid = threadIdx.x;
-    const int wave = tid >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int grp = tid >> 4;      // row group within the workgroup, 0 .. GROUPS-1
     const int cl = tid & 15;       // column lane within the group: elements 16 W c + W cl .. of a row
     const int R = a.G * a.Tq;
@@ -230,11 +230,14 @@ __global__ __launch_bounds__(64 * NW) void attn_decode_kernel(AttnArgs a)
         // the kept summaries (first run only)
         auto load_sum = [&](int n, int cnt, Batch &b) __attribute__((always_inline)) {
             const int base = n * (GROUPS * U) + grp;
+            const int c_wave = __builtin_amdgcn_readfirstlane(idx0[0]);      // (all lanes are here)
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                const int jc = min(base + GROUPS * u, cnt - 1);
-                // (idx0[u] is entry min(j, k_cap - 1) of the list: the right one whenever row j exists)
-                int c = idx ? (n == 0 ? idx0[u] : idx[jc]) : jc;
+                const int j = base + GROUPS * u, jc = min(j, cnt - 1);
+                // idx0[u] is entry min(j, k_cap - 1) of the list: the right one whenever row j exists.  A slot past the
+                // count takes the wave's first row instead (there is one: see total).  Its weight is 0, but what a stale
+                // entry points to need not be finite (0 x NaN), and may never have been written.
+                int c = idx ? (n == 0 ? (j < cnt ? idx0[u] : c_wave) : idx[jc]) : jc;
                 c = min(max(c, 0), a.N_cap - 1);
                 fetch(b, Kbar, Vbar, u, (seq_sum + c) * D);
             }
@@ -243,7 +246,8 @@ __global__ __launch_bounds__(64 * NW) void attn_decode_kernel(AttnArgs a)
         Batch b0, b1;
         if (nraw > 0) load_raw(0, b0);
         const int cnt = min(max(cnt_raw, 0), a.k_cap);
-        const int total = nraw + (cnt + GROUPS * U - 1) / (GROUPS * U);
+        const int wcnt = max(cnt - wave * 4, 0);         // entries from the wave's first on: its last batch holds a row of it
+        const int total = nraw + (wcnt + GROUPS * U - 1) / (GROUPS * U);
         auto load = [&](int n, Batch &b) __attribute__((always_inline)) {
             if (n < nraw) load_raw(n, b);
             else load_sum(n - nraw, cnt, b);

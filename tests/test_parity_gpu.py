@@ -165,6 +165,72 @@ def test_streaming_loads_change_no_bit(cfg):
     assert_close_storage(outs[1][0], ref, cfg.dtype, "gated O, streaming loads")
 
 
+POISON_CASES = [
+    _cfg(271, "bf16", d=128, T=1000, C=32, W=100, k=9, Tq=1),                # 9 summaries: the last lane groups of the first batch have none
+    _cfg(272, "f32", d=64, T=700, C=16, W=50, k=70, Tq=2),
+    _cfg(273, "bf16", d=64, T=640, C=32, W=0, k=5, Tq=5),                    # no raw row in most sequences' window
+    _cfg(274, "f32", d=128, T=640, C=8, W=0, k=3, Tq=1),
+    _cfg(275, "bf16", d=128, T=1300, C=32, W=256, k=12, Tq=40),              # matrix cores
+]
+
+
+@pytest.mark.parametrize("bad", [float("nan"), float("inf")])
+@pytest.mark.parametrize("cfg", POISON_CASES, ids=lambda c: c.name)
+def test_rows_that_are_not_attended_never_matter(cfg, bad):
+    """Eq. 1 runs over the kept summaries and the raw window.  Whatever lies elsewhere (raw rows past T or before the window,
+    summaries that are not kept or not yet pooled, list entries and store rows past the count) changes no bit, not even as
+    NaN or infinity."""
+    T_cap, pad = cfg.T + 40, 6
+    N_cap = T_cap // cfg.C
+    k_cap = min(cfg.k, N_cap) + pad
+    lead = (cfg.L, cfg.B, cfg.H)
+    t = synth.make_qkv(cfg, "cpu", T_cap=T_cap)
+    g_ = torch.Generator().manual_seed(cfg.number)
+    Kbar = torch.randn(lead + (N_cap, cfg.d), generator=g_).to(cfg.torch_dtype)
+    Vbar = torch.randn(lead + (N_cap, cfg.d), generator=g_).to(cfg.torch_dtype)
+    util = torch.randn(lead + (N_cap,), generator=g_)
+    idx, count = orc.select_topk(util, cfg.T, cfg.C, cfg.W, cfg.k, k_cap)
+    idx, count = torch.from_numpy(idx), torch.from_numpy(count)
+    kept = torch.zeros(lead + (N_cap,), dtype=torch.bool)
+    listed = torch.arange(k_cap) < count[..., None]
+    kept.scatter_(-1, torch.where(listed, idx, idx[..., :1]).long(), True)
+    win0 = cfg.N_cand * cfg.C
+    seen = (torch.arange(T_cap) >= win0) & (torch.arange(T_cap) < cfg.T)
+    sh = kb.make_shape(cfg, T_cap=T_cap, N_cap=N_cap)
+    shw = kb.make_shape(cfg, T=cfg.T - win0, T_cap=T_cap, N_cap=1)
+    ws = kb.alloc_workspace(max(kb.workspace_bytes(kb.OP_GATED_ATTENTION, sh, cfg.Tq, k_cap),
+                                kb.workspace_bytes(kb.OP_DENSE_ATTENTION, sh, cfg.Tq),
+                                kb.workspace_bytes(kb.OP_COMPACT_ATTENTION, shw, cfg.Tq, k_cap)))
+    Q = t["Q"].cuda()
+    outs = []
+    for poison in (False, True):
+        K, V, Kb, Vb, ix = t["K"].clone(), t["V"].clone(), Kbar.clone(), Vbar.clone(), idx.clone()
+        Kd, Vd = K.clone(), V.clone()
+        order = torch.where(listed, idx, 0).long()[..., None].expand(lead + (k_cap, cfg.d))
+        Kc, Vc = Kb.gather(3, order), Vb.gather(3, order)
+        if poison:
+            for x in (K, V):
+                x[..., ~seen, :] = bad
+            for x in (Kd, Vd):
+                x[..., cfg.T:, :] = bad
+            for x in (Kb, Vb):
+                x[~kept] = bad
+            for x in (Kc, Vc):
+                x[~listed] = bad
+            ix[~listed] = N_cap - 1                # a summary that has not been pooled yet
+        roll = torch.arange(T_cap).add(win0) % T_cap       # the compact form's buffer: the window first
+        Kw, Vw = K[..., roll, :].contiguous(), V[..., roll, :].contiguous()
+        Og, Od, Oc = (torch.full_like(Q, 7.0) for _ in range(3))
+        kb.kvev_gated_attention(sh, Q, cfg.Tq, K.cuda(), V.cuda(), Kb.cuda(), Vb.cuda(), ix.cuda(), count.cuda(), k_cap, Og, ws)
+        kb.kvev_dense_attention(sh, Q, cfg.Tq, Kd.cuda(), Vd.cuda(), Od, ws)
+        kb.kvev_compact_attention(shw, Q, cfg.Tq, Kw.cuda(), Vw.cuda(), Kc.cuda(), Vc.cuda(), count.cuda(), k_cap, Oc, ws)
+        torch.cuda.synchronize()
+        outs.append((Og, Od, Oc))
+    for clean, poisoned in zip(*outs):
+        assert torch.isfinite(clean).all() and torch.equal(clean, poisoned)
+    assert torch.equal(outs[0][0], outs[0][2])
+
+
 def test_attention_empty_cases():
     cfg = _cfg(129, "f32", T=0)
     t = synth.make_qkv(cfg, "cpu", T_cap=16)
