@@ -231,6 +231,88 @@ def test_rows_that_are_not_attended_never_matter(cfg, bad):
     assert torch.equal(outs[0][0], outs[0][2])
 
 
+SPECIAL_CASES = [
+    _cfg(276, "bf16", d=128, T=333, Tq=1, L=1, B=1, H=6),
+    _cfg(277, "f32", d=64, T=333, Tq=3, L=1, B=1, H=6),
+    _cfg(278, "bf16", d=64, T=333, Tq=30, L=1, B=1, H=6),         # matrix cores
+]
+
+
+@pytest.mark.parametrize("cfg", SPECIAL_CASES, ids=lambda c: c.name)
+def test_attention_special_values_stay_where_they_are(cfg):
+    """A NaN in a row of V makes its column NaN for every query of that cache, an infinity makes it infinite or NaN, and
+    neither touches another column or another cache; a NaN in a row of K touches no other cache."""
+    t = synth.make_qkv(cfg, "cpu")
+    sh = kb.make_shape(cfg)
+    ws = kb.alloc_workspace(kb.workspace_bytes(kb.OP_DENSE_ATTENTION, sh, cfg.Tq))
+    V2, K2 = t["V"].clone(), t["K"].clone()
+    V2[0, 0, 1, 170, 5] = float("nan")
+    V2[0, 0, 2, 332, 9] = float("inf")
+    K2[0, 0, 4, 20, 3] = float("nan")
+    outs = []
+    for K, V in ((t["K"], t["V"]), (K2, V2)):
+        O = torch.empty_like(t["Q"]).cuda()
+        kb.kvev_dense_attention(sh, t["Q"].cuda(), cfg.Tq, K.cuda(), V.cuda(), O, ws)
+        torch.cuda.synchronize()
+        outs.append(O[0, 0].cpu())
+    clean, got = outs
+    assert torch.isnan(got[1, :, 5]).all() and not torch.isfinite(got[2, :, 9]).any()
+    same = torch.ones_like(clean, dtype=torch.bool)
+    same[1, :, 5] = same[2, :, 9] = False
+    same[4] = False
+    assert torch.equal(clean[same], got[same])
+
+
+@pytest.mark.parametrize("tiny", ["K", "Q"])
+@pytest.mark.parametrize("cfg", SPECIAL_CASES, ids=lambda c: c.name)
+def test_attention_takes_subnormal_rows_as_they_are(cfg, tiny):
+    """Subnormal keys against large queries (and the other way round) give scores of order 1: an instruction that took
+    subnormals as zeros would leave a flat softmax."""
+    t = synth.make_qkv(cfg, "cpu")
+    up, down = 2.0 ** 125, 2.0 ** -127
+    t["Q"], t["K"] = t["Q"] * (down if tiny == "Q" else up), t["K"] * (down if tiny == "K" else up)
+    flat = vals(t["V"]).mean(axis=3, keepdims=True)
+    sh = kb.make_shape(cfg)
+    ws = kb.alloc_workspace(kb.workspace_bytes(kb.OP_DENSE_ATTENTION, sh, cfg.Tq))
+    O = torch.empty_like(t["Q"]).cuda()
+    kb.kvev_dense_attention(sh, t["Q"].cuda(), cfg.Tq, t["K"].cuda(), t["V"].cuda(), O, ws)
+    torch.cuda.synchronize()
+    ref = orc.dense_attention(t["Q"], t["K"], t["V"], cfg.T)
+    assert np.abs(vals(ref) - flat).max() > 0.03          # (the bar below is about 1e-3 here)
+    assert_close_storage(O, ref, cfg.dtype, "dense O")
+
+
+@pytest.mark.parametrize("dtype,d_sum", [("bf16", 64), ("bf16", 50), ("f32", 64)])       # matrix-core kernel, fp32-arithmetic kernel
+def test_pool_special_values(dtype, d_sum):
+    """Mean and maximum of subnormal rows (the mean within half a step of the storage type's subnormals and the fp32 sum's
+    rounding, the maximum exactly), and of rows with an infinity: it makes its own element of its own chunk infinite (or
+    NaN, where the value is carried as a sum of bf16 terms) and touches no other."""
+    cfg = _cfg(279, dtype, d=128, T=320, C=10, d_sum=d_sum, L=1, B=1, H=3)
+    N = cfg.T // cfg.C
+    g_ = torch.Generator().manual_seed(279)
+    X = (torch.randn((1, 1, 3, cfg.T, cfg.d), generator=g_) * 2.0 ** -127).to(cfg.torch_dtype)
+    Y = torch.randn((1, 1, 3, cfg.T, cfg.d), generator=g_).to(cfg.torch_dtype)
+    Z = Y.clone()
+    Z[0, 0, 1, 57, 11] = float("inf")
+    sh = kb.make_shape(cfg)
+
+    def pool(mode, rows):
+        Kb, Vb = (torch.zeros((1, 1, 3, N, cfg.d), dtype=cfg.torch_dtype, device="cuda") for _ in range(2))
+        kb.kvev_chunk_pool(sh, rows.cuda(), rows.cuda(), mode, None, None, 0, N, Kb, Vb)
+        torch.cuda.synchronize()
+        return Kb.cpu()
+
+    chunks = X.double().view(1, 1, 3, N, cfg.C, cfg.d)
+    step = 2.0 ** -133 if dtype == "bf16" else 2.0 ** -149
+    assert (pool(kb.POOL_MEAN, X).double() - chunks.mean(4)).abs().max() <= 0.5 * step + 4 * 2.0 ** -149
+    assert torch.equal(pool(kb.POOL_MAX, X).double(), chunks.amax(4))
+    for mode in (kb.POOL_MEAN, kb.POOL_MAX):
+        clean, got = pool(mode, Y), pool(mode, Z)
+        assert not torch.isfinite(got[0, 0, 1, 5, 11])
+        got[0, 0, 1, 5, 11] = clean[0, 0, 1, 5, 11]
+        assert torch.equal(clean, got)
+
+
 def test_attention_empty_cases():
     cfg = _cfg(129, "f32", T=0)
     t = synth.make_qkv(cfg, "cpu", T_cap=16)
@@ -353,6 +435,21 @@ def test_chunk_pool(cfg, mode):
         assert ulp <= 1 and frac < 5e-3, (frac, ulp)
 
 
+def gate_form(cfg):
+    """Which workgroups share a group of sequences in the gate (bf16): (members, sequences per group), by the rule of the
+    library's dispatch at this device's compute units.  (1, ..) stands for every form on one workgroup."""
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    bh = cfg.B * cfg.kv_heads
+    groups8, groups16 = cfg.L * ((bh + 7) // 8), cfg.L * ((bh + 15) // 16)
+    if cfg.d_g == 512 and bh > 16:
+        return 4, 32
+    if cfg.d_g == 256 and 4 * groups8 <= cus:
+        return 4, 8
+    if cfg.d_g == 256 and 2 * groups8 <= cus:
+        return 2, 8
+    return (2, 16) if cfg.d_g in (256, 512) and 2 * groups16 <= cus else (1, 16)
+
+
 LSTM_CASES = [
     _cfg(141, "f32", d=64, T=1024, C=16, d_g=64, L=1, B=1, H=4),
     _cfg(142, "f32", d=128, T=200, C=8, d_g=24),
@@ -361,8 +458,8 @@ LSTM_CASES = [
     _cfg(145, "bf16", d=128, T=320, C=32, d_g=40),                        # d_g the MFMA tiling does not take
     _cfg(146, "bf16", d=128, T=768, C=32, d_g=512, L=1, B=1, H=3),        # widest gate: unit tiles one after the other
     _cfg(147, "bf16", d=64, T=576, C=16, d_g=128, L=2, B=2, H=9),         # W_hh fully resident on chip
-    _cfg(148, "bf16", d=128, T=800, C=32, d_g=256, L=1, B=2, H=24),       # 3 full groups, each on a pair of workgroups
-    _cfg(149, "bf16", d=64, T=192, C=32, d_g=256, L=8, B=4, H=64),        # 128 groups: the largest paired launch (a workgroup per compute unit)
+    _cfg(148, "bf16", d=128, T=800, C=32, d_g=256, L=1, B=2, H=24),       # 3 full groups of 16: six of 8, each on four workgroups
+    _cfg(149, "bf16", d=64, T=192, C=32, d_g=256, L=8, B=4, H=64),        # 128 groups of 16: the largest paired launch (a workgroup per compute unit)
     _cfg(150, "bf16", d=64, T=192, C=32, d_g=256, L=26, B=5, H=16),       # 130 groups: one workgroup per group again
     _cfg(152, "bf16", d=128, T=288, C=32, d_g=512, L=2, B=2, H=12),       # widest gate, 24 sequences per layer: four workgroups per 32 sequences, the second block of 16 half empty
     _cfg(153, "bf16", d=128, T=1024, C=32, d_g=512, L=1, B=2, H=16),      # one full group of 32 on four workgroups, 32 steps
@@ -422,7 +519,9 @@ def test_lstm_gate(cfg):
 
 NAN_CASES = [
     (_cfg(157, "bf16", d=128, T=256, C=32, d_g=512, L=1, B=1, H=40), 0),     # four workgroups per 32 sequences: h travels with a flag in a bit of its hi terms
-    (_cfg(158, "bf16", d=64, T=256, C=32, d_g=256, L=1, B=1, H=20), 0),      # four workgroups per 8 sequences: a flag in a bit of hi and lo terms
+    (_cfg(158, "bf16", d=64, T=256, C=32, d_g=256, L=1, B=1, H=20), 0),      # four workgroups per 8 sequences: a stamp beside every 4 bytes of h
+    (_cfg(262, "bf16", d=64, T=160, C=32, d_g=256, L=13, B=1, H=37), 0),     # two workgroups per 8 sequences
+    (_cfg(263, "bf16", d=64, T=160, C=32, d_g=256, L=13, B=5, H=16), 0),     # pairs of workgroups at d_g = 256
     (_cfg(159, "bf16", d=128, T=256, C=32, d_g=256, L=1, B=1, H=40), 1),     # the single-kernel form
     (_cfg(160, "bf16", d=128, T=256, C=32, d_g=512, L=1, B=1, H=9), 0),      # pairs at d_g = 512
 ]
@@ -436,7 +535,7 @@ def test_lstm_gate_nan_stays_in_its_sequence(cfg, fused):
     N = cfg.T // cfg.C
     w = synth.make_weights(cfg, "cpu")
     Kbar, Vbar = _summaries(cfg, N)
-    bad = [(0, 0, 3, 2), (0, 0, cfg.H - 2, 5)]                 # (layer, batch row, head, first bad step)
+    bad = [(0, 0, 3, 2), (0, 0, cfg.H - 2, min(5, N - 1))]     # (layer, batch row, head, first bad step)
     for l, b, hd, t in bad:
         Kbar[l, b, hd, t, 7] = float("nan")
     sh = kb.make_shape(cfg, N_cap=N)
@@ -556,13 +655,14 @@ OCT_CASES = [
     _cfg(172, "bf16", d=64, T=9 * 32, C=32, d_g=256, L=13, B=1, H=37),      # 65 groups: two workgroups per 8 sequences
     _cfg(173, "bf16", d=128, T=1 * 32, C=32, d_g=256, L=1, B=1, H=1),       # one sequence, one step
     _cfg(174, "bf16", d=128, T=2 * 32, C=32, d_g=256, L=2, B=2, H=8),       # two steps: every slot used once
+    _cfg(264, "bf16", d=128, T=9 * 32, C=32, d_g=256, L=13, B=5, H=15),     # 65 groups of 16: pairs of workgroups, ragged
 ]
 
 
 @pytest.mark.parametrize("cfg", OCT_CASES, ids=lambda c: c.name)
 def test_lstm_gate_eight_sequences_per_group(cfg):
-    """The form of the gate that small launches take at d_g = 256: groups of 8 sequences on two or four workgroups.  One
-    call, then the same range cut into calls that carry the state (with scratch for two steps per launch, so that the
+    """The forms of the gate that launches of few sequences take at d_g = 256: groups of 8 sequences on two or four
+    workgroups, then groups of 16 on two.  One call, then the same range cut into calls that carry the state (with scratch for two steps per launch, so that the
     exchange slots start anew inside a call): the same bits."""
     N = cfg.T // cfg.C
     w = synth.make_weights(cfg, "cpu")
@@ -588,21 +688,6 @@ def test_lstm_gate_eight_sequences_per_group(cfg):
     rh, rc, ru, rg = orc.lstm_gate(Kbar, Vbar, kb.lstm_weights(w), 0, N)
     for got, ref, tol in zip(outs[0], (rh, rc, ru, rg), (SCORE_TOL, 2 * SCORE_TOL, SCORE_TOL, SCORE_TOL)):
         assert np.abs(got.cpu().numpy() - ref).max() <= tol
-
-
-def gate_form(cfg):
-    """Which workgroups share a group of sequences in the gate (bf16): (members, sequences per group), by the rule of the
-    library's dispatch at this device's compute units.  (1, ..) stands for every form on one workgroup."""
-    cus = torch.cuda.get_device_properties(0).multi_processor_count
-    bh = cfg.B * cfg.kv_heads
-    groups8, groups16 = cfg.L * ((bh + 7) // 8), cfg.L * ((bh + 15) // 16)
-    if cfg.d_g == 512 and bh > 16:
-        return 4, 32
-    if cfg.d_g == 256 and 4 * groups8 <= cus:
-        return 4, 8
-    if cfg.d_g == 256 and 2 * groups8 <= cus:
-        return 2, 8
-    return (2, 16) if cfg.d_g in (256, 512) and 2 * groups16 <= cus else (1, 16)
 
 
 # one case per form in which workgroups hand each other h
@@ -696,14 +781,17 @@ def test_lstm_gate_replaces_h_only_after_hearing_from_all_members(cfg, form):
 
 
 WAIT_CASES = [
-    _cfg(151, "bf16", d=64, T=320, C=32, d_g=256, L=1, B=1, H=5),         # a pair of workgroups
+    _cfg(151, "bf16", d=64, T=320, C=32, d_g=256, L=1, B=1, H=5),         # four workgroups per 8 sequences
+    _cfg(265, "bf16", d=64, T=128, C=32, d_g=256, L=13, B=1, H=37),       # two workgroups per 8 sequences
+    _cfg(266, "bf16", d=128, T=128, C=32, d_g=256, L=13, B=5, H=15),      # pairs of workgroups
+    _cfg(267, "bf16", d=64, T=128, C=32, d_g=512, L=2, B=1, H=16),        # pairs at d_g = 512
     _cfg(156, "bf16", d=64, T=320, C=32, d_g=512, L=1, B=1, H=20),        # four workgroups per 32 sequences
 ]
 
 
 @pytest.mark.parametrize("cfg", WAIT_CASES, ids=lambda c: c.name)
 def test_lstm_pair_wait_expires_cleanly(cfg):
-    """The recurrence on workgroups that exchange h every step (pairs at d_g = 256, quadruples at d_g = 512; few
+    """The recurrence on workgroups that exchange h every step (two or four per group of sequences; few
     groups) with one member's publications withheld and a tiny bound on the polls: every workgroup gives up, every
     kernel ends normally, the launch's scores and cell state are NaN and the status word at the head of the workspace
     is set; it stays set until the caller clears it, and the next call (defaults restored) computes as usual."""
@@ -749,11 +837,13 @@ def test_lstm_pair_wait_expires_cleanly(cfg):
 
 
 PREPARED_CASES = [
-    (_cfg(191, "bf16", d=128, T=384, C=32, d_g=256, L=1, B=1, H=20), 0),     # pairs of workgroups
+    (_cfg(191, "bf16", d=128, T=384, C=32, d_g=256, L=1, B=1, H=20), 0),     # four workgroups per 8 sequences
+    (_cfg(268, "bf16", d=64, T=224, C=32, d_g=256, L=13, B=1, H=37), 0),     # two workgroups per 8 sequences
+    (_cfg(269, "bf16", d=128, T=224, C=32, d_g=256, L=13, B=5, H=16), 0),    # pairs of workgroups
     (_cfg(192, "bf16", d=64, T=256, C=32, d_g=256, L=26, B=5, H=16), 0),     # one workgroup per group
     (_cfg(193, "bf16", d=128, T=256, C=32, d_g=256, L=2, B=2, H=20), 1),     # the single-kernel form
     (_cfg(194, "bf16", d=64, T=320, C=32, d_g=128, L=2, B=1, H=9), 0),       # all of W_hh in LDS
-    (_cfg(195, "bf16", d=128, T=256, C=32, d_g=512, L=1, B=1, H=18), 0),     # widest gate, on pairs
+    (_cfg(195, "bf16", d=128, T=256, C=32, d_g=512, L=1, B=1, H=18), 0),     # widest gate, four workgroups per 32 sequences
     (_cfg(196, "f32", d=64, T=256, C=32, d_g=48, L=1, B=2, H=3), 0),         # nothing to prepare: the generic kernels
 ]
 
@@ -798,6 +888,15 @@ def test_lstm_prepare_once_gate_many(cfg, fused):
         assert torch.equal(x, y)
     _, _, ru, _ = orc.lstm_gate(Kbar, Vbar, kb.lstm_weights(w), 0, N)
     assert np.abs(outs[1][2].cpu().numpy() - ru).max() <= SCORE_TOL
+
+
+def test_gate_cases_reach_the_forms_they_claim():
+    claims = {148: (4, 8), 149: (2, 16), 150: (1, 16), 151: (4, 8), 152: (4, 32), 155: (2, 16), 156: (4, 32), 157: (4, 32), 158: (4, 8),
+              160: (2, 16), 171: (4, 8), 172: (2, 8), 191: (4, 8), 192: (1, 16), 195: (4, 32), 262: (2, 8), 263: (2, 16), 264: (2, 16),
+              265: (2, 8), 266: (2, 16), 267: (2, 16), 268: (2, 8), 269: (2, 16)}
+    cases = [c if not isinstance(c, tuple) else c[0] for c in LSTM_CASES + OCT_CASES + WAIT_CASES + NAN_CASES + PREPARED_CASES]
+    found = {c.number: gate_form(c) for c in cases if c.number in claims}
+    assert found == claims
 
 
 def _run_cold(cfg, t, g):
