@@ -63,23 +63,26 @@ static int env_int(const char *name, int dflt)
     return v && *v ? atoi(v) : dflt;
 }
 // Tuning knobs (environment, read once; unset = the rule below): workgroups wanted per launch and the smallest
-// run of raw rows worth a workgroup.  The rule: with fewer key-value units than compute units the launch is filled
-// with up to one workgroup per compute unit.
-//   * Fewer than 64 units: runs of at least 64 rows (one batch of a 4-wave workgroup; 48 units x 283 rows: 6.6 us in 5
-//     runs, 6.9 us in one).
-//   * From 64 units on the merge of a split costs more than it saves on a short cache, and the more units share the
-//     memory, the longer a run pays to be: up to 1024 rows in one run (64 units x 283 rows, bf16, d = 128: 8.5 us in 4
-//     runs, 7.8 us in one; 128 x 700: 16.2 us in 2, 15.2 us in one; 240 x 1000: 29.7 us in 2, 28.3 us in one), then runs
-//     of at least 1024.
+// run of raw rows worth a workgroup.  A split costs its merge (partials out and acknowledged, a ticket, partials in: about
+// 1.5 us), which a short run does not earn back.  With fewer key-value units than compute units (figures: one run against
+// the split that the rule would take, bf16, d = 128, one query, where nothing else is said):
+//   * Fewer than 64 units: one run up to kShortRows rows (up to 32 units also of at most kShortBytes), above as many runs of
+//     at least 64 rows (a batch of a 4-wave workgroup) as the compute units take at once; the number is rounded up for up
+//     to 32 units and above 1024 rows.  (32 units x 96 rows 4.5 and 6.1 us, x 283 6.1 and 6.5 us, x 400 6.9 and 6.9 us, x
+//     600 8.2 and 7.4 us; 8 x 283 6.0 and 6.3 us, x 500 6.8 and 6.0 us; 56 x 283 6.3 and 7.1 us, x 600 8.2 and 7.7 us, with
+//     one run more than fits 8.7 us; four queries each, 32 x 283 10.0 and 10.6 us, x 400 13.1 and 11.3 us; fp32 32 x 200
+//     7.4 and 7.8 us, x 283 8.5 and 8.1 us.  Rounded up or down: 24 x 500 7.2 and 7.3 us, 63 x 1500 13.7 and 14.4 us.)
+//   * From 64 units on the more units share the memory, the longer a run pays to be: up to 1024 rows in one run (64 x 283:
+//     7.8 and 8.5 us; 128 x 700: 15.2 and 16.2 us; 240 x 1000: 28.3 and 29.7 us), then runs of at least 1024.
 //   * But up to 128 units, when a unit has more than kSplitRows rows and they take more than kSplitBytes times the number
 //     of units, as many runs as the compute units take at once: one workgroup per unit then leaves too much of the chip
-//     idle for too long (one run against 2 to 4: bf16 64 x 620 rows 10.5 and 9.8 us, 64 x 1000 14.8 and 11.7 us, 72 x 850
-//     14.4 and 12.0 us, 96 x 1000 18.7 and 16.5 us; fp32 64 x 1000 24.8 and 16.9 us, 96 x 610 17.4 and 15.6 us, 128 x 650
-//     24.4 and 21.5 us.  Short of either border one run is the faster or about the same: bf16 96 x 700 12.4 and 13.8 us,
-//     112 x 700 14.0 and 15.2 us, 64 x 512 9.5 and 9.3 us; fp32 64 x 350 9.3 and 10.3 us.  One run more than fits at once:
-//     fp32 72 x 601 14.6 us, 13.7 us with as many as fit).  Above 1024 rows the runs of at least 1024 are as good or
-//     better (64 x 1500: 14.8 us in 2 runs, 15.6 us in 4).
+//     idle for too long (64 x 620 10.5 and 9.8 us, 64 x 1000 14.8 and 11.7 us, 72 x 850 14.4 and 12.0 us, 96 x 1000 18.7
+//     and 16.5 us; fp32 64 x 1000 24.8 and 16.9 us, 96 x 610 17.4 and 15.6 us, 128 x 650 24.4 and 21.5 us.  Short of either
+//     border one run is the faster or about the same: 96 x 700 12.4 and 13.8 us, 112 x 700 14.0 and 15.2 us, 64 x 512 9.5
+//     and 9.3 us; fp32 64 x 350 9.3 and 10.3 us).  Above 1024 rows the runs of at least 1024 are as good or better (64 x
+//     1500: 14.8 us in 2 runs, 15.6 us in 4).
 // With more units than compute units, four 4-wave workgroups per compute unit and runs of at least 512 rows.
+constexpr int64_t kShortRows = 320, kShortBytes = 200 << 10;
 constexpr int64_t kSplitRows = 600, kSplitBytes = 4864;
 static const int g_attn_target_blocks = env_int("KVEV_ATTN_TARGET_BLOCKS", -1);
 static const int g_attn_min_rows = env_int("KVEV_ATTN_MIN_ROWS", -1);
@@ -104,10 +107,19 @@ static AttnPlan plan_attn(const kvev_shape *sh, int Tq, int n_rows)
     const int target = g_attn_target_blocks > 0 ? g_attn_target_blocks : few ? 256 : 1024;
     const int64_t row_bytes = (int64_t)sh->d * 2 * (sh->dtype == KVEV_F32 ? 4 : 2);
     auto runs = [&](int64_t rows) {
-        const bool large = g_attn_min_rows <= 0 && units >= 64 && units <= 128 && rows > kSplitRows && rows <= 1024 && rows * row_bytes > units * kSplitBytes;
-        const int64_t min_rows = g_attn_min_rows > 0 ? g_attn_min_rows : units < 64 || large ? 64 : few ? 1024 : 512;
-        const int64_t n = std::min(large ? target / units : (target + units - 1) / units, (rows + min_rows - 1) / min_rows);
-        return std::max<int64_t>(std::min<int64_t>(n, KVEV_ATTN_MAX_SPLIT), 1);
+        const int64_t fit = target / units, fill = (target + units - 1) / units;
+        auto cut = [&](int64_t most, int64_t min_rows) {
+            const int64_t n = std::min(most, (rows + min_rows - 1) / min_rows);
+            return std::max<int64_t>(std::min<int64_t>(n, KVEV_ATTN_MAX_SPLIT), 1);
+        };
+        if (g_attn_min_rows > 0) return cut(fill, g_attn_min_rows);
+        if (!few) return cut(fill, 512);
+        if (units < 64) {
+            const bool brief = rows <= kShortRows && (units > 32 || rows * row_bytes <= kShortBytes);
+            return brief ? (int64_t)1 : cut(units > 32 && rows <= 1024 ? fit : fill, 64);
+        }
+        const bool large = units <= 128 && rows > kSplitRows && rows <= 1024 && rows * row_bytes > units * kSplitBytes;
+        return large ? cut(fit, 64) : cut(fill, 1024);
     };
     const int64_t want = runs(n_rows);
     int rps = (int)((n_rows + want - 1) / want);

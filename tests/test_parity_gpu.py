@@ -41,7 +41,12 @@ ATTN_CASES = [
     _cfg(176, "bf16", d=128, T=333, Tq=2, L=1, B=2, H=32),
     _cfg(177, "f32", d=64, T=341, Tq=4, L=1, B=2, H=32),
     _cfg(178, "f32", d=128, T=400, Tq=1, L=1, B=2, H=32),
-    # from 64 units on: one run, short runs, long runs, at both sides of the borders
+    # one run, short runs, long runs, at both sides of the borders
+    _cfg(280, "bf16", d=128, T=320, Tq=1, L=1, B=1, H=32),
+    _cfg(281, "bf16", d=128, T=321, Tq=1, L=1, B=1, H=32),
+    _cfg(282, "f32", d=128, T=200, Tq=1, L=1, B=1, H=32),
+    _cfg(283, "f32", d=128, T=201, Tq=4, L=1, B=1, H=32),
+    _cfg(284, "bf16", d=64, T=321, Tq=3, L=1, B=1, H=33),
     _cfg(256, "f32", d=128, T=600, Tq=1, L=1, B=2, H=36),
     _cfg(257, "f32", d=128, T=601, Tq=1, L=1, B=2, H=36),
     _cfg(258, "bf16", d=128, T=1024, Tq=1, L=1, B=2, H=32),
