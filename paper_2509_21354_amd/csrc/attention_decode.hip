@@ -8,7 +8,7 @@
 // covers 4 consecutive rows per load instruction and a workgroup 16, so every
 // wave-level load is one contiguous 1 KiB piece of the cache.  Each lane group
 // keeps its own online-softmax state (m, l, o); the groups are merged by
-// shuffles, the waves through LDS, and the splits of one sequence inside the
+// lane exchanges, the waves through LDS, and the splits of one sequence inside the
 // same launch: every split leaves its partial (o, m, l) in scratch and draws an
 // integer ticket; the workgroup that draws the last one merges all partials in
 // split order (so the result does not depend on who arrives when, and no float
@@ -81,7 +81,8 @@ template <int L> __device__ __forceinline__ float row_lane(float v) { return dpp
 // the lanes together (every lane is left with one score, so an exponential is taken once and not in 16 lanes), all on
 // the vector unit: summing one score at a time with shuffles kept the LDS pipe busier than the memory.  Measured (from
 // graphs): 2048 sequences x 333 rows for 4 queries each 87 -> 66 us (5.3 TB/s); 256 x 2000 rows, 8 queries 112 -> 89 us;
-// 512 x 320 rows, one query 16.4 -> 15.7 us; 32 x 315 rows 7.4 -> 6.3 us (launch, three round trips and the ticket).
+// 512 x 320 rows, one query 16.4 -> 15.7 us; fp32, one query 1024 x 544 rows 102 -> 86 us, four queries 2048 x 320 rows 132 -> 114
+// us.  32 x 315 rows: 7.4 us -> 6.25 us, unsplit (launch and three round trips).
 template <typename T, int D, int NQ, int NW>
 __global__ __launch_bounds__(64 * NW) void attn_decode_kernel(AttnArgs a)
 {

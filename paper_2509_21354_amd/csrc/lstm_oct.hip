@@ -23,7 +23,8 @@
 // (P = 4; about 0.95 us of a step are its own work, the rest is the exchange).  512 sequences x 64 steps: 183 -> 160 us,
 // x 8 steps: 40.6 -> 35.6 us; 1024 x 64 (P = 2): 245 -> 224 us.  Members on one XCD that exchange by plain stores through
 // its L2 took 185 us, but publications of that kind were lost under cache pressure (seen in lstm_quad.hip; cause not
-// shown), so all stores write through.
+// shown), so all stores write through.  (With those a flag bit per use, as in
+// lstm_quad.hip, would do in the stamps' place: 233, 149 and 209 us.)
 #include "common.hpp"
 #include "kernels.hpp"
 #include "lstm_common.hpp"

@@ -25,7 +25,8 @@
 // by step parity: a slot is rewritten two steps later, which its writer reaches only after all three readers have
 // consumed it (it needs their next h, published after that read); so a reader finds either the step it waits for or
 // the use before it (or the zeros that a small launch leaves in all slots first), and one bit, flipped from use to
-// use and set on the first one, tells them apart.  (A NaN in h has bit 14 set in its hi term: the reader recognises
+// use and set on the first one, tells them apart.  (It cannot find an older use: it has itself taken the one before from
+// the same addresses, and loads that look past the caches do not go back at a location.)  (A NaN in h has bit 14 set in its hi term: the reader recognises
 // the exponent that no |h| <= 1 can have once the flag is masked off and puts the NaN back.)
 //
 // A step:  products over the own quarter of h (no exchange needed) | take the partners' quarters, stage them in LDS |

@@ -242,8 +242,8 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 3 : 1) void pool_mfma_kernel(Poo
             }
             // over the 4 lane rows, all on the vector unit: a lane is left with 2 neighbouring elements of K and of V, and all
             // lanes take part in the division and the split.  (Shuffles, 32 per tile row, go through LDS and left 3/4 of the
-            // lanes idle after them: 8 layers x 256 sequences x 256 chunks of 32 1553 -> 1417 us, chunks of 16 1166 -> 1018
-            // us, the mean alone 1453 -> 1411 us; the same bits.)
+            // lanes idle after them: 8 layers x 256 sequences x 256 chunks of 32 1497 -> 1441 us, both timed in turn; in a
+            // sweep, chunks of 16 1166 -> 1018 us, the mean alone 1453 -> 1411 us; the same bits.)
             const float cf = is_max ? 1.f : (float)a.C;
             auto reduce = [&](float (&v)[EPL], int kv) __attribute__((always_inline)) {
                 if (is_max) rows_fold2(v, [](float x, float y) __attribute__((always_inline)) { return fmaxf(x, y); });
