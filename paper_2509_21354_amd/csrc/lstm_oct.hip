@@ -265,6 +265,7 @@ __global__ __launch_bounds__(1024 / P) void lstm_rec_oct_kernel(LstmArgs a, int 
             const uint32_t stamp = (uint32_t)tt + 1;
             const u32x4_t out = {mine[0], stamp, mine[1], stamp};
             __builtin_amdgcn_raw_buffer_store_b128(out, e_rsrc, n * kOwn * 4 + wave * 64 + g4 * 16, (int)((cur * P + member) * kSlot), 16);
+            hold_store_data(out);
         }
         *reinterpret_cast<u32x2_t *>(h_wr) = mine;
         upart = rows_sum(upart);

@@ -1,5 +1,7 @@
 """Properties of the kernels that only their generated code shows: the device code is compiled as the library's is, on
 the CPU, and its assembly looked through."""
+import concurrent.futures
+import glob
 import os
 import re
 import subprocess
@@ -69,3 +71,75 @@ def test_retention_leaves_room_for_eight_waves(tmp_path):
     used = [int(v) for v in re.findall(r"\.vgpr_count:\s+(\d+)", asm)]
     spilt = [int(v) for v in re.findall(r"\.vgpr_spill_count:\s+(\d+)", asm)]
     assert len(used) == len(spilt) == 5 and max(used) <= 64 and max(spilt) == 0, (used, spilt)
+
+
+def registers(operand):
+    m = re.match(r"([va])\[(\d+):(\d+)\]$", operand)
+    if m:
+        return {(m.group(1), i) for i in range(int(m.group(2)), int(m.group(3)) + 1)}
+    m = re.match(r"([va])(\d+)$", operand)
+    return {(m.group(1), int(m.group(2)))} if m else set()
+
+
+def written(instruction):
+    """the vector registers that a vector instruction writes at once (a matrix instruction takes longer than what is
+    looked for here)"""
+    op, _, rest = instruction.partition(" ")
+    if not op.startswith("v_") or op.startswith(("v_mfma", "v_cmp", "v_readfirstlane", "v_readlane")):
+        return set()
+    ops = [o.strip() for o in rest.split(",")]
+    return registers(ops[0]) | (registers(ops[1]) if "swap" in op else set())
+
+
+def early_overwrites(lines):
+    """(store, instruction) for every store of more than 8 bytes whose data registers a following instruction may
+    overwrite before the hardware has read them: 1 instruction further on at the least for a buffer store with its offset
+    in a scalar register, 2 otherwise (s_nop n counts n + 1), along every path."""
+    label = {s[:-1]: i for i, s in enumerate(lines) if s.endswith(":")}
+    found = []
+    for i, store in enumerate(lines):
+        m = re.match(r"(buffer|global|flat|scratch)_store_dwordx[34]\s+(.*)", store)
+        if not m:
+            continue
+        ops = [o.strip() for o in m.group(2).split(",")]
+        data = registers(ops[0] if m.group(1) == "buffer" else ops[1])
+        assert data, store
+        need = 1 if m.group(1) == "buffer" and re.match(r"s\d+", ops[3]) else 2
+        todo, seen = [(i + 1, 0)], set()
+        while todo:
+            k, distance = todo.pop()
+            if distance >= need or k >= len(lines) or (k, distance) in seen:
+                continue
+            seen.add((k, distance))
+            s = lines[k]
+            if not s or s.startswith(".") or s.endswith(":"):
+                todo.append((k + 1, distance))
+            elif written(s) & data:
+                found.append((store, s))
+            elif not s.startswith("s_endpgm"):
+                nop = re.match(r"s_nop (\d+)", s)
+                distance += int(nop.group(1)) + 1 if nop else 1
+                branch = re.match(r"s_c?branch\w*\s+(\S+)", s)
+                if branch:
+                    todo.append((label[branch.group(1)], distance))
+                if not s.startswith("s_branch"):
+                    todo.append((k + 1, distance))
+    return found
+
+
+def test_early_overwrites_are_recognised():
+    store, nt = "buffer_store_dwordx4 v[4:7], v1, s[0:3], s9 offen sc1", "global_store_dwordx4 v[2:3], v[4:7], off"
+    assert early_overwrites([store, ".LBB0_1:", "v_mov_b32_e32 v7, v9"])
+    assert not early_overwrites([store, "s_nop 0", "v_mov_b32_e32 v7, v9"])
+    assert early_overwrites([nt, "s_nop 0", "v_mov_b32_e32 v4, v9"])
+    assert not early_overwrites([nt, "s_nop 1", "v_mov_b32_e32 v4, v9"])
+    assert early_overwrites([nt, "s_cbranch_vccnz .LBB0_2", "s_endpgm", ".LBB0_2:", "v_permlane16_swap_b32_e32 v9, v4"])
+    assert not early_overwrites([nt, "s_branch .LBB0_2", "v_mov_b32_e32 v4, v9", ".LBB0_2:", "v_add_f32_e32 v9, v4, v5", "v_mov_b32_e32 v4, v9"])
+
+
+def test_store_data_is_read_before_it_is_overwritten(tmp_path):
+    """Every kernel: see hold_store_data in common.hpp."""
+    names = sorted(os.path.basename(p) for p in glob.glob(os.path.join(kvev_build.CSRC, "*.hip")))
+    with concurrent.futures.ThreadPoolExecutor(max_workers=min(8, len(names))) as ex:
+        found = {n: f for asm in ex.map(lambda n: assembly(n, tmp_path), names) for n, lines in kernels(asm).items() if (f := early_overwrites(lines))}
+    assert not found, found
