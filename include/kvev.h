@@ -275,7 +275,8 @@ int kvev_compact_attention(const kvev_shape *shape, const void *Q, int Tq, const
  * (KVEV_OP_LSTM_PREPARE: the size of the packed weights).  `n` is Tq
  * for the attention ops and chunk_end - chunk_begin for pool / gate; k_cap is
  * used by KVEV_OP_GATED_ATTENTION and KVEV_OP_COMPACT_ATTENTION only.  Returns 0 when none is needed or the
- * arguments are invalid. */
+ * arguments are invalid.  For the attention ops the result covers every smaller T of the same shape as well, and for
+ * KVEV_OP_GATED_ATTENTION every T up to T_cap: a growing cache needs one query. */
 size_t kvev_workspace_bytes(int op, const kvev_shape *shape, int n, int k_cap);
 
 /* Static description of a status code. */

@@ -635,10 +635,10 @@ size_t kvev_workspace_bytes(int op, const kvev_shape *sh, int n, int k_cap)
         return lstm_takes_mfma(sh) ? lstm_ws_weights(sh) : 0;
     case KVEV_OP_GATED_ATTENTION: {
         if (k_cap < 0) return 0;
-        const int ncand = n_cand_of(sh);
-        const int kmax = k_cap < ncand ? k_cap : ncand;
-        (void)kmax;
-        return attn_takes_mq(sh, n) ? 0 : plan_attn(sh, n, sh->T - ncand * sh->C).ws_reported;
+        // (as the cache grows its raw rows go up and down between W and W + C - 1: enough for all of them)
+        const int64_t most = std::min<int64_t>(sh->T_cap, (int64_t)sh->W + sh->C - 1);
+        const int rows = std::max(sh->T - n_cand_of(sh) * sh->C, (int)most);
+        return attn_takes_mq(sh, n) ? 0 : plan_attn(sh, n, rows).ws_reported;
     }
     case KVEV_OP_DENSE_ATTENTION:
         return attn_takes_mq(sh, n) ? 0 : plan_attn(sh, n, sh->T).ws_reported;

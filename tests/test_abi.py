@@ -165,6 +165,14 @@ def test_attention_scratch_never_shrinks_with_the_rows(H, dtype, d):
     assert all(a <= b for a, b in zip(need, need[1:]))
 
 
+@pytest.mark.parametrize("H,W", [(16, 256), (32, 250), (32, 500), (40, 600), (64, 590), (96, 1010)])
+def test_gated_attention_scratch_is_the_same_at_every_length(H, W):
+    """The raw rows of a growing cache go up and down within a chunk: one query serves the whole stream."""
+    need = {kb.workspace_bytes(kb.OP_GATED_ATTENTION, kb.make_shape(L=1, B=1, H=H, d=128, T=T, T_cap=3000, C=32, N_cap=100, W=W, d_sum=64,
+                                                                    d_g=64, dtype=kb.BF16), 1, 16) for T in range(1, 3001)}
+    assert len(need) == 1
+
+
 def test_workspace_query():
     L_ = kb.lib()
     sh = _shape()

@@ -90,6 +90,27 @@ def test_attention_scratch_sized_at_capacity(H, dtype):
         assert_close_storage(O, orc.dense_attention(t["Q"], t["K"], t["V"], T), dtype, f"dense O, {T} rows")
 
 
+@pytest.mark.parametrize("H,W", [(64, 590), (32, 300)])
+def test_gated_attention_scratch_sized_once(H, W):
+    """... and for the gated form every length of the stream, though its raw rows go up and down (here across the border
+    from one run to several)."""
+    cfg = _cfg(285, "bf16", d=128, T=960, C=32, W=W, k=4, L=1, B=1, H=H)
+    t = synth.make_qkv(cfg, "cpu")
+    g = dev(t)
+    g_ = torch.Generator().manual_seed(5)
+    Kbar = torch.randn((1, 1, H, cfg.N, cfg.d), generator=g_).to(cfg.torch_dtype)
+    util = torch.randn((1, 1, H, cfg.N), generator=g_)
+    ws = kb.alloc_workspace(kb.workspace_bytes(kb.OP_GATED_ATTENTION, kb.make_shape(cfg, T=W + 1, T_cap=cfg.T), 1, cfg.k))
+    for T in (W + 1, W + 31, W + 32, W + 63, 900, 959):
+        sh = kb.make_shape(cfg, T=T, T_cap=cfg.T)
+        idx, count = orc.select_topk(util, T, cfg.C, W, cfg.k, cfg.k)
+        O = torch.full_like(g["Q"], 7.0)
+        kb.kvev_gated_attention(sh, g["Q"], 1, g["K"], g["V"], Kbar.cuda(), Kbar.cuda(), torch.from_numpy(idx).cuda(),
+                                torch.from_numpy(count).cuda(), cfg.k, O, ws)
+        torch.cuda.synchronize()
+        assert_close_storage(O, orc.gated_attention(t["Q"], t["K"], t["V"], Kbar, Kbar, idx, count, T, cfg.C, W), "bf16", f"O at {T}")
+
+
 GATED_CASES = [
     _cfg(111, "f32", d=64, T=1024, C=16, W=64, k=16),
     _cfg(112, "bf16", d=128, T=1000, C=32, W=100, k=9, Tq=2),    # T, W not multiples of C
