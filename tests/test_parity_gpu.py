@@ -191,6 +191,63 @@ def test_streaming_loads_change_no_bit(cfg):
     assert_close_storage(outs[1][0], ref, cfg.dtype, "gated O, streaming loads")
 
 
+# Launches that fill the chip with 256 compute units: 8 waves on 256 queries or 4 on 128, several items per workgroup
+FRAME_CASES = [
+    # (config, causal)
+    (_cfg(286, "bf16", d=64, T=203, C=16, W=70, k=5, Tq=160, L=1, B=20, H=25), 0),     # 8 waves, the last three idle; 500 items on 256 workgroups
+    (_cfg(287, "bf16", d=128, T=420, C=16, W=230, k=9, Tq=215, L=1, B=20, H=25), 1),   # 8 waves, causal: 4 tiles of rows, ragged
+    (_cfg(288, "bf16", d=128, T=160, C=16, W=110, k=3, Tq=75, L=1, B=26, H=20), 0),    # 4 waves: 520 items on 512 workgroups
+    (_cfg(289, "bf16", d=64, T=150, C=16, W=64, k=64, Tq=300, L=1, B=13, H=23), 0),    # three tiles of 128 queries each, the last ragged
+    (_cfg(290, "bf16", d=128, T=150, C=8, W=1, k=300, Tq=100, L=1, B=9, H=30), 0),     # four queries a head, hardly a raw row, all summaries
+    (_cfg(291, "bf16", d=128, T=129, C=16, W=40, k=2, Tq=10, L=1, B=24, H=64, H_kv=32), 1),   # 20 queries of a group: 4 waves when streamed
+    (_cfg(292, "bf16", d=128, T=64, C=16, W=64, k=2, Tq=140, L=1, B=10, H=27), 0),     # exactly one tile of rows
+]
+
+
+@pytest.mark.parametrize("cfg,causal", FRAME_CASES, ids=lambda c: getattr(c, "name", None))
+def test_frames_that_fill_the_chip(cfg, causal):
+    """Query frames on the matrix cores (Eq. 1), gated, dense and over the compact store with its window in a ring, against
+    the oracle; a sixth of the sequences keeps nothing, and the streaming hint changes no bit."""
+    t = synth.make_qkv(cfg, "cpu")
+    g_ = torch.Generator().manual_seed(cfg.number)
+    lead = (cfg.L, cfg.B, cfg.kv_heads)
+    Kbar, Vbar = (torch.randn(lead + (cfg.N, cfg.d), generator=g_).to(cfg.torch_dtype) for _ in range(2))
+    k_cap = max(1, min(cfg.k, cfg.N_cand)) + 1
+    idx, count = orc.select_topk(torch.randn(lead + (cfg.N,), generator=g_), cfg.T, cfg.C, cfg.W, cfg.k, k_cap)
+    count = count * (torch.rand(lead, generator=g_) > 1 / 6).numpy().astype(count.dtype)
+    n_raw = cfg.T - cfg.N_cand * cfg.C
+    g = dev(t)
+    sh, shw = kb.make_shape(cfg), kb.make_shape(cfg, T=n_raw, T_cap=cfg.T, N_cap=k_cap)
+    ws = kb.alloc_workspace(max(256, kb.workspace_bytes(kb.OP_GATED_ATTENTION, sh, cfg.Tq, k_cap), kb.workspace_bytes(kb.OP_DENSE_ATTENTION, sh, cfg.Tq),
+                                kb.workspace_bytes(kb.OP_COMPACT_ATTENTION, shw, cfg.Tq, k_cap)))
+    di, dc = torch.from_numpy(idx).cuda(), torch.from_numpy(count).cuda()
+    order = torch.from_numpy(idx).long().clamp(0)[..., None].expand(lead + (k_cap, cfg.d))
+    Kc, Vc = Kbar.gather(3, order).cuda(), Vbar.gather(3, order).cuda()
+    first = cfg.T - n_raw // 2 - 1            # the window's rows run across the end of the ring
+    roll = (torch.arange(cfg.T) + cfg.N_cand * cfg.C - first) % cfg.T
+    Kw, Vw = g["K"][..., roll, :].contiguous(), g["V"][..., roll, :].contiguous()
+    outs = []
+    try:
+        for nbytes in (0, 1):
+            kb.kvev_debug_attn_stream_bytes(nbytes)
+            Og, Od, Oc = (torch.full_like(g["Q"], 7.0) for _ in range(3))
+            kb.kvev_gated_attention(sh, g["Q"], cfg.Tq, g["K"], g["V"], Kbar.cuda(), Vbar.cuda(), di, dc, k_cap, Og, ws, causal=causal)
+            kb.kvev_dense_attention(sh, g["Q"], cfg.Tq, g["K"], g["V"], Od, ws, causal=causal)
+            kb.kvev_compact_attention(shw, g["Q"], cfg.Tq, Kw, Vw, Kc, Vc, dc, k_cap, Oc, ws, causal=causal, win_first=first)
+            torch.cuda.synchronize()
+            outs.append((Og, Od, Oc))
+    finally:
+        kb.kvev_debug_attn_stream_bytes(0)
+    ref = orc.attention_ext(t["Q"], t["K"], t["V"], cfg.T, cfg.C, cfg.W, Kbar, Vbar, idx, count, causal=causal)
+    refd = orc.attention_ext(t["Q"], t["K"], t["V"], cfg.T, causal=causal)
+    for Og, Od, Oc in outs:
+        assert_close_storage(Og, ref, cfg.dtype, "O gated")
+        assert_close_storage(Od, refd, cfg.dtype, "O dense")
+        assert torch.equal(Og, Oc)
+    if cfg.H // cfg.kv_heads * cfg.Tq > 64:
+        assert all(torch.equal(a, b) for a, b in zip(*outs))
+
+
 POISON_CASES = [
     _cfg(271, "bf16", d=128, T=1000, C=32, W=100, k=9, Tq=1),                # 9 summaries: the last lane groups of the first batch have none
     _cfg(272, "f32", d=64, T=700, C=16, W=50, k=70, Tq=2),
