@@ -22,10 +22,12 @@
 //   * the utility head runs after each block over the block's 16 states.
 // Measured (fp32, d_g = 64, d = 64, 4 sequences x 64 steps): 1346 us with one
 // row of W_ih and W_hh at a time per lane group, dependent loads from L2 in every
-// step; 64 us now (1 us per step, the projections included).  d_g = 256, d = 128, 32 sequences x 64 steps: 11.4 ms
+// step; 64 us (1 us per step, the projections included); lstm_chain_kernel below takes 42 us.  d_g = 256, d = 128, 32 sequences x 64 steps: 11.4 ms
 // -> 0.69 ms, bound by the 1 MiB of W_hh that a workgroup streams per step.
+#include <utility>
 #include "common.hpp"
 #include "kernels.hpp"
+#include "lstm_common.hpp"
 
 namespace kvev {
 
@@ -226,6 +228,229 @@ __global__ __launch_bounds__(kGenThreads, RES == 1 && MB == 1 ? 8 : 4) void lstm
     }
 }
 
+// ---- d_g <= 64, one sequence per workgroup --------------------------------------------------------------------------
+// Nonlinearities of the step below: the hardware exp2 and reciprocal, the latter with one Newton step, and for small
+// arguments of tanh an odd polynomial (x + x^3 P(x^2), relative error 1.4e-9, a weighted least-squares fit iterated
+// towards the minimax one).  All stay within about 1 ulp, as expf, a division and tanhf do, in a third of the
+// instructions and without branches.  NaN stays NaN.
+__device__ __forceinline__ float rcp_newton(float d)
+{
+    const float r = __builtin_amdgcn_rcpf(d);
+    return fmaf(fmaf(-d, r, 1.f), r, r);
+}
+// 1 / (1 + 2^y): y is cut at 80, where the result is 1e-24
+__device__ __forceinline__ float inv_1p_exp2(float y) { return rcp_newton(1.f + __builtin_amdgcn_exp2f(y > 80.f ? 80.f : y)); }
+constexpr float kTanhSmall = 0.5625f;
+__device__ __forceinline__ float tanh_small(float x)
+{
+    const float s = x * x;
+    const float p = fmaf(fmaf(fmaf(fmaf(-0.006179808871800135f, s, 0.021007458045466547f), s, -0.05383742992718666f), s, 0.13332452268837372f), s, -0.3333331388797284f);
+    return fmaf(x * s, p, x);
+}
+// tanh x from r = 1 / (1 + e^2|x|)
+__device__ __forceinline__ float tanh_of(float x, float r)
+{
+    return fabsf(x) < kTanhSmall ? tanh_small(x) : copysignf(fmaf(-2.f, r, 1.f), x);
+}
+
+// What bounds a small launch is the chain of one step on one compute unit, so a step is as short as its dependences: a
+// thread owns one gate row (its 64 weights in registers) and one nonlinearity, a quad of lanes the four gates of a unit.
+// Four waves, one per SIMD, do nothing else.  Four more sit beside them and make the input projections of the next 16
+// steps on the matrix cores, a sixteenth per step, and the scores; what they read from memory was asked for steps ahead
+// (d = 64: their rows of W_ih stay in registers).  One barrier per step.
+// Measured (fp32, d_g = 64, the kernel above and this one): d = 64, 4 sequences x 256 steps 248 and 142 us (0.52 us a step, of
+// which about 0.1 are the products, 0.15 the nonlinearities, the rest LDS and the barrier), x 16 steps 18.7 and 16.0 us; d = 128,
+// 256 x 64 steps 81 and 57 us; bf16, d_g = 50, d = 128, 96 x 128 steps 145 and 121 us.  One workgroup per compute unit: launches
+// of more sequences than that are faster above (512 x 64 steps 78 and 108 us).
+template <typename T, int D>
+__global__ __launch_bounds__(512, 2) void lstm_chain_kernel(LstmArgs a)
+{
+    constexpr int NU = 64, TB = 16, CT = 2 * D / 16;         // units; steps of a block; 16-element chunks of an input row
+    constexpr int TILES = 4 * NU / 16 / 4, CH = TILES * CT / TB;     // tiles of 16 gate rows per projecting wave; chunks per step
+    constexpr int PPT = CT / CH;                             // steps per tile
+    static_assert(CT % CH == 0 && PPT * TILES == TB, "a step stays within one tile");
+    __shared__ __align__(16) float s_h[2][NU], s_pre[2][TB][4 * NU];
+    const int dg = a.d_g, lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int l = blockIdx.x / a.BH, n = a.c1 - a.c0;
+    const size_t s = blockIdx.x;                             // (layers are contiguous)
+    const T *W_ih = static_cast<const T *>(a.W_ih) + (size_t)l * 4 * dg * 2 * D;
+    const bool fresh = a.c0 == 0;        // the recurrence starts from a zero state at chunk 0, whatever the buffers hold
+
+    // ---- the projections, a tile of 16 gate rows x 16 steps at a time: gate row 4 u + q of the tile order is row q d_g + u
+    //      of W_ih.  A contraction index may be permuted as long as both operands agree: lane group g takes elements
+    //      16 c + 4 g .. + 3 of chunk c ----
+    const int cl = lane & 15, g = lane >> 4;
+    auto load_w = [&](int tile, int c, float (&o)[4]) __attribute__((always_inline)) {
+        const int row = tile * 16 + cl, u = min(row >> 2, dg - 1);
+        VecLoad<T, 4>::run(W_ih + ((size_t)(row & 3) * dg + u) * 2 * D + 16 * c + 4 * g, o);
+    };
+    auto load_x = [&](int block, float (&o)[CT][4]) __attribute__((always_inline)) {         // column cl: step cl of the block
+        const size_t chunk = (s * a.N_cap + min(a.c0 + block * TB + cl, a.c1 - 1)) * D;
+#pragma unroll
+        for (int c = 0; c < CT; ++c) VecLoad<T, 4>::run(static_cast<const T *>(c < CT / 2 ? a.Kbar : a.Vbar) + chunk + 16 * (c % (CT / 2)) + 4 * g, o[c]);
+    };
+    // (two chains of sums: even and odd elements)
+    auto multiply = [&](const float (&w)[4], const float (&x)[4], f32x4_t (&acc)[2]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[e & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[e], x[e], acc[e & 1], 0, 0, 0);
+    };
+    auto load_bias = [&](int tile) __attribute__((always_inline)) {
+        const int u = min((tile * 16 + 4 * g) >> 2, dg - 1);
+        f32x4_t v;
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            v[r] = Storage<T>::load(static_cast<const T *>(a.b_ih) + (size_t)l * 4 * dg + r * dg + u) +
+                   Storage<T>::load(static_cast<const T *>(a.b_hh) + (size_t)l * 4 * dg + r * dg + u);
+        return v;
+    };
+    auto put = [&](int block, int tile, const f32x4_t &v) __attribute__((always_inline)) {
+        *reinterpret_cast<f32x4_t *>(&s_pre[block & 1][cl][tile * 16 + 4 * g]) = v;
+    };
+    constexpr bool RES = CT <= 8;                            // a projecting wave's weights all in registers, else WA steps ahead
+    if constexpr (!RES) {       // the first block's, by all waves
+        float x[CT][4];
+        load_x(0, x);
+        for (int tile = wave; tile < NU / 4; tile += 8) {
+            float w[CT][4];
+#pragma unroll
+            for (int c = 0; c < CT; ++c) load_w(tile, c, w[c]);
+            const f32x4_t bias = load_bias(tile);
+            f32x4_t acc[2] = {};
+#pragma unroll
+            for (int c = 0; c < CT; ++c) multiply(w[c], x[c], acc);
+            put(0, tile, acc[0] + acc[1] + bias);
+        }
+    }
+
+    if (wave < 4) {
+        // ---- the recurring waves: a quad of lanes has unit 16 wave + lane / 4; lane k of it multiplies elements 16 k .. + 15 of
+        //      its four rows (each thread a row of its own would read four times as much of h from LDS) and ends, after
+        //      a transposing reduction, with one gate ----
+        const int kq = lane & 3, gate = value_of_lane(lane), unit = wave * 16 + (lane >> 2), u = min(unit, dg - 1);
+        float w[4][16], c = 0.f, hn = 0.f;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const T *row = static_cast<const T *>(a.W_hh) + ((size_t)l * 4 * dg + (size_t)r * dg + u) * dg;
+#pragma unroll
+            for (int k = 0; k < 16; k += 4) {
+                float v[4];
+                if (dg % 4 == 0) load4<T, true>(row, 16 * kq + k, dg, v);
+                else load4<T, false>(row, 16 * kq + k, dg, v);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) w[r][k + e] = v[e];
+            }
+        }
+        if (!fresh) {
+            c = a.c[s * dg + u];
+            hn = a.h[s * dg + u];
+        }
+        if (kq == 0) s_h[0][unit] = unit < dg ? hn : 0.f;
+        const bool b0 = lane & 1, b1 = lane & 2, is_g = gate == 2;
+        const float mul = is_g ? 2.8853900817779268f : -1.4426950408889634f;         // of |x| for tanh, of x for the sigmoids
+        lds_barrier();
+        for (int t = 0; t < n; ++t) {
+            const float *h = s_h[t & 1] + 16 * kq;
+            const float x = s_pre[(t / TB) & 1][t % TB][4 * unit + gate];
+            float z[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int k = 0; k < 16; k += 4) {
+                const float4 hv = *reinterpret_cast<const float4 *>(h + k);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) z[r] = fmaf(w[r][k + 3], hv.w, fmaf(w[r][k + 2], hv.z, fmaf(w[r][k + 1], hv.y, fmaf(w[r][k], hv.x, z[r]))));
+            }
+            const float r0 = (b0 ? z[2] : z[0]) + dpp_move<kQuadXor1>(b0 ? z[0] : z[2]);
+            const float r1 = (b0 ? z[3] : z[1]) + dpp_move<kQuadXor1>(b0 ? z[1] : z[3]);
+            const float zz = (b1 ? r1 : r0) + dpp_move<kQuadXor2>(b1 ? r0 : r1) + x;
+            const float r = inv_1p_exp2(mul * (is_g ? fabsf(zz) : zz));
+            const float act = is_g ? tanh_of(zz, r) : r;
+            // lanes 0, 2, 1, 3 of a quad hold i, f, g, o
+            const float ig = dpp_move<0x00>(act), fg = dpp_move<0xAA>(act), gg = dpp_move<0x55>(act), og = dpp_move<0xFF>(act);
+            c = fmaf(fg, c, ig * gg);
+            hn = og * tanh_of(c, inv_1p_exp2(2.8853900817779268f * fabsf(c)));
+            if (kq == 0) s_h[(t + 1) & 1][unit] = unit < dg ? hn : 0.f;
+            lds_barrier();
+        }
+        if (kq == 0 && unit < dg) {
+            a.h[s * dg + unit] = hn;
+            a.c[s * dg + unit] = c;
+        }
+        return;
+    }
+
+    // ---- the projecting waves ----
+    constexpr int WA = 2;
+    const int tile0 = (wave - 4) * TILES;
+    float w[RES ? TB : WA][CH][4], xc[CT][4], xn[CT][4];
+    f32x4_t bias[TILES], acc[2];
+    static_for<TILES>([&](auto ic) __attribute__((always_inline)) { bias[decltype(ic)::value] = load_bias(tile0 + decltype(ic)::value); });
+    auto load_part = [&](int part, float (&o)[CH][4]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int k = 0; k < CH; ++k) load_w(tile0 + part / PPT, part % PPT * CH + k, o[k]);
+    };
+    static_for<(RES ? TB : WA)>([&](auto ic) __attribute__((always_inline)) { load_part(decltype(ic)::value, w[decltype(ic)::value]); });
+    // the score of step t from h_t: a unit per lane; the first of these waves writes a block's scores together
+    const float w_s = lane < dg ? Storage<T>::load(static_cast<const T *>(a.w_s) + (size_t)l * dg + lane) : 0.f;
+    const float b_s = Storage<T>::load(static_cast<const T *>(a.b_s) + l);
+    float held = 0.f;
+    auto score = [&](int t) __attribute__((always_inline)) {
+        float u = w_s * s_h[(t + 1) & 1][lane];
+        asm volatile("" : "+v"(u));      // the rounded product wherever this is inlined (never an fma with the next sum)
+        u += dpp_move<kQuadXor1>(u);
+        u += dpp_move<kQuadXor2>(u);
+        u += dpp_move<kRowRor4>(u);
+        u += dpp_move<kRowRor8>(u);
+        // (lanes add their quads in different orders: the score is the first lane's, whichever lane will hold it)
+        u = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(rows_sum(u)))) + b_s;
+        held = lane == (t & (TB - 1)) ? u : held;
+    };
+    auto write_scores = [&](int t) __attribute__((always_inline)) {          // of the block up to step t
+        if (wave == 4 && lane <= (t & (TB - 1))) {
+            const size_t at = s * a.N_cap + a.c0 + (t & ~(TB - 1)) + lane;
+            a.util[at] = held;
+            a.gate[at] = inv_1p_exp2(-1.4426950408889634f * held);
+        }
+    };
+    if constexpr (RES) {        // the first block's
+        load_x(0, xc);
+        if (n > TB) load_x(1, xn);
+        static_for<TB>([&](auto pc) __attribute__((always_inline)) {
+            constexpr int part = decltype(pc)::value;
+            if constexpr (part % PPT == 0) acc[0] = acc[1] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+            static_for<CH>([&](auto kc) __attribute__((always_inline)) { multiply(w[part][decltype(kc)::value], xc[part % PPT * CH + decltype(kc)::value], acc); });
+            if constexpr (part % PPT == PPT - 1) put(0, tile0 + part / PPT, acc[0] + acc[1] + bias[part / PPT]);
+        });
+    } else if (n > TB) {
+        load_x(1, xn);
+    }
+    lds_barrier();
+    int t = 0;
+    for (int block = 0; (block + 1) * TB < n; ++block) {
+#pragma unroll
+        for (int c = 0; c < CT; ++c)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) xc[c][e] = xn[c][e];
+        if ((block + 2) * TB < n) load_x(block + 2, xn);
+        static_for<TB>([&](auto pc) __attribute__((always_inline)) {
+            constexpr int part = decltype(pc)::value, slot = RES ? part : part % WA;
+            score(t - 1);           // (of no step at t = 0)
+            if (part == 0 && t > 0) write_scores(t - 1);
+            if constexpr (part % PPT == 0) acc[0] = acc[1] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+            static_for<CH>([&](auto kc) __attribute__((always_inline)) { multiply(w[slot][decltype(kc)::value], xc[part % PPT * CH + decltype(kc)::value], acc); });
+            if constexpr (!RES) load_part((part + WA) % TB, w[slot]);
+            if constexpr (part % PPT == PPT - 1) put(block + 1, tile0 + part / PPT, acc[0] + acc[1] + bias[part / PPT]);
+            lds_barrier();
+            ++t;
+        });
+    }
+    for (; t < n; ++t) {
+        score(t - 1);
+        if (t % TB == 0 && t > 0) write_scores(t - 1);
+        lds_barrier();
+    }
+    score(n - 1);
+    write_scores(n - 1);
+}
+
 template <typename T, int D, int MB, int RES, int KC>
 static hipError_t launch_v(const LstmArgs &a, hipStream_t st)
 {
@@ -249,6 +474,11 @@ static hipError_t launch_t(const LstmArgs &a, hipStream_t st)
     // instead of in four quads.  (fp32, one against four per workgroup: 2048 sequences x 64
     // steps at d_g = 64 359 -> 340 us, x 1 step 53 -> 20 us; x 8 steps at d_g = 256 843 -> 324 us.)
     const bool four = (long long)a.L * ((a.BH + 3) / 4) >= a.compute_units && gen_tb(D, a.d_g, 4) > 0;
+    // (a workgroup takes a compute unit to itself: see lstm_chain_kernel)
+    if (a.d_g <= 64 && (long long)a.L * a.BH <= a.compute_units) {
+        hipLaunchKernelGGL((lstm_chain_kernel<T, D>), dim3((unsigned)((size_t)a.L * a.BH)), dim3(512), 0, st, a);
+        return hipGetLastError();
+    }
     if (a.d_g <= 64) return four ? launch_v<T, D, 4, 1, 1>(a, st) : launch_v<T, D, 1, 1, 1>(a, st);
     if (a.d_g <= 128) return four ? launch_v<T, D, 4, 2, 2>(a, st) : launch_v<T, D, 1, 2, 2>(a, st);
     return four ? launch_v<T, D, 4, 0, 1>(a, st) : launch_v<T, D, 1, 0, 1>(a, st);

@@ -973,6 +973,38 @@ def test_lstm_prepare_once_gate_many(cfg, fused):
     assert np.abs(outs[1][2].cpu().numpy() - ru).max() <= SCORE_TOL
 
 
+@pytest.mark.parametrize("steps", [1, 15, 16, 17, 33, 50])
+@pytest.mark.parametrize("cfg", [
+    _cfg(293, "f32", d=64, C=8, d_g=64, L=2, B=1, H=3),
+    _cfg(294, "f32", d=128, C=8, d_g=63, L=1, B=2, H=2),
+    _cfg(295, "bf16", d=128, C=8, d_g=27, L=2, B=1, H=2),
+    _cfg(296, "bf16", d=64, C=8, d_g=40, L=1, B=1, H=1),
+    _cfg(297, "f32", d=64, C=8, d_g=64, L=1, B=8, H=32),        # a workgroup for every compute unit
+], ids=lambda c: c.name)
+def test_lstm_gate_narrow_widths(cfg, steps):
+    """The fp32-arithmetic gate at up to 64 units and one sequence per workgroup: blocks of 16 steps with their projections
+    made a block ahead, complete and ragged, against the oracle; a run cut into calls gives one call's bits."""
+    cfg = cfg.replace(T=steps * cfg.C)
+    t = synth.make_inputs(cfg, "cpu")
+    g_ = torch.Generator().manual_seed(cfg.number)
+    lead = (cfg.L, cfg.B, cfg.H)
+    Kb, Vb = ((torch.randn(lead + (steps, cfg.d), generator=g_) * 0.5).to(cfg.torch_dtype) for _ in range(2))
+    sh, g = kb.make_shape(cfg), dev(t)
+    ws = kb.alloc_workspace(kb.workspace_bytes(kb.OP_LSTM_GATE, sh, steps))
+    got = []
+    for cuts in ([0, steps], sorted({0, 1, steps // 2, max(0, steps - 1), steps})):
+        h, c = (torch.full(lead + (cfg.d_g,), 7.0, dtype=torch.float32, device="cuda") for _ in range(2))
+        util, gate = (torch.zeros(lead + (steps,), dtype=torch.float32, device="cuda") for _ in range(2))
+        for c0, c1 in zip(cuts, cuts[1:]):
+            kb.kvev_lstm_gate(sh, Kb.cuda(), Vb.cuda(), kb.lstm_weights(g), c0, c1, h, c, util, gate, ws)
+        torch.cuda.synchronize()
+        got.append((h.cpu(), c.cpu(), util.cpu(), gate.cpu()))
+    assert [torch.equal(x, y) for x, y in zip(*got)] == [True] * 4
+    for x, ref in zip(got[0], orc.lstm_gate(Kb, Vb, kb.lstm_weights(t), 0, steps)):
+        assert np.abs(x.numpy() - ref).max() <= 1e-6          # a handful of fp32 roundings per step (the bar elsewhere is 1e-5)
+
+
+
 def test_gate_cases_reach_the_forms_they_claim():
     claims = {148: (4, 8), 149: (2, 16), 150: (1, 16), 151: (4, 8), 152: (4, 32), 155: (2, 16), 156: (4, 32), 157: (4, 32), 158: (4, 8),
               160: (2, 16), 171: (4, 8), 172: (2, 8), 191: (4, 8), 192: (1, 16), 195: (4, 32), 262: (2, 8), 263: (2, 16), 264: (2, 16),
