@@ -10,21 +10,23 @@
 //     same sums share the four units between them.  Half the matrix work, half the nonlinearities and half the exchange
 //     per group, on compute units that were idle;
 //   * P = 4 workgroups of 4 waves where the launch leaves room for them, else 2 of 8: a wave owns 16 units either way;
-//   * 16 bytes per lane carry 4 units of one column as {payload, stamp, payload, stamp} (stamp = step + 1 within the
-//     launch; 8 aligned bytes are written and read as one).  Two slots by step parity, cleared before the launch: a slot
-//     is rewritten two steps later, by a workgroup that has seen its partners' h of the step between, whose waves had all
-//     read this one: they publish behind a barrier that follows the reads.  Stores write through and loads look past the
-//     caches of one XCD (device scope): the members sit on different ones;
+//   * 8 bytes per lane carry 4 units of one column: |h| <= 1 leaves bit 14 of an fp16 term free (of hi and of lo), and the
+//     first term of every aligned 8-byte word, which is written and read as one, carries a flag there that flips from one
+//     use of a slot to the next.  Two slots by step parity, cleared before the launch: a slot is rewritten two steps
+//     later, by a workgroup that has seen its partners' h of the step between, whose waves had all read this one: they
+//     publish behind a barrier that follows the reads.  Stores write through and loads look past the caches of one XCD
+//     (device scope): the members sit on different ones.  A reader has itself taken the use before from the same
+//     addresses, and such loads do not go back at a location, so it meets the use that it waits for or the one before,
+//     and one bit tells them apart (the first use is told from zeros);
 //   * the input projections of the next step are requested in this one, into registers of their own.
 // A step: products over the own units | take the partners' h, stage in LDS | barrier | products over the partners' units |
 // cell, publish, own h to LDS | barrier.  Bounded waits, status word and the layout of weights and projections: as the
 // paired kernel.
-// Measured (the whole gate call, weights prepared, 32 sequences x 128 steps): 304 us on pairs per 16 sequences, 249 us here
-// (P = 4; about 0.95 us of a step are its own work, the rest is the exchange).  512 sequences x 64 steps: 183 -> 160 us,
-// x 8 steps: 40.6 -> 35.6 us; 1024 x 64 (P = 2): 245 -> 224 us.  Members on one XCD that exchange by plain stores through
-// its L2 took 185 us, but publications of that kind were lost under cache pressure (seen in lstm_quad.hip; cause not
-// shown), so all stores write through.  (With those a flag bit per use, as in
-// lstm_quad.hip, would do in the stamps' place: 233, 149 and 209 us.)
+// Measured (the whole gate call, weights prepared): 32 sequences x 128 steps 304 us on pairs per 16 sequences, 233 us here (P =
+// 4; about 0.95 us of a step are its own work, the rest is the exchange), 248 us with 16 bytes per lane, a stamp of the
+// step beside every two units, in the flag's place; 512 x 64 183, 145 and 156 us; 1024 x 64 (P = 2) 245, 218 and 219 us.
+// Members on one XCD that exchange by plain stores through its L2 took 185 us at the first shape, but publications of that
+// kind were lost under cache pressure (seen in lstm_quad.hip; cause not shown), so all stores write through.
 #include "common.hpp"
 #include "kernels.hpp"
 #include "lstm_common.hpp"
@@ -33,7 +35,7 @@ namespace kvev {
 
 namespace {
 constexpr int kDG = 256, kKS = kDG / 32;
-constexpr uint32_t kGroupSlots = 2 * kDG * 16 * 4;           // [parity][member][column 16][own units], 4 bytes per unit
+constexpr uint32_t kGroupSlots = 2 * kDG * 16 * 2;           // [parity][member][column 16][own units], an fp16 term per unit
 static_assert(2 * kGroupSlots <= kLstmPairExchBytes256, "two groups of 8 fit the scratch planned for one of 16");
 }
 
@@ -44,7 +46,7 @@ __global__ __launch_bounds__(1024 / P) void lstm_rec_oct_kernel(LstmArgs a, int 
     using G = Geo<kDG>;
     constexpr int kNW = 16 / P, kKH = kKS / P, kKP = kKS - kKH;      // waves; k-steps over own units, over the partners'
     constexpr int kOwn = kDG / P, kOP = kOwn + 8, kPP = kDG - kOwn + 8;     // own units; row pitches in LDS
-    constexpr uint32_t kSlot = 16 * kOwn * 4;                        // one member's h of one step: [column 16][own units]
+    constexpr uint32_t kSlot = 16 * kOwn * sizeof(f16_t);            // one member's h of one step: [column 16][own units]
     constexpr int kLR = kOwn / 4, kRows = 64 / kLR;                  // receiving: lanes per row, rows per wave
     __shared__ __align__(16) f16_t s_h[16 * kOP];            // own units of h, row = column of the operand
     __shared__ __align__(16) f16_t s_p[16 * kPP];            // the partners' units
@@ -100,12 +102,12 @@ __global__ __launch_bounds__(1024 / P) void lstm_rec_oct_kernel(LstmArgs a, int 
     fetch_x(0, xin[0]);
 
     const __amdgpu_buffer_rsrc_t e_rsrc = make_rsrc(a.exch + (size_t)gid * kGroupSlots, kGroupSlots);
-    // a look at the partners' slots of parity `par`: this wave takes rows wave * kRows .. of each, 16 bytes per lane
+    // a look at the partners' slots of parity `par`: this wave takes rows wave * kRows .. of each, 8 bytes per lane
     const int rrow = wave * kRows + lane / kLR, rcol = lane % kLR;       // column of the operand; 4 units from 4 rcol on
-    auto ask = [&](int par, u32x4_t (&v)[P - 1]) __attribute__((always_inline)) {
+    auto ask = [&](int par, u32x2_t (&v)[P - 1]) __attribute__((always_inline)) {
 #pragma unroll
         for (int p = 0; p < P - 1; ++p)
-            v[p] = __builtin_amdgcn_raw_buffer_load_b128(e_rsrc, (int)lane16, (int)((par * P + (member + 1 + p) % P) * kSlot + wave * 1024), 16);
+            v[p] = __builtin_amdgcn_raw_buffer_load_b64(e_rsrc, lane * 8, (int)((par * P + (member + 1 + p) % P) * kSlot + wave * 512), 16);
     };
 
     // h of step t0 - 1, split into two fp16 terms: (hi, lo) pairs of two neighbouring units
@@ -162,16 +164,20 @@ __global__ __launch_bounds__(1024 / P) void lstm_rec_oct_kernel(LstmArgs a, int 
             a.gate[s * a.N_cap + t0 + step] = sigmoid_hw(u);
         }
     };
+    // the flag of the publication of step tt (within the launch)
+    constexpr uint32_t kFlag = 0x4000u;
+    auto flag_of = [](int tt) { return (tt >> 1) & 1 ? 0u : kFlag; };
     // The partners' h of step tt - 1 into LDS, from a look asked for earlier; more looks follow if it is not there yet.
     // Member 0 also sums up this wave's rows for the utility.
-    auto receive = [&](int tt, u32x4_t (&v)[P - 1]) __attribute__((always_inline)) {
+    auto receive = [&](int tt, u32x2_t (&v)[P - 1]) __attribute__((always_inline)) {
         typedef _Float16 f16x4_t __attribute__((ext_vector_type(4)));
         const int par = (tt - 1) & 1;
+        const uint32_t flag = flag_of(tt - 1);
         auto complete = [&]() __attribute__((always_inline)) {
-            bool ok = true;
+            uint32_t off = 0;
 #pragma unroll
-            for (int p = 0; p < P - 1; ++p) ok = ok && v[p][1] == (uint32_t)tt && v[p][3] == (uint32_t)tt;
-            return __all(ok) != 0;
+            for (int p = 0; p < P - 1; ++p) off |= v[p][0] ^ flag;
+            return __all((off & kFlag) == 0) != 0;
         };
         bool got = complete();
         for (int spin = 0; !got && spin < a.pair_spin_limit; ++spin) {
@@ -184,7 +190,10 @@ __global__ __launch_bounds__(1024 / P) void lstm_rec_oct_kernel(LstmArgs a, int 
         float u = 0.f;
 #pragma unroll
         for (int p = 0; p < P - 1; ++p) {
-            const u32x2_t o = {v[p][0], v[p][2]};
+            uint32_t x = v[p][0] & ~kFlag;
+            // a NaN without its flag bit reads as a magnitude above 1 (exponent 15, a mantissa), which no |h| <= 1 has
+            if ((x & 0x7fffu) > 0x3c00u) x |= kFlag;
+            const u32x2_t o = {x, v[p][1]};
             *reinterpret_cast<u32x2_t *>(p_wr + p * kOwn) = o;
             const f16x4_t h4 = __builtin_bit_cast(f16x4_t, o);
 #pragma unroll
@@ -207,7 +216,7 @@ __global__ __launch_bounds__(1024 / P) void lstm_rec_oct_kernel(LstmArgs a, int 
     };
 
     bool failed = false;
-    u32x4_t look[P - 1];
+    u32x2_t look[P - 1];
     // one step; false: a wait in it expired in some wave of the workgroup
     auto step = [&](int tt, auto cur_tag) __attribute__((always_inline)) {
         constexpr int cur = decltype(cur_tag)::value, nxt = cur ^ 1;
@@ -262,10 +271,8 @@ __global__ __launch_bounds__(1024 / P) void lstm_rec_oct_kernel(LstmArgs a, int 
         const u32x2_t mine = gather(hi, lo);
         // to the partner first (the long way), then to this workgroup's own waves
         if (member != a.pair_mute) {
-            const uint32_t stamp = (uint32_t)tt + 1;
-            const u32x4_t out = {mine[0], stamp, mine[1], stamp};
-            __builtin_amdgcn_raw_buffer_store_b128(out, e_rsrc, n * kOwn * 4 + wave * 64 + g4 * 16, (int)((cur * P + member) * kSlot), 16);
-            hold_store_data(out);
+            const u32x2_t out = {(mine[0] & ~kFlag) | flag_of(tt), mine[1]};
+            __builtin_amdgcn_raw_buffer_store_b64(out, e_rsrc, n * kOwn * 2 + wave * 32 + g4 * 8, (int)((cur * P + member) * kSlot), 16);
         }
         *reinterpret_cast<u32x2_t *>(h_wr) = mine;
         upart = rows_sum(upart);
