@@ -34,8 +34,6 @@
 namespace kvev {
 
 constexpr float kNegBigMq = -1.0e30f;
-typedef short v4i16_t __attribute__((ext_vector_type(4)));
-typedef v4i16_t __attribute__((address_space(3))) lds_v4i16_t;
 
 // The two kernels below are this body under two register budgets: launches of at most one workgroup per compute unit are
 // latency chains, and the scheduler spends registers on them that would cost a full chip its occupancy (32 sequences x 197
@@ -272,9 +270,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 // by a factor 2^8, which spares the rescaling (235 us at the first shape, but the largest weight is then rounded like the
 // others: 4 % more error); the queries through the slots of the tile stream (240 us); a barrier for every second tile
 // (no difference); query loads a tile earlier, in registers of their own (no difference).
-typedef __attribute__((address_space(3))) unsigned char lds_byte_t;
-typedef __attribute__((address_space(4))) const int32_t const_int_t;
-
 template <int D, int NWV, int NB> struct Mq32 {
     static constexpr int BN = 64, KS = D / 16, DT = D / 32, BM = 32 * NWV, CPR = D / 8;     // CPR: 16-byte pieces of a row
     static constexpr int TB = BN * D * 2;                   // bytes of a tile of K or of V
@@ -290,15 +285,6 @@ template <int D, int NWV, int NB> struct Mq32 {
     static __device__ __forceinline__ int swz_v(int row) { return D == 128 ? 4 * (row & 3) : 4 * ((row >> 1) & 1); }
 };
 
-// 64 lanes' 16 bytes at src straight into LDS at lds + 16 lane.  Not through the builtin: the compiler then waits for every
-// copy in flight before each transposing LDS load, also of another slot; the kernel's own waits say what a load needs.
-template <bool STREAM> __device__ __forceinline__ void copy_to_lds(const void *src, uint32_t lds)
-{
-    if (STREAM) asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off nt" : : "s"(lds), "v"(src) : "memory");
-    else asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(lds), "v"(src) : "memory");
-}
-template <int N> __device__ __forceinline__ void wait_vmem() { asm volatile("s_waitcnt vmcnt(%0)" : : "n"(N) : "memory"); }
-__device__ __forceinline__ float max3(float x, float y, float z) { return fmaxf(fmaxf(x, y), z); }
 
 template <int D, int NWV, int NB, bool STREAM>
 __global__ __launch_bounds__(64 * NWV, NWV == 4 ? 2 : 1) void attn_mq32_kernel(AttnArgs a, int qtiles, int items)

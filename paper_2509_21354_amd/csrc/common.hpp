@@ -175,6 +175,22 @@ template <typename V> __device__ __forceinline__ V buffer_load16_nt(__amdgpu_buf
 // the registers until they are free.
 __device__ __forceinline__ void hold_store_data(u32x4_t v) { asm volatile("s_nop 1" : : "v"(v) : "memory"); }
 
+typedef __attribute__((address_space(3))) unsigned char lds_byte_t;
+typedef __attribute__((address_space(4))) const int32_t const_int_t;
+
+typedef short v4i16_t __attribute__((ext_vector_type(4)));
+typedef v4i16_t __attribute__((address_space(3))) lds_v4i16_t;
+
+// 64 lanes' 16 bytes at src straight into LDS at lds + 16 lane.  Not through the builtin: the compiler then waits for every
+// copy in flight before each transposing LDS load, also of another slot; the kernel's own waits say what a load needs.
+template <bool STREAM> __device__ __forceinline__ void copy_to_lds(const void *src, uint32_t lds)
+{
+    if (STREAM) asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off nt" : : "s"(lds), "v"(src) : "memory");
+    else asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(lds), "v"(src) : "memory");
+}
+template <int N> __device__ __forceinline__ void wait_vmem() { asm volatile("s_waitcnt vmcnt(%0)" : : "n"(N) : "memory"); }
+__device__ __forceinline__ float max3(float x, float y, float z) { return fmaxf(fmaxf(x, y), z); }
+
 template <class F, int... Is>
 __device__ __forceinline__ void static_for_impl(F &&f, std::integer_sequence<int, Is...>)
 {

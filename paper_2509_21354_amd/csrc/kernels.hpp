@@ -115,6 +115,7 @@ struct RetainArgs {
 };
 
 hipError_t launch_attn_decode(const AttnArgs &a, int dtype, hipStream_t st);
+hipError_t launch_attn_decode_mfma(const AttnArgs &a, hipStream_t st);  // bf16, up to 4 queries per unit, unsplit: large launches
 hipError_t launch_attn_mq(const AttnArgs &a, hipStream_t st);           // bf16 MFMA, many queries
 hipError_t launch_select(const SelectArgs &a, hipStream_t st);
 hipError_t launch_retain(const RetainArgs &a, hipStream_t st);
