@@ -100,6 +100,8 @@ def rec_kernel_name(cfg):
         return f"lstm_quad_kernel<{cfg.d}>"
     if cfg.d_g == 256 and oct_groups(cfg) <= 128:
         return f"lstm_rec_oct_kernel<{4 if oct_groups(cfg) <= 64 else 2}>"
+    if cfg.d_g <= 128:
+        return f"lstm_rec_narrow_kernel<{cfg.d_g}>"
     paired = cfg.d_g in (256, 512) and groups <= 128
     return f"lstm_rec_pair_kernel<{cfg.d_g}>" if paired else f"lstm_rec_kernel<{cfg.d_g}>"
 

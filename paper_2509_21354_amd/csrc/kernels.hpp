@@ -128,6 +128,7 @@ hipError_t launch_lstm_mfma(const LstmArgs &a, hipStream_t st);          // bf16
 hipError_t launch_lstm_prepare(const LstmArgs &a, hipStream_t st);       // bf16: the packed weights alone
 hipError_t launch_stream_probe(const void *src, size_t tiles, int tile_bytes, void *dst, int write_bytes, int hints, hipStream_t st);   // calibration
 hipError_t launch_lstm_quad(const LstmArgs &a, hipStream_t st);          // bf16, d_g = 512: projection and recurrence of 32 sequences on four workgroups (weights already packed)
+hipError_t launch_lstm_narrow(const LstmArgs &a, int t0, int nb, hipStream_t st);   // bf16, d_g = 64, 128: the recurrence, 8 sequences per workgroup
 hipError_t launch_lstm_oct(const LstmArgs &a, int t0, int nb, hipStream_t st);   // bf16, d_g = 256: the recurrence on two or four workgroups per 8 sequences
 hipError_t launch_lstm_fused(const LstmArgs &a, hipStream_t st);         // bf16, d_g = 256: the recurrence with the input projection inside (weights already packed)
 

@@ -6,7 +6,8 @@
 //                       exact in the fp32 accumulator), written to scratch in
 //                       the exact register layout the recurrence reads back;
 //   lstm_rec_kernel     the sequential half: one workgroup owns 16 sequences
-//                       of one layer and walks them through the block's steps;
+//                       of one layer and walks them through the block's steps
+//                       (d_g = 64, 128: lstm_narrow.hip);
 //   lstm_rec_pair_kernel  the same on two workgroups per 16 sequences, each
 //                       with half of the hidden units, for launches small enough
 //                       to be resident at once (further down).
@@ -54,15 +55,14 @@ constexpr int kTT = 8;   // steps per workgroup of the input projection (2 when 
 // clock out of L2, which for d_g = 256 (512 KiB of W_hh per step) is longer than
 // the step's MFMA time, so part of the stream stays on chip: class 0 items sit in
 // LDS, class 1 items in registers, and only class 2 items are streamed from L2
-// every step, through a ring of NSLOT register buffers.  d_g <= 128 keeps the
-// whole matrix in LDS; d_g = 512 has room for neither.  Resident items are spread
+// every step, through a ring of NSLOT register buffers.  d_g = 512 has room for
+// neither; d_g <= 128 goes to lstm_narrow.hip.  Resident items are spread
 // over the step so that the streamed ones arrive at an even pace.
 template <int DG> struct Res {
     using G = Geo<DG>;
     static constexpr int ITEMS = G::ITEMS;
     static constexpr int cls(int i)
     {
-        if (DG <= 128) return 0;
         if (DG == 256) {                       // of 16: 3 in LDS, 7 in registers, 6 streamed
             constexpr int t[16] = {0, 1, 2, 1, 1, 2, 0, 1, 2, 1, 1, 2, 0, 1, 2, 2};
             return t[i];
@@ -76,10 +76,9 @@ template <int DG> struct Res {
     static constexpr int NSLOT = NS == 0 ? 1 : DG == 256 ? 3 : 8;
     static constexpr int PF = NSLOT - 1;
     static_assert(NS % NSLOT == 0, "slot rotation must line up with the item loop");
-    // register buffers for LDS items, read one item ahead: two when LDS items follow each other
+    // (LDS items are read one item ahead into one register buffer)
     static constexpr bool lds_adjacent() { for (int i = 0; i < ITEMS; ++i) if (cls(i) == 0 && cls((i + 1) % ITEMS) == 0) return true; return false; }
-    static constexpr int NWL = lds_adjacent() ? 2 : 1;
-    static_assert(NWL == 1 || LRES % 2 == 0, "buffer parity must survive the wrap into the next step");
+    static_assert(!lds_adjacent(), "two LDS items in a row would need two buffers");
     static constexpr size_t lds_h = (size_t)2 * 2 * 16 * (DG + 8) * sizeof(f16_t);      // 2 buffers x (hi, lo) planes
     static constexpr size_t lds_up = (size_t)2 * G::NW * 16 * sizeof(float);
     static constexpr size_t lds_w = (size_t)G::NW * LRES * 4096;
@@ -260,7 +259,7 @@ __global__ __launch_bounds__(Geo<DG>::THREADS) void lstm_rec_kernel(LstmArgs a, 
     using G = Geo<DG>;
     using R = Res<DG>;
     constexpr int NW = G::NW, KS = G::KS, UT = G::UT, ITEMS = G::ITEMS, HP = DG + 8;
-    constexpr int LRES = R::LRES, RRES = R::RRES, NS = R::NS, NSLOT = R::NSLOT, PF = R::PF, NWL = R::NWL;
+    constexpr int LRES = R::LRES, RRES = R::RRES, NS = R::NS, NSLOT = R::NSLOT, PF = R::PF;
     extern __shared__ __align__(16) unsigned char smem_raw[];
     f16_t *s_h = reinterpret_cast<f16_t *>(smem_raw);                                     // [2][2][16][HP]: buffer, (hi, lo)
     float *s_up = reinterpret_cast<float *>(smem_raw + R::lds_h);                         // [2][NW][16]
@@ -342,11 +341,11 @@ __global__ __launch_bounds__(Geo<DG>::THREADS) void lstm_rec_kernel(LstmArgs a, 
     };
     if constexpr (NS > 0) static_for<PF>(load_w);
     // LDS items pass through a register buffer that is read one item ahead
-    f16x8_t wl[NWL][4];
+    f16x8_t wl[4];
     auto read_wl = [&](auto kc) {              // kc: index within the LDS items
         constexpr int k = decltype(kc)::value;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) wl[k % NWL][q] = *reinterpret_cast<const f16x8_t *>(w_lds + k * 4096 + q * 1024);
+        for (int q = 0; q < 4; ++q) wl[q] = *reinterpret_cast<const f16x8_t *>(w_lds + k * 4096 + q * 1024);
     };
     // the two fp16 terms of h for one k-step, read one item ahead
     f16x8_t hb[2][2];
@@ -411,7 +410,7 @@ __global__ __launch_bounds__(Geo<DG>::THREADS) void lstm_rec_kernel(LstmArgs a, 
                     for (int q = 0; q < 4; ++q)
                         acc[q] = __builtin_amdgcn_mfma_f32_16x16x32_f16(wf[q], hb[i & 1][p], acc[q], 0, 0, 0);
             };
-            if constexpr (c == 0) chain(wl[k % NWL]);
+            if constexpr (c == 0) chain(wl);
             else if constexpr (c == 1) chain(wres[k]);
             else chain(wbuf[k % NSLOT]);
             // the prefetch depths are the ones written here, not whatever the scheduler can hoist
@@ -829,9 +828,11 @@ static hipError_t set_attributes_once()
     if (e != hipSuccess) return e;
     const uint64_t bit = (uint64_t)1 << (dev & 63);
     if (done.load(std::memory_order_acquire) & bit) return hipSuccess;
-    e = hipFuncSetAttribute(reinterpret_cast<const void *>(lstm_rec_kernel<DG>), hipFuncAttributeMaxDynamicSharedMemorySize,
-                            (int)Res<DG>::lds);
-    if (e != hipSuccess) return e;
+    if constexpr (DG >= 256) {
+        e = hipFuncSetAttribute(reinterpret_cast<const void *>(lstm_rec_kernel<DG>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                (int)Res<DG>::lds);
+        if (e != hipSuccess) return e;
+    }
     // (the in-projection's staged rows pass 64 KiB at d = 128)
     e = hipFuncSetAttribute(reinterpret_cast<const void *>(lstm_inproj_kernel<DG, 128, kTT>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)(kTT * 16 * (2 * 128 + 8) * sizeof(bf16_t)));
@@ -872,7 +873,6 @@ static hipError_t launch_dg(const LstmArgs &a, hipStream_t st)
 {
     const int gpl = (a.BH + 15) / 16;
     const unsigned groups = (unsigned)(a.L * gpl);
-    const size_t lds = Res<DG>::lds;
     hipError_t e = set_attributes_once<DG>();
     if (e != hipSuccess) return e;
     if (!a.prepared) {
@@ -911,7 +911,12 @@ static hipError_t launch_dg(const LstmArgs &a, hipStream_t st)
                 continue;
             }
         }
-        hipLaunchKernelGGL((lstm_rec_kernel<DG>), dim3(groups), dim3(Geo<DG>::THREADS), lds, st, a, t0, nb);
+        if constexpr (DG <= 128) {
+            e = launch_lstm_narrow(a, t0, nb, st);
+            if (e != hipSuccess) return e;
+        } else {
+            hipLaunchKernelGGL((lstm_rec_kernel<DG>), dim3(groups), dim3(Geo<DG>::THREADS), Res<DG>::lds, st, a, t0, nb);
+        }
     }
     return hipGetLastError();
 }

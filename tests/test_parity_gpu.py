@@ -778,6 +778,25 @@ def test_lstm_gate_eight_sequences_per_group(cfg):
         assert np.abs(got.cpu().numpy() - ref).max() <= tol
 
 
+# 8 sequences on one workgroup: step counts around the 4 (d_g = 64) or 2 steps of a turn and around the 32 or 64 logits that
+# a lane keeps between two stores; ragged groups of 8, and a second half of 16 that is empty
+NARROW_CASES = [
+    _cfg(271, "bf16", d=128, T=1 * 32, C=32, d_g=64, L=1, B=1, H=1),
+    _cfg(272, "bf16", d=64, T=7 * 32, C=32, d_g=64, L=3, B=1, H=8),
+    _cfg(273, "bf16", d=128, T=38 * 32, C=32, d_g=64, L=2, B=3, H=7),       # the last call has 32 steps
+    _cfg(274, "bf16", d=64, T=71 * 32, C=32, d_g=64, L=1, B=1, H=17),
+    _cfg(275, "bf16", d=64, T=2 * 32, C=32, d_g=128, L=2, B=1, H=9),
+    _cfg(276, "bf16", d=128, T=70 * 32, C=32, d_g=128, L=1, B=1, H=8),      # 64 steps
+    _cfg(277, "bf16", d=64, T=135 * 32, C=32, d_g=128, L=2, B=1, H=5),
+    _cfg(278, "bf16", d=64, T=11 * 32, C=32, d_g=128, L=13, B=5, H=65),     # 533 groups: more than two per compute unit
+]
+
+
+@pytest.mark.parametrize("cfg", NARROW_CASES, ids=lambda c: c.name)
+def test_lstm_gate_narrow(cfg):
+    test_lstm_gate_eight_sequences_per_group(cfg)
+
+
 # one case per form in which workgroups hand each other h
 SHARED_CASES = [
     (_cfg(251, "bf16", d=128, T=6 * 32, C=32, d_g=256, L=4, B=1, H=125), (4, 8)),       # 64 groups: a workgroup per compute unit
