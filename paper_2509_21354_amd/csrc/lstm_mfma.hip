@@ -50,6 +50,13 @@
 namespace kvev {
 
 constexpr int kTT = 8;   // steps per workgroup of the input projection (2 when that leaves compute units idle)
+// The input projection waits on memory (rows in, four times as much out), so it needs waves in flight: at d_g = 64 and 128 a
+// wave takes one unit tile, not two (4 and 8 waves on the staged rows), and at d_g = 64 runs of 4 steps, so that four
+// workgroups fit the LDS of a unit.  Whole gate call of 8192 sequences x 128 steps: d_g = 64 912 us with two tiles and 8 steps, 740 us
+// with two and 4, 632 us with one and 4; d_g = 128 1213, 1216 (464 x 241: 268 and 281) and, with one and 8, 1062 us.
+template <int DG> constexpr int run_steps() { return DG == 64 ? 4 : kTT; }
+template <int DG> constexpr int proj_tiles() { return DG <= 128 ? 1 : Geo<DG>::UT; }
+template <int DG> constexpr int proj_threads() { return DG / 16 / proj_tiles<DG>() * 64; }
 
 // Where the weight items of the recurrence live.  A CU pulls at most 64 bytes per
 // clock out of L2, which for d_g = 256 (512 KiB of W_hh per step) is longer than
@@ -93,9 +100,9 @@ template <int DG> struct Res {
 template <int DG> __device__ void pack_whh_blocks(const LstmArgs &a, int block, int nblocks);
 
 template <int DG, int D, int TT>
-__global__ __launch_bounds__(Geo<DG>::THREADS) void lstm_inproj_kernel(LstmArgs a, int t0, int nb)
+__global__ __launch_bounds__(proj_threads<DG>()) void lstm_inproj_kernel(LstmArgs a, int t0, int nb)
 {
-    constexpr int KS = 2 * D / 32, UT = Geo<DG>::UT, XP = 2 * D + 8, THREADS = Geo<DG>::THREADS;
+    constexpr int KS = 2 * D / 32, UT = proj_tiles<DG>(), XP = 2 * D + 8, THREADS = proj_threads<DG>();
     if (a.exch_bytes) {      // the paired recurrence that follows starts from cleared exchange slots
         const size_t nthreads = (size_t)gridDim.x * gridDim.y * THREADS;
         for (size_t i = ((size_t)blockIdx.y * gridDim.x + blockIdx.x) * THREADS + threadIdx.x; i * 16 < a.exch_bytes; i += nthreads)
@@ -123,7 +130,7 @@ __global__ __launch_bounds__(Geo<DG>::THREADS) void lstm_inproj_kernel(LstmArgs 
     }
     __syncthreads();
 
-    const bf16x8_t *Wp = a.wih_packed + ((size_t)l * Geo<DG>::NW + wave) * UT * 4 * KS * 64 + lane;
+    const bf16x8_t *Wp = a.wih_packed + ((size_t)l * (DG / 16) + wave * UT) * 4 * KS * 64 + lane;
     const bf16_t *b_ih = static_cast<const bf16_t *>(a.b_ih) + (size_t)l * 4 * DG;
     const bf16_t *b_hh = static_cast<const bf16_t *>(a.b_hh) + (size_t)l * 4 * DG;
     const bf16_t *xrd = s_x + (size_t)n * XP + g4 * 8;           // + j*16*XP + ks*32
@@ -155,7 +162,7 @@ __global__ __launch_bounds__(Geo<DG>::THREADS) void lstm_inproj_kernel(LstmArgs 
             }
             if (tt0 + j < nb) {
                 const f32x4_t o = {acc[0] + bias[0], acc[1] + bias[1], acc[2] + bias[2], acc[3] + bias[3]};
-                float *dst = a.xproj + xp_block<DG>(gid, a.tb, tt0 + j, wave, ut, q) * 256 + lane * 4;
+                float *dst = a.xproj + xp_block<DG>(gid, a.tb, tt0 + j, (wave * UT + ut) / Geo<DG>::UT, (wave * UT + ut) % Geo<DG>::UT, q) * 256 + lane * 4;
                 *reinterpret_cast<f32x4_t *>(dst) = o;
             }
         }
@@ -834,8 +841,8 @@ static hipError_t set_attributes_once()
         if (e != hipSuccess) return e;
     }
     // (the in-projection's staged rows pass 64 KiB at d = 128)
-    e = hipFuncSetAttribute(reinterpret_cast<const void *>(lstm_inproj_kernel<DG, 128, kTT>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)(kTT * 16 * (2 * 128 + 8) * sizeof(bf16_t)));
+    e = hipFuncSetAttribute(reinterpret_cast<const void *>(lstm_inproj_kernel<DG, 128, run_steps<DG>()>),
+                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)(run_steps<DG>() * 16 * (2 * 128 + 8) * sizeof(bf16_t)));
     if (e != hipSuccess) return e;
     if constexpr (DG == 256 || DG == 512) {
         static_assert(PairGeo<DG>::exch_bytes == (DG / 256) * kLstmPairExchBytes256, "the scratch planner's figure");
@@ -888,17 +895,17 @@ static hipError_t launch_dg(const LstmArgs &a, hipStream_t st)
     for (int t0 = a.c0; t0 < a.c1; t0 += a.tb) {
         const int nb = a.c1 - t0 < a.tb ? a.c1 - t0 : a.tb;
         // few sequences: shorter runs of steps per workgroup so that the launch still covers the chip
-        const bool small = (size_t)groups * ((nb + kTT - 1) / kTT) < 256;
-        const int tt = small ? 2 : kTT;
+        const bool small = (size_t)groups * ((nb + run_steps<DG>() - 1) / run_steps<DG>()) < 256;
+        const int tt = small ? 2 : run_steps<DG>();
         const int ny_proj = (nb + tt - 1) / tt;
         const dim3 grid_in(groups, (unsigned)ny_proj);
         const size_t lds_in = (size_t)tt * 16 * (2 * a.d + 8) * sizeof(bf16_t);
         if (a.d == 64) {
-            if (small) hipLaunchKernelGGL((lstm_inproj_kernel<DG, 64, 2>), grid_in, dim3(Geo<DG>::THREADS), lds_in, st, a, t0, nb);
-            else hipLaunchKernelGGL((lstm_inproj_kernel<DG, 64, kTT>), grid_in, dim3(Geo<DG>::THREADS), lds_in, st, a, t0, nb);
+            if (small) hipLaunchKernelGGL((lstm_inproj_kernel<DG, 64, 2>), grid_in, dim3(proj_threads<DG>()), lds_in, st, a, t0, nb);
+            else hipLaunchKernelGGL((lstm_inproj_kernel<DG, 64, run_steps<DG>()>), grid_in, dim3(proj_threads<DG>()), lds_in, st, a, t0, nb);
         } else {
-            if (small) hipLaunchKernelGGL((lstm_inproj_kernel<DG, 128, 2>), grid_in, dim3(Geo<DG>::THREADS), lds_in, st, a, t0, nb);
-            else hipLaunchKernelGGL((lstm_inproj_kernel<DG, 128, kTT>), grid_in, dim3(Geo<DG>::THREADS), lds_in, st, a, t0, nb);
+            if (small) hipLaunchKernelGGL((lstm_inproj_kernel<DG, 128, 2>), grid_in, dim3(proj_threads<DG>()), lds_in, st, a, t0, nb);
+            else hipLaunchKernelGGL((lstm_inproj_kernel<DG, 128, run_steps<DG>()>), grid_in, dim3(proj_threads<DG>()), lds_in, st, a, t0, nb);
         }
         if constexpr (DG == 256 || DG == 512) {
             if (DG == 256 && a.split == 2 && lstm_takes_oct(a.L, a.BH, a.compute_units)) {

@@ -15,8 +15,8 @@
 // Two buffers of h and of the shares by step parity: what a step reads, the next one leaves alone.
 // Measured (whole gate call, weights prepared) against 16 sequences per workgroup with the weights in LDS and the
 // projections asked for in the step that uses them (1.7 ... 2 us a step): d_g = 128, 7 layers x 8 sequences x 100 steps
-// 170 -> 93 us, 464 sequences x 241 steps 448 -> 268 us, 8192 x 128 1342 -> 1213 us; d_g = 64, 192 x 11 23.6 -> 15.1 us, 8192 x
-// 128 983 -> 912 us (the last of either are bound by the projections' way through memory).
+// 170 -> 93 us, 464 sequences x 241 steps 448 -> 268 us; d_g = 64, 192 x 11 23.6 -> 15.1 us.  8192 x 128 983 -> 912 us (d_g = 64)
+// and 1342 -> 1213 us (128), bound by the projections' way through memory.
 // Registers are bounded to 128, so that two workgroups of d_g = 128 or four of d_g = 64 run beside each other per unit.
 #include "common.hpp"
 #include "kernels.hpp"
