@@ -135,8 +135,7 @@ static AttnPlan plan_attn(const kvev_shape *sh, int Tq, int n_rows)
 }
 
 // single-query launches that read more than this take their rows with the non-temporal hint
-constexpr size_t kStreamBytesDefault = (size_t)256 << 20;     // what the memory-side cache holds
-static std::atomic<size_t> g_stream_bytes{kStreamBytesDefault};
+static std::atomic<size_t> g_stream_bytes{kCacheBytes};
 
 // a frame of queries per key-value sequence (all heads of a group count) goes to the matrix cores
 static bool attn_takes_mq(const kvev_shape *sh, int Tq)
@@ -585,7 +584,7 @@ int kvev_debug_pair_wait(int spin_limit, int mute_member)
 
 int kvev_debug_attn_stream_bytes(size_t bytes)
 {
-    g_stream_bytes = bytes == 0 ? kStreamBytesDefault : bytes;
+    g_stream_bytes = bytes == 0 ? kCacheBytes : bytes;
     return KVEV_OK;
 }
 

@@ -606,9 +606,10 @@ static hipError_t launch_mq_d(const AttnArgs &a, hipStream_t st)
     // Up to 64 queries: the 64-query tiles, whose several workgroups per compute unit hide each other's waits, unless the
     // launch reads more than the caches hold over many sequences: then the deeper copies win (d = 128, 64 queries, old and
     // new: 1020 sequences x 1000 rows 109 and 97 us, 2040 x 350 90 and 79 us; 600 x 1000 66 and 67 us; d = 64 1020 x 1000
-    // 47 and 51 us).
+    // 47 and 51 us).  Counted by the raw rows alone, as every choice here: the compact and the indexed form over the same rows
+    // have other capacities for the summaries and must sum in the same order (a.stream counts those too).
     if (R <= 64) {
-        if (D == 128 && a.stream && a.S >= 3 * cus) return launch_mq32<D, 4, D == 128 ? 2 : 4>(a, st);
+        if (D == 128 && (size_t)a.S * rows * D * 2 * sizeof(bf16_t) > kCacheBytes && a.S >= 3 * cus) return launch_mq32<D, 4, D == 128 ? 2 : 4>(a, st);
         return launch_mq_t<D, 1, 4>(a, st);
     }
     // Up to 128 queries: at d = 64 the workgroups of attn_mq_kernel are small enough to sit three to a compute unit (1020 x

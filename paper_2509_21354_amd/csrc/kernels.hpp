@@ -8,6 +8,7 @@
 namespace kvev {
 
 #define KVEV_ATTN_MAX_SPLIT 256   // decode attention: most splits of one query's rows
+constexpr size_t kCacheBytes = (size_t)256 << 20;     // what the memory-side cache holds
 
 struct AttnArgs {
     const void *Q, *K, *V, *Kbar, *Vbar;

@@ -199,7 +199,7 @@ FRAME_CASES = [
     (_cfg(288, "bf16", d=128, T=160, C=16, W=110, k=3, Tq=75, L=1, B=26, H=20), 0),    # 4 waves: 520 items on 512 workgroups
     (_cfg(289, "bf16", d=64, T=150, C=16, W=64, k=64, Tq=300, L=1, B=13, H=23), 0),    # three tiles of 128 queries each, the last ragged
     (_cfg(290, "bf16", d=128, T=150, C=8, W=1, k=300, Tq=100, L=1, B=9, H=30), 0),     # four queries a head, hardly a raw row, all summaries
-    (_cfg(291, "bf16", d=128, T=129, C=16, W=40, k=2, Tq=10, L=1, B=24, H=64, H_kv=32), 1),   # 20 queries of a group: 4 waves when streamed
+    (_cfg(291, "bf16", d=128, T=129, C=16, W=40, k=2, Tq=10, L=1, B=24, H=64, H_kv=32), 1),   # 20 queries of a group: tiles of 64 queries
     (_cfg(292, "bf16", d=128, T=64, C=16, W=64, k=2, Tq=140, L=1, B=10, H=27), 0),     # exactly one tile of rows
     # few queries: four to a unit, a wave per 32 rows
     (_cfg(298, "bf16", d=128, T=330, C=16, W=230, k=9, Tq=1, L=1, B=40, H=32, H_kv=8), 0),
@@ -249,8 +249,53 @@ def test_frames_that_fill_the_chip(cfg, causal):
         assert_close_storage(Og, ref, cfg.dtype, "O gated")
         assert_close_storage(Od, refd, cfg.dtype, "O dense")
         assert torch.equal(Og, Oc)
-    if not 16 <= cfg.H // cfg.kv_heads * cfg.Tq <= 64:          # (else the streamed launch takes another kernel)
-        assert all(torch.equal(a, b) for a, b in zip(*outs))
+    assert all(torch.equal(a, b) for a, b in zip(*outs))
+
+
+@pytest.mark.parametrize("Tq", [1, 4, 20, 100])
+def test_compact_store_gives_the_same_bits_at_any_capacity(Tq):
+    """kvev_compact_attention gives the bits of kvev_gated_attention over the same rows (Eq. 1) whatever room the store has,
+    also where that room alone makes a launch count as larger than the caches."""
+    cfg = _cfg(302, "bf16", d=128, T=129, C=16, W=40, k=2, Tq=Tq, L=1, B=24, H=32)
+    g = dev(synth.make_qkv(cfg, "cpu"))
+    g_ = torch.Generator().manual_seed(cfg.number)
+    lead, win0, n_raw = (cfg.L, cfg.B, cfg.H), cfg.N_cand * cfg.C, cfg.T - cfg.N_cand * cfg.C
+    Kbar, Vbar = (torch.randn(lead + (cfg.N, cfg.d), generator=g_).to(cfg.torch_dtype).cuda() for _ in range(2))
+    idx, count = (torch.from_numpy(x).cuda() for x in
+                  orc.select_topk(torch.randn(lead + (cfg.N,), generator=g_), cfg.T, cfg.C, cfg.W, cfg.k, cfg.k))
+    Kw, Vw = g["K"][..., win0:, :].contiguous(), g["V"][..., win0:, :].contiguous()
+    order = idx.long()[..., None].expand(lead + (cfg.k, cfg.d))
+    sh, outs = kb.make_shape(cfg), []
+    kb.kvev_debug_attn_stream_bytes(cfg.B * cfg.H * (n_raw + 20) * cfg.d * 4)      # between a store of 2 and one of 64 rows
+    try:
+        ws = kb.alloc_workspace(max(256, kb.workspace_bytes(kb.OP_GATED_ATTENTION, sh, Tq, cfg.k)))
+        outs.append(torch.full_like(g["Q"], 7.0))
+        kb.kvev_gated_attention(sh, g["Q"], Tq, g["K"], g["V"], Kbar, Vbar, idx, count, cfg.k, outs[0], ws)
+        for room in (cfg.k, 64):
+            shw = kb.make_shape(cfg, T=n_raw, T_cap=n_raw, N_cap=room)
+            Kc, Vc = (torch.zeros(lead + (room, cfg.d), dtype=cfg.torch_dtype, device="cuda") for _ in range(2))
+            Kc[..., :cfg.k, :], Vc[..., :cfg.k, :] = Kbar.gather(3, order), Vbar.gather(3, order)
+            ws = kb.alloc_workspace(max(256, kb.workspace_bytes(kb.OP_COMPACT_ATTENTION, shw, Tq, room)))
+            outs.append(torch.full_like(g["Q"], 7.0))
+            kb.kvev_compact_attention(shw, g["Q"], Tq, Kw, Vw, Kc, Vc, count, room, outs[-1], ws)
+        torch.cuda.synchronize()
+    finally:
+        kb.kvev_debug_attn_stream_bytes(0)
+    assert torch.equal(outs[0], outs[1]) and torch.equal(outs[0], outs[2])
+
+
+def test_frames_of_few_queries_that_pass_the_caches():
+    """Frames of up to 64 queries over more raw rows than the memory-side cache holds take another kernel than smaller ones:
+    against the oracle on some of the sequences."""
+    cfg = _cfg(311, "bf16", d=128, T=705, Tq=20, L=1, B=24, H=32)
+    t = synth.make_qkv(cfg, "cuda")
+    assert cfg.B * cfg.H * cfg.T * cfg.d * 4 > 256 << 20
+    O = torch.full_like(t["Q"], 7.0)
+    kb.kvev_dense_attention(kb.make_shape(cfg), t["Q"], cfg.Tq, t["K"], t["V"], O, None, causal=1)
+    torch.cuda.synchronize()
+    few = {k: v[:, ::23, 3:14].cpu().contiguous() for k, v in t.items()}
+    ref = orc.attention_ext(few["Q"], few["K"], few["V"], cfg.T, causal=1)
+    assert_close_storage(O[:, ::23, 3:14].cpu(), ref, cfg.dtype, "O")
 
 
 POISON_CASES = [
