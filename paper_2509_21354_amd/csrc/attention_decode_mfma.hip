@@ -239,8 +239,11 @@ __global__ __launch_bounds__(64 * kWaves, 1) void attn_decode_mfma_kernel(AttnAr
         for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                o[dt][r] += dpp_move<kRowRor4>(o[dt][r]);
-                o[dt][r] += dpp_move<kRowRor8>(o[dt][r]);
+                // An infinite value is infinite in the first term's column (this lane's, if term is 0) and NaN in others,
+                // where it meets a 0 or a remainder of the other sign; finite values leave no NaN in any column.
+                float sum = o[dt][r] + dpp_move<kRowRor4>(o[dt][r]);
+                sum += dpp_move<kRowRor8>(sum);
+                o[dt][r] = sum == sum ? sum : o[dt][r];
             }
         if (term == 0) {
 #pragma unroll

@@ -396,6 +396,34 @@ def test_attention_special_values_stay_where_they_are(cfg):
     assert torch.equal(clean[same], got[same])
 
 
+INF_CASES = [
+    _cfg(303, "bf16", d=128, T=333, Tq=4, L=1, B=16, H=16),       # decode on the matrix cores
+    _cfg(304, "bf16", d=64, T=361, Tq=5, L=1, B=10, H=27),
+    _cfg(305, "bf16", d=128, T=200, Tq=140, L=1, B=16, H=17),     # frames that fill the chip: 8 waves, 4 waves
+    _cfg(306, "bf16", d=64, T=150, Tq=300, L=1, B=13, H=23),
+]
+
+
+@pytest.mark.parametrize("row", [0, 77])
+@pytest.mark.parametrize("cfg", INF_CASES, ids=lambda c: c.name)
+def test_an_infinite_value_makes_its_column_infinite(cfg, row):
+    """Every weight of Eq. 1 is positive, so an infinite element of V makes its column of the output that infinity, where
+    weights enter the matrix cores rounded as well as where they are cut into three terms; no other output changes."""
+    t = synth.make_qkv(cfg, "cpu")
+    sh, Q, K, V = kb.make_shape(cfg), t["Q"].cuda(), t["K"].cuda(), t["V"].cuda()
+    clean, got = torch.empty_like(Q), torch.empty_like(Q)
+    ws = kb.alloc_workspace(max(256, kb.workspace_bytes(kb.OP_DENSE_ATTENTION, sh, cfg.Tq)))
+    kb.kvev_dense_attention(sh, Q, cfg.Tq, K, V, clean, ws)
+    for head, inf in ((5, float("inf")), (6, float("-inf"))):
+        V[0, 3, head, row, 9] = inf
+    kb.kvev_dense_attention(sh, Q, cfg.Tq, K, V, got, ws)
+    torch.cuda.synchronize()
+    for head, inf in ((5, float("inf")), (6, float("-inf"))):
+        assert (got[0, 3, head, :, 9] == inf).all()
+        got[0, 3, head, :, 9] = clean[0, 3, head, :, 9]
+    assert torch.equal(clean, got)
+
+
 @pytest.mark.parametrize("tiny", ["K", "Q"])
 @pytest.mark.parametrize("cfg", SPECIAL_CASES, ids=lambda c: c.name)
 def test_attention_takes_subnormal_rows_as_they_are(cfg, tiny):
