@@ -92,7 +92,7 @@ __global__ __launch_bounds__(64 * kWaves, 1) void attn_decode_mfma_kernel(AttnAr
 #pragma unroll
         for (int i = 0; i < PER; ++i) {
             const int jb = f_j0 + RPI * i, row = RPI * i + lr;
-            const int j = min(f_j0 + row, f_total - 1);                      // (rows past the end are masked in the softmax)
+            const int j = min(f_j0 + row, f_total - 1);
             int r = a.win0 + min(j, max(nraw - 1, 0)) + a.ring_first;
             r = r >= a.T_cap ? r - a.T_cap : r;
             size_t off = (seq_raw + r) * RB;
@@ -110,6 +110,7 @@ __global__ __launch_bounds__(64 * kWaves, 1) void attn_decode_mfma_kernel(AttnAr
                 off = (seq_sum + min(max(c, 0), a.N_cap - 1)) * RB;
                 if (j >= nraw) { kp = Kbar + off; vp = Vbar + off; }
             }
+            if (jb + RPI > f_total && f_j0 + row >= f_total) kp = vp = kZeroRow;     // (masked in the softmax)
             copy_to_lds<STREAM>(kp + ((pc ^ M::swz_k(row)) << 4), slot + i * 1024);
             copy_to_lds<STREAM>(vp + ((pc ^ M::swz_v(row)) << 4), slot + TB + i * 1024);
         }

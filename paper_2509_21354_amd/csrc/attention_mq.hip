@@ -329,7 +329,7 @@ __global__ __launch_bounds__(64 * NWV, NWV == 4 ? 2 : 1) void attn_mq32_kernel(A
 #pragma unroll
         for (int i = 0; i < PER; ++i) {
             const int q = wave + NWV * i, jb = f_j0 + RPI * q;
-            const int j = min(jb + lr, f_nrows - 1);                      // (rows past the end are masked in the softmax)
+            const int j = min(jb + lr, f_nrows - 1);
             int r = a.win0 + (j - f_cnt) + a.ring_first;
             r = r >= a.T_cap ? r - a.T_cap : r;
             size_t off = (seq_raw + r) * RB;
@@ -347,6 +347,7 @@ __global__ __launch_bounds__(64 * NWV, NWV == 4 ? 2 : 1) void attn_mq32_kernel(A
                 off = (seq_sum + min(max(c, 0), a.N_cap - 1)) * RB;
                 if (j < f_cnt) { kp = Kbar + off; vp = Vbar + off; }
             }
+            if (jb + RPI > f_nrows && jb + lr >= f_nrows) kp = vp = kZeroRow;        // (masked in the softmax)
             const uint32_t dst = (uint32_t)(uintptr_t)lds + f_slot * 2 * TB + q * 1024;
             copy_to_lds<STREAM>(kp + ck, dst);
             copy_to_lds<STREAM>(vp + cv, dst + TB);

@@ -188,6 +188,8 @@ template <bool STREAM> __device__ __forceinline__ void copy_to_lds(const void *s
     if (STREAM) asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off nt" : : "s"(lds), "v"(src) : "memory");
     else asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(lds), "v"(src) : "memory");
 }
+// What slots past the last row of a tile are filled with: their softmax weight is 0, and 0 times an infinite value is NaN.
+static __device__ __align__(256) const unsigned char kZeroRow[256] = {};
 template <int N> __device__ __forceinline__ void wait_vmem() { asm volatile("s_waitcnt vmcnt(%0)" : : "n"(N) : "memory"); }
 __device__ __forceinline__ float max3(float x, float y, float z) { return fmaxf(fmaxf(x, y), z); }
 

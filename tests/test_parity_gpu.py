@@ -404,7 +404,7 @@ INF_CASES = [
 ]
 
 
-@pytest.mark.parametrize("row", [0, 77])
+@pytest.mark.parametrize("row", [0, 77, -1])                      # (the last tile of rows is ragged in every case)
 @pytest.mark.parametrize("cfg", INF_CASES, ids=lambda c: c.name)
 def test_an_infinite_value_makes_its_column_infinite(cfg, row):
     """Every weight of Eq. 1 is positive, so an infinite element of V makes its column of the output that infinity, where
