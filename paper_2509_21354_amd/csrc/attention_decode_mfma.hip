@@ -88,31 +88,48 @@ __global__ __launch_bounds__(64 * kWaves, 1) void attn_decode_mfma_kernel(AttnAr
             f_first = 0;
         }
         const size_t seq_raw = (size_t)f_s * a.T_cap, seq_sum = (size_t)f_s * a.N_cap;
-        const_int_t *idx = (const_int_t *)(uintptr_t)(a.idx ? a.idx + (size_t)f_s * a.k_cap : nullptr);
-#pragma unroll
-        for (int i = 0; i < PER; ++i) {
-            const int jb = f_j0 + RPI * i, row = RPI * i + lr;
-            const int j = min(f_j0 + row, f_total - 1);
-            int r = a.win0 + min(j, max(nraw - 1, 0)) + a.ring_first;
+        auto raw_row = [&](int j) __attribute__((always_inline)) {
+            int r = a.win0 + j + a.ring_first;
             r = r >= a.T_cap ? r - a.T_cap : r;
-            size_t off = (seq_raw + r) * RB;
-            const unsigned char *kp = K + off, *vp = V + off;
-            if (min(jb + RPI, f_total) > nraw) {                             // some of these rows are summaries
-                int c = j - nraw;                                            // (null list: compact store, row j is entry j)
-                if (a.idx) {
-                    c = 0;
-#pragma unroll
-                    for (int e = 0; e < RPI; ++e) {
-                        const int ce = idx[max(min(jb + e, f_total - 1) - nraw, 0)];
-                        c = min(jb + e, f_total - 1) == j ? ce : c;
-                    }
-                }
-                off = (seq_sum + min(max(c, 0), a.N_cap - 1)) * RB;
-                if (j >= nraw) { kp = Kbar + off; vp = Vbar + off; }
-            }
-            if (jb + RPI > f_total && f_j0 + row >= f_total) kp = vp = kZeroRow;     // (masked in the softmax)
+            return (seq_raw + r) * RB;
+        };
+        auto copy = [&](int i, const unsigned char *kp, const unsigned char *vp) __attribute__((always_inline)) {
+            const int row = RPI * i + lr;
             copy_to_lds<STREAM>(kp + ((pc ^ M::swz_k(row)) << 4), slot + i * 1024);
             copy_to_lds<STREAM>(vp + ((pc ^ M::swz_v(row)) << 4), slot + TB + i * 1024);
+        };
+        if (f_j0 + kRows <= nraw) {
+#pragma unroll
+            for (int i = 0; i < PER; ++i) {
+                const size_t off = raw_row(f_j0 + RPI * i + lr);
+                copy(i, K + off, V + off);
+            }
+        } else {
+            const_int_t *idx = (const_int_t *)(uintptr_t)(a.idx ? a.idx + (size_t)f_s * a.k_cap : nullptr);
+#pragma unroll
+            for (int i = 0; i < PER; ++i) {
+                const int jb = f_j0 + RPI * i, j = jb + lr;
+                const unsigned char *kp = kZeroRow, *vp = kZeroRow;          // (rows past the end: masked in the softmax)
+                if (j < nraw) {
+                    const size_t off = raw_row(j);
+                    kp = K + off;
+                    vp = V + off;
+                }
+                if (min(jb + RPI, f_total) > nraw) {                         // some of these rows are summaries
+                    int c = j - nraw;                                        // (null list: compact store, row j is entry j)
+                    if (a.idx) {
+                        c = 0;
+#pragma unroll
+                        for (int e = 0; e < RPI; ++e) {
+                            const int ce = idx[max(min(jb + e, f_total - 1) - nraw, 0)];
+                            c = jb + e == j ? ce : c;
+                        }
+                    }
+                    const size_t off = (seq_sum + min(max(c, 0), a.N_cap - 1)) * RB;
+                    if (j >= nraw && j < f_total) { kp = Kbar + off; vp = Vbar + off; }
+                }
+                copy(i, kp, vp);
+            }
         }
         f_slot = f_slot + 1 == kSlots ? 0 : f_slot + 1;
         ++in_flight;
@@ -236,15 +253,32 @@ __global__ __launch_bounds__(64 * kWaves, 1) void attn_decode_mfma_kernel(AttnAr
         float *const s_o = merge + parity * (M::merge / 4), *const s_ml = s_o + kWaves * 4 * D;      // [wave][query][D], [wave][query] {m, l}
         parity ^= 1;
         l = rows_sum(l);
+        // The fourth group's columns are 0 unless a value is not finite (0 times it is NaN).
+        uint32_t odd = 0;
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) odd |= __float_as_uint(o[dt][r]);
+        if (__builtin_expect(__ballot(term == 3 && odd != 0) != 0, 0)) {
+            // An infinite value is infinite in the first term's column (this lane's, if term is 0) and NaN in others, where
+            // it meets a 0 or a remainder of the other sign; finite values leave no NaN in any column.  The first term's
+            // column of such an element is kept, the others leave the sum.
+#pragma unroll
+            for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    float sum = o[dt][r] + dpp_move<kRowRor4>(o[dt][r]);
+                    sum += dpp_move<kRowRor8>(sum);
+                    asm volatile("" : "+v"(sum));        // (a branch, not selects on the way of every unit)
+                    o[dt][r] = sum == sum || term == 0 ? o[dt][r] : 0.f;
+                }
+        }
 #pragma unroll
         for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                // An infinite value is infinite in the first term's column (this lane's, if term is 0) and NaN in others,
-                // where it meets a 0 or a remainder of the other sign; finite values leave no NaN in any column.
-                float sum = o[dt][r] + dpp_move<kRowRor4>(o[dt][r]);
-                sum += dpp_move<kRowRor8>(sum);
-                o[dt][r] = sum == sum ? sum : o[dt][r];
+                o[dt][r] += dpp_move<kRowRor4>(o[dt][r]);
+                o[dt][r] += dpp_move<kRowRor8>(o[dt][r]);
             }
         if (term == 0) {
 #pragma unroll

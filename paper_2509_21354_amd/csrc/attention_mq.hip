@@ -325,32 +325,48 @@ __global__ __launch_bounds__(64 * NWV, NWV == 4 ? 2 : 1) void attn_mq32_kernel(A
     auto copy_tile = [&]() {
         if (f_it >= it_end) return;
         const size_t seq_raw = (size_t)f_s * a.T_cap, seq_sum = (size_t)f_s * a.N_cap;
-        const_int_t *idx = (const_int_t *)(uintptr_t)(a.idx ? a.idx + (size_t)f_s * a.k_cap : nullptr);
-#pragma unroll
-        for (int i = 0; i < PER; ++i) {
-            const int q = wave + NWV * i, jb = f_j0 + RPI * q;
-            const int j = min(jb + lr, f_nrows - 1);
+        auto raw_row = [&](int j) __attribute__((always_inline)) {
             int r = a.win0 + (j - f_cnt) + a.ring_first;
             r = r >= a.T_cap ? r - a.T_cap : r;
-            size_t off = (seq_raw + r) * RB;
-            const unsigned char *kp = K + off, *vp = V + off;
-            if (jb < f_cnt) {                                             // some of these rows are summaries
-                int c = j;                                                // (null list: compact store, row j is entry j)
-                if (a.idx) {
-                    c = 0;
-#pragma unroll
-                    for (int e = 0; e < RPI; ++e) {
-                        const int ce = idx[min(jb + e, f_cnt - 1)];
-                        c = lr == e ? ce : c;
-                    }
-                }
-                off = (seq_sum + min(max(c, 0), a.N_cap - 1)) * RB;
-                if (j < f_cnt) { kp = Kbar + off; vp = Vbar + off; }
-            }
-            if (jb + RPI > f_nrows && jb + lr >= f_nrows) kp = vp = kZeroRow;        // (masked in the softmax)
+            return (seq_raw + r) * RB;
+        };
+        auto copy = [&](int q, const unsigned char *kp, const unsigned char *vp) __attribute__((always_inline)) {
             const uint32_t dst = (uint32_t)(uintptr_t)lds + f_slot * 2 * TB + q * 1024;
             copy_to_lds<STREAM>(kp + ck, dst);
             copy_to_lds<STREAM>(vp + cv, dst + TB);
+        };
+        if (f_j0 >= f_cnt && f_j0 + BN <= f_nrows) {                      // raw rows only
+#pragma unroll
+            for (int i = 0; i < PER; ++i) {
+                const size_t off = raw_row(f_j0 + RPI * (wave + NWV * i) + lr);
+                copy(wave + NWV * i, K + off, V + off);
+            }
+        } else {
+            const_int_t *idx = (const_int_t *)(uintptr_t)(a.idx ? a.idx + (size_t)f_s * a.k_cap : nullptr);
+#pragma unroll
+            for (int i = 0; i < PER; ++i) {
+                const int q = wave + NWV * i, jb = f_j0 + RPI * q, j = jb + lr;
+                const unsigned char *kp = kZeroRow, *vp = kZeroRow;       // (rows past the end: masked in the softmax)
+                if (j >= f_cnt && j < f_nrows) {
+                    const size_t off = raw_row(j);
+                    kp = K + off;
+                    vp = V + off;
+                }
+                if (jb < f_cnt) {                                         // some of these rows are summaries
+                    int c = j;                                            // (null list: compact store, row j is entry j)
+                    if (a.idx) {
+                        c = 0;
+#pragma unroll
+                        for (int e = 0; e < RPI; ++e) {
+                            const int ce = idx[min(jb + e, f_cnt - 1)];
+                            c = lr == e ? ce : c;
+                        }
+                    }
+                    const size_t off = (seq_sum + min(max(c, 0), a.N_cap - 1)) * RB;
+                    if (j < f_cnt) { kp = Kbar + off; vp = Vbar + off; }
+                }
+                copy(q, kp, vp);
+            }
         }
         f_slot = f_slot + 1 == NB ? 0 : f_slot + 1;
         ++ahead;
