@@ -24,7 +24,7 @@
 namespace kvev {
 
 namespace {
-constexpr float kNone = -1.0e30f;       // finite stand-in for -inf
+constexpr float kNone = -3.0e38f;       // finite stand-in for -inf, below (almost) every unscaled score
 constexpr int kWaves = 4, kRows = 32, kSlots = 2;
 }
 
@@ -225,11 +225,10 @@ __global__ __launch_bounds__(64 * kWaves, 1) void attn_decode_mfma_kernel(AttnAr
                 for (int dt = 0; dt < DT; ++dt) o[dt] *= alpha;
                 m = mx;
             }
-            const float mc = -m * c;
             float w[8];
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
-                w[e] = seen[e] ? __builtin_amdgcn_exp2f(fmaf(x[e], c, mc)) : 0.f;
+                w[e] = seen[e] ? __builtin_amdgcn_exp2f((x[e] - m) * c) : 0.f;       // (1 at the maximum, however large the scores)
                 l += w[e];
             }
             // the lane's bf16 term of each weight: what the terms before it leave (exact differences)

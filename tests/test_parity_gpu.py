@@ -424,6 +424,26 @@ def test_an_infinite_value_makes_its_column_infinite(cfg, row):
     assert torch.equal(clean, got)
 
 
+@pytest.mark.parametrize("size", [2.0 ** 17, -2.0 ** 17, -2.0 ** 47])
+@pytest.mark.parametrize("cfg", [c for c in INF_CASES if c.Tq < 16] + [_cfg(307, "bf16", d=128, T=333, Tq=1, L=1, B=16, H=16)], ids=lambda c: c.name)
+def test_decode_takes_scores_of_any_size(cfg, size):
+    """Scores of 2^41 to 2^102 in magnitude, far apart: the softmax of Eq. 1 is then the mean over the rows that tie for the
+    largest score."""
+    t = synth.make_qkv(cfg, "cpu")
+    g_ = torch.Generator().manual_seed(cfg.number)
+    steps = 1 + torch.randint(0, 100, t["K"].shape[:-1], generator=g_) / 128            # (exact in bf16, as is their product with Q)
+    K = (steps * size)[..., None].expand(t["K"].shape).to(cfg.torch_dtype).contiguous()
+    Q = torch.full_like(t["Q"], abs(size)).cuda()
+    best = (K[..., 0] == K[..., 0].amax(-1, keepdim=True)).double()
+    ref = torch.matmul((best / best.sum(-1, keepdim=True)).unsqueeze(-2), t["V"].double()).expand(Q.shape)
+    sh = kb.make_shape(cfg)
+    ws = kb.alloc_workspace(max(256, kb.workspace_bytes(kb.OP_DENSE_ATTENTION, sh, cfg.Tq)))
+    O = torch.empty_like(Q)
+    kb.kvev_dense_attention(sh, Q, cfg.Tq, K.cuda(), t["V"].cuda(), O, ws)
+    torch.cuda.synchronize()
+    assert_close_storage(O, ref.numpy(), cfg.dtype, "O")
+
+
 @pytest.mark.parametrize("tiny", ["K", "Q"])
 @pytest.mark.parametrize("cfg", SPECIAL_CASES, ids=lambda c: c.name)
 def test_attention_takes_subnormal_rows_as_they_are(cfg, tiny):
