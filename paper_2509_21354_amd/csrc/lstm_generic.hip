@@ -238,8 +238,12 @@ __device__ __forceinline__ float rcp_newton(float d)
     const float r = __builtin_amdgcn_rcpf(d);
     return fmaf(fmaf(-d, r, 1.f), r, r);
 }
-// 1 / (1 + 2^y): y is cut at 80, where the result is 1e-24
-__device__ __forceinline__ float inv_1p_exp2(float y) { return rcp_newton(1.f + __builtin_amdgcn_exp2f(y > 80.f ? 80.f : y)); }
+// 1 / (1 + 2^y); 0 where that is less than 2^-126 (the Newton step has no answer to an infinite 2^y)
+__device__ __forceinline__ float inv_1p_exp2(float y)
+{
+    const float r = rcp_newton(1.f + __builtin_amdgcn_exp2f(y));
+    return y > 126.f ? 0.f : r;
+}
 constexpr float kTanhSmall = 0.5625f;
 __device__ __forceinline__ float tanh_small(float x)
 {
@@ -407,7 +411,7 @@ __global__ __launch_bounds__(512, 2) void lstm_chain_kernel(LstmArgs a)
         if (wave == 4 && lane <= (t & (TB - 1))) {
             const size_t at = s * a.N_cap + a.c0 + (t & ~(TB - 1)) + lane;
             a.util[at] = held;
-            a.gate[at] = inv_1p_exp2(-1.4426950408889634f * held);
+            a.gate[at] = 1.f / (1.f + expf(-held));
         }
     };
     if constexpr (RES) {        // the first block's

@@ -1121,6 +1121,36 @@ def test_lstm_gate_narrow_widths(cfg, steps):
         assert np.abs(x.numpy() - ref).max() <= 1e-6          # a handful of fp32 roundings per step (the bar elsewhere is 1e-5)
 
 
+SIGMOID_CASES = [
+    _cfg(308, "f32", d=64, C=8, T=16, d_g=64, L=24, B=1, H=2),         # a sequence per workgroup, a unit per quad of lanes
+    _cfg(309, "f32", d=64, C=8, T=16, d_g=64, L=24, B=1, H=11),        # more sequences than compute units
+    _cfg(310, "bf16", d=64, C=8, T=16, d_g=60, L=24, B=1, H=2),
+]
+
+
+def _bare_gate(cfg, bias, b_s, c0):
+    """One step, from cell state c0, of a gate whose weights are 0 but for the biases bias [L,4,d_g] and b_s [L]: (h, c, gate)."""
+    t = {n: torch.zeros_like(x) for n, x in synth.make_weights(cfg, "cpu").items()}
+    t["b_ih"].view(bias.shape).copy_(bias)
+    t["b_s"].view(b_s.shape).copy_(b_s)
+    lead = (cfg.L, cfg.B, cfg.H)
+    h, c = torch.zeros(lead + (cfg.d_g,), device="cuda"), torch.full(lead + (cfg.d_g,), c0, device="cuda")
+    util, gate = (torch.zeros(lead + (2,), device="cuda") for _ in range(2))
+    x = torch.zeros(lead + (2, cfg.d), dtype=cfg.torch_dtype, device="cuda")
+    kb.kvev_lstm_gate(kb.make_shape(cfg, N_cap=2), x, x, kb.lstm_weights(dev(t)), 1, 2, h, c, util, gate, None)
+    torch.cuda.synchronize()
+    return h.cpu().double(), c.cpu().double(), gate[..., 1].cpu().double()
+
+
+@pytest.mark.parametrize("cfg", SIGMOID_CASES, ids=lambda c: c.name)
+def test_gate_falls_to_zero(cfg):
+    """gate = s(util) (Eq. 3) over utilities from -200 to 60: it has no floor above fp32's smallest normal number, so that a
+    threshold, however small, divides as the utilities do."""
+    u = torch.linspace(-200, 60, cfg.L).to(cfg.torch_dtype)
+    _, _, gate = _bare_gate(cfg, torch.zeros((cfg.L, 4, cfg.d_g), dtype=cfg.torch_dtype), u, 0.0)
+    want = torch.sigmoid(u.double())[:, None, None].expand(gate.shape)
+    assert ((gate - want).abs() <= 1e-5 * want + 2.0 ** -126).all()
+
 
 def test_gate_cases_reach_the_forms_they_claim():
     claims = {148: (4, 8), 149: (2, 16), 150: (1, 16), 151: (4, 8), 152: (4, 32), 155: (2, 16), 156: (4, 32), 157: (4, 32), 158: (4, 8),
