@@ -231,14 +231,22 @@ __global__ __launch_bounds__(kGenThreads, RES == 1 && MB == 1 ? 8 : 4) void lstm
 // ---- d_g <= 64, one sequence per workgroup --------------------------------------------------------------------------
 // Nonlinearities of the step below: the hardware exp2 and reciprocal, the latter with one Newton step, and for small
 // arguments of tanh an odd polynomial (x + x^3 P(x^2), relative error 1.4e-9, a weighted least-squares fit iterated
-// towards the minimax one).  All stay within about 1 ulp, as expf, a division and tanhf do, in a third of the
-// instructions and without branches.  NaN stays NaN.
+// towards the minimax one), in a third of the instructions of expf, a division and tanhf and without branches.  The
+// sigmoids add back what the product with log2 e was rounded by and stay within 3 ulp of themselves, however small (alone,
+// that rounding grows with the argument: 8 ulp at -20).  tanh stays within 2 ulp: its share of 1 / (1 + e^2|x|) falls as
+// the rounding grows.  NaN stays NaN.
 __device__ __forceinline__ float rcp_newton(float d)
 {
     const float r = __builtin_amdgcn_rcpf(d);
     return fmaf(fmaf(-d, r, 1.f), r, r);
 }
-// 1 / (1 + 2^y); 0 where that is less than 2^-126 (the Newton step has no answer to an infinite 2^y)
+// 1 / (1 + 2^y (1 + rest)); 0 where that is less than 2^-126 (the Newton step has no answer to an infinite 2^y)
+__device__ __forceinline__ float inv_1p_exp2(float y, float rest)
+{
+    const float e = __builtin_amdgcn_exp2f(y);
+    const float r = rcp_newton(fmaf(e, rest, 1.f + e));
+    return y > 126.f ? 0.f : r;
+}
 __device__ __forceinline__ float inv_1p_exp2(float y)
 {
     const float r = rcp_newton(1.f + __builtin_amdgcn_exp2f(y));
@@ -351,6 +359,7 @@ __global__ __launch_bounds__(512, 2) void lstm_chain_kernel(LstmArgs a)
         if (kq == 0) s_h[0][unit] = unit < dg ? hn : 0.f;
         const bool b0 = lane & 1, b1 = lane & 2, is_g = gate == 2;
         const float mul = is_g ? 2.8853900817779268f : -1.4426950408889634f;         // of |x| for tanh, of x for the sigmoids
+        const float mul_rest = is_g ? 2.6699516e-8f : -1.3349758e-8f;               // what the constant lacks, times ln 2
         lds_barrier();
         for (int t = 0; t < n; ++t) {
             const float *h = s_h[t & 1] + 16 * kq;
@@ -365,7 +374,9 @@ __global__ __launch_bounds__(512, 2) void lstm_chain_kernel(LstmArgs a)
             const float r0 = (b0 ? z[2] : z[0]) + dpp_move<kQuadXor1>(b0 ? z[0] : z[2]);
             const float r1 = (b0 ? z[3] : z[1]) + dpp_move<kQuadXor1>(b0 ? z[1] : z[3]);
             const float zz = (b1 ? r1 : r0) + dpp_move<kQuadXor2>(b1 ? r0 : r1) + x;
-            const float r = inv_1p_exp2(mul * (is_g ? fabsf(zz) : zz));
+            const float arg = is_g ? fabsf(zz) : zz, y = mul * arg;
+            const float off = fmaf(fmaf(mul, arg, -y), 0.69314718f, mul_rest * arg);
+            const float r = inv_1p_exp2(y, y >= -126.f ? off : 0.f);         // (minus infinity has none)
             const float act = is_g ? tanh_of(zz, r) : r;
             // lanes 0, 2, 1, 3 of a quad hold i, f, g, o
             const float ig = dpp_move<0x00>(act), fg = dpp_move<0xAA>(act), gg = dpp_move<0x55>(act), og = dpp_move<0xFF>(act);

@@ -1152,6 +1152,27 @@ def test_gate_falls_to_zero(cfg):
     assert ((gate - want).abs() <= 1e-5 * want + 2.0 ** -126).all()
 
 
+@pytest.mark.parametrize("which", ["i", "f", "o", "gate"])
+@pytest.mark.parametrize("cfg", SIGMOID_CASES, ids=lambda c: c.name)
+def test_sigmoids_keep_their_relative_precision(cfg, which):
+    """Each sigmoid of Eq. 3 by itself, arguments from -87 to 30: within 3 ulp (exp2 or exp 1, the sum with 1 and a correction
+    or the rounding of the quotient 1, the reciprocal 1), where a step leaves it as c (times c = 1, or times tanh 30 = 1), as h or as gate."""
+    z = torch.linspace(-87, 30, cfg.L * cfg.d_g).view(cfg.L, cfg.d_g).to(cfg.torch_dtype)
+    bias, c0 = torch.zeros((cfg.L, 4, cfg.d_g), dtype=cfg.torch_dtype), 0.0
+    if which == "i":
+        bias[:, 0], bias[:, 2] = z, 30
+    if which == "f":
+        bias[:, 1], c0 = z, 1.0
+    if which == "o":
+        bias[:, 1], bias[:, 3], c0 = 100, z, 30.0
+    h, c, gate = _bare_gate(cfg, bias, z[:, 0], c0)
+    got, arg = (gate, z[:, None, None, 0]) if which == "gate" else (h if which == "o" else c, z[:, None, None])
+    want = torch.sigmoid(arg.double())
+    worst = ((got - want) / want).abs().max().item()
+    report(f"[{cfg.name}] sigmoid {which}: largest relative error {worst * 2 ** 23:.2f} x 2^-23")
+    assert worst <= 3 * 2.0 ** -23
+
+
 def test_gate_cases_reach_the_forms_they_claim():
     claims = {148: (4, 8), 149: (2, 16), 150: (1, 16), 151: (4, 8), 152: (4, 32), 155: (2, 16), 156: (4, 32), 157: (4, 32), 158: (4, 8),
               160: (2, 16), 171: (4, 8), 172: (2, 8), 191: (4, 8), 192: (1, 16), 195: (4, 32), 262: (2, 8), 263: (2, 16), 264: (2, 16),
