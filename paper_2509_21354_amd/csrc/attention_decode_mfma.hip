@@ -312,7 +312,8 @@ static hipError_t launch_dm(const AttnArgs &a, hipStream_t st)
     const int qgroups = (a.G * a.Tq + 3) / 4;
     const int64_t units = (int64_t)a.S * qgroups;
     const auto kernel = attn_decode_mfma_kernel<D, STREAM>;
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, Dm<D>::lds);
+    static std::atomic<uint64_t> done{0};
+    const hipError_t e = allow_lds(kernel, Dm<D>::lds, done);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(kernel, dim3((unsigned)(units < a.compute_units ? units : a.compute_units)), dim3(64 * kWaves), Dm<D>::lds, st, a, qgroups, (int)units);
     return hipGetLastError();

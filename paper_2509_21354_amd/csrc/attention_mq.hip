@@ -585,7 +585,8 @@ static hipError_t launch_mq32_t(const AttnArgs &a, hipStream_t st)
     using M = Mq32<D, NWV, NB>;
     const int qtiles = (a.G * a.Tq + M::BM - 1) / M::BM;
     const int64_t items = (int64_t)a.S * qtiles, fit = (int64_t)a.compute_units * (NWV == 4 ? 2 : 1);
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(attn_mq32_kernel<D, NWV, NB, STREAM>), hipFuncAttributeMaxDynamicSharedMemorySize, M::lds);
+    static std::atomic<uint64_t> done{0};
+    const hipError_t e = allow_lds(attn_mq32_kernel<D, NWV, NB, STREAM>, M::lds, done);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((attn_mq32_kernel<D, NWV, NB, STREAM>), dim3((unsigned)(items < fit ? items : fit)), dim3(64 * NWV), M::lds, st, a, qtiles, (int)items);
     return hipGetLastError();

@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <atomic>
+
 namespace kvev {
 
 #define KVEV_ATTN_MAX_SPLIT 256   // decode attention: most splits of one query's rows
@@ -114,6 +116,20 @@ struct RetainArgs {
     int32_t *count;               // [S]
     int S, row_bytes, k, k_cap, n_new_cap, first_chunk, n_new;
 };
+
+// Dynamic LDS beyond 64 KiB for a kernel, asked for once per device (a bit of `done` per device id): the attribute costs 0.06 to
+// 0.25 us of host time per call (a decode call: 6).
+template <class F> hipError_t allow_lds(F *kernel, int bytes, std::atomic<uint64_t> &done)
+{
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    const uint64_t bit = (uint64_t)1 << (dev & 63);
+    if (done.load(std::memory_order_acquire) & bit) return hipSuccess;
+    e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+    if (e == hipSuccess) done.fetch_or(bit, std::memory_order_release);
+    return e;
+}
 
 hipError_t launch_attn_decode(const AttnArgs &a, int dtype, hipStream_t st);
 hipError_t launch_attn_decode_mfma(const AttnArgs &a, hipStream_t st);  // bf16, up to 4 queries per unit, unsplit: large launches
