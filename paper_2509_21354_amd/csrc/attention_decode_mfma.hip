@@ -25,6 +25,7 @@ namespace kvev {
 
 namespace {
 constexpr float kNone = -3.0e38f;       // finite stand-in for -inf, below (almost) every unscaled score
+constexpr uint32_t kOdd = 0x7fc1;       // a NaN that marks an output for the second look at the kernel's end
 constexpr int kWaves = 4, kRows = 32, kSlots = 2;
 }
 
@@ -39,6 +40,60 @@ template <int D> struct Dm {
     static __device__ __forceinline__ int swz_v(int row) { return D == 128 ? 4 * (row & 3) : 4 * ((row >> 1) & 1); }
 };
 
+// The units of a workgroup (query group qg of sequence s): an XCD takes a contiguous run, in proportion to its workgroups.
+struct Units { int first, end, step; };
+__device__ __forceinline__ Units units_of(int units)
+{
+    const int xcd = blockIdx.x & 7, step = ((int)gridDim.x + 7 - xcd) >> 3;
+    const int before = xcd * ((int)gridDim.x >> 3) + min(xcd, (int)gridDim.x & 7);
+    return {(int)((int64_t)units * before / gridDim.x) + (int)(blockIdx.x >> 3), (int)((int64_t)units * (before + step) / gridDim.x), step};
+}
+
+// Values that are not finite.  An infinity meets zeros and remainders of the other sign in the columns of the weights' terms, and
+// a slot past the last row its weight of 0: NaN, where Eq. 1 is infinite.  Such outputs were marked; the sum of the values
+// that are not finite, among the rows that the query sees, is their result.  (After all units: a look at every unit's columns
+// and zeros in the slots past the end cost every launch 2 to 5 %, taken or not.)
+template <int D> __device__ void second_look(const AttnArgs &a, int wave, int lane)
+{
+    wait_vmem<0>();
+    const int R = a.G * a.Tq, qgroups = (R + 3) / 4, nraw = a.T - a.win0;
+    const Units us = units_of(a.S * qgroups);
+    for (int u = us.first; u < us.end; u += us.step) {
+        const int s = u / qgroups, r = (u - s * qgroups) * 4 + wave;
+        if (r >= R) continue;
+        uint16_t *O = static_cast<uint16_t *>(a.O) + ((size_t)s * R + r) * D + lane * (D / 64);
+        bool odd[D / 64], some = false;
+#pragma unroll
+        for (int e = 0; e < D / 64; ++e) {
+            odd[e] = O[e] == kOdd;
+            some |= odd[e];
+        }
+        if (!__ballot(some)) continue;
+        const int total = nraw + (a.gated ? min(max(a.count[s], 0), a.k_cap) : 0);
+        const int lim = a.causal ? nraw - (a.Tq - 1 - r % a.Tq) : nraw;
+        float sum[D / 64] = {};
+        for (int p = 0; p < total; ++p) {
+            if (p >= lim && p < nraw) continue;
+            size_t at = (size_t)s * a.N_cap;
+            if (p < nraw) {
+                const int w = a.win0 + p + a.ring_first;
+                at = (size_t)s * a.T_cap + (w >= a.T_cap ? w - a.T_cap : w);
+            } else {
+                at += min(max(a.idx ? a.idx[(size_t)s * a.k_cap + p - nraw] : p - nraw, 0), a.N_cap - 1);
+            }
+            const bf16_t *v = static_cast<const bf16_t *>(p < nraw ? a.V : a.Vbar) + at * D + lane * (D / 64);
+#pragma unroll
+            for (int e = 0; e < D / 64; ++e) {
+                const float x = bf16_to_f32(v[e]);
+                sum[e] += fabsf(x) < __builtin_inff() ? 0.f : x;
+            }
+        }
+#pragma unroll
+        for (int e = 0; e < D / 64; ++e)
+            if (odd[e] && sum[e] != 0.f) O[e] = f32_to_bf16(sum[e]);
+    }
+}
+
 template <int D, bool STREAM>
 __global__ __launch_bounds__(64 * kWaves, 1) void attn_decode_mfma_kernel(AttnArgs a, int qgroups, int units)
 {
@@ -50,11 +105,8 @@ __global__ __launch_bounds__(64 * kWaves, 1) void attn_decode_mfma_kernel(AttnAr
     float *const merge = reinterpret_cast<float *>(smem_dm + kWaves * M::wave_lds);
     const int n = lane & 15, g = lane >> 4, qi = n & 3, term = n >> 2;
 
-    // this workgroup's units (query group qg of sequence s); an XCD takes a contiguous run, in proportion to its workgroups
-    const int xcd = blockIdx.x & 7, step = ((int)gridDim.x + 7 - xcd) >> 3;
-    const int before = xcd * ((int)gridDim.x >> 3) + min(xcd, (int)gridDim.x & 7);
-    const int u_first = (int)((int64_t)units * before / gridDim.x) + (int)(blockIdx.x >> 3);
-    const int u_end = (int)((int64_t)units * (before + step) / gridDim.x);
+    const Units own = units_of(units);
+    const int u_first = own.first, u_end = own.end, step = own.step;
 
     const unsigned char *K = static_cast<const unsigned char *>(a.K), *V = static_cast<const unsigned char *>(a.V);
     const unsigned char *Kbar = static_cast<const unsigned char *>(a.Kbar), *Vbar = static_cast<const unsigned char *>(a.Vbar);
@@ -88,48 +140,30 @@ __global__ __launch_bounds__(64 * kWaves, 1) void attn_decode_mfma_kernel(AttnAr
             f_first = 0;
         }
         const size_t seq_raw = (size_t)f_s * a.T_cap, seq_sum = (size_t)f_s * a.N_cap;
-        auto raw_row = [&](int j) __attribute__((always_inline)) {
-            int r = a.win0 + j + a.ring_first;
+        const_int_t *idx = (const_int_t *)(uintptr_t)(a.idx ? a.idx + (size_t)f_s * a.k_cap : nullptr);
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            const int jb = f_j0 + RPI * i, row = RPI * i + lr;
+            const int j = min(f_j0 + row, f_total - 1);                      // (rows past the end are masked in the softmax)
+            int r = a.win0 + min(j, max(nraw - 1, 0)) + a.ring_first;
             r = r >= a.T_cap ? r - a.T_cap : r;
-            return (seq_raw + r) * RB;
-        };
-        auto copy = [&](int i, const unsigned char *kp, const unsigned char *vp) __attribute__((always_inline)) {
-            const int row = RPI * i + lr;
+            size_t off = (seq_raw + r) * RB;
+            const unsigned char *kp = K + off, *vp = V + off;
+            if (min(jb + RPI, f_total) > nraw) {                             // some of these rows are summaries
+                int c = j - nraw;                                            // (null list: compact store, row j is entry j)
+                if (a.idx) {
+                    c = 0;
+#pragma unroll
+                    for (int e = 0; e < RPI; ++e) {
+                        const int ce = idx[max(min(jb + e, f_total - 1) - nraw, 0)];
+                        c = min(jb + e, f_total - 1) == j ? ce : c;
+                    }
+                }
+                off = (seq_sum + min(max(c, 0), a.N_cap - 1)) * RB;
+                if (j >= nraw) { kp = Kbar + off; vp = Vbar + off; }
+            }
             copy_to_lds<STREAM>(kp + ((pc ^ M::swz_k(row)) << 4), slot + i * 1024);
             copy_to_lds<STREAM>(vp + ((pc ^ M::swz_v(row)) << 4), slot + TB + i * 1024);
-        };
-        if (f_j0 + kRows <= nraw) {
-#pragma unroll
-            for (int i = 0; i < PER; ++i) {
-                const size_t off = raw_row(f_j0 + RPI * i + lr);
-                copy(i, K + off, V + off);
-            }
-        } else {
-            const_int_t *idx = (const_int_t *)(uintptr_t)(a.idx ? a.idx + (size_t)f_s * a.k_cap : nullptr);
-#pragma unroll
-            for (int i = 0; i < PER; ++i) {
-                const int jb = f_j0 + RPI * i, j = jb + lr;
-                const unsigned char *kp = kZeroRow, *vp = kZeroRow;          // (rows past the end: masked in the softmax)
-                if (j < nraw) {
-                    const size_t off = raw_row(j);
-                    kp = K + off;
-                    vp = V + off;
-                }
-                if (min(jb + RPI, f_total) > nraw) {                         // some of these rows are summaries
-                    int c = j - nraw;                                        // (null list: compact store, row j is entry j)
-                    if (a.idx) {
-                        c = 0;
-#pragma unroll
-                        for (int e = 0; e < RPI; ++e) {
-                            const int ce = idx[max(min(jb + e, f_total - 1) - nraw, 0)];
-                            c = jb + e == j ? ce : c;
-                        }
-                    }
-                    const size_t off = (seq_sum + min(max(c, 0), a.N_cap - 1)) * RB;
-                    if (j >= nraw && j < f_total) { kp = Kbar + off; vp = Vbar + off; }
-                }
-                copy(i, kp, vp);
-            }
         }
         f_slot = f_slot + 1 == kSlots ? 0 : f_slot + 1;
         ++in_flight;
@@ -158,6 +192,7 @@ __global__ __launch_bounds__(64 * kWaves, 1) void attn_decode_mfma_kernel(AttnAr
     const int v_row = 4 * g + (n >> 2);
     const int v_rd = TB + v_row * RB + ((((n & 3) >> 1) ^ M::swz_v(v_row)) << 4) + 8 * (n & 1);      // d = 16 dt + 4 (n % 4): ^ (dt << 5)
     int slot = 0, qslot = 0, parity = 0;
+    uint32_t any_odd = 0;
     for (int u = u_first; u < u_end; u += step) {
         const int s = u / qgroups, total = total_of(s), r0 = (u - s * qgroups) * 4;
         // positions p of rows that this lane's query sees: summaries (p >= nraw) and raw rows before lim (causal frame: the
@@ -252,26 +287,6 @@ __global__ __launch_bounds__(64 * kWaves, 1) void attn_decode_mfma_kernel(AttnAr
         float *const s_o = merge + parity * (M::merge / 4), *const s_ml = s_o + kWaves * 4 * D;      // [wave][query][D], [wave][query] {m, l}
         parity ^= 1;
         l = rows_sum(l);
-        // The fourth group's columns are 0 unless a value is not finite (0 times it is NaN).
-        uint32_t odd = 0;
-#pragma unroll
-        for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) odd |= __float_as_uint(o[dt][r]);
-        if (__builtin_expect(__ballot(term == 3 && odd != 0) != 0, 0)) {
-            // An infinite value is infinite in the first term's column (this lane's, if term is 0) and NaN in others, where
-            // it meets a 0 or a remainder of the other sign; finite values leave no NaN in any column.  The first term's
-            // column of such an element is kept, the others leave the sum.
-#pragma unroll
-            for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    float sum = o[dt][r] + dpp_move<kRowRor4>(o[dt][r]);
-                    sum += dpp_move<kRowRor8>(sum);
-                    asm volatile("" : "+v"(sum));        // (a branch, not selects on the way of every unit)
-                    o[dt][r] = sum == sum || term == 0 ? o[dt][r] : 0.f;
-                }
-        }
 #pragma unroll
         for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
@@ -299,10 +314,22 @@ __global__ __launch_bounds__(64 * kWaves, 1) void attn_decode_mfma_kernel(AttnAr
         const float inv = L > 0.f ? 1.f / L : 0.f;
         // (the descriptor ends with the sequence's last query: every wave issues one store, which wait_tile counts)
         const __amdgpu_buffer_rsrc_t o_rsrc = make_rsrc(static_cast<unsigned char *>(a.O) + (size_t)s * R * RB, (uint32_t)R * RB);
-        const uint32_t out = pack_bf16x2(acc[0] * inv, acc[D / 64 - 1] * inv);
+        uint32_t out = pack_bf16x2(acc[0] * inv, acc[D / 64 - 1] * inv);
+        const bool odd_lo = acc[0] != acc[0], odd_hi = acc[D / 64 - 1] != acc[D / 64 - 1];
+        if (__builtin_expect(__ballot(odd_lo || odd_hi) != 0, 0)) {
+            out = L != L ? 0x7fc07fc0u : (odd_lo ? kOdd : out & 0xffffu) | (odd_hi ? kOdd << 16 : out & 0xffff0000u);
+            any_odd = 1;
+        }
         if (D == 128) __builtin_amdgcn_raw_buffer_store_b32(out, o_rsrc, (r0 + wave) * RB + lane * 4, 0, 0);
         else __builtin_amdgcn_raw_buffer_store_b16((uint16_t)out, o_rsrc, (r0 + wave) * RB + lane * 2, 0, 0);
         stored = in_flight;
+    }
+
+    if (__builtin_expect(any_odd, 0)) {
+        // (the arguments again: kept through the loop for this, they would not fit the scalar registers)
+        auto *args = (const __attribute__((address_space(4))) AttnArgs *)__builtin_amdgcn_kernarg_segment_ptr();
+        asm volatile("" : "+s"(args));
+        second_look<D>(*(const AttnArgs *)args, wave, lane);
     }
 }
 

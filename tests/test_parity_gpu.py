@@ -424,6 +424,41 @@ def test_an_infinite_value_makes_its_column_infinite(cfg, row):
     assert torch.equal(clean, got)
 
 
+@pytest.mark.parametrize("cfg", [_cfg(312, "bf16", d=128, T=330, C=16, W=230, k=4, Tq=4, L=1, B=8, H=36), _cfg(313, "bf16", d=64, T=361, C=16, W=325, k=1, Tq=5, L=1, B=8, H=36)],
+                         ids=lambda c: c.name)
+def test_infinite_summaries_and_window_rows(cfg):
+    """... in a kept summary for every query, in a row of the window for the queries of a causal frame that see it, through the
+    index list and in the compact store with its window in a ring; a summary that is not kept changes nothing."""
+    t = synth.make_qkv(cfg, "cpu")
+    g_ = torch.Generator().manual_seed(cfg.number)
+    lead, win0, n_raw, inf = (cfg.L, cfg.B, cfg.H), cfg.N_cand * cfg.C, cfg.T - cfg.N_cand * cfg.C, float("inf")
+    Kbar, Vbar = (torch.randn(lead + (cfg.N, cfg.d), generator=g_).to(cfg.torch_dtype) for _ in range(2))
+    idx, count = (torch.from_numpy(x) for x in orc.select_topk(torch.randn(lead + (cfg.N,), generator=g_), cfg.T, cfg.C, cfg.W, cfg.k, cfg.k))
+    V = t["V"]
+    Vbar[0, 1, 2, idx[0, 1, 2, -1], 7] = -inf
+    dropped = next(c for c in range(cfg.N_cand) if c not in idx[0, 1, 5].tolist())
+    Vbar[0, 1, 5, dropped, 7] = inf
+    V[0, 1, 3, cfg.T - 1, 8] = inf                    # seen by the last query alone
+    V[0, 1, 4, win0 + 3, 9] = inf
+    order = idx.long()[..., None].expand(lead + (cfg.k, cfg.d))
+    first = cfg.T - n_raw // 2 - 1
+    roll = (torch.arange(cfg.T) + win0 - first) % cfg.T
+    sh, shw = kb.make_shape(cfg), kb.make_shape(cfg, T=n_raw, T_cap=cfg.T, N_cap=cfg.k)
+    ws = kb.alloc_workspace(max(256, kb.workspace_bytes(kb.OP_GATED_ATTENTION, sh, cfg.Tq, cfg.k), kb.workspace_bytes(kb.OP_COMPACT_ATTENTION, shw, cfg.Tq, cfg.k)))
+    Og, Oc = (torch.full_like(t["Q"], 7.0).cuda() for _ in range(2))
+    dc = count.cuda()
+    kb.kvev_gated_attention(sh, t["Q"].cuda(), cfg.Tq, t["K"].cuda(), V.cuda(), Kbar.cuda(), Vbar.cuda(), idx.cuda(), dc, cfg.k, Og, ws, causal=1)
+    kb.kvev_compact_attention(shw, t["Q"].cuda(), cfg.Tq, t["K"][..., roll, :].contiguous().cuda(), V[..., roll, :].contiguous().cuda(),
+                              Kbar.gather(3, order).cuda(), Vbar.gather(3, order).cuda(), dc, cfg.k, Oc, ws, causal=1, win_first=first)
+    torch.cuda.synchronize()
+    assert torch.equal(Og.view(torch.int16), Oc.view(torch.int16))
+    odd = torch.zeros(Og.shape, dtype=torch.bool)
+    odd[0, 1, 2, :, 7] = odd[0, 1, 3, :, 8] = odd[0, 1, 4, :, 9] = True
+    got = Og.cpu()
+    assert torch.isfinite(got[~odd]).all() and not torch.isfinite(got[odd]).all()
+    assert (got[0, 1, 2, :, 7] == -inf).all() and got[0, 1, 3, -1, 8] == inf and (got[0, 1, 4, :, 9] == inf).all()
+
+
 @pytest.mark.parametrize("size", [2.0 ** 17, -2.0 ** 17, -2.0 ** 47])
 @pytest.mark.parametrize("cfg", [c for c in INF_CASES if c.Tq < 16] + [_cfg(307, "bf16", d=128, T=333, Tq=1, L=1, B=16, H=16)], ids=lambda c: c.name)
 def test_decode_takes_scores_of_any_size(cfg, size):
