@@ -185,8 +185,8 @@ typedef v4i16_t __attribute__((address_space(3))) lds_v4i16_t;
 // copy in flight before each transposing LDS load, also of another slot; the kernel's own waits say what a load needs.
 template <bool STREAM> __device__ __forceinline__ void copy_to_lds(const void *src, uint32_t lds)
 {
-    if (STREAM) asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off nt" : : "s"(lds), "v"(src) : "memory");
-    else asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(lds), "v"(src) : "memory");
+    if (STREAM) asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %1, off nt" : : "{m0}"(lds), "v"(src) : "memory");
+    else asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %1, off" : : "{m0}"(lds), "v"(src) : "memory");
 }
 // What slots past the last row of a tile are filled with: their softmax weight is 0, and 0 times an infinite value is NaN.
 static __device__ __align__(256) const unsigned char kZeroRow[256] = {};

@@ -73,6 +73,33 @@ def test_retention_leaves_room_for_eight_waves(tmp_path):
     assert len(used) == len(spilt) == 5 and max(used) <= 64 and max(spilt) == 0, (used, spilt)
 
 
+M0_PROBE = """
+#include "%s/common.hpp"
+extern "C" __global__ void probe(const uint32_t *src, uint32_t *out, int at)
+{
+    __shared__ uint32_t s[4096];
+    auto *l = (__attribute__((address_space(3))) uint32_t *)s;
+    auto *g = (const __attribute__((address_space(1))) uint32_t *)src;
+    __builtin_amdgcn_global_load_lds(g + threadIdx.x, l + at, 4, 0, 0);
+    kvev::copy_to_lds<false>(src + 4 * threadIdx.x, 8192);
+    __builtin_amdgcn_global_load_lds(g + 64 + threadIdx.x, l + at, 4, 0, 0);
+    kvev::wait_vmem<0>();
+    out[threadIdx.x] = s[threadIdx.x];
+}
+"""
+
+
+def test_copies_to_lds_own_up_to_m0(tmp_path):
+    """The copies that are written as assembly take their LDS address from m0, as the compiler's own do: between two of the
+    compiler's to one address it has to set the register again."""
+    src, out = tmp_path / "probe.hip", tmp_path / "probe.s"
+    src.write_text(M0_PROBE % kvev_build.CSRC)
+    r = subprocess.run([kvev_build.HIPCC, *kvev_build.FLAGS, "-S", "--cuda-device-only", str(src), "-o", str(out)], capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-3000:]
+    seen = [w[0] for line in out.read_text().splitlines() if (w := re.findall(r"^\s(global_load_lds_\w+|s_\w+\s+m0,)", line))]
+    assert [w.split("_")[0] for w in seen] == ["s", "global"] * 3, seen
+
+
 def registers(operand):
     m = re.match(r"([va])\[(\d+):(\d+)\]$", operand)
     if m:
