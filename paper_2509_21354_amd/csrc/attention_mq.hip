@@ -39,10 +39,10 @@ constexpr float kNegBigMq = -1.0e30f;
 // latency chains, and the scheduler spends registers on them that would cost a full chip its occupancy (32 sequences x 197
 // queries x 312 rows: 11.6 us with the budget of a full chip, 10.1 us with that of two waves per SIMD; 2048 x 256 queries
 // the other way round: 307 and 358 us).
-template <int D, int QS, int NWV>
+template <int D, int QS>
 __device__ __forceinline__ void attn_mq_body(const AttnArgs &a, int qtiles, int nblocks)
 {
-    constexpr int BN = 64, RP = D + 8, KS = D / 32, DT = D / 16, BM = 16 * NWV * QS, NT = 64 * NWV;
+    constexpr int BN = 64, RP = D + 8, KS = D / 32, DT = D / 16, BM = 64 * QS, NT = 256;
     // V rows are padded by 32 bytes: the transposing load has 16 lanes read 8 bytes each from 4 consecutive
     // rows, and a row pitch of 8 banks (mod 64) puts those 16 pieces in 16 different bank pairs; the 16-byte
     // row reads of K want the 16-byte padding instead
@@ -235,15 +235,15 @@ __device__ __forceinline__ void attn_mq_body(const AttnArgs &a, int qtiles, int 
     }
 }
 
-template <int D, int QS, int NWV>
+template <int D, int QS>
 __global__ __launch_bounds__(256, 2) void attn_mq_kernel(AttnArgs a, int qtiles, int nblocks)
 {
-    attn_mq_body<D, QS, NWV>(a, qtiles, nblocks);
+    attn_mq_body<D, QS>(a, qtiles, nblocks);
 }
 template <int D>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_mq_small_kernel(AttnArgs a, int qtiles, int nblocks)
 {
-    attn_mq_body<D, 1, 4>(a, qtiles, nblocks);
+    attn_mq_body<D, 1>(a, qtiles, nblocks);
 }
 
 #undef KVEV_MQ_FETCH
@@ -598,13 +598,13 @@ static hipError_t launch_mq32(const AttnArgs &a, hipStream_t st)
     return a.stream && a.G * a.Tq <= 32 * NWV ? launch_mq32_t<D, NWV, NB, true>(a, st) : launch_mq32_t<D, NWV, NB, false>(a, st);
 }
 
-template <int D, int QS, int NWV>
+template <int D, int QS>
 static hipError_t launch_mq_t(const AttnArgs &a, hipStream_t st)
 {
-    const int qtiles = (a.G * a.Tq + 16 * NWV * QS - 1) / (16 * NWV * QS);
+    const int qtiles = (a.G * a.Tq + 64 * QS - 1) / (64 * QS);
     const size_t blocks = (size_t)a.S * qtiles;
     if (blocks == 0) return hipSuccess;
-    hipLaunchKernelGGL((attn_mq_kernel<D, QS, NWV>), dim3((unsigned)blocks), dim3(64 * NWV), 0, st, a, qtiles, (int)blocks);
+    hipLaunchKernelGGL((attn_mq_kernel<D, QS>), dim3((unsigned)blocks), dim3(256), 0, st, a, qtiles, (int)blocks);
     return hipGetLastError();
 }
 
@@ -628,13 +628,13 @@ static hipError_t launch_mq_d(const AttnArgs &a, hipStream_t st)
     // have other capacities for the summaries and must sum in the same order (a.stream counts those too).
     if (R <= 64) {
         if (D == 128 && (size_t)a.S * rows * D * 2 * sizeof(bf16_t) > kCacheBytes && a.S >= 3 * cus) return launch_mq32<D, 4, D == 128 ? 2 : 4>(a, st);
-        return launch_mq_t<D, 1, 4>(a, st);
+        return launch_mq_t<D, 1>(a, st);
     }
     // Up to 128 queries: at d = 64 the workgroups of attn_mq_kernel are small enough to sit three to a compute unit (1020 x
     // 128 x 350: 27.6 and 29.2 us); at d = 128 they are only worth it for a few short rows (400 x 80 x 100: 10.9 and 11.4
     // us, x 350: 22.5 and 20.3 us; 600 x 80 x 100: 19.1 and 16.9 us).
     if (R <= 128) {
-        if (D == 64 || (a.S <= 2 * cus && rows < 192)) return launch_mq_t<D, 2, 4>(a, st);
+        if (D == 64 || (a.S <= 2 * cus && rows < 192)) return launch_mq_t<D, 2>(a, st);
         return launch_mq32<D, 4, D == 128 ? 2 : 4>(a, st);
     }
     // More: 8 waves on 256 queries stage a tile once for all of them; 4 waves on 128 leave less of a ragged frame's last
