@@ -106,6 +106,18 @@ def rec_kernel_name(cfg):
     return f"lstm_rec_pair_kernel<{cfg.d_g}>" if paired else f"lstm_rec_kernel<{cfg.d_g}>"
 
 
+def attn_kernel_name(cfg, rows):
+    """The attention kernel of a launch over `rows` raw rows (unsplit; the library's rule has more borders than the
+    workloads of this file come near)."""
+    queries, seqs = cfg.Tq * (cfg.H // cfg.kv_heads), cfg.L * cfg.B * cfg.kv_heads
+    if cfg.dtype == "bf16" and queries >= 16:
+        return "attn_mq32_kernel" if queries > 128 and seqs * (-(-queries // 64)) > 256 else "attn_mq_kernel"
+    units = seqs * (-(-queries // 4))
+    if cfg.dtype == "bf16" and queries == 4 and cfg.d == 128 and rows >= 192 and units >= 1024:
+        return "attn_decode_mfma_kernel"
+    return "attn_decode_kernel"
+
+
 def recurrence_occupancy(cfg, gate_us):
     """The recurrence is N dependent steps on the compute units its sequences occupy, so for small launches its
     share of the whole chip's MFMA peak says little.  This is the local figure: clocks the matrix pipe of an
@@ -192,8 +204,8 @@ class Bench:
             "gate": (f"{rec_kernel_name(cfg)} (the whole kvev_lstm_gate_prepared call)"
                      if mfma and cfg.d_g in (64, 128, 256, 512) else "lstm_generic_kernel"),
             "select": "select_kernel",
-            "attend": "attn_mq_kernel" if mfma and Tq * (cfg.H // cfg.kv_heads) >= 16 else "attn_decode_kernel",
-            "dense": "attn_mq_kernel" if mfma and Tq * (cfg.H // cfg.kv_heads) >= 16 else "attn_decode_kernel"}
+            "attend": attn_kernel_name(cfg, cfg.T - cfg.N_cand * cfg.C),
+            "dense": attn_kernel_name(cfg, cfg.T)}
 
     def time_alone(self, f, iters):
         torch = self.torch
@@ -251,7 +263,7 @@ class Bench:
         for r in rooflines:
             if r["stage"] == "gate" and self.mfma and cfg.d_g in (64, 128, 256, 512):
                 r["recurrence"] = recurrence_occupancy(cfg, r["us_per_launch"])
-            if r["stage"] == "attend" and r["kernel"] == "attn_mq_kernel":
+            if r["stage"] == "attend" and r["kernel"].startswith("attn_mq"):
                 r["mfma"] = {"bound": "mfma", "achieved": round(self.cost["attend"]["flops"] / r["us_per_launch"] / 1e6, 2),
                              "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
                              "frac": round(self.cost["attend"]["flops"] / r["us_per_launch"] / 1e6 / PEAK_BF16_TFLOPS, 5)}
@@ -284,7 +296,7 @@ class Bench:
         r_att = roof("attend_steady_state", self.kernels["attend"], cost["attend"], t_att, "hbm", None)
         r_att["traffic"] = measured_traffic(cfg.name, "attend")
         r_den = roof("dense", self.kernels["dense"], cost["dense"], t_den, "hbm", cfg.name)
-        if self.kernels["dense"] == "attn_mq_kernel":
+        if self.kernels["dense"].startswith("attn_mq"):
             for r, c in ((r_att, cost["attend"]), (r_den, cost["dense"])):
                 r["mfma"] = {"bound": "mfma", "achieved": round(c["flops"] / r["us_per_launch"] / 1e6, 2), "peak": PEAK_BF16_TFLOPS,
                              "unit": "TFLOP/s", "frac": round(c["flops"] / r["us_per_launch"] / 1e6 / PEAK_BF16_TFLOPS, 5)}
@@ -637,6 +649,7 @@ def grouped_query_cfg3(torch, kb, synth, gated_us_32_heads):
     kv_frac = c3g.kv_heads / c3g.H
     return {"workload": c3.name + " with 8 key-value heads for 32 query heads (grouped-query attention; random "
                                   "summaries and scores, attention kernels only)",
+            "kernel": attn_kernel_name(c3g, c3g.T - c3g.N_cand * c3g.C),
             "gated_us": round(tgg, 2), "gated_GBps_unique_rows": round(co3["attend"]["bytes"] * kv_frac / tgg / 1e3, 1),
             "dense_us": round(tdg, 2), "dense_GBps_unique_rows": round(co3["dense"]["bytes"] * kv_frac / tdg / 1e3, 1),
             "speedup_vs_dense": round(tdg / tgg, 2),
