@@ -396,11 +396,11 @@ hipError_t launch_attn_decode(const AttnArgs &a, int dtype, hipStream_t st)
 {
     // Four queries or more that share bf16 rows, at least one unit (a group of four) per compute unit, unsplit: on the matrix
     // cores, but for short runs of raw rows, where the several workgroups per compute unit here hide each other's starts,
-    // and for many units of middling length (this kernel and that one: d = 128, one group of 4, 1024 units x 352 rows 34.6
-    // and 32.0 us, 2048 x 96 25.4 and 27.7 us; two or three groups, 2048 units x 364 67.2 and 67.7 us, 3072 x 364 91 and 94 us, 960 x
-    // 364 36 and 32 us, 3072 x 790 207 and 158 us; d = 64, 256 x 352 10.7 and 6.9 us, 512 x 220 and 164 summaries 14.7 and 15.4
-    // us, 2048 x 352 35.1 and 36.4 us, x 1000 89 and 85 us).  With fewer queries the vector unit has time to spare (one
-    // query: 1024 x 352 28.3 and 31.5 us).
+    // and for many units of middling length (this kernel and that one, rows that the memory-side cache holds where they
+    // fit it: d = 128, one group of 4, 1024 units x 352 rows 34.6 and 32.0 us, 2048 x 96 25.4 and 27.7 us; two or three groups,
+    // 2048 units x 364 67.2 and 67.7 us, 3072 x 364 91 and 94 us, 960 x 364 36 and 32 us, 3072 x 790 207 and 158 us; d = 64, 256 x
+    // 352 10.7 and 6.9 us, 512 x 220 and 164 summaries 14.7 and 15.4 us, 2048 x 352 35.1 and 36.4 us, x 1000 89 and 85
+    // us).  With fewer queries the vector unit has time to spare (one query: 1024 x 352 28.3 and 31.5 us).
     const int64_t R = (int64_t)a.G * a.Tq, units = a.S * ((R + 3) / 4), cus = a.compute_units;
     const int rows = a.T - a.win0;
     const bool long_enough = a.d == 128 ? rows >= 192 && (R == 4 || units <= 4 * cus || rows >= 600)

@@ -13,9 +13,10 @@
 // fourth tile of its workgroup's unit, two tiles ahead and on into the next unit, whose queries ride along.  One barrier
 // per unit, where the four waves' partial results meet.  K and V tiles lie in LDS with their 16-byte pieces exchanged
 // within a row so that no bank is touched twice by a read; V is read with the transposing load (see attention_mq.hip).
-// Measured in turn, attn_decode_kernel and this one, d = 128: 2048 sequences x 333 rows, 4 queries 68.3 and 64.5 us (5.2 TB/s; the
-// copies alone 58 us: the 128 KiB of LDS that can be under way per compute unit are what bounds it now); 1024 x 333 43.7 and
-// 39.7 us; 8 queries, 512 x 1000 82 and 59 us.
+// Measured in turn, attn_decode_kernel and this one, d = 128, on changing inputs: 2048 sequences x 325 rows, 4 queries 67.9 and
+// 64.1 us (5.4 TB/s; matrix cores 3 %, vector unit 28 % busy: the 128 KiB of LDS that can be under way per compute unit
+// are what bounds it now); 1024 x 333 38.8 and 36.1 us (33.8 and 31.3 us on inputs that the memory-side cache holds); 8
+// queries, 512 x 1000 81 and 64 us (83 and 57 us).
 #include "common.hpp"
 #include "kernels.hpp"
 #include "lstm_common.hpp"
