@@ -252,9 +252,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 
 // ---- launches that fill the chip ------------------------------------------------------------------------------------
 // The same products with 32 queries per wave on v_mfma_f32_32x32x16_bf16 (C: query lane % 32, 16 of 32 keys in a lane's
-// registers).  What bounds it: power on long rows (at 8192 rows and more the chip clocks it at 1.65 GHz, matrix cores 52 %, vector unit 51 %
-// busy, 19 % of it together; a bf16 product of 8192^3 reaches 1.27 PFLOP/s here), on short ones the ends of an item (640 rows: 35,
-// 46 and 14 % at 2.0 GHz; 51 % of the HBM peak).  What is different from the kernel above:
+// registers).  What bounds it: power on long rows (32768 rows: the chip clocks it at 1.65 GHz, matrix cores 52 %,
+// vector unit 51 % busy, 19 % of it together; a bf16 product of 8192^3 reaches 1.27 PFLOP/s here), on short ones the
+// ends of an item (640 rows: 35, 46 and 14 % at 2.0 GHz; 51 % of the HBM peak).  What is different from the kernel above:
 //   * a 32 x 32 x 16 instruction takes half the LDS fragments per flop, and vector instructions run beside it that do not
 //     beside a 16 x 16 x 32 one (two waves per SIMD, 128 matrix clocks against 16 fma + 4 exp2 per wave: 140 clocks
 //     together, 202 with the smaller one);
