@@ -121,15 +121,17 @@ int kvev_chunk_pool(const kvev_shape *shape, const void *K, const void *V, int p
  * from the caller instead), and for most shapes fp32 input projections of a
  * block of steps: any size from one step's worth up is accepted, smaller blocks
  * mean more launches.  Launches of bf16 storage with d_g = 256 that give every
- * compute unit a group of 32 sequences, and with d_g = 512 and more than 16
- * sequences per layer, run as one kernel (at d_g = 512 once per compute
- * units / 4 groups of 32 sequences) and keep no projections at all.  Calls that share a workspace
+ * compute unit a group of 32 sequences, and with d_g = 512, more than 16
+ * sequences per layer and either more than one group of 16 sequences per 8
+ * compute units or N_cap < 16, run as one kernel (at d_g = 512 once per compute
+ * units / 4 groups of 32 sequences) and keep no projections at all.  (At d_g =
+ * 512 a workspace of that size is accepted below that number of groups too.)  Calls that share a workspace
  * must not overlap (it also carries what the workgroups of one launch
  * exchange).
  * Status word: the first int32 of the workspace.  Small launches (bf16; d_g =
  * 256 or 512 with at most one group of 16 sequences per 2 compute units of the
- * device, or the groups of 32 at d_g = 512 above) run each group on two or four
- * cooperating workgroups, which wait for each other's data with a bounded
+ * device, or the groups of 32 at d_g = 512 above) run each group on two, four or
+ * eight cooperating workgroups, which wait for each other's data with a bounded
  * number of polls.  Should the bound ever
  * expire (the GPU held by other work for seconds), the launch still ends
  * normally, its util, gate and c entries are NaN, and it stores 1 in the status

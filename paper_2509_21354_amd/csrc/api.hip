@@ -310,9 +310,10 @@ static size_t lstm_ws_weights(const kvev_shape *sh)
 constexpr size_t kLstmWsHead = 256;
 // KVEV_LSTM_QUAD=0 (read once) keeps d_g = 512 on pairs of workgroups where quadruples would be taken.
 static const int g_lstm_quad = env_int("KVEV_LSTM_QUAD", 1);
+// (N_cap = 0: the form of a call whose scratch has no room for the projections of the eight-workgroup form)
 static int lstm_split_of(const kvev_shape *sh)
 {
-    return lstm_takes_fused(sh) ? 0 : lstm_split(sh->d_g, sh->L, sh->B * kv_heads(sh), device_compute_units(), g_lstm_quad != 0);
+    return lstm_takes_fused(sh) ? 0 : lstm_split(sh->d_g, sh->L, sh->B * kv_heads(sh), sh->N_cap, device_compute_units(), g_lstm_quad != 0);
 }
 // groups of 32 sequences that one launch of the four-workgroup kernel takes: a workgroup per compute unit at most
 // (kvev_debug_lstm_quad_groups lowers it, so that a small shape walks the several-launches path)
@@ -438,6 +439,12 @@ static int lstm_gate_common(const kvev_shape *sh, const void *Kbar, const void *
     hipStream_t st = static_cast<hipStream_t>(stream);
     hipError_t e;
     if (lstm_takes_mfma(sh)) {
+        kvev_shape small = *sh;
+        // scratch of the size that quadruples need, which keep no projections, stays accepted, and takes them
+        if (lstm_split_of(sh) == 8 && ws_bytes < lstm_ws_pack(sh, prepared) + lstm_ws_per_step(sh)) {
+            small.N_cap = 0;
+            sh = &small;
+        }
         const size_t per = lstm_ws_per_step(sh), pack = lstm_ws_pack(sh, prepared);
         if (!ws || !aligned16(ws) || ws_bytes < pack + per) return KVEV_ERR_WORKSPACE;
         a.fused = lstm_takes_fused(sh) ? 1 : 0;

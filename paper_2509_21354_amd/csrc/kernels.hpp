@@ -58,7 +58,7 @@ struct LstmArgs {
     const __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 *wih_packed;   // workspace: W_ih in fragment order
     unsigned char *exch;  // workspace: exchange slots of the split recurrence (lstm_split_exch_bytes), or null
     size_t exch_bytes;    // 0: one workgroup per sequence group
-    int split;            // workgroups that share a sequence group in the recurrence: 0 (one), 2 or 4 (lstm_split)
+    int split;            // workgroups that share a sequence group in the recurrence: 0 (one), 2, 4 or 8 (lstm_split)
     int quad_groups;      // split == 4: groups of 32 sequences per launch at most (compute units / 4)
     int pair_spin_limit;  // polls a wave of the paired recurrence spends on one wait before it gives up
     int pair_mute;        // member (0, 1) whose publications are withheld, -1: none (failure-path tests only)
@@ -78,11 +78,19 @@ struct LstmArgs {
 // on four workgroups (a quarter of the stream each, and every fragment serves two blocks of sequences); a launch
 // takes at most one workgroup per compute unit, larger calls are cut into several launches.  So all workgroups of a
 // launch can be resident together on an idle device (bounded waits in the kernels cover the rest).
+// Eight (lstm_rec_oct_kernel): at d_g = 512 while eight workgroups per 16 sequences fit the chip, which keeps all of W_hh in
+// registers; up to there it is the faster one whatever the sequences per layer (512 x 64 steps 341 against 570 us, 16 a layer 387
+// against 910; 1024 in two launches 730 against 579, so it ends there).  Caches of fewer than kLstmOctMinChunks chunks keep the
+// others, which need no scratch for projections (8 KiB per sequence and step): 8 steps of 512 sequences take 80 against 91 us, a
+// difference that such a cache pays only once or twice.
 constexpr size_t kLstmPairExchBytes256 = 65536;     // scratch per group of 16 sequences and 256 hidden units
+constexpr int kLstmOctMinChunks = 16;
+constexpr size_t kLstmOctExchBytes512 = 32768;      // scratch per 8 sequences at d_g = 512 on eight workgroups
 constexpr size_t kLstmQuadExchBytes = 131072;       // scratch per group of 32 sequences
-inline int lstm_split(int d_g, int L, int BH, int compute_units, bool quad_allowed)
+inline int lstm_split(int d_g, int L, int BH, int N_cap, int compute_units, bool quad_allowed)
 {
     const long long g16 = (long long)L * ((BH + 15) / 16);
+    if (d_g == 512 && quad_allowed && N_cap >= kLstmOctMinChunks && 8 * g16 <= compute_units) return 8;
     if (d_g == 512 && quad_allowed && BH > 16 && compute_units >= 4) return 4;     // (more groups than fit at once: several launches)
     if ((d_g == 256 || d_g == 512) && 2 * g16 <= compute_units) return 2;
     return 0;
@@ -96,6 +104,7 @@ inline size_t lstm_split_exch_bytes(int split, int d_g, int L, int BH, int quad_
         const long long g32 = (long long)L * ((BH + 31) / 32);
         return (size_t)(g32 < quad_groups ? g32 : quad_groups) * kLstmQuadExchBytes;
     }
+    if (split == 8) return (size_t)L * ((BH + 15) / 16) * 2 * kLstmOctExchBytes512;
     if (split == 2) return (size_t)L * ((BH + 15) / 16) * (d_g / 256) * kLstmPairExchBytes256;
     return 0;
 }

@@ -908,7 +908,7 @@ static hipError_t launch_dg(const LstmArgs &a, hipStream_t st)
             else hipLaunchKernelGGL((lstm_inproj_kernel<DG, 128, run_steps<DG>()>), grid_in, dim3(proj_threads<DG>()), lds_in, st, a, t0, nb);
         }
         if constexpr (DG == 256 || DG == 512) {
-            if (DG == 256 && a.split == 2 && lstm_takes_oct(a.L, a.BH, a.compute_units)) {
+            if (a.split == 8 || (DG == 256 && a.split == 2 && lstm_takes_oct(a.L, a.BH, a.compute_units))) {
                 e = launch_lstm_oct(a, t0, nb, st);
                 if (e != hipSuccess) return e;
                 continue;

@@ -1,0 +1,93 @@
+"""The gate at d_g = 512 on eight workgroups per 8 or 16 sequences (bf16, Eq. 3), which caches of 16 chunks and more take while
+the launch fits the chip: against the CPU oracle, and the things that must not depend on how a call is cut."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import kvev_oracle as orc
+from paper_2509_21354_amd import binding as kb
+from paper_2509_21354_amd import synth
+from tests import test_parity_gpu as base
+
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    base._cfg(401, "bf16", d=128, T=17 * 32, C=32, d_g=512, L=1, B=1, H=1),      # one sequence
+    base._cfg(402, "bf16", d=64, T=16 * 32, C=32, d_g=512, L=3, B=1, H=13),      # a ragged second group of 8 in every layer
+    base._cfg(403, "bf16", d=128, T=19 * 32, C=32, d_g=512, L=4, B=2, H=32),     # 32 groups of 8: a workgroup on every compute unit
+    base._cfg(404, "bf16", d=64, T=16 * 32, C=32, d_g=512, L=11, B=1, H=19),     # two groups in turn; three a layer, the last ragged, the fourth empty
+    base._cfg(405, "bf16", d=128, T=18 * 32, C=32, d_g=512, L=32, B=1, H=9),     # two in turn in every layer, the second with one sequence
+]
+
+
+@pytest.mark.parametrize("cfg", CASES, ids=lambda c: c.name)
+def test_eight_workgroups(cfg):
+    """... in one call, in pieces with scratch for two steps and for all, one step per call, and with the scratch of a plan that
+    keeps no projections (which takes another form: the oracle's values, not the same bits)."""
+    assert 8 * cfg.L * ((cfg.B * cfg.kv_heads + 15) // 16) <= torch.cuda.get_device_properties(0).multi_processor_count
+    N = cfg.T // cfg.C
+    w = synth.make_weights(cfg, "cpu")
+    Kbar, Vbar = base._summaries(cfg, N)
+    sh = kb.make_shape(cfg, N_cap=N)
+    lead = (cfg.L, cfg.B, cfg.H)
+    gw, Kb, Vb = base.dev(w), Kbar.cuda(), Vbar.cuda()
+    plain = kb.workspace_bytes(kb.OP_LSTM_GATE, kb.make_shape(cfg, N_cap=15, T=15 * cfg.C), 0)
+    outs = []
+    for cuts, steps in (([(0, N)], N), ([(0, 1), (1, 6), (6, N)], 2), ([(t, t + 1) for t in range(N)], 1), ([(0, N)], None)):
+        ws = kb.alloc_workspace(plain if steps is None else kb.workspace_bytes(kb.OP_LSTM_GATE, sh, steps))
+        h = torch.full(lead + (cfg.d_g,), 7.0, device="cuda")
+        c = torch.full_like(h, float("nan"))
+        util = torch.full(lead + (N,), 9.0, device="cuda")
+        gate = torch.full_like(util, 9.0)
+        for a, b in cuts:
+            kb.kvev_lstm_gate(sh, Kb, Vb, kb.lstm_weights(gw), a, b, h, c, util, gate, ws)
+        torch.cuda.synchronize()
+        assert int(ws[:4].view(torch.int32).item()) == 0
+        outs.append((h, c, util, gate))
+    for out in outs[1:3]:
+        assert all(torch.equal(x, y) for x, y in zip(outs[0], out))
+    ref = orc.lstm_gate(Kbar, Vbar, kb.lstm_weights(w), 0, N)
+    for out in (outs[0], outs[3]):
+        for got, r, tol in zip(out, ref, (1, 2, 1, 1)):
+            assert np.abs(got.cpu().numpy() - r).max() <= tol * base.SCORE_TOL
+
+
+@pytest.mark.parametrize("cfg", [CASES[1], CASES[3]], ids=lambda c: c.name)
+def test_eight_workgroups_wait_expires(cfg):
+    """A member that withholds its publications: every wait ends, scores and cell state come back NaN, the status word is set."""
+    base.test_lstm_pair_wait_expires_cleanly(cfg)
+
+
+@pytest.mark.parametrize("cfg", [CASES[1], CASES[3]], ids=lambda c: c.name)
+def test_eight_workgroups_keep_h(cfg):
+    """No member replaces its units of the carried h before it has heard from all others."""
+    N, t, width = 16, 2, cfg.d_g // 8
+    w = synth.make_weights(cfg, "cpu")
+    Kbar, Vbar = base._summaries(cfg, N)
+    sh = kb.make_shape(cfg, N_cap=N, T=N * cfg.C)
+    gw, Kb, Vb = base.dev(w), Kbar.cuda(), Vbar.cuda()
+    ws = kb.alloc_workspace(kb.workspace_bytes(kb.OP_LSTM_GATE, sh, N))
+    h0 = torch.zeros((cfg.L, cfg.B, cfg.H, cfg.d_g), device="cuda")
+    c0, util = torch.zeros_like(h0), torch.zeros((cfg.L, cfg.B, cfg.H, N), device="cuda")
+    gate = torch.zeros_like(util)
+    kb.kvev_lstm_gate(sh, Kb, Vb, kb.lstm_weights(gw), 0, t, h0, c0, util, gate, ws)
+
+    def step():
+        h, c = h0.clone(), c0.clone()
+        kb.kvev_lstm_gate(sh, Kb, Vb, kb.lstm_weights(gw), t, t + 1, h, c, util, gate, ws)
+        torch.cuda.synchronize()
+        return h, c
+
+    good_h, good_c = step()
+    kb.kvev_debug_pair_wait(4096, 1)
+    try:
+        h, c = step()
+    finally:
+        kb.kvev_debug_pair_wait()
+    assert int(ws[:4].view(torch.int32).item()) == 1
+    for m in range(8):
+        u = slice(m * width, (m + 1) * width)
+        if m == 1:
+            assert torch.equal(c[..., u], good_c[..., u]) and torch.equal(h[..., u], good_h[..., u])
+        else:
+            assert torch.isnan(c[..., u]).all() and torch.equal(h[..., u], h0[..., u])
