@@ -57,6 +57,11 @@ template <int N, class F> __device__ __forceinline__ void rows_fold2(float (&v)[
 // NW waves per workgroup: 4 when the launch fills the chip several times over, 16 (one tile row per wave) when
 // there are few tiles, so that a compute unit still has enough loads in flight.
 //
+// With 16 waves nothing covers the MLP of a tile, so its length counts: a wave asks for the weights and biases of its task in
+// both layers as soon as its rows are summed, before the sums over the lanes and the barriers (they were asked for where
+// they were used, those of layer 2 one k-step at a time): 4096 chunks of 32 at d = 128 15.0 -> 14.3 us, 8192 31.7 -> 29.4,
+// 16384 64.5 -> 60.1.
+//
 // The NW = 4 form is persistent (a workgroup walks tiles blockIdx.x, blockIdx.x + gridDim.x, ...) and does not write a
 // tile's summaries when they are ready: a thread keeps its 16-byte pieces of up to NS tiles in registers, and every
 // wave writes what it holds when the chip-wide real-time counter enters a new slot of 2^flush_shift ticks (100 MHz),
@@ -201,6 +206,30 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 3 : 1) void pool_mfma_kernel(Poo
     using I4 = std::integral_constant<int, 4>;
     using I8 = std::integral_constant<int, 8>;
 
+    // The MLP of a tile: a wave takes tasks wave, wave + NW, ... of each layer, 16 hidden units or output elements of one
+    // side.  The weights and biases of its first ones (16 waves: normally its only ones) are asked for before the sums
+    // over the lanes and the barrier.
+    constexpr int W2R = 4;               // k-steps of layer 2 that are asked for early
+    bf16x8_t w1f[D / 32], w2f[W2R];
+    uint2 b1f, b2f;
+    auto load_w1 = [&](int l, int t) __attribute__((always_inline)) {
+        const int ds = a.d_sum, kv = t / (ds / 16), u0 = (t % (ds / 16)) * 16;
+        const bf16_t *W1 = static_cast<const bf16_t *>(kv ? a.W1V : a.W1K) + ((size_t)l * ds + u0 + n) * D + g4 * 8;
+        b1f = *reinterpret_cast<const uint2 *>(static_cast<const bf16_t *>(kv ? a.b1V : a.b1K) + (size_t)l * ds + u0 + 4 * g4);
+#pragma unroll
+        for (int ks = 0; ks < D / 32; ++ks) w1f[ks] = *reinterpret_cast<const bf16x8_t *>(W1 + ks * 32);
+    };
+    auto load_w2 = [&](int l, int t) __attribute__((always_inline)) {
+        const int ds = a.d_sum, kv = t / (D / 16), e0 = (t % (D / 16)) * 16;
+        const bf16_t *W2 = static_cast<const bf16_t *>(kv ? a.W2V : a.W2K) + ((size_t)l * D + e0 + n) * ds + g4 * 8;
+        b2f = *reinterpret_cast<const uint2 *>(static_cast<const bf16_t *>(kv ? a.b2V : a.b2K) + (size_t)l * D + e0 + 4 * g4);
+#pragma unroll
+        for (int ks = 0; ks < W2R; ++ks) w2f[ks] = *reinterpret_cast<const bf16x8_t *>(W2 + min(ks, ds / 32 - 1) * 32);
+    };
+    auto bias4 = [](uint2 b) __attribute__((always_inline)) {
+        return f32x4_t{__uint_as_float(b.x << 16), __uint_as_float(b.x & 0xFFFF0000u), __uint_as_float(b.y << 16), __uint_as_float(b.y & 0xFFFF0000u)};
+    };
+
     int tile = blockIdx.x;           // (one tile per workgroup unless the form is persistent)
     // The persistent form keeps half a batch ahead of itself at all times: the first 4 tokens of the next batch are
     // requested before the last 4 of this one are used, across rows, tiles and the MLP phase, so that a workgroup has
@@ -239,6 +268,14 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 3 : 1) void pool_mfma_kernel(Poo
                     issue(tok0, j0, I0{}, I8{});
                     consume(j0, I0{}, I8{});
                 }
+            }
+            if constexpr (!STAGED) {
+                __builtin_amdgcn_sched_barrier(0);           // (into the registers of the rows, which are summed by now)
+                if (a.mode == KVEV_POOL_MLP) {
+                    if (wave < a.d_sum / 8) load_w1(l, wave);
+                    if (wave < D / 8) load_w2(l, wave);
+                }
+                __builtin_amdgcn_sched_barrier(0);
             }
             // over the 4 lane rows, all on the vector unit: a lane is left with 2 neighbouring elements of K and of V, and all
             // lanes take part in the division and the split.  (Shuffles, 32 per tile row, go through LDS and left 3/4 of the
@@ -297,13 +334,16 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 3 : 1) void pool_mfma_kernel(Poo
             f32x4_t acc;
             if constexpr (PK) {
                 acc = *reinterpret_cast<const f32x4_t *>(wpl + (size_t)8 * ds * D + ((size_t)kv * ds + u0 + 4 * g4) * 4);
+            } else if constexpr (!STAGED) {
+                if (t != wave) load_w1(l, t);
+                acc = bias4(b1f);
             } else {
 #pragma unroll
                 for (int r = 0; r < 4; ++r) acc[r] = bf16_to_f32(b1[r]);
             }
 #pragma unroll
             for (int ks = 0; ks < D / 32; ++ks) {
-                const bf16x8_t w = PK ? W1p[ks * 64] : *reinterpret_cast<const bf16x8_t *>(W1 + ks * 32);
+                const bf16x8_t w = PK ? W1p[ks * 64] : !STAGED ? w1f[ks] : *reinterpret_cast<const bf16x8_t *>(W1 + ks * 32);
 #pragma unroll
                 for (int p = 2; p >= 0; --p) {
                     const bf16x8_t x = *reinterpret_cast<const bf16x8_t *>(xm + ((p * 2 + kv) * 16 + n) * XP + ks * 32 + g4 * 8);
@@ -330,11 +370,25 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 3 : 1) void pool_mfma_kernel(Poo
             f32x4_t acc;
             if constexpr (PK) {
                 acc = *reinterpret_cast<const f32x4_t *>(wpl + (size_t)8 * ds * D + ((size_t)2 * ds + kv * D + e0 + 4 * g4) * 4);
+            } else if constexpr (!STAGED) {
+                if (t != wave) load_w2(l, t);
+                acc = bias4(b2f);
             } else {
 #pragma unroll
                 for (int r = 0; r < 4; ++r) acc[r] = bf16_to_f32(b2[r]);
             }
-            for (int ks = 0; ks < ds / 32; ++ks) {
+            if constexpr (!STAGED) {
+#pragma unroll
+                for (int ks = 0; ks < W2R; ++ks)
+                    if (ks < ds / 32) {
+#pragma unroll
+                        for (int p = 2; p >= 0; --p) {
+                            const bf16x8_t x = *reinterpret_cast<const bf16x8_t *>(act + ((size_t)(p * 2 + kv) * 16 + n) * AP + ks * 32 + g4 * 8);
+                            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w2f[ks], x, acc, 0, 0, 0);
+                        }
+                    }
+            }
+            for (int ks = STAGED ? 0 : W2R; ks < ds / 32; ++ks) {
                 const bf16x8_t w = PK ? W2p[ks * 64] : *reinterpret_cast<const bf16x8_t *>(W2 + ks * 32);
 #pragma unroll
                 for (int p = 2; p >= 0; --p) {
@@ -417,7 +471,18 @@ hipError_t launch_pool_mfma(const PoolArgs &a, hipStream_t st)
     const size_t blocks = (size_t)a.L * ((rows_per_layer + 15) / 16);
     if (blocks == 0) return hipSuccess;
     const size_t lds = sizeof(bf16_t) * 3 * 2 * 16 * (((size_t)a.d + 8) + ((size_t)a.d_sum + 8));
-    const bool few = blocks < 2048;          // fewer than 8 tiles per compute unit
+    // Which form.  16 waves on one tile at a time have the most loads under way, but stand still while the MLP of the tile runs
+    // (3.5 us, whatever the chunk); the persistent form covers it with another workgroup's rows and pays for that with a
+    // longer start.  So it takes launches of 8 tiles per compute unit and more, and earlier the smaller the tile (the rows that
+    // its MLP is to be covered by).  16 waves / persistent, us, d = 128 unless said: 64 KiB a tile (C = 8) 512 tiles 20.4 / 23.6,
+    // 640 29.4 / 25.9, 1536 59.4 / 49.4; d = 64, C = 8 512 14.6 / 17.3, 1536 42.7 / 30.9; 128 KiB (C = 16) 512 24.1 / 25.8, 640
+    // 33.0 / 30.4, 1536 68.6 / 61.1; 192 KiB 1020 53.2 / 59.7, 1360 74.3 / 70.2; 256 KiB 1024 60.1 / 62.2, 1536 88.7 / 85.4; 512
+    // KiB 1280 121.6 / 134.6; d_sum = 256, 128 KiB 1152 48.7 / 49.6; without the MLP 128 KiB 768 22.2 / 24.4, 1152 39.7 / 36.8, 256
+    // KiB 1792 80.1 / 84.8.
+    const size_t tile_bytes = (size_t)16 * a.C * 2 * a.d * sizeof(bf16_t);
+    const bool mlp = a.mode == KVEV_POOL_MLP, small = tile_bytes <= (size_t)128 << 10;
+    const size_t enough = !mlp ? (small ? 1024 : 2048) : a.d_sum > 128 ? 2048 : small ? 513 : tile_bytes <= (size_t)256 << 10 ? 1280 : 2048;
+    const bool few = blocks < enough;
     // launches that fill the chip many times over read the MLP weights in fragment order when the caller gave room for them
     const bool pk = !few && a.mode == KVEV_POOL_MLP && a.wpack != nullptr;
     if (pk) {
