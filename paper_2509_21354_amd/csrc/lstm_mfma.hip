@@ -43,6 +43,7 @@
 #include "common.hpp"
 #include "kernels.hpp"
 #include "lstm_common.hpp"
+#include <algorithm>
 #include <atomic>
 #include <utility>
 
@@ -97,16 +98,24 @@ template <int DG> struct Res {
 // LDS (every wave needs all of them as the B operand); a wave keeps the 2d-long weight rows of one (unit tile,
 // gate) in registers and walks the TT steps with them.  Its output is the bulk of the traffic (4*d_g floats per
 // sequence and step), written as 1 KiB per wave-level store in the fragment layout the recurrence reads back.
-template <int DG> __device__ void pack_whh_blocks(const LstmArgs &a, int block, int nblocks);
+template <int DG> __device__ void pack_whh_blocks(const LstmArgs &a, int block, int threads, int nblocks);
 
-template <int DG, int D, int TT>
-__global__ __launch_bounds__(proj_threads<DG>()) void lstm_inproj_kernel(LstmArgs a, int t0, int nb)
+//
+// Z: workgroups that share the gate rows of one tile of steps (blockIdx.z): a wave's rows come out of L2 a (unit tile, gate)
+// at a time, and where the launch is small that chain of round trips is its length.  The first pack_rows rows of the grid re-lay
+// W_hh for the recurrence, beside the projection, which does not need it.
+template <int DG, int D, int TT, int Z>
+__global__ __launch_bounds__(proj_threads<DG>()) void lstm_inproj_kernel(LstmArgs a, int t0, int nb, int pack_rows)
 {
-    constexpr int KS = 2 * D / 32, UT = proj_tiles<DG>(), XP = 2 * D + 8, THREADS = proj_threads<DG>();
+    constexpr int KS = 2 * D / 32, UT = proj_tiles<DG>(), XP = 2 * D + 8, THREADS = proj_threads<DG>(), NI = UT * 4 / Z;
     if (a.exch_bytes) {      // the paired recurrence that follows starts from cleared exchange slots
-        const size_t nthreads = (size_t)gridDim.x * gridDim.y * THREADS;
-        for (size_t i = ((size_t)blockIdx.y * gridDim.x + blockIdx.x) * THREADS + threadIdx.x; i * 16 < a.exch_bytes; i += nthreads)
+        const size_t nthreads = (size_t)gridDim.x * gridDim.y * gridDim.z * THREADS;
+        for (size_t i = (((size_t)blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x) * THREADS + threadIdx.x; i * 16 < a.exch_bytes; i += nthreads)
             reinterpret_cast<uint4 *>(a.exch)[i] = make_uint4(0u, 0u, 0u, 0u);
+    }
+    if ((int)blockIdx.y < pack_rows) {
+        pack_whh_blocks<DG>(a, ((int)blockIdx.z * pack_rows + (int)blockIdx.y) * (int)gridDim.x + (int)blockIdx.x, THREADS, Z * pack_rows * (int)gridDim.x);
+        return;
     }
     extern __shared__ __align__(16) unsigned char smem_in[];
     bf16_t *s_x = reinterpret_cast<bf16_t *>(smem_in);           // [TT][16][XP]
@@ -115,7 +124,13 @@ __global__ __launch_bounds__(proj_threads<DG>()) void lstm_inproj_kernel(LstmArg
     const int gpl = (a.BH + 15) / 16;
     const int gid = xcd_order(blockIdx.x, gridDim.x);
     const int l = gid / gpl, grp = gid % gpl;
-    const int tt0 = blockIdx.y * TT;
+    const int tt0 = ((int)blockIdx.y - pack_rows) * TT;
+
+    const bf16x8_t *Wp = a.wih_packed + ((size_t)l * (DG / 16) + wave * UT) * 4 * KS * 64 + lane;
+    const int it0 = Z == 1 ? 0 : (int)blockIdx.z * NI;
+    bf16x8_t wf[2][KS];
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) wf[0][ks] = Wp[((size_t)it0 * KS + ks) * 64];
 
     // stage the rows: 16-byte pieces, 2D/8 per row (the first D/8 from Kbar, the rest from Vbar)
     const bf16_t *Kbar = static_cast<const bf16_t *>(a.Kbar), *Vbar = static_cast<const bf16_t *>(a.Vbar);
@@ -130,21 +145,17 @@ __global__ __launch_bounds__(proj_threads<DG>()) void lstm_inproj_kernel(LstmArg
     }
     __syncthreads();
 
-    const bf16x8_t *Wp = a.wih_packed + ((size_t)l * (DG / 16) + wave * UT) * 4 * KS * 64 + lane;
     const bf16_t *b_ih = static_cast<const bf16_t *>(a.b_ih) + (size_t)l * 4 * DG;
     const bf16_t *b_hh = static_cast<const bf16_t *>(a.b_hh) + (size_t)l * 4 * DG;
     const bf16_t *xrd = s_x + (size_t)n * XP + g4 * 8;           // + j*16*XP + ks*32
-    bf16x8_t wf[2][KS];
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) wf[0][ks] = Wp[(size_t)ks * 64];
-#pragma unroll
-    for (int it = 0; it < UT * 4; ++it) {
-        const int ut = it / 4, q = it % 4;
+    for (int it = 0; it < NI; ++it) {
+        const int ut = (it0 + it) / 4, q = (it0 + it) % 4;
         const int row0 = q * DG + wave * 16 * UT + ut * 16;
         // the next (unit tile, gate)'s weight rows travel while this one is used
-        if (it + 1 < UT * 4) {
+        if (it + 1 < NI) {
 #pragma unroll
-            for (int ks = 0; ks < KS; ++ks) wf[(it + 1) & 1][ks] = Wp[((size_t)(it + 1) * KS + ks) * 64];
+            for (int ks = 0; ks < KS; ++ks) wf[(it + 1) & 1][ks] = Wp[((size_t)(it0 + it + 1) * KS + ks) * 64];
         }
         float bias[4];
 #pragma unroll
@@ -221,15 +232,15 @@ __global__ __launch_bounds__(256) void lstm_prep_kernel(const bf16_t *W_ih, bf16
 // wave-level load of the recurrence is one contiguous 1 KiB piece (the row-major
 // matrix would give 16 half-used cache lines per load):
 // [layer][wave][item][gate][lane][8], items in the order the wave walks them.
-// Run by `nblocks` workgroups of the input projection's first launch; one 16-byte fragment per thread and turn.
-template <int DG> __device__ void pack_whh_blocks(const LstmArgs &a, int block, int nblocks)
+// Run by `nblocks` workgroups of `threads` threads; one 16-byte fragment per thread and turn.
+template <int DG> __device__ void pack_whh_blocks(const LstmArgs &a, int block, int threads, int nblocks)
 {
     using G = Geo<DG>;
-    constexpr int NW = G::NW, UT = G::UT, THREADS = G::THREADS;
+    constexpr int NW = G::NW, UT = G::UT;
     const bf16_t *W_hh = static_cast<const bf16_t *>(a.W_hh);
     f16x8_t *packed = reinterpret_cast<f16x8_t *>(const_cast<bf16x8_t *>(a.whh_packed));
     const size_t total = (size_t)a.L * NW * G::ITEMS * 4 * 64;
-    for (size_t frag = (size_t)block * THREADS + threadIdx.x; frag < total; frag += (size_t)nblocks * THREADS) {
+    for (size_t frag = (size_t)block * threads + threadIdx.x; frag < total; frag += (size_t)nblocks * threads) {
         const int lane = frag % 64;
         size_t r = frag / 64;
         const int q = r % 4; r /= 4;
@@ -257,7 +268,7 @@ template <int DG> __device__ void pack_whh_blocks(const LstmArgs &a, int block, 
 template <int DG>
 __global__ __launch_bounds__(Geo<DG>::THREADS) void lstm_pack_whh_kernel(LstmArgs a)
 {
-    pack_whh_blocks<DG>(a, (int)blockIdx.x, (int)gridDim.x);
+    pack_whh_blocks<DG>(a, (int)blockIdx.x, Geo<DG>::THREADS, (int)gridDim.x);
 }
 
 template <int DG>
@@ -841,7 +852,7 @@ static hipError_t set_attributes_once()
         if (e != hipSuccess) return e;
     }
     // (the in-projection's staged rows pass 64 KiB at d = 128)
-    e = hipFuncSetAttribute(reinterpret_cast<const void *>(lstm_inproj_kernel<DG, 128, run_steps<DG>()>),
+    e = hipFuncSetAttribute(reinterpret_cast<const void *>(lstm_inproj_kernel<DG, 128, run_steps<DG>(), 1>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)(run_steps<DG>() * 16 * (2 * 128 + 8) * sizeof(bf16_t)));
     if (e != hipSuccess) return e;
     if constexpr (DG == 256 || DG == 512) {
@@ -855,9 +866,10 @@ static hipError_t set_attributes_once()
 }
 
 // Weight preparation: W_ih into fragment order and the partial maxima of |W_hh| (one launch), then W_hh scaled,
-// converted and re-laid (a second one, which needs the maxima).  What it leaves depends on the weights alone.
+// converted and re-laid (a second one, which needs the maxima; pack = false: the input projection's launch does it).  What
+// it leaves depends on the weights alone.
 template <int DG>
-static hipError_t prepare_dg(const LstmArgs &a, hipStream_t st)
+static hipError_t prepare_dg(const LstmArgs &a, hipStream_t st, bool pack = true)
 {
     const size_t frags_i = (size_t)a.L * 4 * DG * 2 * a.d / 8;
     const int nb_wih = (int)((frags_i + 255) / 256);
@@ -868,6 +880,7 @@ static hipError_t prepare_dg(const LstmArgs &a, hipStream_t st)
     else
         hipLaunchKernelGGL((lstm_prep_kernel<DG, 128>), grid_p, dim3(256), 0, st, static_cast<const bf16_t *>(a.W_ih),
                            const_cast<bf16x8_t *>(a.wih_packed), static_cast<const bf16_t *>(a.W_hh), a.whh_max_bits, a.L, nb_wih);
+    if (!pack) return hipGetLastError();
     // W_hh fragments: 16 bytes per thread and turn, about 4 turns per packing workgroup
     const size_t frags_h = (size_t)a.L * 4 * DG * DG / 8;
     const size_t want = (frags_h + (size_t)4 * Geo<DG>::THREADS - 1) / ((size_t)4 * Geo<DG>::THREADS);
@@ -882,8 +895,9 @@ static hipError_t launch_dg(const LstmArgs &a, hipStream_t st)
     const unsigned groups = (unsigned)(a.L * gpl);
     hipError_t e = set_attributes_once<DG>();
     if (e != hipSuccess) return e;
+    const bool single = (DG == 256 && a.fused) || (DG == 512 && a.split == 4);      // one kernel for both halves
     if (!a.prepared) {
-        e = prepare_dg<DG>(a, st);
+        e = prepare_dg<DG>(a, st, single);
         if (e != hipSuccess) return e;
     }
     if constexpr (DG == 256) {
@@ -894,18 +908,30 @@ static hipError_t launch_dg(const LstmArgs &a, hipStream_t st)
     }
     for (int t0 = a.c0; t0 < a.c1; t0 += a.tb) {
         const int nb = a.c1 - t0 < a.tb ? a.c1 - t0 : a.tb;
-        // few sequences: shorter runs of steps per workgroup so that the launch still covers the chip
+        // few sequences: shorter runs of steps per workgroup so that the launch still covers the chip, and, where that is
+        // 256 workgroups or less, the gate rows over four of them (whole gate call, d_g = 256: 512 sequences x 8 steps 35.2 -> 33.0
+        // us, 128 x 32 71.5 -> 69.1; d_g = 512 256 x 8 60.1 -> 52.8; up to 1024 workgroups 1024 x 16 would take 65.2 against 61.6)
         const bool small = (size_t)groups * ((nb + run_steps<DG>() - 1) / run_steps<DG>()) < 256;
         const int tt = small ? 2 : run_steps<DG>();
-        const int ny_proj = (nb + tt - 1) / tt;
-        const dim3 grid_in(groups, (unsigned)ny_proj);
+        const unsigned ny_proj = (unsigned)((nb + tt - 1) / tt);
+        const bool spread = small && (size_t)groups * ny_proj <= 256;
+        unsigned pack_rows = 0;
+        if (!a.prepared && t0 == a.c0) {         // W_hh: about one 16-byte fragment per thread, 4096 workgroups at most
+            const size_t want = std::min<size_t>(((size_t)a.L * 4 * DG * DG / 8 + proj_threads<DG>() - 1) / proj_threads<DG>(), 4096);
+            const unsigned per_row = groups * (spread ? 4 : 1);
+            pack_rows = (unsigned)((want + per_row - 1) / per_row);
+        }
+        const dim3 grid_in(groups, ny_proj + pack_rows, spread ? 4 : 1), threads(proj_threads<DG>());
         const size_t lds_in = (size_t)tt * 16 * (2 * a.d + 8) * sizeof(bf16_t);
+        auto project = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid_in, threads, lds_in, st, a, t0, nb, (int)pack_rows); };
         if (a.d == 64) {
-            if (small) hipLaunchKernelGGL((lstm_inproj_kernel<DG, 64, 2>), grid_in, dim3(proj_threads<DG>()), lds_in, st, a, t0, nb);
-            else hipLaunchKernelGGL((lstm_inproj_kernel<DG, 64, run_steps<DG>()>), grid_in, dim3(proj_threads<DG>()), lds_in, st, a, t0, nb);
+            if (spread) project(lstm_inproj_kernel<DG, 64, 2, 4>);
+            else if (small) project(lstm_inproj_kernel<DG, 64, 2, 1>);
+            else project(lstm_inproj_kernel<DG, 64, run_steps<DG>(), 1>);
         } else {
-            if (small) hipLaunchKernelGGL((lstm_inproj_kernel<DG, 128, 2>), grid_in, dim3(proj_threads<DG>()), lds_in, st, a, t0, nb);
-            else hipLaunchKernelGGL((lstm_inproj_kernel<DG, 128, run_steps<DG>()>), grid_in, dim3(proj_threads<DG>()), lds_in, st, a, t0, nb);
+            if (spread) project(lstm_inproj_kernel<DG, 128, 2, 4>);
+            else if (small) project(lstm_inproj_kernel<DG, 128, 2, 1>);
+            else project(lstm_inproj_kernel<DG, 128, run_steps<DG>(), 1>);
         }
         if constexpr (DG == 256 || DG == 512) {
             if (a.split == 8 || (DG == 256 && a.split == 2 && lstm_takes_oct(a.L, a.BH, a.compute_units))) {
