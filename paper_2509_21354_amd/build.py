@@ -2,7 +2,8 @@
 
 Run as ``python -m paper_2509_21354_amd.build`` (add ``--force`` to recompile
 everything).  Objects go to ``_build/`` next to this file; the shared library
-stays in-tree next to the sources so that it travels with the checkout.
+and the extension module ``_native.so`` (marshalling, built with g++) stay
+in-tree next to the sources so that they travel with the checkout.
 """
 from __future__ import annotations
 
@@ -11,13 +12,16 @@ import glob
 import os
 import subprocess
 import sys
+import sysconfig
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(_HERE, "csrc")
 OBJ_DIR = os.path.join(_HERE, "_build")
 LIB_PATH = os.path.join(_HERE, "libkvev.so")
+NATIVE_PATH = os.path.join(_HERE, "_native.so")      # CPython module: marshalling of calls into the library
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+CXX = os.environ.get("CXX", "g++")
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",
     # packed fp32 VALU forms stay off (device-code feature; the host pass ignores it)
@@ -57,6 +61,10 @@ def build(force: bool = False, verbose: bool = False) -> str:
         for warn in ex.map(lambda j: _compile(*j), jobs):
             if warn.strip() and verbose:
                 print(warn, file=sys.stderr)
+    native = os.path.join(CSRC, "native_call.cpp")
+    if force or not os.path.exists(NATIVE_PATH) or os.path.getmtime(NATIVE_PATH) < max(os.path.getmtime(native), hdr):
+        subprocess.check_call([CXX, "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-I", sysconfig.get_paths()["include"], native,
+                               "-o", NATIVE_PATH])
     if jobs or not os.path.exists(LIB_PATH):
         subprocess.check_call([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB_PATH, *objs])
     return LIB_PATH

@@ -1,0 +1,60 @@
+"""The extension module that marshals calls into the library: what it does not take is left to ctypes, whose errors a caller
+sees, and nothing is left behind by a call that fails on the way."""
+import ctypes
+import sys
+
+import pytest
+import torch
+
+from paper_2509_21354_amd import binding as kb
+
+
+def _args(**kw):
+    kb.lib()
+    t = torch.zeros(64)
+    a = dict(shape=kb.make_shape(L=1, B=1, H=1, d=64, T=8, T_cap=8, C=4, N_cap=2, W=4, d_sum=32, d_g=64, dtype=kb.F32, H_kv=0),
+             Q=t, Tq=1, K=t, V=t, Kbar=t, Vbar=t, idx=t.int(), count=t.int(), k_cap=1, O=t, ws=None, causal=0)
+    a.update(kw)
+    return a
+
+
+def _call(**kw):
+    return kb._native.gated_attention(*_args(**kw).values())
+
+
+@pytest.mark.skipif(torch.cuda.is_available(), reason="the GPU is not initialised here")
+def test_plain_calls_wait_for_the_gpu():
+    assert _call() is None                   # (ctypes' way then says that there is no GPU)
+    with pytest.raises((RuntimeError, AssertionError)):
+        kb.kvev_gated_attention(**_args())
+
+
+@pytest.mark.parametrize("kw", [dict(shape=None), dict(shape=ctypes.c_int(0)), dict(Tq=1.0), dict(Tq=2 ** 40), dict(k_cap="1"), dict(Q=3),
+                                dict(ws=kb.RowsFrom(torch.zeros(4, 4), 1, 4)), dict(causal=None)])
+def test_other_arguments_are_left_to_ctypes(kw):
+    assert _call(**kw) is None
+
+
+def test_wrong_number_of_arguments_is_not_taken():
+    assert kb._native.gated_attention() is None
+    assert kb._native.retain(*range(40)) is None
+
+
+def test_strided_tensors_are_refused():
+    with pytest.raises(AssertionError, match="contiguous"):
+        _call(V=torch.zeros(4, 4).t())
+    with pytest.raises(AssertionError, match="contiguous"):
+        kb.kvev_gated_attention(**_args(V=torch.zeros(4, 4).t()))
+
+
+def test_errors_of_a_tensor_reach_the_caller_and_nothing_is_held():
+    class Odd(torch.Tensor):
+        def data_ptr(self):
+            raise ValueError("no address")
+
+    a = _args(K=torch.zeros(4).as_subclass(Odd))
+    before = sys.getrefcount(a["shape"]), sys.getrefcount(a["K"])
+    for _ in range(3):
+        with pytest.raises(ValueError, match="no address"):
+            kb._native.gated_attention(*a.values())
+    assert (sys.getrefcount(a["shape"]), sys.getrefcount(a["K"])) == before
