@@ -387,6 +387,19 @@ template <typename T, int D>
 static hipError_t launch_decode_t(const AttnArgs &a, hipStream_t st)
 {
     const int R = a.G * a.Tq;
+    // A workgroup that serves one query is the shortest (four queries: the fold of 16 sums, four weights per row), so queries
+    // that share rows only share a workgroup where there would be too many of them: one each up to 128 workgroups, then pairs
+    // up to 192 (their rows come out of the caches after the first).  Unsplit launches only: the plan's runs, partials and
+    // tickets are for groups of four.  Four / two / one query, us, d = 128, 287 rows: 8 sequences x 4 heads 8.8 / 7.0 / 6.1, 32 x
+    // 4 9.0 / 7.1 / 6.2, 40 x 4 9.0 / 7.1 / 7.1, 64 x 4 9.0 / 7.2 / 8.7, 72 x 4 9.0 / 7.2 / 11.1, 128 x 4 9.1 / 9.8 / 16.7; 107
+    // rows 96 x 4 7.4 / 5.9 / 6.0; 32 x 8 9.1 / 7.4 / 8.8; two heads 64 x 2 - / 7.2 / 6.3, 128 x 2 - / 7.3 / 8.7; fp32, 160 rows 32
+    // x 4 8.5 / 6.9 / 6.5.  (Runs of more than 320 rows go to 8 or 16 waves: 64 x 2 x 616 rows - / 9.1 / 10.0, 64 x 4 x 516 11.8 /
+    // 9.3 / 14.1.)
+    if (a.nsplit == 1) {
+        const int64_t S = a.S;
+        if (R > 1 && S * R <= 128 && a.rows_per_split <= 320) return launch_decode_q<T, D, 1>(a, st);
+        if (R > 2 && S * ((R + 1) / 2) <= 192) return launch_decode_q<T, D, 2>(a, st);
+    }
     if (R >= 4) return launch_decode_q<T, D, 4>(a, st);
     if (R >= 2) return launch_decode_q<T, D, 2>(a, st);
     return launch_decode_q<T, D, 1>(a, st);
