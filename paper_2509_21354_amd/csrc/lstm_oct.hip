@@ -362,19 +362,285 @@ __global__ __launch_bounds__(4 * DG / P) void lstm_rec_oct_kernel(LstmArgs a, in
     if (failed && tid == 0) __hip_atomic_store(a.status, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // sticky: the caller's to clear
 }
 
+// The same for launches so small that groups of 4 sequences fit the chip, P workgroups of 4 waves each.  The 16 columns of a
+// matrix instruction hold their hi and lo terms twice over, and the four lanes that then hold the same sums take one of the four
+// units each: half the nonlinearities and half the exchange.  A unit travels as a 4-byte word {hi, lo} whose hi carries the
+// flag (a NaN keeps its lo term), so a lane takes four units of a sequence in 16 bytes, and a wave takes the slots of its own
+// partners (one, at d_g = 512 two) instead of a part of everybody's.
+// Measured (whole gate call, weights prepared; groups of 8 and groups of 4 on one machine): d_g = 256 32 sequences x 128 steps 226 ->
+// 187 us, 64 x 64 127 -> 105, 256 x 64 132 -> 130; d_g = 512 32 x 128 319 -> 291, 128 x 64 208 -> 176.  (From machine to machine the same code
+// takes 187 to 215 and 114 to 130 us at the first and third shape.)  At d_g = 256 a wave asks again 512 clocks after its first look and
+// takes that answer, which is there when the first one would have had to be repeated: 187 -> 174 and 211 -> 205, 130 -> 126 and 114 -> 111
+// us (with the later look alone 184 .. 187; sleeps of 4, 6 and 8 x 64 clocks 211, 208, 205).  Two looks that are both examined: 203; a look at four
+// times the bytes per wave, straight into operand registers (no LDS, one barrier less): 283 against 226 with groups of 8.
+template <int DG, int P>
+__global__ __launch_bounds__(256) void lstm_rec_few_kernel(LstmArgs a, int t0, int nb)
+{
+    using G = Geo<DG>;
+    constexpr int kKS = DG / 32, kNW = 4, kKH = kKS / P, kKP = kKS - kKH;       // k-steps; waves; k-steps over own units, over the partners'
+    constexpr int NS = 4, kOwn = DG / P, kOP = kOwn + 8, kPP = DG - kOwn + 8;      // sequences; own units; row pitches in LDS
+    constexpr int kMine = (P - 1 + kNW - 1) / kNW;                                 // partners of a wave, at most
+    constexpr uint32_t kSlot = NS * kOwn * 4, kGroup = 2 * P * kSlot, kFlag = 0x4000u;      // [parity][member][unit / 4][sequence][unit % 4]
+    constexpr int kPin = DG == 512 ? 15 : 0;                                    // k-steps whose weights are kept in accumulation registers
+    static_assert(kOwn == 64, "a wave per 16 units, 16 lanes of 4 units per slot");
+    static_assert(16 / NS * kGroup <= (DG == 256 ? kLstmPairExchBytes256 : 2 * kLstmOctExchBytes512), "the scratch planned for 16 sequences");
+    __shared__ __align__(16) f16_t s_h[2 * NS * kOP], s_p[2 * NS * kPP];       // own units and the partners', row = plane * NS + sequence
+    __shared__ float s_up[2][kNW][NS], s_up2[kNW][NS];                         // shares of the utility logit: own units (by step parity), partners'
+    __shared__ int s_fail;
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n = lane & 15, g4 = lane >> 4, sn = n % NS, j = n / NS;
+    const int gpl = (a.BH + NS - 1) / NS;
+    const int member = blockIdx.x % P, gid = blockIdx.x / P;
+    const int l = gid / gpl, grp = gid % gpl;
+    const bool live = grp * NS + sn < a.BH;
+    const size_t s = (size_t)l * a.BH + min(grp * NS + sn, a.BH - 1);
+    auto par_of = [&](int i) __attribute__((always_inline)) { return (member + 1 + i / kKH) % P; };
+    const int tile = member * kNW + wave, own = wave * 16 + 4 * g4 + j, unit = member * kOwn + own;    // this lane's cell
+
+    const bf16_t *w_s = static_cast<const bf16_t *>(a.w_s) + (size_t)l * DG;
+    const float b_s = bf16_to_f32(static_cast<const bf16_t *>(a.b_s)[l]);
+    const float inv_scale = ldexpf(1.f, -whh_scale_exp(whh_layer_max(a.whh_max_bits, l)));
+    if (tid == 0) s_fail = 0;
+
+    const __amdgpu_buffer_rsrc_t w_rsrc = make_rsrc(
+        reinterpret_cast<const unsigned char *>(a.whh_packed + (((size_t)l * G::NW + tile / G::UT) * G::ITEMS + (tile % G::UT) * kKS) * 4 * 64),
+        kKS * 4096);
+    f16x8_t w[kKS][4];          // own units' k-steps, then the partners'
+#pragma unroll
+    for (int i = 0; i < kKS; ++i)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            w[i][q] = buffer_load16<f16x8_t>(w_rsrc, lane * 16 + q * 1024, (uint32_t)((i < kKH ? member * kKH + i : par_of(i - kKH) * kKH + (i - kKH) % kKH) * 4096));
+            if (i < kPin) asm volatile("" : "+a"(w[i][q]));      // (left to itself the compiler moves them to vector registers before every use)
+        }
+
+    const __amdgpu_buffer_rsrc_t x_rsrc = make_rsrc(
+        reinterpret_cast<const f32x4_t *>(a.xproj) + xp_block<DG>(l * ((a.BH + 15) / 16) + grp / (16 / NS), a.tb, 0, tile / G::UT, tile % G::UT, 0) * 64,
+        (uint32_t)nb * G::NW * G::UT * 4096 - (uint32_t)tile * 4096);
+    const uint32_t xoff = (uint32_t)((g4 * 16 + grp % (16 / NS) * NS + sn) * 16 + j * 4);
+    // (two sets by step parity: a set in flight across the step boundary is not copied, which would wait for it)
+    float xin[2][4];
+    auto fetch_x = [&](int tt, float (&x)[4]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            x[q] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(x_rsrc, (int)(xoff + q * 1024), (int)((uint32_t)tt * G::NW * G::UT * 4096), 2));
+    };
+    fetch_x(0, xin[0]);
+
+    const __amdgpu_buffer_rsrc_t e_rsrc = make_rsrc(a.exch + (size_t)gid * kGroup, kGroup);
+    // the m-th partner that this wave takes the slot of, 0 .. P - 2, if there is one
+    auto partner_of = [&](int m) __attribute__((always_inline)) { return wave + m * kNW; };
+    // a look at their slots of parity `par`: sequence lane % 4, units 4 (lane / 4) .. + 3
+    auto ask = [&](int par, u32x4_t (&v)[kMine]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int m = 0; m < kMine; ++m)
+            if (const int p = partner_of(m); p < P - 1)
+                v[m] = __builtin_amdgcn_raw_buffer_load_b128(e_rsrc, lane * 16, (int)((par * P + (member + 1 + p) % P) * kSlot), 16);
+    };
+    auto split = [](float h, f16_t &hi, f16_t &lo) __attribute__((always_inline)) {
+        hi = (f16_t)h;
+        lo = (f16_t)(h - (float)hi);
+    };
+    f16_t *const h_wr = s_h + (size_t)sn * kOP + own;                                     // + NS kOP: the lo terms
+    const f16_t *const h_rd = s_h + (size_t)(n % (2 * NS)) * kOP + g4 * 8, *const p_rd = s_p + (size_t)(n % (2 * NS)) * kPP + g4 * 8;    // + i * 32
+    f16_t *const p_wr = s_p + (size_t)(lane & 3) * kPP + (lane >> 2) * 4;      // + partner * kOwn, + NS kPP: the lo terms
+
+    float c_reg = 0.f, h_last = 0.f;
+    const float ws_own = bf16_to_f32(w_s[unit]);
+#pragma unroll
+    for (int p = 0; p < P; ++p) {        // own units, then the partners'
+        const int u = (member + p) % P * kOwn + own;
+        // (chunk 0 starts the recurrence from a zero state, whatever the buffers hold)
+        const float h0 = live && t0 > 0 ? a.h[s * DG + u] : 0.f;
+        if (p == 0) c_reg = live && t0 > 0 ? a.c[s * DG + u] : 0.f;
+        f16_t hi, lo;
+        split(h0, hi, lo);
+        f16_t *dst = p == 0 ? h_wr : s_p + (size_t)sn * kPP + (p - 1) * kOwn + own;
+        dst[0] = hi;
+        dst[NS * (p == 0 ? kOP : kPP)] = lo;
+    }
+    float ws_par[kMine][4];              // of the units that this lane receives
+#pragma unroll
+    for (int m = 0; m < kMine; ++m)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) ws_par[m][e] = bf16_to_f32(w_s[(member + 1 + min(partner_of(m), P - 2)) % P * kOwn + (lane >> 2) * 4 + e]);
+    __syncthreads();
+
+    // the logit of a step from the shares of all members, by the last wave of member 0 (it receives least)
+    auto write_util = [&](int step) __attribute__((always_inline)) {
+        float u = b_s;
+#pragma unroll
+        for (int w_ = 0; w_ < kNW; ++w_)
+            if (w_ < P - 1) u += s_up2[w_][sn];
+#pragma unroll
+        for (int w_ = 0; w_ < kNW; ++w_) u += s_up[step & 1][w_][sn];
+        if (live && lane < NS) {
+            a.util[s * a.N_cap + t0 + step] = u;
+            a.gate[s * a.N_cap + t0 + step] = sigmoid_hw(u);
+        }
+    };
+    auto flag_of = [](int tt) { return (tt >> 1) & 1 ? 0u : kFlag; };      // of the publication of step tt
+    // The partners' h of step tt - 1 into LDS, from a look asked for earlier; more looks follow if it is not there yet.
+    auto receive = [&](int tt, u32x4_t (&v)[kMine]) __attribute__((always_inline)) {
+        typedef _Float16 f16x4_t __attribute__((ext_vector_type(4)));
+        const uint32_t flag = flag_of(tt - 1);
+        auto complete = [&]() __attribute__((always_inline)) {
+            uint32_t off = 0;
+#pragma unroll
+            for (int m = 0; m < kMine; ++m)
+                if (partner_of(m) < P - 1) off |= (v[m][0] ^ flag) | (v[m][1] ^ flag) | (v[m][2] ^ flag) | (v[m][3] ^ flag);
+            return __all((off & kFlag) == 0) != 0;
+        };
+        bool got = complete();
+        for (int spin = 0; !got && spin < a.pair_spin_limit; ++spin) {
+            asm volatile("" ::: "memory");
+            if ((spin & 255) == 255 && s_fail) break;
+            ask((tt - 1) & 1, v);
+            got = complete();
+        }
+        if (!got) s_fail = 1;
+        float u = 0.f;
+#pragma unroll
+        for (int m = 0; m < kMine; ++m)
+            if (const int p = partner_of(m); p < P - 1) {
+                const u32x2_t hi = {__builtin_amdgcn_perm(v[m][1], v[m][0], 0x05040100u) & ~(kFlag | kFlag << 16),
+                                    __builtin_amdgcn_perm(v[m][3], v[m][2], 0x05040100u) & ~(kFlag | kFlag << 16)};
+                const u32x2_t lo = {__builtin_amdgcn_perm(v[m][1], v[m][0], 0x07060302u), __builtin_amdgcn_perm(v[m][3], v[m][2], 0x07060302u)};
+                *reinterpret_cast<u32x2_t *>(p_wr + p * kOwn) = hi;
+                *reinterpret_cast<u32x2_t *>(p_wr + p * kOwn + NS * kPP) = lo;
+                const f16x4_t hi4 = __builtin_bit_cast(f16x4_t, hi), lo4 = __builtin_bit_cast(f16x4_t, lo);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) u = fmaf(ws_par[m][e], (float)lo4[e], fmaf(ws_par[m][e], (float)hi4[e], u));
+            }
+        return u;
+    };
+    // sums over the lanes of a sequence
+    auto lanes_sum = [](float u) __attribute__((always_inline)) {
+        u += dpp_move<kRowRor4>(u);
+        u += dpp_move<kRowRor8>(u);
+        return rows_sum(u);
+    };
+    // ... of what was received, which the products do not wait for
+    auto put_share = [&](float u) __attribute__((always_inline)) {
+        u = lanes_sum(u);
+        if (wave < P - 1 && lane < NS) s_up2[wave][lane] = u;
+    };
+
+    bool failed = false;
+    u32x4_t look[kMine];
+    // one step; false: a wait in it expired in some wave of the workgroup
+    auto step = [&](int tt, auto cur_tag) __attribute__((always_inline)) {
+        constexpr int cur = decltype(cur_tag)::value, nxt = cur ^ 1;
+        f32x4_t acc[4];
+        auto products = [&](const f16_t *rd, auto first_tag, auto count_tag) __attribute__((always_inline)) {
+            constexpr int first = decltype(first_tag)::value, count = decltype(count_tag)::value;
+            f16x8_t hb[count];
+#pragma unroll
+            for (int i = 0; i < count; ++i) hb[i] = *reinterpret_cast<const f16x8_t *>(rd + i * 32);
+#pragma unroll
+            for (int i = 0; i < count; ++i)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const f32x4_t zero = {0.f, 0.f, 0.f, 0.f};
+                    acc[q] = __builtin_amdgcn_mfma_f32_16x16x32_f16(w[first + i][q], hb[i], first + i == 0 ? zero : acc[q], 0, 0, 0);
+                }
+        };
+        products(h_rd, std::integral_constant<int, 0>{}, std::integral_constant<int, kKH>{});
+        if (tt > 0) ask(nxt, look);
+        if (DG == 256) {         // asked again, later: see above
+            __builtin_amdgcn_sched_barrier(0);
+            __builtin_amdgcn_s_sleep(8);
+            if (tt > 0) ask(nxt, look);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        if (tt > 1 && member == 0 && wave == kNW - 1) write_util(tt - 2);
+        float share = 0.f;
+        if (tt > 0) share = receive(tt, look);
+        lds_barrier();
+        if (s_fail) return false;
+        products(p_rd, std::integral_constant<int, kKH>{}, std::integral_constant<int, kKP>{});
+        if (tt > 0 && member == 0) put_share(share);
+
+        // ---- hi + lo products of this lane's unit, the cell, the new h ----
+        float z[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            float y[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) y[r] = acc[q][r] + dpp_move<kRowRor4>(acc[q][r]);
+            const float y0 = j & 1 ? y[1] : y[0], y1 = j & 1 ? y[3] : y[2];
+            z[q] = fmaf(j & 2 ? y1 : y0, inv_scale, xin[cur][q]);
+        }
+        fetch_x(min(tt + 1, nb - 1), xin[nxt]);
+        const float ig = sigmoid_hw(z[0]), fg = sigmoid_hw(z[1]), gg = tanh_hw(z[2]), og = sigmoid_hw(z[3]);
+        c_reg = fmaf(fg, c_reg, ig * gg);
+        h_last = og * tanh_hw(c_reg);
+        asm volatile("" : "+v"(h_last));     // opaque to the optimiser: the rounded product from here on
+        f16_t hi, lo;
+        split(h_last, hi, lo);
+        // to the partners first (the long way), then to this workgroup's own waves
+        if (member != a.pair_mute) {
+            const uint32_t word = __builtin_bit_cast(uint16_t, hi) | (uint32_t)__builtin_bit_cast(uint16_t, lo) << 16;
+            __builtin_amdgcn_raw_buffer_store_b32((word & ~kFlag) | flag_of(tt), e_rsrc, ((wave * 4 + g4) * NS + sn) * 16 + j * 4,
+                                                  (int)((cur * P + member) * kSlot), 16);
+        }
+        h_wr[0] = hi;
+        h_wr[NS * kOP] = lo;
+        const float upart = lanes_sum(ws_own * h_last);
+        if (lane < NS) s_up[cur][wave][lane] = upart;
+        lds_barrier();
+        return true;
+    };
+    for (int tt = 0; tt < nb && !failed; tt += 2) {
+        failed = !step(tt, std::integral_constant<int, 0>{});
+        if (tt + 1 < nb && !failed) failed = !step(tt + 1, std::integral_constant<int, 1>{});
+    }
+    if (!failed) {      // the last step's logit needs the partners' last h
+        if (nb > 1 && member == 0 && wave == kNW - 1) write_util(nb - 2);
+        lds_barrier();
+        ask((nb - 1) & 1, look);
+        put_share(receive(nb, look));
+        lds_barrier();
+        failed = s_fail != 0;
+        if (!failed && member == 0 && wave == kNW - 1) write_util(nb - 1);
+    }
+    // (not before this point: see lstm_rec_oct_kernel)
+    if (live) {
+        if (!failed) a.h[s * DG + unit] = h_last;
+        a.c[s * DG + unit] = failed ? __builtin_nanf("") : c_reg;
+    }
+    if (failed && tid == 0) __hip_atomic_store(a.status, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // sticky: the caller's to clear
+    if (failed && tid < NS && live) {
+        for (int t = 0; t < nb; ++t) {
+            a.util[s * a.N_cap + t0 + t] = __builtin_nanf("");
+            a.gate[s * a.N_cap + t0 + t] = __builtin_nanf("");
+        }
+    }
+}
+
 template <int DG, int P, int SUB>
 static void launch_oct(const LstmArgs &a, int t0, int nb, hipStream_t st)
 {
     hipLaunchKernelGGL((lstm_rec_oct_kernel<DG, P, SUB>), dim3(P * a.L * ((a.BH + 8 * SUB - 1) / (8 * SUB))), dim3(4 * DG / P), 0, st, a, t0, nb);
 }
 
+template <int DG, int P>
+static void launch_few(const LstmArgs &a, int t0, int nb, hipStream_t st)
+{
+    hipLaunchKernelGGL((lstm_rec_few_kernel<DG, P>), dim3(P * a.L * ((a.BH + 3) / 4)), dim3(256), 0, st, a, t0, nb);
+}
+
+// The smallest groups that the compute units hold at once, P workgroups each.
 hipError_t launch_lstm_oct(const LstmArgs &a, int t0, int nb, hipStream_t st)
 {
-    const int groups = a.L * ((a.BH + 7) / 8);
+    const int fours = a.L * ((a.BH + 3) / 4), eights = a.L * ((a.BH + 7) / 8);
     if (a.d_g == 512) {
-        if (8 * groups <= a.compute_units) launch_oct<512, 8, 1>(a, t0, nb, st);
+        if (8 * fours <= a.compute_units) launch_few<512, 8>(a, t0, nb, st);
+        else if (8 * eights <= a.compute_units) launch_oct<512, 8, 1>(a, t0, nb, st);
         else launch_oct<512, 8, 2>(a, t0, nb, st);
-    } else if (4 * groups <= a.compute_units) launch_oct<256, 4, 1>(a, t0, nb, st);
+    } else if (4 * fours <= a.compute_units) launch_few<256, 4>(a, t0, nb, st);
+    else if (4 * eights <= a.compute_units) launch_oct<256, 4, 1>(a, t0, nb, st);
     else launch_oct<256, 2, 1>(a, t0, nb, st);
     return hipGetLastError();
 }
