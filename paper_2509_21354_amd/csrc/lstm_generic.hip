@@ -17,8 +17,12 @@
 //     reduction that leaves one gate's sum in each lane of a quad, where its
 //     nonlinearity is evaluated; c_t and h_t follow in the same lanes, so a
 //     step has one barrier;
-//   * up to d_g = 128 the four rows stay in registers for the whole call (RES > 0);
-//     wider gates read them from L2 every step, 16 bytes per lane;
+//   * up to d_g = 128 the four rows stay in registers for the whole call (RES > 0),
+//     and up to 192 with bf16 storage, as the pairs that they are (two shifts and masks
+//     per pair and step; what bounds the streamed form there is its chain of dependent
+//     loads, of single elements where d_g is no multiple of 4: d_g = 163, 32 sequences x
+//     32 steps 586 -> 135 us, 512 x 32 1173 -> 276, 1024 x 32 770 (four a workgroup) ->
+//     549); wider gates read them from L2 every step, 16 bytes per lane;
 //   * the utility head runs after each block over the block's 16 states.
 // Measured (fp32, d_g = 64, d = 64, 4 sequences x 64 steps): 1346 us with one
 // row of W_ih and W_hh at a time per lane group, dependent loads from L2 in every
@@ -83,7 +87,11 @@ __global__ __launch_bounds__(kGenThreads, RES == 1 && MB == 1 ? 8 : 4) void lstm
     }
     for (int j = tid; j < MB * dg; j += kGenThreads) cs[j] = fresh ? 0.f : a.c[seq(j / dg) * dg + j % dg];
 
-    float w[RES > 0 ? RES : 1][4][KC][4];
+    // (at three units of three chunks only as the bf16 pairs that they are)
+    constexpr bool PACKED = RES == 3;
+    static_assert(!PACKED || sizeof(T) == 2, "two elements of a row in a register");
+    constexpr int WN = PACKED ? 2 : 4;
+    float w[RES > 0 ? RES : 1][4][KC][WN];
     if constexpr (RES > 0) {
 #pragma unroll
         for (int i = 0; i < RES; ++i) {
@@ -91,7 +99,14 @@ __global__ __launch_bounds__(kGenThreads, RES == 1 && MB == 1 ? 8 : 4) void lstm
 #pragma unroll
             for (int q = 0; q < 4; ++q)
 #pragma unroll
-                for (int c = 0; c < KC; ++c) load4<T, VEC>(W_hh + (size_t)(q * dg + u) * dg, 64 * c + 4 * cl, dg, w[i][q][c]);
+                for (int c = 0; c < KC; ++c) {
+                    float v[4];
+                    load4<T, VEC>(W_hh + (size_t)(q * dg + u) * dg, 64 * c + 4 * cl, dg, v);
+#pragma unroll
+                    for (int e = 0; e < WN; ++e)
+                        w[i][q][c][e] = PACKED ? __uint_as_float(__float_as_uint(v[2 * e]) >> 16 | __float_as_uint(v[2 * e + 1 < 4 ? 2 * e + 1 : 3])) : v[e];
+                    if (PACKED) __builtin_amdgcn_sched_barrier(0);      // (not all of the matrix under way as single elements)
+                }
         }
     }
 
@@ -157,6 +172,12 @@ __global__ __launch_bounds__(kGenThreads, RES == 1 && MB == 1 ? 8 : 4) void lstm
 #pragma unroll
                 for (int i = 0; i < RES; ++i) {
                     const int u = grp + kGenThreads / 16 * i;
+                    if constexpr (PACKED) {          // (else the compiler unpacks them all once, before the steps, and spills)
+#pragma unroll
+                        for (int q = 0; q < 4; ++q)
+#pragma unroll
+                            for (int c = 0; c < KC; ++c) asm volatile("" : "+v"(w[i][q][c][0]), "+v"(w[i][q][c][1]));
+                    }
                     if (u < dg) {
                         float part[MB][4];
 #pragma unroll
@@ -169,7 +190,11 @@ __global__ __launch_bounds__(kGenThreads, RES == 1 && MB == 1 ? 8 : 4) void lstm
 #pragma unroll
                                 for (int q = 0; q < 4; ++q)
 #pragma unroll
-                                    for (int e = 0; e < 4; ++e) part[m][q] = fmaf(w[i][q][c][e], hv[e], part[m][q]);
+                                    for (int e = 0; e < 4; ++e) {
+                                        const float we = !PACKED ? w[i][q][c][e % WN] : e % 2 ? __uint_as_float(__float_as_uint(w[i][q][c][e / 2 % WN]) & 0xFFFF0000u)
+                                                                                                : __uint_as_float(__float_as_uint(w[i][q][c][e / 2 % WN]) << 16);
+                                        part[m][q] = fmaf(we, hv[e], part[m][q]);
+                                    }
                             }
                         }
                         cell(tt, u, part);
@@ -488,7 +513,17 @@ static hipError_t launch_t(const LstmArgs &a, hipStream_t st)
     // streamed, are then read once for all of them, and the nonlinearities, which bound a full chip, are evaluated once
     // instead of in four quads.  (fp32, one against four per workgroup: 2048 sequences x 64
     // steps at d_g = 64 359 -> 340 us, x 1 step 53 -> 20 us; x 8 steps at d_g = 256 843 -> 324 us.)
-    const bool four = (long long)a.L * ((a.BH + 3) / 4) >= a.compute_units && gen_tb(D, a.d_g, 4) > 0;
+    // Above 128 units, where W_hh is streamed and a workgroup has a compute unit to itself, by rounds of the chip: a round of four
+    // sequences each takes under two of one (32 steps, one against four: fp32, d_g = 256 369 and 630 us, 512 682 and 1000; bf16,
+    // d_g = 200 373 and 681; fp32, 130 535 and 692), but for narrow aligned rows just over (fp32, d_g = 132 165 and 350).
+    // 384 sequences, fp32, d_g = 256, once one each until 1024: 718 -> 629 us; 512 x 16 steps at d_g = 512 1365 -> 1000.
+    const long long rounds1 = ((long long)a.L * a.BH + a.compute_units - 1) / a.compute_units;
+    const long long rounds4 = ((long long)a.L * ((a.BH + 3) / 4) + a.compute_units - 1) / a.compute_units;
+    // (Of many layers of one sequence each there is nothing to share: 300, fp32, d_g = 200 1521 -> 1065; of two it still pays to read
+    // each layer's weights once: bf16 1578, one each 1854.)
+    const bool chip = (long long)a.L * ((a.BH + 3) / 4) >= a.compute_units;
+    const bool rounds = rounds1 >= 2 * rounds4 + (a.d_g < 192 && a.d_g % 4 == 0 ? 1 : 0);
+    const bool four = (a.d_g <= 128 ? chip : rounds || (chip && a.BH > 1)) && gen_tb(D, a.d_g, 4) > 0;
     // (a workgroup takes a compute unit to itself: see lstm_chain_kernel)
     if (a.d_g <= 64 && (long long)a.L * a.BH <= a.compute_units) {
         hipLaunchKernelGGL((lstm_chain_kernel<T, D>), dim3((unsigned)((size_t)a.L * a.BH)), dim3(512), 0, st, a);
@@ -496,6 +531,10 @@ static hipError_t launch_t(const LstmArgs &a, hipStream_t st)
     }
     if (a.d_g <= 64) return four ? launch_v<T, D, 4, 1, 1>(a, st) : launch_v<T, D, 1, 1, 1>(a, st);
     if (a.d_g <= 128) return four ? launch_v<T, D, 4, 2, 2>(a, st) : launch_v<T, D, 1, 2, 2>(a, st);
+    if constexpr (sizeof(T) == 2) {
+        // (one sequence each at any number of them: four take more registers than there are beside the rows)
+        if (a.d_g <= 192) return launch_v<T, D, 1, 3, 3>(a, st);
+    }
     return four ? launch_v<T, D, 4, 0, 1>(a, st) : launch_v<T, D, 1, 0, 1>(a, st);
 }
 
