@@ -87,19 +87,28 @@ def roof(name, kernel, cost, us, bound, workload=None):
     return r
 
 
-def oct_groups(cfg):
-    return cfg.L * ((cfg.B * cfg.kv_heads + 7) // 8)
+def few_form(cfg):
+    """(kernel, workgroups per group, sequences per group) of the gate of few sequences, or None where they are too many."""
+    bh = cfg.B * cfg.kv_heads
+    groups = lambda n: cfg.L * ((bh + n - 1) // n)
+    if cfg.d_g == 512 and cfg.N >= 16 and 8 * groups(16) <= 256:
+        forms = [("few", 8, 4), ("oct", 8, 8), ("oct", 8, 16)]
+    else:
+        forms = [("few", 4, 4), ("oct", 4, 8), ("oct", 2, 8)] if cfg.d_g == 256 else []
+    for kind, members, seqs in forms:
+        if members * groups(seqs) <= 256:
+            return f"lstm_rec_{kind}_kernel<{cfg.d_g}, {members}" + (f", {seqs // 8}>" if kind == "oct" else ">"), members, seqs
+    return None
 
 
 def rec_kernel_name(cfg):
     groups = cfg.L * ((cfg.B * cfg.kv_heads + 15) // 16)
     if cfg.d_g == 256 and groups >= 257:
         return f"lstm_fused_kernel<{cfg.d}>"
-    bh = cfg.B * cfg.kv_heads
-    if cfg.d_g == 512 and bh > 16:      # (more groups than fit at once: several launches of the same kernel)
+    if few_form(cfg):
+        return few_form(cfg)[0]
+    if cfg.d_g == 512 and cfg.B * cfg.kv_heads > 16:      # (more groups than fit at once: several launches of the same kernel)
         return f"lstm_quad_kernel<{cfg.d}>"
-    if cfg.d_g == 256 and oct_groups(cfg) <= 128:
-        return f"lstm_rec_oct_kernel<{4 if oct_groups(cfg) <= 64 else 2}>"
     if cfg.d_g <= 128:
         return f"lstm_rec_narrow_kernel<{cfg.d_g}>"
     paired = cfg.d_g in (256, 512) and groups <= 128
@@ -128,17 +137,17 @@ def recurrence_occupancy(cfg, gate_us):
     paired = rec_kernel_name(cfg).startswith("lstm_rec_pair")
     fused = rec_kernel_name(cfg).startswith("lstm_fused")
     quad = rec_kernel_name(cfg).startswith("lstm_quad")
-    octs = rec_kernel_name(cfg).startswith("lstm_rec_oct")
+    few = few_form(cfg)
     members, seqs = 4 if quad else 2 if paired else 1, 32 if fused or quad else 16
     if fused or quad:              # 32 sequences per workgroup (or four of them), the input projection's MFMAs inside the step
         wgs = members * cfg.L * ((cfg.B * cfg.kv_heads + 31) // 32)
         cus, rounds = min(256, wgs), -(-wgs // 256)
         mfma_per_group_step = 2 * (2 * (4 * cfg.d_g // 16) * (cfg.d_g // 32) + (4 * cfg.d_g // 16) * (2 * cfg.d // 32))
         per_simd = mfma_per_group_step / members / 4 * rounds
-    elif octs:      # 8 sequences on 4 or 2 workgroups, both terms of h in one instruction
-        members, seqs = 4 if oct_groups(cfg) <= 64 else 2, 8
-        cus = members * oct_groups(cfg)
-        per_simd = (4 * cfg.d_g // 16) * (cfg.d_g // 32) / members / 4
+    elif few:      # both terms of h of 4 or 8 sequences in one instruction
+        _, members, seqs = few
+        cus = members * cfg.L * ((cfg.B * cfg.kv_heads + seqs - 1) // seqs)
+        per_simd = (4 * cfg.d_g // 16) * (cfg.d_g // 32) / members / 4 * max(1, seqs // 8)
     else:
         cus = min(256, groups * (2 if paired else 1))
         rounds = -(-groups * (2 if paired else 1) // 256)

@@ -78,7 +78,7 @@ struct LstmArgs {
 // on four workgroups (a quarter of the stream each, and every fragment serves two blocks of sequences); a launch
 // takes at most one workgroup per compute unit, larger calls are cut into several launches.  So all workgroups of a
 // launch can be resident together on an idle device (bounded waits in the kernels cover the rest).
-// Eight (lstm_rec_oct_kernel): at d_g = 512 while eight workgroups per 16 sequences fit the chip, which keeps all of W_hh in
+// Eight (lstm_oct.hip): at d_g = 512 while eight workgroups per 16 sequences fit the chip, which keeps all of W_hh in
 // registers; up to there it is the faster one whatever the sequences per layer (512 x 64 steps 341 against 570 us, 16 a layer 387
 // against 910; 1024 in two launches 730 against 579, so it ends there).  Caches of fewer than kLstmOctMinChunks chunks keep the
 // others, which need no scratch for projections (8 KiB per sequence and step): 8 steps of 512 sequences take 80 against 91 us, a
@@ -95,7 +95,7 @@ inline int lstm_split(int d_g, int L, int BH, int N_cap, int compute_units, bool
     if ((d_g == 256 || d_g == 512) && 2 * g16 <= compute_units) return 2;
     return 0;
 }
-// At d_g = 256, launches that fit the chip with two workgroups per 8 sequences take lstm_rec_oct_kernel (four per 8 where
+// At d_g = 256, launches that fit the chip with two workgroups per 8 sequences take lstm_rec_oct_kernel (four per 8 or per 4 where
 // that fits too): 1024 sequences x 64 steps 224 us against 245 us on pairs per 16; above, the pairs remain.
 inline bool lstm_takes_oct(int L, int BH, int compute_units) { return 2ll * L * ((BH + 7) / 8) <= compute_units; }
 inline size_t lstm_split_exch_bytes(int split, int d_g, int L, int BH, int quad_groups)
@@ -155,7 +155,7 @@ hipError_t launch_lstm_prepare(const LstmArgs &a, hipStream_t st);       // bf16
 hipError_t launch_stream_probe(const void *src, size_t tiles, int tile_bytes, void *dst, int write_bytes, int hints, hipStream_t st);   // calibration
 hipError_t launch_lstm_quad(const LstmArgs &a, hipStream_t st);          // bf16, d_g = 512: projection and recurrence of 32 sequences on four workgroups (weights already packed)
 hipError_t launch_lstm_narrow(const LstmArgs &a, int t0, int nb, hipStream_t st);   // bf16, d_g = 64, 128: the recurrence, 8 sequences per workgroup
-hipError_t launch_lstm_oct(const LstmArgs &a, int t0, int nb, hipStream_t st);   // bf16, d_g = 256: the recurrence on two or four workgroups per 8 sequences
+hipError_t launch_lstm_oct(const LstmArgs &a, int t0, int nb, hipStream_t st);   // bf16: the recurrence on two or four workgroups per 8 sequences or four per 4 (d_g = 256), on eight per 4, 8 or 16 (512)
 hipError_t launch_lstm_fused(const LstmArgs &a, hipStream_t st);         // bf16, d_g = 256: the recurrence with the input projection inside (weights already packed)
 
 }  // namespace kvev

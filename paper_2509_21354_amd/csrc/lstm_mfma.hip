@@ -10,7 +10,8 @@
 //                       (d_g = 64, 128: lstm_narrow.hip);
 //   lstm_rec_pair_kernel  the same on two workgroups per 16 sequences, each
 //                       with half of the hidden units, for launches small enough
-//                       to be resident at once (further down).
+//                       to be resident at once (further down); smaller ones yet
+//                       take four or eight workgroups per 4 or 8 sequences (lstm_oct.hip).
 // Before them, once per set of weights: lstm_prep_kernel (W_ih into fragment
 // order, per-layer scale of W_hh) and lstm_pack_whh_kernel.  Launches with more
 // sequence groups than compute units take one kernel for both halves instead

@@ -1,5 +1,5 @@
 // Recurrent gate, Eq. 3 of the paper, bf16 storage, d_g = 256 and 512: the sequential half for launches of few sequences,
-// 8 sequences on four or two compute units (256), 8 or 16 on eight (512).
+// 4 or 8 sequences on four or 8 on two compute units (256), 4, 8 or 16 on eight (512).
 //
 // What bounds such a launch is the chain of one step, and the chip is mostly idle.  As in lstm_rec_pair_kernel
 // (lstm_mfma.hip) the workgroups of a group share the hidden units, keep their rows of W_hh in registers and exchange
@@ -23,8 +23,8 @@
 // A step: products over the own units | take the partners' h, stage in LDS | barrier | products over the partners' units |
 // cell, publish, own h to LDS | barrier.  Bounded waits, status word and the layout of weights and projections: as the
 // paired kernel.
-// Measured (the whole gate call, weights prepared): 32 sequences x 128 steps 304 us on pairs per 16 sequences, 233 us here (P =
-// 4; about 0.95 us of a step are its own work, the rest is the exchange), 248 us with 16 bytes per lane, a stamp of the
+// Measured (the whole gate call, weights prepared): 32 sequences x 128 steps 304 us on pairs per 16 sequences, 233 us in groups of 8 (P =
+// 4; 175 to 205 in lstm_rec_few_kernel's groups of 4, below; about 0.95 us of a step are its own work, the rest is the exchange), 248 us with 16 bytes per lane, a stamp of the
 // step beside every two units, in the flag's place; 512 x 64 183, 145 and 156 us; 1024 x 64 (P = 2) 245, 218 and 219 us.
 // Members on one XCD that exchange by plain stores through its L2 took 185 us at the first shape, but publications of that
 // kind were lost under cache pressure (seen in lstm_quad.hip; cause not shown), so all stores write through.
