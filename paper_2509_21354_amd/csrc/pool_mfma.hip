@@ -59,8 +59,8 @@ template <int N, class F> __device__ __forceinline__ void rows_fold2(float (&v)[
 //
 // With 16 waves nothing covers the MLP of a tile, so its length counts: a wave asks for the weights and biases of its task in
 // both layers as soon as its rows are summed, before the sums over the lanes and the barriers (they were asked for where
-// they were used, those of layer 2 one k-step at a time): 4096 chunks of 32 at d = 128 15.0 -> 14.3 us, 8192 31.7 -> 29.4,
-// 16384 64.5 -> 60.1.
+// they were used, those of layer 2 one k-step at a time): 4096 chunks of 32 at d = 128 15.3 -> 14.1 us, 8192 31.2 -> 28.5,
+// 16384 64.6 -> 59.1; 2748 at d_sum = 64 11.0 -> 10.5 (11.4 with requests for k-steps that d_sum does not have).
 //
 // The NW = 4 form is persistent (a workgroup walks tiles blockIdx.x, blockIdx.x + gridDim.x, ...) and does not write a
 // tile's summaries when they are ready: a thread keeps its 16-byte pieces of up to NS tiles in registers, and every
@@ -224,7 +224,8 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 3 : 1) void pool_mfma_kernel(Poo
         const bf16_t *W2 = static_cast<const bf16_t *>(kv ? a.W2V : a.W2K) + ((size_t)l * D + e0 + n) * ds + g4 * 8;
         b2f = *reinterpret_cast<const uint2 *>(static_cast<const bf16_t *>(kv ? a.b2V : a.b2K) + (size_t)l * D + e0 + 4 * g4);
 #pragma unroll
-        for (int ks = 0; ks < W2R; ++ks) w2f[ks] = *reinterpret_cast<const bf16x8_t *>(W2 + min(ks, ds / 32 - 1) * 32);
+        for (int ks = 0; ks < W2R; ++ks)
+            if (ks < ds / 32) w2f[ks] = *reinterpret_cast<const bf16x8_t *>(W2 + ks * 32);      // (requests take their time even where a line is there)
     };
     auto bias4 = [](uint2 b) __attribute__((always_inline)) {
         return f32x4_t{__uint_as_float(b.x << 16), __uint_as_float(b.x & 0xFFFF0000u), __uint_as_float(b.y << 16), __uint_as_float(b.y & 0xFFFF0000u)};
