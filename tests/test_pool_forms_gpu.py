@@ -16,6 +16,7 @@ pytestmark = pytest.mark.gpu
     (64, 16, 9, 914, 64, kb.POOL_MLP),          # 515, the last one ragged
     (128, 29, 41, 500, 96, kb.POOL_MLP),        # 1282: a long chunk whose tail is padded
     (64, 24, 41, 400, 256, kb.POOL_MLP),        # 1025, wide hidden layer: 16 waves, two tasks a wave
+    (64, 16, 9, 914, 32, kb.POOL_MLP),          # one k-step in the second layer
     (128, 16, 41, 400, 128, kb.POOL_MEAN),      # 1025
     (64, 8, 41, 400, 128, kb.POOL_MAX),
 ])
