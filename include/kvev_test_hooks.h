@@ -1,13 +1,15 @@
 /*
  * kvev test hooks: entry points that exist for the tests of the library, not for
- * its users.  They change process-wide settings (atomically; a call that is
- * already being planned may see the old or the new value) and are declared here,
+ * its users.  Most change process-wide settings (atomically; a call that is
+ * already being planned may see the old or the new value); all are declared here,
  * apart from kvev.h, so that nothing in the public interface depends on them.
  */
 #ifndef KVEV_TEST_HOOKS_H
 #define KVEV_TEST_HOOKS_H
 
 #include <stddef.h>
+
+#include "kvev.h"
 
 #ifdef __cplusplus
 extern "C" {
@@ -36,6 +38,11 @@ int kvev_debug_lstm_fused_min_groups(int min_groups);
  * that a shape the CPU oracle finishes in seconds takes several launches; 0 restores the default (compute units / 4).
  * Errors: INVALID_ARG for a negative value. */
 int kvev_debug_lstm_quad_groups(int groups);
+
+/* How kvev_lstm_gate (prepared = 0) or kvev_lstm_gate_prepared (1) runs `steps` chunks of a bf16 shape with d_g = 64, 128,
+ * 256 or 512 with ws_bytes of scratch: the workgroups that share a group of sequences (0: one) and the steps per launch
+ * (0: the scratch is refused).  No GPU is needed.  Errors: INVALID_ARG. */
+int kvev_debug_lstm_plan(const kvev_shape *shape, int prepared, int steps, size_t ws_bytes, int *workgroups, int *block);
 
 /* The single-query attention kernels read their rows with the non-temporal hint
  * when a launch reads more than `bytes` (default 256 MiB, what the memory-side

@@ -339,6 +339,27 @@ static size_t lstm_ws_per_step(const kvev_shape *sh)
     return (size_t)lstm_groups(sh) * 16 * 4 * sh->d_g * sizeof(float);
 }
 
+// Most steps of one launch of the two-kernel forms, however much scratch there is: the recurrence addresses the projections of a
+// group of 16 sequences with 32 bits (d_g = 512: 128 KiB a step, 2 GiB in all), and their grid has a row per 2 steps or more.
+constexpr int kLstmMaxBlock = 16384;
+
+// How a call runs: the workgroups that share a group of sequences (LstmArgs::split), the steps per launch (0: the scratch does
+// not hold one) and where in the scratch the projections begin.
+struct LstmPlan { int split, block; size_t pack, exch_bytes; };
+static LstmPlan lstm_plan(const kvev_shape *sh, bool prepared, int steps, size_t ws_bytes)
+{
+    kvev_shape small = *sh;
+    // scratch of the size that quadruples need, which keep no projections, stays accepted, and takes them
+    if (lstm_split_of(sh) == 8 && ws_bytes < lstm_ws_pack(sh, prepared) + lstm_ws_per_step(sh)) {
+        small.N_cap = 0;
+        sh = &small;
+    }
+    const size_t per = lstm_ws_per_step(sh), pack = lstm_ws_pack(sh, prepared);
+    size_t block = ws_bytes < pack + per ? 0 : per == 0 ? (size_t)steps : std::min<size_t>((ws_bytes - pack) / per, kLstmMaxBlock);
+    block = std::min(block, (size_t)steps);
+    return {lstm_split_of(sh), (int)block, pack, lstm_exch_bytes(sh)};
+}
+
 }  // namespace kvev
 
 using namespace kvev;
@@ -439,19 +460,11 @@ static int lstm_gate_common(const kvev_shape *sh, const void *Kbar, const void *
     hipStream_t st = static_cast<hipStream_t>(stream);
     hipError_t e;
     if (lstm_takes_mfma(sh)) {
-        kvev_shape small = *sh;
-        // scratch of the size that quadruples need, which keep no projections, stays accepted, and takes them
-        if (lstm_split_of(sh) == 8 && ws_bytes < lstm_ws_pack(sh, prepared) + lstm_ws_per_step(sh)) {
-            small.N_cap = 0;
-            sh = &small;
-        }
-        const size_t per = lstm_ws_per_step(sh), pack = lstm_ws_pack(sh, prepared);
-        if (!ws || !aligned16(ws) || ws_bytes < pack + per) return KVEV_ERR_WORKSPACE;
+        const LstmPlan plan = lstm_plan(sh, prepared, chunk_end - chunk_begin, ws_bytes);
+        if (!ws || !aligned16(ws) || plan.block < 1) return KVEV_ERR_WORKSPACE;
         a.fused = lstm_takes_fused(sh) ? 1 : 0;
-        a.split = lstm_split_of(sh);
-        size_t tb = per == 0 ? (size_t)(chunk_end - chunk_begin) : (ws_bytes - pack) / per;
-        if (tb > (size_t)(chunk_end - chunk_begin)) tb = (size_t)(chunk_end - chunk_begin);
-        a.tb = (int)tb;
+        a.split = plan.split;
+        a.tb = plan.block;
         unsigned char *p = static_cast<unsigned char *>(ws);
         a.status = reinterpret_cast<int32_t *>(p);
         p += kLstmWsHead;
@@ -462,10 +475,10 @@ static int lstm_gate_common(const kvev_shape *sh, const void *Kbar, const void *
             lstm_packed_pointers(sh, p, a);
             p += lstm_ws_weights(sh);
         }
-        a.exch_bytes = lstm_exch_bytes(sh);
+        a.exch_bytes = plan.exch_bytes;
         a.quad_groups = lstm_quad_groups();
         a.exch = a.exch_bytes ? p : nullptr;
-        a.xproj = reinterpret_cast<float *>(static_cast<unsigned char *>(ws) + pack);
+        a.xproj = reinterpret_cast<float *>(static_cast<unsigned char *>(ws) + plan.pack);
         a.pair_spin_limit = g_pair_spin_limit.load();
         a.pair_mute = g_pair_mute.load();
         e = launch_lstm_mfma(a, st);
@@ -592,6 +605,15 @@ int kvev_debug_pair_wait(int spin_limit, int mute_member)
 int kvev_debug_attn_stream_bytes(size_t bytes)
 {
     g_stream_bytes = bytes == 0 ? kCacheBytes : bytes;
+    return KVEV_OK;
+}
+
+int kvev_debug_lstm_plan(const kvev_shape *sh, int prepared, int steps, size_t ws_bytes, int *workgroups, int *block)
+{
+    if (check_shape(sh) != KVEV_OK || steps < 1 || !workgroups || !block || !lstm_takes_mfma(sh)) return KVEV_ERR_INVALID_ARG;
+    const LstmPlan plan = lstm_plan(sh, prepared != 0, steps, ws_bytes);
+    *workgroups = plan.split;
+    *block = plan.block;
     return KVEV_OK;
 }
 

@@ -96,3 +96,25 @@ def test_h_is_kept_until_all_are_heard(cfg, members):
             assert torch.equal(c[..., u], good_c[..., u]) and torch.equal(h[..., u], good_h[..., u])
         else:
             assert torch.isnan(c[..., u]).all() and torch.equal(h[..., u], h0[..., u])
+
+
+def test_projections_of_many_steps():
+    """Scratch for more steps than 32 bits address the projections of (d_g = 512: 128 KiB a step): the bits of a call whose
+    projections are made 128 steps at a time."""
+    N = 32768 + 40
+    cfg = base._cfg(411, "bf16", d=64, T=N, C=1, W=0, d_g=512, L=1, B=1, H=1)
+    gen = torch.Generator(device="cuda").manual_seed(1)
+    Kb, Vb = (torch.randn((1, 1, 1, N, 64), device="cuda", generator=gen).mul_(0.25).bfloat16() for _ in range(2))
+    sh, gw = kb.make_shape(cfg, N_cap=N), base.dev(synth.make_weights(cfg, "cpu"))
+    small = kb.workspace_bytes(kb.OP_LSTM_GATE, sh, 128)
+    outs = []
+    for nbytes in (small, small + (N - 128) * 131072):
+        ws = kb.alloc_workspace(nbytes)
+        h, c = (torch.zeros((1, 1, 1, 512), device="cuda") for _ in range(2))
+        util, gate = (torch.zeros((1, 1, 1, N), device="cuda") for _ in range(2))
+        kb.kvev_lstm_gate(sh, Kb, Vb, kb.lstm_weights(gw), 0, N, h, c, util, gate, ws)
+        torch.cuda.synchronize()
+        assert int(ws[:4].view(torch.int32).item()) == 0
+        outs.append((h, c, util, gate))
+    assert all(torch.equal(x, y) for x, y in zip(*outs))
+    assert 0 < float(outs[0][2].std())

@@ -1,0 +1,31 @@
+"""How the recurrent gate (bf16, Eq. 3) uses the scratch it is given: the form and the steps per launch, as the library plans them
+(no GPU needed)."""
+import pytest
+
+from paper_2509_21354_amd import binding as kb
+
+
+def _shape(d_g, L=1, BH=1, N_cap=64, d=128):
+    return kb.make_shape(L=L, B=1, H=BH, d=d, T=N_cap, T_cap=N_cap, C=1, N_cap=N_cap, W=0, d_sum=32, d_g=d_g, dtype=kb.BF16, H_kv=0)
+
+
+def _fixed(shape):
+    """scratch that does not grow with the steps (prepared weights), and what a step adds"""
+    one, two = (kb.workspace_bytes(kb.OP_LSTM_GATE_PREPARED, shape, n) for n in (17, 18))
+    return one - 17 * (two - one), two - one
+
+
+@pytest.mark.parametrize("d_g", [64, 128, 256, 512])
+@pytest.mark.parametrize("BH", [1, 16])
+def test_projections_of_a_launch_stay_within_32_bits(d_g, BH):
+    """The recurrence addresses the projections of a group of 16 sequences with 32 bits: a launch takes fewer steps than overflow
+    them, however much scratch there is."""
+    sh = _shape(d_g, BH=BH, N_cap=1 << 20)
+    fixed, step = _fixed(sh)
+    workgroups, block = kb.kvev_debug_lstm_plan(sh, True, 1 << 20, fixed + (step << 20))
+    assert step == 16 * 4 * d_g * 4 and workgroups != 4
+    assert 4096 <= block and block * step < 1 << 32
+    assert block // 2 + 4096 < 1 << 16           # rows of the projection's grid: two steps each at least, and those that re-lay weights
+    assert kb.kvev_debug_lstm_plan(sh, True, 1 << 20, fixed + 100 * step)[1] == 100
+    assert kb.kvev_debug_lstm_plan(sh, True, 5, fixed + 100 * step)[1] == 5
+    assert kb.kvev_debug_lstm_plan(sh, True, 5, fixed + step - 1)[1] == 0
