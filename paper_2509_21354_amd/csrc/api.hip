@@ -654,10 +654,13 @@ size_t kvev_workspace_bytes(int op, const kvev_shape *sh, int n, int k_cap)
         return pool_ws_bytes(sh);
     case KVEV_OP_LSTM_GATE:
     case KVEV_OP_LSTM_GATE_PREPARED: {
-        const size_t per = lstm_ws_per_step(sh);
-        const int tb = n < 128 ? n : 128;
         if (!lstm_takes_mfma(sh)) return 0;
-        return lstm_ws_pack(sh, op == KVEV_OP_LSTM_GATE_PREPARED) + per * (size_t)(tb < 1 ? 1 : tb);
+        const int tb = n < 1 ? 1 : n < 128 ? n : 128;
+        auto need = [&](const kvev_shape *s) { return lstm_ws_pack(s, op == KVEV_OP_LSTM_GATE_PREPARED) + lstm_ws_per_step(s) * (size_t)tb; };
+        // (one query serves caches of every capacity: the short ones take other forms, see lstm_split)
+        kvev_shape small = *sh;
+        if (lstm_split_of(sh) == 8) small.N_cap = 0;
+        return std::max(need(sh), need(&small));
     }
     case KVEV_OP_LSTM_PREPARE:
         return lstm_takes_mfma(sh) ? lstm_ws_weights(sh) : 0;

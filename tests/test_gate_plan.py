@@ -28,4 +28,16 @@ def test_projections_of_a_launch_stay_within_32_bits(d_g, BH):
     assert block // 2 + 4096 < 1 << 16           # rows of the projection's grid: two steps each at least, and those that re-lay weights
     assert kb.kvev_debug_lstm_plan(sh, True, 1 << 20, fixed + 100 * step)[1] == 100
     assert kb.kvev_debug_lstm_plan(sh, True, 5, fixed + 100 * step)[1] == 5
-    assert kb.kvev_debug_lstm_plan(sh, True, 5, fixed + step - 1)[1] == 0
+    assert kb.kvev_debug_lstm_plan(sh, True, 5, step)[1] == 0
+
+
+@pytest.mark.parametrize("L,BH", [(1, 1), (1, 16), (3, 13), (32, 16), (1, 17), (2, 64), (1, 512)])
+@pytest.mark.parametrize("n", [1, 2, 8, 128])
+@pytest.mark.parametrize("prepared", [False, True])
+def test_scratch_serves_caches_of_other_capacities(L, BH, n, prepared):
+    """d_g = 512 takes other forms for short caches: scratch that was asked for with one capacity is accepted with any."""
+    op = kb.OP_LSTM_GATE_PREPARED if prepared else kb.OP_LSTM_GATE
+    for asked in (1, 15, 16, 256):
+        nbytes = kb.workspace_bytes(op, _shape(512, L, BH, asked), n)
+        for used in (1, 15, 16, 256):
+            assert kb.kvev_debug_lstm_plan(_shape(512, L, BH, used), prepared, used, nbytes)[1] >= min(n, used)
