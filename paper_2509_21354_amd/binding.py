@@ -107,7 +107,7 @@ def lib() -> ctypes.CDLL:
         for n in ("kvev_chunk_pool", "kvev_lstm_gate", "kvev_lstm_prepare", "kvev_lstm_gate_prepared", "kvev_select", "kvev_gated_attention",
                   "kvev_gated_attention_static", "kvev_dense_attention", "kvev_retain", "kvev_compact_attention", "kvev_version"):
             getattr(L, n).restype = ci
-        _native.bind(Shape, RowsFrom, torch.Tensor, torch.cuda.__dict__, getattr(torch._C, "_cuda_getDevice", None),
+        _native.bind(Shape, RowsFrom, torch.Tensor, torch.cuda.is_initialized, getattr(torch._C, "_cuda_getDevice", None),
                      getattr(torch._C, "_cuda_getCurrentRawStream", None),
                      {n: ctypes.cast(getattr(L, n), vp).value for n in EXPORTS})
         _lib = L

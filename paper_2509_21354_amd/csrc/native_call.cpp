@@ -19,8 +19,8 @@
 namespace {
 
 // bound once by binding.py: types, what the current stream is asked of, and the library's entry points
-PyObject *g_shape_type, *g_rows_type, *g_tensor_type, *g_cuda_dict, *g_get_device, *g_raw_stream;
-PyObject *s_is_contiguous, *s_data_ptr, *s_numel, *s_ptr, *s_initialized;
+PyObject *g_shape_type, *g_rows_type, *g_tensor_type, *g_initialized, *g_get_device, *g_raw_stream;
+PyObject *s_is_contiguous, *s_data_ptr, *s_numel, *s_ptr;
 
 enum Entry { kPool, kGate, kGatePrepared, kSelect, kGated, kDense, kRetain, kCompact, kEntries };
 const char *const kNames[kEntries] = {"kvev_chunk_pool", "kvev_lstm_gate", "kvev_lstm_gate_prepared", "kvev_select",
@@ -144,8 +144,11 @@ struct Reader {
     void *stream()
     {
         if (!ok()) return nullptr;
-        PyObject *up = PyDict_GetItemWithError(g_cuda_dict, s_initialized);      // (a forked child finds it False)
-        if (up != Py_True) { plain = false; return nullptr; }
+        PyObject *up = PyObject_CallNoArgs(g_initialized);      // (asked of torch: the flag behind it stays set in a forked child)
+        if (!up) { error = true; return nullptr; }
+        const bool is_up = up == Py_True;
+        Py_DECREF(up);
+        if (!is_up) { plain = false; return nullptr; }
         PyObject *dev = PyObject_CallNoArgs(g_get_device);
         if (!dev) { error = true; return nullptr; }
         PyObject *r = PyObject_CallOneArg(g_raw_stream, dev);
@@ -290,11 +293,11 @@ PyObject *compact_attention(PyObject *, PyObject *const *args, Py_ssize_t n)
     return r.run([&] { return ENTRY(kCompact, kvev_compact_attention)(sh, Q, Tq, Kw, Vw, first, Kc, Vc, (int32_t *)count, k_cap, causal, O, ws, bytes, st); });
 }
 
-// bind(Shape, RowsFrom, Tensor, dict of torch.cuda, get_device, raw_stream, {name: address})
+// bind(Shape, RowsFrom, Tensor, is_initialized, get_device, raw_stream, {name: address})
 PyObject *bind(PyObject *, PyObject *args)
 {
-    PyObject *shape, *rows, *tensor, *cuda, *dev, *raw, *entries;
-    if (!PyArg_ParseTuple(args, "O!O!O!O!OOO!", &PyType_Type, &shape, &PyType_Type, &rows, &PyType_Type, &tensor, &PyDict_Type, &cuda, &dev, &raw, &PyDict_Type, &entries))
+    PyObject *shape, *rows, *tensor, *up, *dev, *raw, *entries;
+    if (!PyArg_ParseTuple(args, "O!O!O!OOOO!", &PyType_Type, &shape, &PyType_Type, &rows, &PyType_Type, &tensor, &up, &dev, &raw, &PyDict_Type, &entries))
         return nullptr;
     void *found[kEntries];
     for (int e = 0; e < kEntries; ++e) {
@@ -304,8 +307,8 @@ PyObject *bind(PyObject *, PyObject *args)
         if (PyErr_Occurred()) return nullptr;
     }
     for (int e = 0; e < kEntries; ++e) g_entry[e] = found[e];
-    Py_INCREF(rows); Py_INCREF(tensor); Py_INCREF(cuda); Py_INCREF(dev); Py_INCREF(raw); Py_INCREF(shape);
-    g_rows_type = rows; g_tensor_type = tensor; g_cuda_dict = cuda; g_get_device = dev; g_raw_stream = raw;
+    Py_INCREF(rows); Py_INCREF(tensor); Py_INCREF(up); Py_INCREF(dev); Py_INCREF(raw); Py_INCREF(shape);
+    g_rows_type = rows; g_tensor_type = tensor; g_initialized = up; g_get_device = dev; g_raw_stream = raw;
     g_shape_type = shape;           // (the last one: its presence says that all are there)
     Py_RETURN_NONE;
 }
@@ -325,7 +328,6 @@ PyMODINIT_FUNC PyInit__native(void)
     s_data_ptr = PyUnicode_InternFromString("data_ptr");
     s_numel = PyUnicode_InternFromString("numel");
     s_ptr = PyUnicode_InternFromString("ptr");
-    s_initialized = PyUnicode_InternFromString("_initialized");
-    if (!s_is_contiguous || !s_data_ptr || !s_numel || !s_ptr || !s_initialized) return nullptr;
+    if (!s_is_contiguous || !s_data_ptr || !s_numel || !s_ptr) return nullptr;
     return PyModule_Create(&g_module);
 }

@@ -1,6 +1,8 @@
 """The extension module that marshals calls into the library: what it does not take is left to ctypes, whose errors a caller
 sees, and nothing is left behind by a call that fails on the way."""
 import ctypes
+import os
+import subprocess
 import sys
 
 import pytest
@@ -58,3 +60,40 @@ def test_errors_of_a_tensor_reach_the_caller_and_nothing_is_held():
         with pytest.raises(ValueError, match="no address"):
             kb._native.gated_attention(*a.values())
     assert (sys.getrefcount(a["shape"]), sys.getrefcount(a["K"])) == before
+
+
+CHILD = """
+import torch
+from paper_2509_21354_amd import binding as kb
+torch.cuda._initialized = True                 # what a process forked from one that used the GPU finds
+torch.cuda.is_initialized = lambda: False      # what torch answers there
+kb.lib()
+t = torch.zeros(64)
+sh = kb.make_shape(L=1, B=1, H=1, d=64, T=8, T_cap=8, C=4, N_cap=2, W=4, d_sum=32, d_g=64, dtype=kb.F32, H_kv=0)
+assert kb._native.gated_attention(sh, t, 1, t, t, t, t, t.int(), t.int(), 1, t, None, 0) is None
+"""
+
+
+def test_torch_is_asked_whether_the_gpu_is_up():
+    """A forked child inherits torch's flag, not the GPU: torch says no there, and ctypes' way raises torch's error."""
+    r = subprocess.run([sys.executable, "-c", CHILD], capture_output=True, text=True, cwd=os.path.dirname(os.path.dirname(os.path.abspath(__file__))))
+    assert r.returncode == 0, r.stderr[-2000:]
+
+
+@pytest.mark.gpu
+def test_a_forked_child_is_refused():
+    """... before anything reaches the GPU (the child makes no call of it)."""
+    rows = torch.zeros(8, 64)
+    a = {k: v.cuda() if isinstance(v, torch.Tensor) else v for k, v in _args(K=rows, V=rows, Kbar=rows, Vbar=rows).items()}
+    kb.kvev_gated_attention(**a)
+    torch.cuda.synchronize()
+    pid = os.fork()
+    if pid == 0:
+        code = 1
+        try:
+            kb.kvev_gated_attention(**a)
+        except RuntimeError as e:
+            code = 0 if "fork" in str(e) else 2
+        finally:
+            os._exit(code)
+    assert os.waitpid(pid, 0)[1] == 0
