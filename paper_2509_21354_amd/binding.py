@@ -2,16 +2,18 @@
 
 Argument marshalling only: every step of the path runs in the HIP kernels of
 ``libkvev.so``.  The calls of the path are marshalled by the extension module
-``_native`` (``csrc/native_call.cpp``); what it does not take (arguments of
-other kinds, the first call of a process) goes through ctypes, with ctypes'
-errors.  Tensors are torch device tensors (torch is used for device
+``_native`` (``csrc/native_call.cpp``) where it is built; what it does not
+take (arguments of other kinds, the first call of a process) goes through
+ctypes, with ctypes' errors.  Tensors are torch device tensors (torch is used for device
 memory and streams, nothing else); work is enqueued on torch's current stream.
 There is no CPU fallback: if the library is missing, loading raises.
 """
 from __future__ import annotations
 
 import ctypes
+import importlib
 import os
+import warnings
 from typing import Dict, Optional, Tuple
 
 import torch
@@ -20,11 +22,6 @@ from . import synth
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libkvev.so")
-
-try:
-    from . import _native
-except ImportError:          # not built yet: lib() says so
-    _native = None
 
 OK, ERR_INVALID_ARG, ERR_UNSUPPORTED, ERR_WORKSPACE, ERR_HIP, ERR_STATIC_SCRATCH = range(6)
 STATIC_SCRATCH_BYTES = 4 << 20
@@ -63,16 +60,29 @@ class KvevError(RuntimeError):
 _lib = None
 
 
+def _import_native():
+    """The extension module, or None: every call then goes through ctypes."""
+    importlib.invalidate_caches()          # (it may have been built since this process began)
+    try:
+        return importlib.import_module("._native", __package__)
+    except ModuleNotFoundError:            # not built: a few microseconds more per call
+        return None
+    except ImportError as e:
+        warnings.warn(f"the marshalling extension does not load, calls go through ctypes: {e}")
+        return None
+
+
+_native = _import_native()
+
+
 def lib() -> ctypes.CDLL:
     """Loads libkvev.so (built by ``python -m paper_2509_21354_amd.build``)."""
-    global _lib
+    global _lib, _native
     if _lib is None:
         if not os.path.exists(LIB_PATH):
             raise FileNotFoundError(
                 f"{LIB_PATH} is missing: build it with `python -m paper_2509_21354_amd.build`; "
                 "there is no fallback path")
-        if _native is None:
-            raise FileNotFoundError(f"{_HERE}/_native.so is missing: build it with `python -m paper_2509_21354_amd.build`")
         L = ctypes.CDLL(LIB_PATH)
         vp, ci, sz = ctypes.c_void_p, ctypes.c_int, ctypes.c_size_t
         shp = ctypes.POINTER(Shape)
@@ -107,9 +117,11 @@ def lib() -> ctypes.CDLL:
         for n in ("kvev_chunk_pool", "kvev_lstm_gate", "kvev_lstm_prepare", "kvev_lstm_gate_prepared", "kvev_select", "kvev_gated_attention",
                   "kvev_gated_attention_static", "kvev_dense_attention", "kvev_retain", "kvev_compact_attention", "kvev_version"):
             getattr(L, n).restype = ci
-        _native.bind(Shape, RowsFrom, torch.Tensor, torch.cuda.is_initialized, getattr(torch._C, "_cuda_getDevice", None),
-                     getattr(torch._C, "_cuda_getCurrentRawStream", None),
-                     {n: ctypes.cast(getattr(L, n), vp).value for n in EXPORTS})
+        _native = _native or _import_native()
+        if _native:
+            _native.bind(Shape, RowsFrom, torch.Tensor, torch.cuda.is_initialized, getattr(torch._C, "_cuda_getDevice", None),
+                         getattr(torch._C, "_cuda_getCurrentRawStream", None),
+                         {n: ctypes.cast(getattr(L, n), vp).value for n in EXPORTS})
         _lib = L
     return _lib
 
@@ -204,7 +216,7 @@ def _mlp(w: Optional[Tuple[torch.Tensor, ...]]):
 
 
 def kvev_chunk_pool(shape: Shape, K, V, pool_mode, wK, wV, chunk_begin, chunk_end, Kbar, Vbar, ws=None):
-    st = _native.chunk_pool(shape, K, V, pool_mode, wK, wV, chunk_begin, chunk_end, Kbar, Vbar, ws) if _lib else None
+    st = _native.chunk_pool(shape, K, V, pool_mode, wK, wV, chunk_begin, chunk_end, Kbar, Vbar, ws) if _native else None
     if st is None:
         st = lib().kvev_chunk_pool(ctypes.byref(shape), _ptr(K), _ptr(V), pool_mode, _mlp(wK), _mlp(wV),
                                    chunk_begin, chunk_end, _ptr(Kbar), _ptr(Vbar), _ptr(ws),
@@ -214,7 +226,7 @@ def kvev_chunk_pool(shape: Shape, K, V, pool_mode, wK, wV, chunk_begin, chunk_en
 
 
 def kvev_lstm_gate(shape: Shape, Kbar, Vbar, w, chunk_begin, chunk_end, h, c, util, gate, ws=None):
-    st = _native.lstm_gate(shape, Kbar, Vbar, w, chunk_begin, chunk_end, h, c, util, gate, ws) if _lib else None
+    st = _native.lstm_gate(shape, Kbar, Vbar, w, chunk_begin, chunk_end, h, c, util, gate, ws) if _native else None
     if st is None:
         lw = LstmW(*[t.data_ptr() for t in w])
         st = lib().kvev_lstm_gate(ctypes.byref(shape), _ptr(Kbar), _ptr(Vbar), ctypes.byref(lw), chunk_begin,
@@ -232,7 +244,7 @@ def kvev_lstm_prepare(shape: Shape, w, packed):
 
 
 def kvev_lstm_gate_prepared(shape: Shape, Kbar, Vbar, w, packed, chunk_begin, chunk_end, h, c, util, gate, ws=None):
-    st = _native.lstm_gate_prepared(shape, Kbar, Vbar, w, packed, chunk_begin, chunk_end, h, c, util, gate, ws) if _lib else None
+    st = _native.lstm_gate_prepared(shape, Kbar, Vbar, w, packed, chunk_begin, chunk_end, h, c, util, gate, ws) if _native else None
     if st is None:
         lw = LstmW(*[t.data_ptr() for t in w])
         st = lib().kvev_lstm_gate_prepared(ctypes.byref(shape), _ptr(Kbar), _ptr(Vbar), ctypes.byref(lw), _ptr(packed),
@@ -244,7 +256,7 @@ def kvev_lstm_gate_prepared(shape: Shape, Kbar, Vbar, w, packed, chunk_begin, ch
 
 
 def kvev_select(shape: Shape, util, gate, mode, k, tau, k_cap, idx, count):
-    st = _native.select(shape, util, gate, mode, k, tau, k_cap, idx, count) if _lib else None
+    st = _native.select(shape, util, gate, mode, k, tau, k_cap, idx, count) if _native else None
     if st is None:
         st = lib().kvev_select(ctypes.byref(shape), _ptr(util), _ptr(gate), mode, k, float(tau), k_cap,
                                _ptr(idx), _ptr(count), _stream())
@@ -253,7 +265,7 @@ def kvev_select(shape: Shape, util, gate, mode, k, tau, k_cap, idx, count):
 
 
 def kvev_gated_attention(shape: Shape, Q, Tq, K, V, Kbar, Vbar, idx, count, k_cap, O, ws=None, causal=0):
-    st = _native.gated_attention(shape, Q, Tq, K, V, Kbar, Vbar, idx, count, k_cap, O, ws, causal) if _lib else None
+    st = _native.gated_attention(shape, Q, Tq, K, V, Kbar, Vbar, idx, count, k_cap, O, ws, causal) if _native else None
     if st is None:
         st = lib().kvev_gated_attention(ctypes.byref(shape), _ptr(Q), Tq, _ptr(K), _ptr(V), _ptr(Kbar),
                                         _ptr(Vbar), _ptr(idx), _ptr(count), k_cap, causal, _ptr(O), _ptr(ws),
@@ -269,7 +281,7 @@ def kvev_gated_attention_static(shape: Shape, Q, Tq, K, V, Kbar, Vbar, idx, coun
 
 
 def kvev_dense_attention(shape: Shape, Q, Tq, K, V, O, ws=None, causal=0):
-    st = _native.dense_attention(shape, Q, Tq, K, V, O, ws, causal) if _lib else None
+    st = _native.dense_attention(shape, Q, Tq, K, V, O, ws, causal) if _native else None
     if st is None:
         st = lib().kvev_dense_attention(ctypes.byref(shape), _ptr(Q), Tq, _ptr(K), _ptr(V), causal, _ptr(O),
                                         _ptr(ws), ws.numel() if ws is not None else 0, _stream())
@@ -280,7 +292,7 @@ def kvev_dense_attention(shape: Shape, Q, Tq, K, V, O, ws=None, causal=0):
 def kvev_retain(shape: Shape, k, k_cap, Kbar_new, Vbar_new, util_new, n_new_cap, first_chunk, n_new, Kc, Vc,
                 chunk_id, util_c, count):
     st = _native.retain(shape, k, k_cap, Kbar_new, Vbar_new, util_new, n_new_cap, first_chunk, n_new, Kc, Vc,
-                              chunk_id, util_c, count) if _lib else None
+                              chunk_id, util_c, count) if _native else None
     if st is None:
         st = lib().kvev_retain(ctypes.byref(shape), k, k_cap, _ptr(Kbar_new), _ptr(Vbar_new), _ptr(util_new),
                                n_new_cap, first_chunk, n_new, _ptr(Kc), _ptr(Vc), _ptr(chunk_id), _ptr(util_c),
@@ -290,7 +302,7 @@ def kvev_retain(shape: Shape, k, k_cap, Kbar_new, Vbar_new, util_new, n_new_cap,
 
 
 def kvev_compact_attention(shape: Shape, Q, Tq, Kw, Vw, Kc, Vc, count, k_cap, O, ws=None, causal=0, win_first=0):
-    st = _native.compact_attention(shape, Q, Tq, Kw, Vw, Kc, Vc, count, k_cap, O, ws, causal, win_first) if _lib else None
+    st = _native.compact_attention(shape, Q, Tq, Kw, Vw, Kc, Vc, count, k_cap, O, ws, causal, win_first) if _native else None
     if st is None:
         st = lib().kvev_compact_attention(ctypes.byref(shape), _ptr(Q), Tq, _ptr(Kw), _ptr(Vw), win_first, _ptr(Kc), _ptr(Vc),
                                           _ptr(count), k_cap, causal, _ptr(O), _ptr(ws),

@@ -2,8 +2,9 @@
 
 Run as ``python -m paper_2509_21354_amd.build`` (add ``--force`` to recompile
 everything).  Objects go to ``_build/`` next to this file; the shared library
-and the extension module ``_native.so`` (marshalling, built with g++) stay
-in-tree next to the sources so that they travel with the checkout.
+and the extension module ``_native`` (marshalling, built with g++; optional:
+without it calls go through ctypes) stay in-tree next to the sources so that
+they travel with the checkout.
 """
 from __future__ import annotations
 
@@ -18,7 +19,8 @@ _HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(_HERE, "csrc")
 OBJ_DIR = os.path.join(_HERE, "_build")
 LIB_PATH = os.path.join(_HERE, "libkvev.so")
-NATIVE_PATH = os.path.join(_HERE, "_native.so")      # CPython module: marshalling of calls into the library
+# CPython module: marshalling of calls into the library (its name says which Python it is for)
+NATIVE_PATH = os.path.join(_HERE, "_native" + sysconfig.get_config_var("EXT_SUFFIX"))
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 CXX = os.environ.get("CXX", "g++")
@@ -47,6 +49,19 @@ def _compile(src: str, obj: str) -> str:
     return "\n".join(line for line in r.stderr.splitlines() if noise not in line)
 
 
+def _build_native(force: bool, hdr: float) -> None:
+    src = os.path.join(CSRC, "native_call.cpp")
+    if not force and os.path.exists(NATIVE_PATH) and os.path.getmtime(NATIVE_PATH) >= max(os.path.getmtime(src), hdr):
+        return
+    cmd = [CXX, "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-I", sysconfig.get_paths()["include"], src, "-o", NATIVE_PATH]
+    try:
+        subprocess.run(cmd, check=True, capture_output=True, text=True)
+    except (OSError, subprocess.CalledProcessError) as e:
+        if os.path.exists(NATIVE_PATH):          # (an old one may not fit the library)
+            os.remove(NATIVE_PATH)
+        print(f"the marshalling extension is not built, calls will go through ctypes: {e}\n{getattr(e, 'stderr', '')}", file=sys.stderr)
+
+
 def build(force: bool = False, verbose: bool = False) -> str:
     os.makedirs(OBJ_DIR, exist_ok=True)
     hdr = _headers_mtime()
@@ -61,10 +76,7 @@ def build(force: bool = False, verbose: bool = False) -> str:
         for warn in ex.map(lambda j: _compile(*j), jobs):
             if warn.strip() and verbose:
                 print(warn, file=sys.stderr)
-    native = os.path.join(CSRC, "native_call.cpp")
-    if force or not os.path.exists(NATIVE_PATH) or os.path.getmtime(NATIVE_PATH) < max(os.path.getmtime(native), hdr):
-        subprocess.check_call([CXX, "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-I", sysconfig.get_paths()["include"], native,
-                               "-o", NATIVE_PATH])
+    _build_native(force, hdr)
     if jobs or not os.path.exists(LIB_PATH):
         subprocess.check_call([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB_PATH, *objs])
     return LIB_PATH

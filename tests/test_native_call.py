@@ -2,13 +2,16 @@
 sees, and nothing is left behind by a call that fails on the way."""
 import ctypes
 import os
+import shutil
 import subprocess
 import sys
+import sysconfig
 
 import pytest
 import torch
 
 from paper_2509_21354_amd import binding as kb
+from paper_2509_21354_amd import build as kvev_build
 
 
 def _args(**kw):
@@ -97,3 +100,59 @@ def test_a_forked_child_is_refused():
         finally:
             os._exit(code)
     assert os.waitpid(pid, 0)[1] == 0
+
+
+WITHOUT = """
+import ctypes, os, sys, warnings
+warnings.simplefilter("error" if {quiet} else "always")
+from paper_2509_21354_amd import binding as kb
+assert os.path.dirname(kb.__file__) == {where!r}
+{between}
+sh = kb.make_shape(L=1, B=1, H=1, d=64, T=8, T_cap=8, C=4, N_cap=2, W=4, d_sum=32, d_g=64, dtype=kb.BF16, H_kv=0)
+assert kb.workspace_bytes(kb.OP_LSTM_GATE, sh, 2) > 0
+print("native" if kb._native else "ctypes")
+"""
+
+
+def _package_without_extension(tmp_path):
+    where = tmp_path / "paper_2509_21354_amd"
+    where.mkdir()
+    for name in ("__init__.py", "binding.py", "build.py", "synth.py", "cost_model.py", "libkvev.so"):
+        shutil.copy(os.path.join(os.path.dirname(kb.__file__), name), where / name)
+    return where
+
+
+def _child(where, between="", quiet=True):
+    code = WITHOUT.format(where=str(where), between=between, quiet=quiet)
+    r = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, cwd=where.parent)
+    assert r.returncode == 0, r.stderr[-2000:]
+    return r.stdout.strip(), r.stderr
+
+
+def test_the_library_works_without_the_extension(tmp_path):
+    assert _child(_package_without_extension(tmp_path))[0] == "ctypes"
+
+
+def test_an_extension_built_after_the_import_is_taken(tmp_path):
+    where = _package_without_extension(tmp_path)
+    assert _child(where, f"import shutil; shutil.copy({kvev_build.NATIVE_PATH!r}, {str(where)!r})")[0] == "native"
+
+
+def test_an_extension_that_does_not_load_is_named(tmp_path):
+    where = _package_without_extension(tmp_path)
+    (where / os.path.basename(kvev_build.NATIVE_PATH)).write_bytes(b"no shared object")
+    out, err = _child(where, quiet=False)
+    assert out == "ctypes" and "does not load" in err
+
+
+def test_build_goes_on_without_a_host_compiler(tmp_path, monkeypatch, capsys):
+    stale = tmp_path / os.path.basename(kvev_build.NATIVE_PATH)
+    stale.write_bytes(b"old")
+    monkeypatch.setattr(kvev_build, "NATIVE_PATH", str(stale))
+    monkeypatch.setattr(kvev_build, "CXX", str(tmp_path / "no-such-compiler"))
+    kvev_build._build_native(True, 0.0)
+    assert not stale.exists() and "ctypes" in capsys.readouterr().err
+
+
+def test_the_extension_is_named_for_its_python():
+    assert kvev_build.NATIVE_PATH.endswith(sysconfig.get_config_var("EXT_SUFFIX"))
