@@ -124,8 +124,13 @@ int kvev_chunk_pool(const kvev_shape *shape, const void *K, const void *V, int p
  * compute unit a group of 32 sequences, and with d_g = 512, more than 16
  * sequences per layer and either more than one group of 16 sequences per 8
  * compute units or N_cap < 16, run as one kernel (at d_g = 512 once per compute
- * units / 4 groups of 32 sequences) and keep no projections at all.  (At d_g =
- * 512 a workspace of that size is accepted below that number of groups too.)  Calls that share a workspace
+ * units / 4 groups of 32 sequences) and keep no projections at all.  At d_g =
+ * 512 a call below that number of groups does the same when its workspace holds
+ * fewer than 6 or 12 steps of projections (the query answers at least those):
+ * its other form would be the slower one.  (A caller with 129 sequences or more
+ * that gates one or two chunks per call gains from such a workspace, e.g. the
+ * answer for N_cap = 15.)  A run cut into calls keeps its bits as long as the
+ * workspace's size stays the same.  Calls that share a workspace
  * must not overlap (it also carries what the workgroups of one launch
  * exchange).
  * Status word: the first int32 of the workspace.  Small launches (bf16; d_g =

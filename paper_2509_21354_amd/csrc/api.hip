@@ -323,6 +323,8 @@ static int lstm_quad_groups()
     const int forced = g_lstm_quad_groups.load(), fit = device_compute_units() / 4;
     return forced > 0 && forced < fit ? forced : (fit > 0 ? fit : 1);
 }
+// the fewest steps that scratch has to hold for the eight-workgroup form
+static size_t lstm_oct_steps(const kvev_shape *sh) { return lstm_oct_min_block(sh->L, sh->B * kv_heads(sh), device_compute_units()); }
 static size_t lstm_exch_bytes(const kvev_shape *sh)
 {
     return lstm_split_exch_bytes(lstm_split_of(sh), sh->d_g, sh->L, sh->B * kv_heads(sh), lstm_quad_groups());
@@ -349,8 +351,8 @@ struct LstmPlan { int split, block; size_t pack, exch_bytes; };
 static LstmPlan lstm_plan(const kvev_shape *sh, bool prepared, int steps, size_t ws_bytes)
 {
     kvev_shape small = *sh;
-    // scratch of the size that quadruples need, which keep no projections, stays accepted, and takes them
-    if (lstm_split_of(sh) == 8 && ws_bytes < lstm_ws_pack(sh, prepared) + lstm_ws_per_step(sh)) {
+    // scratch for fewer steps takes quadruples, which keep no projections
+    if (lstm_split_of(sh) == 8 && ws_bytes < lstm_ws_pack(sh, prepared) + lstm_ws_per_step(sh) * lstm_oct_steps(sh)) {
         small.N_cap = 0;
         sh = &small;
     }
@@ -655,7 +657,8 @@ size_t kvev_workspace_bytes(int op, const kvev_shape *sh, int n, int k_cap)
     case KVEV_OP_LSTM_GATE:
     case KVEV_OP_LSTM_GATE_PREPARED: {
         if (!lstm_takes_mfma(sh)) return 0;
-        const int tb = n < 1 ? 1 : n < 128 ? n : 128;
+        // (at least what the eight-workgroup form asks for where it applies, so that the form is the same whatever n)
+        const int tb = std::max(n < 128 ? n : 128, lstm_split_of(sh) == 8 ? (int)lstm_oct_steps(sh) : 1);
         auto need = [&](const kvev_shape *s) { return lstm_ws_pack(s, op == KVEV_OP_LSTM_GATE_PREPARED) + lstm_ws_per_step(s) * (size_t)tb; };
         // (one query serves caches of every capacity: the short ones take other forms, see lstm_split)
         kvev_shape small = *sh;

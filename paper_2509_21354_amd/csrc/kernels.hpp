@@ -79,10 +79,18 @@ struct LstmArgs {
 // takes at most one workgroup per compute unit, larger calls are cut into several launches.  So all workgroups of a
 // launch can be resident together on an idle device (bounded waits in the kernels cover the rest).
 // Eight (lstm_oct.hip): at d_g = 512 while eight workgroups per 16 sequences fit the chip, which keeps all of W_hh in
-// registers; up to there it is the faster one whatever the sequences per layer (512 x 64 steps 341 against 570 us, 16 a layer 387
+// registers; up to there it is the faster one whatever the sequences per layer (512 x 64 steps 361 against 570 us, 16 a layer 392
 // against 910; 1024 in two launches 730 against 579, so it ends there).  Caches of fewer than kLstmOctMinChunks chunks keep the
-// others, which need no scratch for projections (8 KiB per sequence and step): 8 steps of 512 sequences take 80 against 91 us, a
-// difference that such a cache pays only once or twice.
+// others, which need no scratch for projections (8 KiB per sequence and step): 512 sequences x 8 steps take 77 us on four
+// workgroups and 69 on eight, a difference that such a cache pays only once or twice.
+// Its launches begin with all of W_hh from memory, so the form depends on the steps that the scratch holds as well; not on the
+// steps of a call, so that a run cut into calls keeps its bits.  (What that costs: calls of 1 and 4 steps of 512 sequences
+// take 23 and 46 us, four workgroups 18 and 44; one step of 15 layers of 17 sequences 33 and 22, of 256 in one layer 18.6 and
+// 17.9; with 128 sequences and fewer it is the faster one.  A caller of such steps passes less scratch.)
+// lstm_oct_min_block: the fewest steps per launch with which it is no slower than the kernel on four workgroups.  48 steps, four
+// workgroups against eight with scratch for 4, 6, 8, 10 and 12 steps, us: d = 64, 512 sequences 377, eight 601 477 415 386 354;
+// 15 layers of 17 433, 628 517 458 424 380; 8 layers of 32 376, 410 324 280; 256 in one 364, 363 304 291; d = 128, 512 434, 606
+// 500 430 405 369, 8 layers of 32 430, 442 345.  Where pairs are the other form (at most 16 sequences a layer) it wins with any.
 constexpr size_t kLstmPairExchBytes256 = 65536;     // scratch per group of 16 sequences and 256 hidden units
 constexpr int kLstmOctMinChunks = 16;
 constexpr size_t kLstmOctExchBytes512 = 32768;      // scratch per 8 sequences at d_g = 512 on eight workgroups
@@ -94,6 +102,10 @@ inline int lstm_split(int d_g, int L, int BH, int N_cap, int compute_units, bool
     if (d_g == 512 && quad_allowed && BH > 16 && compute_units >= 4) return 4;     // (more groups than fit at once: several launches)
     if ((d_g == 256 || d_g == 512) && 2 * g16 <= compute_units) return 2;
     return 0;
+}
+inline int lstm_oct_min_block(int L, int BH, int compute_units)
+{
+    return BH <= 16 ? 1 : 8ll * L * ((BH + 7) / 8) <= compute_units ? 6 : 12;
 }
 // At d_g = 256, launches that fit the chip with two workgroups per 8 sequences take lstm_rec_oct_kernel (four per 8 or per 4 where
 // that fits too): 1024 sequences x 64 steps 224 us against 245 us on pairs per 16; above, the pairs remain.

@@ -41,3 +41,18 @@ def test_scratch_serves_caches_of_other_capacities(L, BH, n, prepared):
         nbytes = kb.workspace_bytes(op, _shape(512, L, BH, asked), n)
         for used in (1, 15, 16, 256):
             assert kb.kvev_debug_lstm_plan(_shape(512, L, BH, used), prepared, used, nbytes)[1] >= min(n, used)
+
+
+@pytest.mark.parametrize("L,BH,least", [(1, 512, 12), (15, 17, 12), (2, 256, 12), (1, 256, 6), (8, 32, 6), (1, 17, 6), (1, 16, 1), (32, 16, 1)])
+def test_eight_workgroups_take_scratch_of_a_useful_block(L, BH, least):
+    """d_g = 512: the form that begins every launch with all of W_hh from memory is taken when the scratch holds enough steps per
+    launch, whatever the steps of a call; with less, four workgroups in one launch.  The query always answers enough."""
+    sh = _shape(512, L, BH, N_cap=256)
+    groups = L * ((BH + 15) // 16)
+    fixed, step = 256 + groups * 65536, groups * 131072
+    for steps in (1, 5, 64):
+        for held in (1, 2, 5, 6, 11, 12, 64):
+            workgroups, block = kb.kvev_debug_lstm_plan(sh, True, steps, fixed + held * step)
+            assert (workgroups, block) == ((8, min(held, steps)) if held >= least else (4, steps))
+    for n in (0, 1, 2, 8, 64):
+        assert kb.kvev_debug_lstm_plan(sh, True, 64, kb.workspace_bytes(kb.OP_LSTM_GATE_PREPARED, sh, n))[0] == 8
