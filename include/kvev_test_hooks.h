@@ -44,6 +44,10 @@ int kvev_debug_lstm_quad_groups(int groups);
  * (0: the scratch is refused).  No GPU is needed.  Errors: INVALID_ARG. */
 int kvev_debug_lstm_plan(const kvev_shape *shape, int prepared, int steps, size_t ws_bytes, int *workgroups, int *block);
 
+/* The same for the shapes that go to the fp32-arithmetic gate: 0 = up to 64 units, projections a block ahead; 1, 2 = one or four
+ * sequences per workgroup; 3 = one, rows of up to 192 units in registers as pairs.  No GPU is needed.  Errors: INVALID_ARG. */
+int kvev_debug_lstm_form(const kvev_shape *shape, int steps, int *form);
+
 /* The single-query attention kernels read their rows with the non-temporal hint
  * when a launch reads more than `bytes` (default 256 MiB, what the memory-side
  * cache holds; 0 restores the default).  Lowering it to 1 lets a parity test run

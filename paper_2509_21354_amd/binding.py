@@ -35,7 +35,7 @@ EXPORTS = ("kvev_chunk_pool", "kvev_lstm_gate", "kvev_lstm_prepare", "kvev_lstm_
            "kvev_gated_attention_static", "kvev_dense_attention", "kvev_retain", "kvev_compact_attention", "kvev_workspace_bytes",
            "kvev_status_string", "kvev_last_hip_error", "kvev_version")
 TEST_HOOKS = ("kvev_debug_pair_wait", "kvev_debug_lstm_fused_min_groups", "kvev_debug_lstm_quad_groups", "kvev_debug_stream_probe",
-              "kvev_debug_attn_stream_bytes", "kvev_debug_lstm_plan")      # include/kvev_test_hooks.h
+              "kvev_debug_attn_stream_bytes", "kvev_debug_lstm_plan", "kvev_debug_lstm_form")      # include/kvev_test_hooks.h
 
 
 class Shape(ctypes.Structure):
@@ -107,6 +107,8 @@ def lib() -> ctypes.CDLL:
         L.kvev_debug_lstm_fused_min_groups.restype = ci
         L.kvev_debug_lstm_quad_groups.argtypes = [ci]
         L.kvev_debug_lstm_quad_groups.restype = ci
+        L.kvev_debug_lstm_form.argtypes = [shp, ci, ctypes.POINTER(ci)]
+        L.kvev_debug_lstm_form.restype = ci
         L.kvev_debug_lstm_plan.argtypes = [shp, ci, ci, sz, ctypes.POINTER(ci), ctypes.POINTER(ci)]
         L.kvev_debug_lstm_plan.restype = ci
         L.kvev_debug_stream_probe.argtypes = [vp, sz, ci, vp, sz, ci, ci, vp]
@@ -187,6 +189,12 @@ def kvev_debug_lstm_plan(shape: Shape, prepared: bool, steps: int, ws_bytes: int
     st = lib().kvev_debug_lstm_plan(ctypes.byref(shape), int(prepared), steps, ws_bytes, ctypes.byref(workgroups), ctypes.byref(block))
     _check(st, "kvev_debug_lstm_plan")
     return workgroups.value, block.value
+
+
+def kvev_debug_lstm_form(shape: Shape, steps: int) -> str:
+    form = ctypes.c_int()
+    _check(lib().kvev_debug_lstm_form(ctypes.byref(shape), steps, ctypes.byref(form)), "kvev_debug_lstm_form")
+    return ("chain", "one", "four", "kept")[form.value]
 
 
 def kvev_debug_lstm_fused_min_groups(min_groups: int = 0) -> None:

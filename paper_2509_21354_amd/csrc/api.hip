@@ -619,6 +619,16 @@ int kvev_debug_lstm_plan(const kvev_shape *sh, int prepared, int steps, size_t w
     return KVEV_OK;
 }
 
+int kvev_debug_lstm_form(const kvev_shape *sh, int steps, int *form)
+{
+    if (check_shape(sh) != KVEV_OK || steps < 1 || !form || lstm_takes_mfma(sh)) return KVEV_ERR_INVALID_ARG;
+    LstmArgs a;
+    memset(&a, 0, sizeof a);
+    a.L = sh->L; a.BH = sh->B * kv_heads(sh); a.d = sh->d; a.d_g = sh->d_g; a.c1 = steps; a.compute_units = device_compute_units();
+    *form = (int)lstm_generic_form(a, sh->dtype);
+    return KVEV_OK;
+}
+
 int kvev_debug_lstm_quad_groups(int groups)
 {
     if (groups < 0) return KVEV_ERR_INVALID_ARG;

@@ -271,7 +271,8 @@ template <int N, class F> __device__ __forceinline__ void rows_fold(float (&v)[N
 __device__ __forceinline__ int rows_value(int i, int row) { return 4 * i + 2 * (row >> 1) + (row & 1); }
 
 // The sums over 16 lanes of four values at once: lane q (mod 4) receives the sum of v[value_of_lane(q)].
-// (every exchange halves the values a lane still carries: 4 -> 2 -> 1, then the four quads are added)
+// (every exchange halves the values a lane still carries: 4 -> 2 -> 1, then the four quads are added: those eight lanes
+// apart first, in fold8 and fold16 too, so that a sum has the same bits whichever of them takes it)
 __device__ __forceinline__ int value_of_lane(int lane) { return ((lane & 1) << 1) | ((lane >> 1) & 1); }
 __device__ __forceinline__ float fold4(const float (&v)[4], int lane)
 {
@@ -279,8 +280,8 @@ __device__ __forceinline__ float fold4(const float (&v)[4], int lane)
     const float r0 = (b0 ? v[2] : v[0]) + dpp_move<kQuadXor1>(b0 ? v[0] : v[2]);
     const float r1 = (b0 ? v[3] : v[1]) + dpp_move<kQuadXor1>(b0 ? v[1] : v[3]);
     float q = (b1 ? r1 : r0) + dpp_move<kQuadXor2>(b1 ? r0 : r1);
-    q += dpp_move<kRowRor4>(q);
     q += dpp_move<kRowRor8>(q);
+    q += dpp_move<kRowRor4>(q);
     return q;
 }
 

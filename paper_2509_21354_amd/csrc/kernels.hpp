@@ -162,6 +162,10 @@ hipError_t launch_pool_mfma(const PoolArgs &a, hipStream_t st);          // bf16
 hipError_t launch_pool_token_mfma(const PoolArgs &a, hipStream_t st);    // bf16, the MLP on every token
 size_t pool_token_mfma_lds(int d, int d_sum);                            // its LDS need in bytes
 hipError_t launch_lstm_generic(const LstmArgs &a, int dtype, hipStream_t st);
+// its forms: up to 64 units, one sequence per workgroup with projections a block ahead; one or four sequences per workgroup (W_hh
+// in registers up to 128 units, else read every step); one, bf16 rows of up to 192 units in registers as pairs
+enum class LstmForm { chain, one, four, kept };
+LstmForm lstm_generic_form(const LstmArgs &a, int dtype);
 hipError_t launch_lstm_mfma(const LstmArgs &a, hipStream_t st);          // bf16
 hipError_t launch_lstm_prepare(const LstmArgs &a, hipStream_t st);       // bf16: the packed weights alone
 hipError_t launch_stream_probe(const void *src, size_t tiles, int tile_bytes, void *dst, int write_bytes, int hints, hipStream_t st);   // calibration

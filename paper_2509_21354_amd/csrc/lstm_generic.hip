@@ -21,8 +21,9 @@
 //     and up to 192 with bf16 storage, as the pairs that they are (two shifts and masks
 //     per pair and step; what bounds the streamed form there is its chain of dependent
 //     loads, of single elements where d_g is no multiple of 4: d_g = 163, 32 sequences x
-//     32 steps 586 -> 135 us, 512 x 32 1173 -> 276, 1024 x 32 770 (four a workgroup) ->
-//     549); wider gates read them from L2 every step, 16 bytes per lane;
+//     32 steps 586 -> 131 us, 512 x 32 1173 -> 262, 1024 x 32 772 (four a workgroup) ->
+//     521; short calls of many sequences keep the streamed form: see launch_t); wider
+//     gates read them from L2 every step, 16 bytes per lane;
 //   * the utility head runs after each block over the block's 16 states.
 // Measured (fp32, d_g = 64, d = 64, 4 sequences x 64 steps): 1346 us with one
 // row of W_ih and W_hh at a time per lane group, dependent loads from L2 in every
@@ -50,6 +51,40 @@ static int gen_tb(int d, int dg, int mb)
     int tb = kGenCols / mb;
     while (tb > 0 && gen_lds(d, dg, mb, tb) > kGenLdsMax) --tb;
     return tb;
+}
+
+// Four bf16 elements of R rows `pitch` elements apart, from each of k, k + 64, .. on, as the pairs that they are, zeros at and past n.
+// Rows that allow no wider load are read by the element, without a branch: all requests leave before the first is waited for.
+template <int R, int KC, bool VEC> __device__ __forceinline__ void load_pairs(const bf16_t *mat, uint32_t at, uint32_t pitch, int k, int n, float (*o)[KC][2])
+{
+    if constexpr (VEC) {
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+#pragma unroll
+            for (int c = 0; c < KC; ++c) {
+                const uint2 v = 64 * c + k < n ? *reinterpret_cast<const uint2 *>(mat + (at + r * pitch + 64 * c + k)) : make_uint2(0u, 0u);
+                o[r][c][0] = __uint_as_float(v.x);
+                o[r][c][1] = __uint_as_float(v.y);
+            }
+    } else {
+        uint32_t v[R][KC][4];
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+#pragma unroll
+            for (int c = 0; c < KC; ++c)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[r][c][e] = mat[at + r * pitch + (uint32_t)min(64 * c + k + e, n - 1)];
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+#pragma unroll
+            for (int c = 0; c < KC; ++c)
+#pragma unroll
+                for (int e = 0; e < 2; ++e) {
+                    const int j = 64 * c + k + 2 * e;
+                    o[r][c][e] = __uint_as_float((j < n ? v[r][c][2 * e] : 0u) | (j + 1 < n ? v[r][c][2 * e + 1] << 16 : 0u));
+                    asm volatile("" : "+v"(o[r][c][e]));         // (the pair is kept, not its elements until it is used)
+                }
+    }
 }
 
 // MB: sequences of one layer per workgroup.  RES: hidden units per lane group whose rows of W_hh stay in registers, KC
@@ -96,17 +131,15 @@ __global__ __launch_bounds__(kGenThreads, RES == 1 && MB == 1 ? 8 : 4) void lstm
 #pragma unroll
         for (int i = 0; i < RES; ++i) {
             const int u = min(grp + kGenThreads / 16 * i, dg - 1);
+            if constexpr (PACKED) {
+                load_pairs<2, KC, VEC>(W_hh, (uint32_t)u * dg, (uint32_t)dg * dg, 4 * cl, dg, w[i]);
+                load_pairs<2, KC, VEC>(W_hh, (uint32_t)(2 * dg + u) * dg, (uint32_t)dg * dg, 4 * cl, dg, w[i] + 2);
+            } else {
 #pragma unroll
-            for (int q = 0; q < 4; ++q)
+                for (int q = 0; q < 4; ++q)
 #pragma unroll
-                for (int c = 0; c < KC; ++c) {
-                    float v[4];
-                    load4<T, VEC>(W_hh + (size_t)(q * dg + u) * dg, 64 * c + 4 * cl, dg, v);
-#pragma unroll
-                    for (int e = 0; e < WN; ++e)
-                        w[i][q][c][e] = PACKED ? __uint_as_float(__float_as_uint(v[2 * e]) >> 16 | __float_as_uint(v[2 * e + 1 < 4 ? 2 * e + 1 : 3])) : v[e];
-                    if (PACKED) __builtin_amdgcn_sched_barrier(0);      // (not all of the matrix under way as single elements)
-                }
+                    for (int c = 0; c < KC; ++c) load4<T, VEC>(W_hh + (size_t)(q * dg + u) * dg, 64 * c + 4 * cl, dg, w[i][q][c]);
+            }
         }
     }
 
@@ -505,10 +538,10 @@ static hipError_t launch_v(const LstmArgs &a, hipStream_t st)
     return hipGetLastError();
 }
 
-template <typename T, int D>
-static hipError_t launch_t(const LstmArgs &a, hipStream_t st)
+LstmForm lstm_generic_form(const LstmArgs &a, int dtype)
 {
-    if ((size_t)a.L * a.BH == 0 || a.c1 == a.c0) return hipSuccess;
+    // (a workgroup takes a compute unit to itself: see lstm_chain_kernel)
+    if (a.d_g <= 64 && (long long)a.L * a.BH <= a.compute_units) return LstmForm::chain;
     // Launches that give every compute unit four sequences put four into a workgroup: W_ih, and W_hh where it is
     // streamed, are then read once for all of them, and the nonlinearities, which bound a full chip, are evaluated once
     // instead of in four quads.  (fp32, one against four per workgroup: 2048 sequences x 64
@@ -519,22 +552,40 @@ static hipError_t launch_t(const LstmArgs &a, hipStream_t st)
     // 384 sequences, fp32, d_g = 256, once one each until 1024: 718 -> 629 us; 512 x 16 steps at d_g = 512 1365 -> 1000.
     const long long rounds1 = ((long long)a.L * a.BH + a.compute_units - 1) / a.compute_units;
     const long long rounds4 = ((long long)a.L * ((a.BH + 3) / 4) + a.compute_units - 1) / a.compute_units;
+    const bool aligned = a.d_g % 4 == 0;
+    if (dtype == KVEV_BF16 && a.d_g > 128 && a.d_g <= 192) {
+        // Rows kept in registers, one sequence each (four take more registers than there are beside the rows), or read every step by
+        // one or four: by their times for a round of the chip, start and steps, in steps of the first (2.9 us at d_g = 163).  They
+        // add in the same order, so that a run cut into calls keeps its bits.  Kept / read, us, d = 128: aligned rows (d_g = 164) 32
+        // sequences x 1 step 29.8 / 31.2, 1024 x 1 116 / 34 (by four), x 8 175 / 111, x 32 469 / 432; single elements (163) 32 x 1
+        // 43 / 41, x 2 45 / 58, 1024 x 1 168 / 44, x 8 228 / 196, x 32 521 / 772.
+        const long long n = a.c1 - a.c0, kept = rounds1 * ((aligned ? 9 : 14) + n);
+        const long long one = rounds1 * (8 + (aligned ? 3 : 6) * n), four = rounds4 * (7 + (aligned ? 4 : 8) * n);
+        return kept <= (one < four ? one : four) ? LstmForm::kept : one <= four ? LstmForm::one : LstmForm::four;
+    }
     // (Of many layers of one sequence each there is nothing to share: 300, fp32, d_g = 200 1521 -> 1065; of two it still pays to read
     // each layer's weights once: bf16 1578, one each 1854.)
     const bool chip = (long long)a.L * ((a.BH + 3) / 4) >= a.compute_units;
-    const bool rounds = rounds1 >= 2 * rounds4 + (a.d_g < 192 && a.d_g % 4 == 0 ? 1 : 0);
-    const bool four = (a.d_g <= 128 ? chip : rounds || (chip && a.BH > 1)) && gen_tb(D, a.d_g, 4) > 0;
-    // (a workgroup takes a compute unit to itself: see lstm_chain_kernel)
-    if (a.d_g <= 64 && (long long)a.L * a.BH <= a.compute_units) {
+    const bool rounds = rounds1 >= 2 * rounds4 + (a.d_g < 192 && aligned ? 1 : 0);
+    const bool four = (a.d_g <= 128 ? chip : rounds || (chip && a.BH > 1)) && gen_tb(a.d, a.d_g, 4) > 0;
+    return four ? LstmForm::four : LstmForm::one;
+}
+
+template <typename T, int D>
+static hipError_t launch_t(const LstmArgs &a, hipStream_t st)
+{
+    if ((size_t)a.L * a.BH == 0 || a.c1 == a.c0) return hipSuccess;
+    const LstmForm form = lstm_generic_form(a, sizeof(T) == 2 ? KVEV_BF16 : KVEV_F32);
+    const bool four = form == LstmForm::four;
+    if (form == LstmForm::chain) {
         hipLaunchKernelGGL((lstm_chain_kernel<T, D>), dim3((unsigned)((size_t)a.L * a.BH)), dim3(512), 0, st, a);
         return hipGetLastError();
     }
+    if constexpr (sizeof(T) == 2) {
+        if (form == LstmForm::kept) return launch_v<T, D, 1, 3, 3>(a, st);
+    }
     if (a.d_g <= 64) return four ? launch_v<T, D, 4, 1, 1>(a, st) : launch_v<T, D, 1, 1, 1>(a, st);
     if (a.d_g <= 128) return four ? launch_v<T, D, 4, 2, 2>(a, st) : launch_v<T, D, 1, 2, 2>(a, st);
-    if constexpr (sizeof(T) == 2) {
-        // (one sequence each at any number of them: four take more registers than there are beside the rows)
-        if (a.d_g <= 192) return launch_v<T, D, 1, 3, 3>(a, st);
-    }
     return four ? launch_v<T, D, 4, 0, 1>(a, st) : launch_v<T, D, 1, 0, 1>(a, st);
 }
 

@@ -22,6 +22,8 @@ CASES = [
     (base._cfg(428, "bf16", d=128, C=8, d_g=200, L=1, B=1, H=257), 17),    # ... four, the last workgroup with one
     (base._cfg(429, "f32", d=64, C=8, d_g=130, L=1, B=8, H=32), 5),        # a sequence for every compute unit
     (base._cfg(430, "f32", d=128, C=8, d_g=129, L=3, B=2, H=43), 5),       # 258 sequences, the last of a layer's workgroups with two
+    (base._cfg(434, "bf16", d=64, C=8, d_g=163, L=1, B=1, H=1030), 40),   # a call of all steps keeps its rows, one of a single step reads them for four
+    (base._cfg(435, "bf16", d=128, C=8, d_g=164, L=2, B=3, H=100), 40),    # the same at rows of whole groups of four
     (base._cfg(432, "f32", d=64, C=8, d_g=132, L=3, B=3, H=57), 5),        # 513: four a workgroup at aligned rows too, the last with three
 ]
 

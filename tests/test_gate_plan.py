@@ -56,3 +56,15 @@ def test_eight_workgroups_take_scratch_of_a_useful_block(L, BH, least):
             assert (workgroups, block) == ((8, min(held, steps)) if held >= least else (4, steps))
     for n in (0, 1, 2, 8, 64):
         assert kb.kvev_debug_lstm_plan(sh, True, 64, kb.workspace_bytes(kb.OP_LSTM_GATE_PREPARED, sh, n))[0] == 8
+
+
+@pytest.mark.parametrize("d_g,L,BH,steps,form", [
+    (164, 1, 32, 1, "kept"), (164, 1, 32, 100, "kept"), (164, 1, 512, 1, "four"), (164, 1, 512, 32, "kept"), (164, 1, 1024, 32, "four"),
+    (192, 1, 8192, 1, "four"), (192, 1, 8192, 500, "four"), (160, 300, 2, 1, "four"), (160, 300, 2, 8, "kept"), (160, 1024, 1, 1, "kept"),
+    (163, 1, 32, 1, "one"), (163, 1, 32, 2, "kept"), (163, 1, 512, 1, "four"), (163, 1, 512, 8, "kept"), (163, 1, 1024, 8, "four"),
+    (163, 1, 1024, 32, "kept"), (129, 1, 8192, 2, "four"), (163, 300, 1, 8, "kept"), (193, 1, 32, 8, "one"), (200, 1, 512, 8, "four")])
+def test_rows_are_kept_where_there_are_steps_to_pay_for_it(d_g, L, BH, steps, form):
+    """bf16, 129 to 192 units: a workgroup that keeps its rows in registers serves one sequence and starts with all of them; short
+    calls of many sequences read them every step for four."""
+    sh = kb.make_shape(L=L, B=1, H=BH, d=128, T=512, T_cap=512, C=1, N_cap=512, W=0, d_sum=32, d_g=d_g, dtype=kb.BF16, H_kv=0)
+    assert kb.kvev_debug_lstm_form(sh, steps) == form
