@@ -48,6 +48,11 @@ int kvev_debug_lstm_plan(const kvev_shape *shape, int prepared, int steps, size_
  * sequences per workgroup; 3 = one, rows of up to 192 units in registers as pairs.  No GPU is needed.  Errors: INVALID_ARG. */
 int kvev_debug_lstm_form(const kvev_shape *shape, int steps, int *form);
 
+/* How kvev_chunk_pool runs `chunks` chunks of a shape that goes to the matrix cores (pool_mode MEAN, MLP or MAX), with or without
+ * scratch: 0 = 16 waves on one tile at a time; 1, 2 = persistent workgroups, MLP weights as given or re-laid first.  No GPU is
+ * needed.  Errors: INVALID_ARG. */
+int kvev_debug_pool_form(const kvev_shape *shape, int pool_mode, int chunks, int scratch, int *form);
+
 /* The single-query attention kernels read their rows with the non-temporal hint
  * when a launch reads more than `bytes` (default 256 MiB, what the memory-side
  * cache holds; 0 restores the default).  Lowering it to 1 lets a parity test run

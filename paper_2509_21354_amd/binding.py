@@ -35,7 +35,8 @@ EXPORTS = ("kvev_chunk_pool", "kvev_lstm_gate", "kvev_lstm_prepare", "kvev_lstm_
            "kvev_gated_attention_static", "kvev_dense_attention", "kvev_retain", "kvev_compact_attention", "kvev_workspace_bytes",
            "kvev_status_string", "kvev_last_hip_error", "kvev_version")
 TEST_HOOKS = ("kvev_debug_pair_wait", "kvev_debug_lstm_fused_min_groups", "kvev_debug_lstm_quad_groups", "kvev_debug_stream_probe",
-              "kvev_debug_attn_stream_bytes", "kvev_debug_lstm_plan", "kvev_debug_lstm_form")      # include/kvev_test_hooks.h
+              "kvev_debug_attn_stream_bytes", "kvev_debug_lstm_plan", "kvev_debug_lstm_form",
+              "kvev_debug_pool_form")      # include/kvev_test_hooks.h
 
 
 class Shape(ctypes.Structure):
@@ -107,6 +108,8 @@ def lib() -> ctypes.CDLL:
         L.kvev_debug_lstm_fused_min_groups.restype = ci
         L.kvev_debug_lstm_quad_groups.argtypes = [ci]
         L.kvev_debug_lstm_quad_groups.restype = ci
+        L.kvev_debug_pool_form.argtypes = [shp, ci, ci, ci, ctypes.POINTER(ci)]
+        L.kvev_debug_pool_form.restype = ci
         L.kvev_debug_lstm_form.argtypes = [shp, ci, ctypes.POINTER(ci)]
         L.kvev_debug_lstm_form.restype = ci
         L.kvev_debug_lstm_plan.argtypes = [shp, ci, ci, sz, ctypes.POINTER(ci), ctypes.POINTER(ci)]
@@ -193,8 +196,14 @@ def kvev_debug_lstm_plan(shape: Shape, prepared: bool, steps: int, ws_bytes: int
 
 def kvev_debug_lstm_form(shape: Shape, steps: int) -> str:
     form = ctypes.c_int()
-    _check(lib().kvev_debug_lstm_form(ctypes.byref(shape), steps, ctypes.byref(form)), "kvev_debug_lstm_form")
+    _check(lib().kvev_debug_lstm_form(ctypes.byref(shape), steps, ctypes.byref(form)), "kvev_debug_lstm_form", "kvev_debug_pool_form")
     return ("chain", "one", "four", "kept")[form.value]
+
+
+def kvev_debug_pool_form(shape: Shape, pool_mode: int, chunks: int, scratch: bool) -> str:
+    form = ctypes.c_int()
+    _check(lib().kvev_debug_pool_form(ctypes.byref(shape), pool_mode, chunks, int(scratch), ctypes.byref(form)), "kvev_debug_pool_form")
+    return ("one tile", "persistent", "packed")[form.value]
 
 
 def kvev_debug_lstm_fused_min_groups(min_groups: int = 0) -> None:

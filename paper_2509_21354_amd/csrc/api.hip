@@ -619,6 +619,19 @@ int kvev_debug_lstm_plan(const kvev_shape *sh, int prepared, int steps, size_t w
     return KVEV_OK;
 }
 
+int kvev_debug_pool_form(const kvev_shape *sh, int pool_mode, int chunks, int scratch, int *form)
+{
+    if (check_shape(sh) != KVEV_OK || pool_mode < KVEV_POOL_MEAN || pool_mode > KVEV_POOL_MAX || chunks < 1 || !form || !pool_takes_mfma(sh))
+        return KVEV_ERR_INVALID_ARG;
+    PoolArgs a;
+    memset(&a, 0, sizeof a);
+    a.L = sh->L; a.BH = sh->B * kv_heads(sh); a.d = sh->d; a.C = sh->C; a.d_sum = sh->d_sum; a.c1 = chunks; a.mode = pool_mode;
+    a.compute_units = device_compute_units();
+    a.wpack = scratch && pool_mode == KVEV_POOL_MLP ? &a : nullptr;
+    *form = (int)pool_mfma_form(a);
+    return KVEV_OK;
+}
+
 int kvev_debug_lstm_form(const kvev_shape *sh, int steps, int *form)
 {
     if (check_shape(sh) != KVEV_OK || steps < 1 || !form || lstm_takes_mfma(sh)) return KVEV_ERR_INVALID_ARG;

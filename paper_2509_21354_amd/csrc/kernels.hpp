@@ -159,6 +159,9 @@ hipError_t launch_select(const SelectArgs &a, hipStream_t st);
 hipError_t launch_retain(const RetainArgs &a, hipStream_t st);
 hipError_t launch_pool_generic(const PoolArgs &a, int dtype, hipStream_t st);
 hipError_t launch_pool_mfma(const PoolArgs &a, hipStream_t st);          // bf16
+// 16 waves on one tile at a time; workgroups that stay, with the MLP weights as given or re-laid in fragment order before
+enum class PoolForm { one_tile, persistent, persistent_packed };
+PoolForm pool_mfma_form(const PoolArgs &a);
 hipError_t launch_pool_token_mfma(const PoolArgs &a, hipStream_t st);    // bf16, the MLP on every token
 size_t pool_token_mfma_lds(int d, int d_sum);                            // its LDS need in bytes
 hipError_t launch_lstm_generic(const LstmArgs &a, int dtype, hipStream_t st);

@@ -465,13 +465,12 @@ template <int D> static int persistent_grid(size_t lds, int compute_units)
     return per_cu * compute_units;
 }
 
-hipError_t launch_pool_mfma(const PoolArgs &a, hipStream_t st)
+// tiles of 16 (sequence, chunk) rows: they never straddle layers
+static size_t pool_tiles(const PoolArgs &a) { return (size_t)a.L * (((size_t)a.BH * (a.c1 - a.c0) + 15) / 16); }
+
+PoolForm pool_mfma_form(const PoolArgs &a)
 {
-    const int nch = a.c1 - a.c0;
-    const size_t rows_per_layer = (size_t)a.BH * nch;
-    const size_t blocks = (size_t)a.L * ((rows_per_layer + 15) / 16);
-    if (blocks == 0) return hipSuccess;
-    const size_t lds = sizeof(bf16_t) * 3 * 2 * 16 * (((size_t)a.d + 8) + ((size_t)a.d_sum + 8));
+    const size_t blocks = pool_tiles(a);
     // Which form.  16 waves on one tile at a time have the most loads under way, but stand still while the MLP of the tile runs
     // (3.5 us, whatever the chunk); the persistent form covers it with another workgroup's rows and pays for that with a
     // longer start.  So it takes launches of 8 tiles per compute unit and more, and earlier the smaller the tile (the rows that
@@ -483,9 +482,23 @@ hipError_t launch_pool_mfma(const PoolArgs &a, hipStream_t st)
     const size_t tile_bytes = (size_t)16 * a.C * 2 * a.d * sizeof(bf16_t);
     const bool mlp = a.mode == KVEV_POOL_MLP, small = tile_bytes <= (size_t)128 << 10;
     const size_t enough = !mlp ? (small ? 1024 : 2048) : a.d_sum > 128 ? 2048 : small ? 513 : tile_bytes <= (size_t)256 << 10 ? 1280 : 2048;
-    const bool few = blocks < enough;
-    // launches that fill the chip many times over read the MLP weights in fragment order when the caller gave room for them
-    const bool pk = !few && a.mode == KVEV_POOL_MLP && a.wpack != nullptr;
+    if (blocks < enough) return PoolForm::one_tile;
+    // The persistent form reads the MLP weights in fragment order when the caller gave room for them and there are tiles enough to
+    // pay for the launch that re-lays those of all layers.  Re-laid / as given, us, d = d_sum = 128, C = 8: one layer 1024 tiles
+    // 36.9 / 37.5, 2016 60.6 / 65.6; 4 layers 1024 41.7 / 37.7, 1280 44.7 / 44.1, 1536 49.9 / 50.3; 8 layers 1024 42.4 / 37.9, 1536
+    // 51.5 / 50.9, 2016 62.3 / 66.3; 32 layers (16 waves 31.6, 43.5, 82.7) 640 34.2 / 29.4, 1024 47.0 / 42.6, 2016 70.3 / 69.2; C = 16
+    // 32 layers (16 waves 35.8, 50.6) 640 40.0 / 34.6, 1024 55.5 / 50.8; d_sum = 64 8 layers 1536 43.0 / 41.6, 2016 52.3 / 52.7.
+    const size_t border = a.d_sum <= 64 ? 1920 : std::min<size_t>(1024 + 128 * (size_t)std::max(a.L - 2, 0), 1920);
+    return mlp && a.wpack != nullptr && blocks >= border ? PoolForm::persistent_packed : PoolForm::persistent;
+}
+
+hipError_t launch_pool_mfma(const PoolArgs &a, hipStream_t st)
+{
+    const size_t blocks = pool_tiles(a);
+    if (blocks == 0) return hipSuccess;
+    const size_t lds = sizeof(bf16_t) * 3 * 2 * 16 * (((size_t)a.d + 8) + ((size_t)a.d_sum + 8));
+    const PoolForm form = pool_mfma_form(a);
+    const bool few = form == PoolForm::one_tile, pk = form == PoolForm::persistent_packed;
     if (pk) {
         const size_t pieces = pool_pack_bytes(a.L, a.d, a.d_sum) / 16;
         const dim3 pgrid((unsigned)((pieces + 255) / 256));

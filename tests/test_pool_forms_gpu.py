@@ -19,6 +19,7 @@ pytestmark = pytest.mark.gpu
     (64, 16, 9, 914, 32, kb.POOL_MLP),          # one k-step in the second layer
     (128, 16, 41, 400, 128, kb.POOL_MEAN),      # 1025
     (64, 8, 41, 400, 128, kb.POOL_MAX),
+    (128, 8, 41, 400, 128, kb.POOL_MLP),        # 1025: weights re-laid first
 ])
 def test_pooling_in_one_call_and_in_pieces(d, C, BH, N, d_sum, mode):
     cfg = base._cfg(501, "bf16", d=d, C=C, T=N * C, d_sum=d_sum, L=1, B=1, H=BH)
