@@ -53,6 +53,11 @@ int kvev_debug_lstm_form(const kvev_shape *shape, int steps, int *form);
  * needed.  Errors: INVALID_ARG. */
 int kvev_debug_pool_form(const kvev_shape *shape, int pool_mode, int chunks, int scratch, int *form);
 
+/* How many of the queries that share rows a workgroup of the vector kernel of kvev_gated_attention serves: 1, 2 or 4 (launches
+ * of many sequences may go to the matrix cores instead).  No GPU is needed.  Errors: INVALID_ARG, also for the query frames
+ * that always do. */
+int kvev_debug_decode_queries(const kvev_shape *shape, int Tq, int k_cap, int *queries);
+
 /* The single-query attention kernels read their rows with the non-temporal hint
  * when a launch reads more than `bytes` (default 256 MiB, what the memory-side
  * cache holds; 0 restores the default).  Lowering it to 1 lets a parity test run

@@ -36,7 +36,7 @@ EXPORTS = ("kvev_chunk_pool", "kvev_lstm_gate", "kvev_lstm_prepare", "kvev_lstm_
            "kvev_status_string", "kvev_last_hip_error", "kvev_version")
 TEST_HOOKS = ("kvev_debug_pair_wait", "kvev_debug_lstm_fused_min_groups", "kvev_debug_lstm_quad_groups", "kvev_debug_stream_probe",
               "kvev_debug_attn_stream_bytes", "kvev_debug_lstm_plan", "kvev_debug_lstm_form",
-              "kvev_debug_pool_form")      # include/kvev_test_hooks.h
+              "kvev_debug_pool_form", "kvev_debug_decode_queries")      # include/kvev_test_hooks.h
 
 
 class Shape(ctypes.Structure):
@@ -110,6 +110,8 @@ def lib() -> ctypes.CDLL:
         L.kvev_debug_lstm_quad_groups.restype = ci
         L.kvev_debug_pool_form.argtypes = [shp, ci, ci, ci, ctypes.POINTER(ci)]
         L.kvev_debug_pool_form.restype = ci
+        L.kvev_debug_decode_queries.argtypes = [shp, ci, ci, ctypes.POINTER(ci)]
+        L.kvev_debug_decode_queries.restype = ci
         L.kvev_debug_lstm_form.argtypes = [shp, ci, ctypes.POINTER(ci)]
         L.kvev_debug_lstm_form.restype = ci
         L.kvev_debug_lstm_plan.argtypes = [shp, ci, ci, sz, ctypes.POINTER(ci), ctypes.POINTER(ci)]
@@ -204,6 +206,12 @@ def kvev_debug_pool_form(shape: Shape, pool_mode: int, chunks: int, scratch: boo
     form = ctypes.c_int()
     _check(lib().kvev_debug_pool_form(ctypes.byref(shape), pool_mode, chunks, int(scratch), ctypes.byref(form)), "kvev_debug_pool_form")
     return ("one tile", "persistent", "packed")[form.value]
+
+
+def kvev_debug_decode_queries(shape: Shape, Tq: int, k_cap: int) -> int:
+    queries = ctypes.c_int()
+    _check(lib().kvev_debug_decode_queries(ctypes.byref(shape), Tq, k_cap, ctypes.byref(queries)), "kvev_debug_decode_queries")
+    return queries.value
 
 
 def kvev_debug_lstm_fused_min_groups(min_groups: int = 0) -> None:

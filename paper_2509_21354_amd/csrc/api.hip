@@ -230,7 +230,7 @@ static int attention_common(const kvev_shape *sh, const void *Q, int Tq, const v
     a.G = sh->H / kv_heads(sh); a.Hkv = kv_heads(sh); a.causal = causal;
     a.T = sh->T; a.T_cap = sh->T_cap; a.N_cap = compact ? k_cap : sh->N_cap; a.k_cap = k_cap;
     a.win0 = win0; a.ring_first = ring_first; a.gated = gated ? 1 : 0;
-    a.nsplit = p.nsplit; a.rows_per_split = p.rows_per_split; a.compute_units = device_compute_units();
+    a.nsplit = p.nsplit; a.rows_per_split = p.rows_per_split; a.rows_all = n_rows; a.compute_units = device_compute_units();
     // rows that no cache can hold until the next call are read with the streaming hint (256 MB: the memory-side cache)
     a.stream = (size_t)a.S * (size_t)n_rows * sh->d * 2 * (sh->dtype == KVEV_F32 ? 4 : 2) > g_stream_bytes.load(std::memory_order_relaxed) ? 1 : 0;
     a.scale_log2e = (float)(1.4426950408889634 / sqrt((double)sh->d));
@@ -616,6 +616,20 @@ int kvev_debug_lstm_plan(const kvev_shape *sh, int prepared, int steps, size_t w
     const LstmPlan plan = lstm_plan(sh, prepared != 0, steps, ws_bytes);
     *workgroups = plan.split;
     *block = plan.block;
+    return KVEV_OK;
+}
+
+int kvev_debug_decode_queries(const kvev_shape *sh, int Tq, int k_cap, int *queries)
+{
+    if (check_shape(sh) != KVEV_OK || Tq < 1 || k_cap < 0 || !queries || attn_takes_mq(sh, Tq)) return KVEV_ERR_INVALID_ARG;
+    const int ncand = n_cand_of(sh), raw = sh->T - ncand * sh->C;
+    const AttnPlan p = plan_attn(sh, Tq, raw);
+    AttnArgs a;
+    memset(&a, 0, sizeof a);
+    a.S = sh->L * sh->B * kv_heads(sh); a.Tq = Tq; a.d = sh->d; a.G = sh->H / kv_heads(sh);
+    a.nsplit = p.nsplit; a.rows_per_split = p.rows_per_split; a.rows_all = raw + std::min(k_cap, ncand);
+    a.compute_units = device_compute_units();
+    *queries = decode_queries(a, sh->dtype == KVEV_F32 ? 4 : 2);
     return KVEV_OK;
 }
 

@@ -17,6 +17,7 @@
 // frame).
 #include "common.hpp"
 #include "kernels.hpp"
+#include <algorithm>
 #include <type_traits>
 
 namespace kvev {
@@ -383,26 +384,40 @@ static hipError_t launch_decode_q(const AttnArgs &a, hipStream_t st)
     return hipGetLastError();
 }
 
+// Queries per workgroup.  A workgroup that serves one query is the shortest (four queries: the fold of 16 sums, four weights per
+// row), so queries that share rows only share a workgroup where there would be too many of them: one each up to half as many
+// workgroups as compute units, then pairs up to three quarters.  Unsplit launches only: the plan's runs, partials and tickets
+// are for groups of four.  Every query then reads the rows for itself, each XCD into an L2 of its own, which pays while the rows
+// of all workgroups stay there: 24 MiB, a little more for single queries that four would share and for pairs of short runs
+// (and for bf16 pairs where the rows of workgroups of four do not stay either).
+// Runs of more than 320 raw rows go to 8 or 16 waves: pairs there, in fp32 only of d = 64 and up to 160.
+// Four / two / one query a workgroup, us, 287 or 319 rows: d = 128 8 sequences x 4 queries 8.8 / 7.0 / 5.6, 32 x 4 8.8 / 7.1 / 5.6, 40 x
+// 4 8.9 / 6.7 / 7.1, 64 x 4 8.9 / 6.8 / 8.7, 96 x 4 8.9 / 7.4 / 16, 64 x 2 - / 7.0 / 5.6; d = 64 16 x 4 7.4 / - / 5.4, 32 x 4 7.4 / - / 5.1,
+// 64 x 4 7.5 / 5.9 / -, 64 x 2 - / 6.2 / 5.1; fp32, d = 128, 160 rows 32 x 4 7.6 / - / 5.4, 96 x 4 x 250 8.8 / 10.6 / -.  With kept
+// summaries: 287 + 256 rows, d = 128 16 x 4 14.2 / - / 9.3, 48 x 2 - / 11.0 / 11.8, 96 x 4 17.1 / 16.2 / -; 319 + 512 32 x 2 - / 15.6 /
+// 17.0, 48 x 2 - / 16.2 / 21.0, 16 x 4 19.6 / 15.6 / 14.8, 48 x 4 19.8 / 22.8 / -, 96 x 4 26.9 /
+// 24.1 / -, d = 64 64 x 2 - / 14.0 / 16.1, 48 x 8 16.9 / 21.6 / -; fp32, d = 128, 32 + 256 64 x 2 - / 9.0 / 11.8, 96 x 4 x 340 13.5 / 16.3 / -.
+// The choice may look at the kept capacity, which differs between the indexed and the compact form, up to 320 raw rows: there
+// all have 4 waves and add in the same order (fold4, fold8, fold16), so that the bits are those of any other choice.
+int decode_queries(const AttnArgs &a, size_t elem)
+{
+    const int64_t R = (int64_t)a.G * a.Tq, one = a.S * R, two = a.S * ((R + 1) / 2), units = a.S * ((R + 3) / 4);
+    const int64_t unit = (int64_t)a.rows_all * a.d * 2 * elem, cus = a.compute_units;
+    const int most = R >= 4 ? 4 : R >= 2 ? 2 : 1;
+    if (a.nsplit > 1) return most;
+    if (a.rows_per_split <= 320) {
+        if (one <= cus / 2 && one * unit <= (int64_t)(R >= 4 ? 26 : 24) << 20) return 1;
+        const bool fit = two * unit <= (int64_t)(a.rows_all <= 352 ? 32 : 24) << 20, neither = elem == 2 && units * unit > 28ll << 20;
+        return two <= cus * 3 / 4 && (fit || neither) ? std::min(most, 2) : most;
+    }
+    return two <= (elem == 2 ? cus * 3 / 4 : a.d == 64 ? cus * 5 / 8 : 0) ? std::min(most, 2) : most;
+}
+
 template <typename T, int D>
 static hipError_t launch_decode_t(const AttnArgs &a, hipStream_t st)
 {
-    const int R = a.G * a.Tq;
-    // A workgroup that serves one query is the shortest (four queries: the fold of 16 sums, four weights per row), so queries
-    // that share rows only share a workgroup where there would be too many of them: one each up to 128 workgroups, then pairs
-    // up to 192 (their rows come out of the caches after the first).  Unsplit launches only: the plan's runs, partials and
-    // tickets are for groups of four.  Four / two / one query, us, d = 128, 287 rows: 8 sequences x 4 heads 8.8 / 7.0 / 6.1, 32 x
-    // 4 9.0 / 7.1 / 6.2, 40 x 4 9.0 / 7.1 / 7.1, 64 x 4 9.0 / 7.2 / 8.7, 72 x 4 9.0 / 7.2 / 11.1, 128 x 4 9.1 / 9.8 / 16.7; 107
-    // rows 96 x 4 7.4 / 5.9 / 6.0; 32 x 8 9.1 / 7.4 / 8.8; two heads 64 x 2 - / 7.2 / 6.3, 128 x 2 - / 7.3 / 8.7; fp32, 160 rows 32
-    // x 4 8.5 / 6.9 / 6.5.  (Runs of more than 320 rows go to 8 or 16 waves: 64 x 2 x 616 rows - / 9.1 / 10.0, 64 x 4 x 516 11.8 /
-    // 9.3 / 14.1.)
-    if (a.nsplit == 1) {
-        const int64_t S = a.S;
-        if (R > 1 && S * R <= 128 && a.rows_per_split <= 320) return launch_decode_q<T, D, 1>(a, st);
-        if (R > 2 && S * ((R + 1) / 2) <= 192) return launch_decode_q<T, D, 2>(a, st);
-    }
-    if (R >= 4) return launch_decode_q<T, D, 4>(a, st);
-    if (R >= 2) return launch_decode_q<T, D, 2>(a, st);
-    return launch_decode_q<T, D, 1>(a, st);
+    const int nq = decode_queries(a, sizeof(T));
+    return nq == 4 ? launch_decode_q<T, D, 4>(a, st) : nq == 2 ? launch_decode_q<T, D, 2>(a, st) : launch_decode_q<T, D, 1>(a, st);
 }
 
 hipError_t launch_attn_decode(const AttnArgs &a, int dtype, hipStream_t st)

@@ -26,6 +26,7 @@ struct AttnArgs {
     int ring_first;       // compact form: the window buffer is a ring, its token t sits in row (ring_first + t) mod T_cap; else 0
     int gated;            // 1: kept summaries precede the raw rows
     int nsplit, rows_per_split;
+    int rows_all;         // raw rows and kept summaries that a sequence can have
     int compute_units;    // of the device the launch goes to
     int stream;           // 1: the launch reads more than the memory-side cache holds: single-query loads carry the non-temporal hint
     float scale_log2e;    // log2(e) / sqrt(d)
@@ -153,6 +154,7 @@ template <class F> hipError_t allow_lds(F *kernel, int bytes, std::atomic<uint64
 }
 
 hipError_t launch_attn_decode(const AttnArgs &a, int dtype, hipStream_t st);
+int decode_queries(const AttnArgs &a, size_t elem);                       // its queries per workgroup: 1, 2 or 4 (elem: bytes of an element)
 hipError_t launch_attn_decode_mfma(const AttnArgs &a, hipStream_t st);  // bf16, up to 4 queries per unit, unsplit: large launches
 hipError_t launch_attn_mq(const AttnArgs &a, hipStream_t st);           // bf16 MFMA, many queries
 hipError_t launch_select(const SelectArgs &a, hipStream_t st);

@@ -1,8 +1,11 @@
 """Decode attention (Eq. 1) whose queries share rows, around the sizes where a workgroup serves one, two or four of them: the
 whole chain, the compact form's bits and the causal mask against the oracle, as for the other grouped-query shapes."""
 import pytest
+import torch
 
+from paper_2509_21354_amd import binding as kb
 from tests import test_gqa_causal_gpu as base
+from tests.test_decode_plan import shape
 
 pytestmark = pytest.mark.gpu
 
@@ -23,3 +26,32 @@ CASES = [
 @pytest.mark.parametrize("cfg,causal", CASES, ids=[c.name for c, _ in CASES])
 def test_queries_that_share_rows(cfg, causal):
     base.test_chain_and_attention_with_grouped_heads_and_causal_frames(cfg, causal)
+
+
+@pytest.mark.parametrize("S,G,d,dtype,few,many", [
+    (48, 2, 128, kb.BF16, 1, 2), (32, 4, 128, kb.BF16, 1, 2), (96, 4, 64, kb.BF16, 2, 4), (64, 2, 64, kb.F32, 1, 2), (48, 4, 128, kb.F32, 2, 4)])
+def test_the_choice_changes_no_bit(S, G, d, dtype, few, many):
+    """The choice looks at the capacity for kept summaries, which an indexed call and a compact store need not have in common:
+    8 summaries kept of 8 and of 256, and in a store of 256 (Eq. 1)."""
+    sh, kept = shape(S, G, 287, 256, d, dtype), 8
+    assert (kb.kvev_debug_decode_queries(sh, 1, kept), kb.kvev_debug_decode_queries(sh, 1, 256)) == (few, many)
+    T, N, win0 = sh.T, sh.N_cap, sh.T - 287
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    dt = torch.float32 if dtype == kb.F32 else torch.bfloat16
+    Q, K, V, Kb, Vb = (torch.randn((1, 1) + s + (d,), device="cuda", generator=gen).to(dt) for s in ((S * G, 1), (S, T), (S, T), (S, N), (S, N)))
+    pick = torch.stack([torch.randperm(256, device="cuda", generator=gen)[:kept].sort().values for _ in range(S)]).int()
+    count = torch.full((1, 1, S), kept, dtype=torch.int32, device="cuda")
+    outs = []
+    for cap in (kept, 256):
+        idx = torch.zeros((1, 1, S, cap), dtype=torch.int32, device="cuda")
+        idx[0, 0, :, :kept] = pick
+        outs.append(torch.zeros_like(Q))
+        kb.kvev_gated_attention(sh, Q, 1, K, V, Kb, Vb, idx, count, cap, outs[-1])
+    store = [torch.zeros((1, 1, S, 256, d), dtype=dt, device="cuda") for _ in range(2)]
+    for dst, src in zip(store, (Kb, Vb)):
+        dst[0, 0, :, :kept] = src[0, 0].gather(1, pick.long()[..., None].expand(-1, -1, d))
+    wsh = kb.make_shape(L=1, B=1, H=S * G, d=d, T=287, T_cap=287, C=8, N_cap=256, W=287, d_sum=32, d_g=64, dtype=dtype, H_kv=S)
+    outs.append(torch.zeros_like(Q))
+    kb.kvev_compact_attention(wsh, Q, 1, K[..., win0:, :].contiguous(), V[..., win0:, :].contiguous(), *store, count, 256, outs[-1])
+    torch.cuda.synchronize()
+    assert torch.equal(outs[0], outs[1]) and torch.equal(outs[0], outs[2]) and float(outs[0].float().abs().max()) > 0
