@@ -897,8 +897,16 @@ static hipError_t launch_dg(const LstmArgs &a, hipStream_t st)
     hipError_t e = set_attributes_once<DG>();
     if (e != hipSuccess) return e;
     const bool single = (DG == 256 && a.fused) || (DG == 512 && a.split == 4);      // one kernel for both halves
+    // few sequences: shorter runs of steps per workgroup so that the launch still covers the chip
+    auto few = [&](int nb) { return (size_t)groups * ((nb + run_steps<DG>() - 1) / run_steps<DG>()) < 256; };
+    // Plain weights: W_hh is re-laid beside the first projection, which saves a launch, unless there is so much of it that the
+    // registers and LDS that its workgroups then have for nothing count: 32 layers of 16 sequences x 64 steps, d = 128, apart / beside,
+    // d_g = 128 82.6 / 85.6, 256 174 / 183 us; 8 of 64 x 64, 256 157.7 / 161.3; 32 of 16 x 1, 512 88.1 / 94.5; d = 64, 32 of 16 x 64,
+    // 128 77.5 / 73.2, 256 168.8 / 172.5; where projections are few 32 of 16 x 1, d_g = 256 40.6 / 35.1, 128 26.7 / 19.8.
+    const int nb0 = a.c1 - a.c0 < a.tb ? a.c1 - a.c0 : a.tb;
+    const bool beside = !single && (size_t)a.L * DG * DG * 8 <= (size_t)(few(nb0) ? 24 : a.d == 64 ? 4 : 2) << 20;
     if (!a.prepared) {
-        e = prepare_dg<DG>(a, st, single);
+        e = prepare_dg<DG>(a, st, !beside);
         if (e != hipSuccess) return e;
     }
     if constexpr (DG == 256) {
@@ -909,15 +917,15 @@ static hipError_t launch_dg(const LstmArgs &a, hipStream_t st)
     }
     for (int t0 = a.c0; t0 < a.c1; t0 += a.tb) {
         const int nb = a.c1 - t0 < a.tb ? a.c1 - t0 : a.tb;
-        // few sequences: shorter runs of steps per workgroup so that the launch still covers the chip, and, where that is
-        // 256 workgroups or less, the gate rows over four of them (whole gate call, d_g = 256: 512 sequences x 8 steps 35.2 -> 33.0
-        // us, 128 x 32 71.5 -> 69.1; d_g = 512 256 x 8 60.1 -> 52.8; up to 1024 workgroups 1024 x 16 would take 65.2 against 61.6)
-        const bool small = (size_t)groups * ((nb + run_steps<DG>() - 1) / run_steps<DG>()) < 256;
+        // Small launches of 256 workgroups or less: the gate rows over four of them (whole gate call, d_g = 256: 512 sequences x 8 steps
+        // 35.2 -> 33.0 us, 128 x 32 71.5 -> 69.1; d_g = 512 256 x 8 60.1 -> 52.8; up to 1024 workgroups 1024 x 16 would take 65.2
+        // against 61.6)
+        const bool small = few(nb);
         const int tt = small ? 2 : run_steps<DG>();
         const unsigned ny_proj = (unsigned)((nb + tt - 1) / tt);
         const bool spread = small && (size_t)groups * ny_proj <= 256;
         unsigned pack_rows = 0;
-        if (!a.prepared && t0 == a.c0) {         // W_hh: about one 16-byte fragment per thread, 4096 workgroups at most
+        if (!a.prepared && beside && t0 == a.c0) {         // W_hh: about one 16-byte fragment per thread, 4096 workgroups at most
             const size_t want = std::min<size_t>(((size_t)a.L * 4 * DG * DG / 8 + proj_threads<DG>() - 1) / proj_threads<DG>(), 4096);
             const unsigned per_row = groups * (spread ? 4 : 1);
             pack_rows = (unsigned)((want + per_row - 1) / per_row);

@@ -118,3 +118,27 @@ def test_projections_of_many_steps():
         outs.append((h, c, util, gate))
     assert all(torch.equal(x, y) for x, y in zip(*outs))
     assert 0 < float(outs[0][2].std())
+
+
+@pytest.mark.parametrize("L,BH,d,d_g,N", [
+    (4, 16, 128, 256, 8), (9, 64, 128, 256, 64), (9, 64, 64, 256, 64), (32, 16, 128, 128, 64), (32, 16, 64, 128, 64), (12, 4, 64, 512, 2), (13, 4, 128, 512, 2)])
+def test_plain_and_prepared_weights(L, BH, d, d_g, N):
+    """W_hh re-laid beside the first projection, in a launch of its own and by kvev_lstm_prepare: the same bits."""
+    cfg = base._cfg(412, "bf16", d=d, T=N * 8, C=8, d_g=d_g, L=L, B=1, H=BH)
+    gen = torch.Generator(device="cuda").manual_seed(1)
+    Kb, Vb = (torch.randn((L, 1, BH, N, d), device="cuda", generator=gen).mul_(0.25).bfloat16() for _ in range(2))
+    sh, w = kb.make_shape(cfg, N_cap=N), kb.lstm_weights(base.dev(synth.make_weights(cfg, "cpu")))
+    packed = kb.alloc_workspace(kb.workspace_bytes(kb.OP_LSTM_PREPARE, sh, 0))
+    kb.kvev_lstm_prepare(sh, w, packed)
+    outs = []
+    for prepared in (False, True):
+        ws = kb.alloc_workspace(kb.workspace_bytes(kb.OP_LSTM_GATE_PREPARED if prepared else kb.OP_LSTM_GATE, sh, N))
+        h, c = (torch.zeros((L, 1, BH, d_g), device="cuda") for _ in range(2))
+        util, gate = (torch.zeros((L, 1, BH, N), device="cuda") for _ in range(2))
+        if prepared:
+            kb.kvev_lstm_gate_prepared(sh, Kb, Vb, w, packed, 0, N, h, c, util, gate, ws)
+        else:
+            kb.kvev_lstm_gate(sh, Kb, Vb, w, 0, N, h, c, util, gate, ws)
+        torch.cuda.synchronize()
+        outs.append((h, c, util, gate))
+    assert all(torch.equal(x, y) for x, y in zip(*outs)) and float(outs[0][2].std()) > 0
