@@ -88,7 +88,7 @@ __global__ __launch_bounds__(4 * DG / P) void lstm_rec_oct_kernel(LstmArgs a, in
     const float inv_scale = ldexpf(1.f, -whh_scale_exp(whh_layer_max(a.whh_max_bits, l)));
     if (tid == 0) s_fail = 0;
 
-    // ---- all weights of the wave: 8 k-steps x 4 gates, own units first ----
+    // ---- all weights of the wave: kKS k-steps x 4 gates, own units first ----
     const uint32_t lane16 = lane * 16;
     const __amdgpu_buffer_rsrc_t w_rsrc = make_rsrc(
         reinterpret_cast<const unsigned char *>(a.whh_packed + (((size_t)l * G::NW + tile / G::UT) * G::ITEMS + (tile % G::UT) * kKS) * 4 * 64),
@@ -547,11 +547,18 @@ __global__ __launch_bounds__(256) void lstm_rec_few_kernel(LstmArgs a, int t0, i
                 }
         };
         products(h_rd, std::integral_constant<int, 0>{}, std::integral_constant<int, kKH>{});
-        if (tt > 0) ask(nxt, look);
-        if (DG == 256) {         // asked again, later: see above
+        u32x4_t early[kMine];
+        if (tt > 0) ask(nxt, DG == 256 ? early : look);
+        if (DG == 256) {         // asked again, later, and that answer is taken: see above
             __builtin_amdgcn_sched_barrier(0);
             __builtin_amdgcn_s_sleep(8);
-            if (tt > 0) ask(nxt, look);
+            if (tt > 0) {
+                ask(nxt, look);
+                // (the first answer is thrown away, but it is asked for: without a use the request would be the compiler's to drop)
+#pragma unroll
+                for (int m = 0; m < kMine; ++m)
+                    if (partner_of(m) < P - 1) asm volatile("" ::"v"(early[m]));
+            }
         }
         __builtin_amdgcn_sched_barrier(0);
         if (tt > 1 && member == 0 && wave == kNW - 1) write_util(tt - 2);

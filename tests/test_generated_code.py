@@ -170,3 +170,15 @@ def test_store_data_is_read_before_it_is_overwritten(tmp_path):
     with concurrent.futures.ThreadPoolExecutor(max_workers=min(8, len(names))) as ex:
         found = {n: f for asm in ex.map(lambda n: assembly(n, tmp_path), names) for n, lines in kernels(asm).items() if (f := early_overwrites(lines))}
     assert not found, found
+
+
+def test_the_small_gate_asks_early_and_again(tmp_path):
+    """lstm_rec_few_kernel at 256 units: a look at the partners' slots that is thrown away, a pause, the look that is taken, in both
+    copies of the step (the compiler may drop a request that it finds no use for; without it a step takes 7 % longer)."""
+    lines = next(ls for n, ls in kernels(assembly("lstm_oct.hip", tmp_path)).items() if "lstm_rec_few_kernelILi256" in n)
+    look = re.compile(r"buffer_load_dwordx4 (v\[\d+:\d+\]),.* sc1")
+    at = [i for i, s in enumerate(lines) if s.startswith("s_sleep 8")]
+    assert len(at) == 2
+    for i in at:
+        before, after = (next(m.group(1) for s in part if (m := look.match(s))) for part in (lines[i - 1:i - 16:-1], lines[i + 1:i + 16]))
+        assert before != after
