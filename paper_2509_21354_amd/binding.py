@@ -198,7 +198,7 @@ def kvev_debug_lstm_plan(shape: Shape, prepared: bool, steps: int, ws_bytes: int
 
 def kvev_debug_lstm_form(shape: Shape, steps: int) -> str:
     form = ctypes.c_int()
-    _check(lib().kvev_debug_lstm_form(ctypes.byref(shape), steps, ctypes.byref(form)), "kvev_debug_lstm_form", "kvev_debug_pool_form")
+    _check(lib().kvev_debug_lstm_form(ctypes.byref(shape), steps, ctypes.byref(form)), "kvev_debug_lstm_form")
     return ("chain", "one", "four", "kept")[form.value]
 
 
