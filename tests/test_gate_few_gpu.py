@@ -14,7 +14,7 @@ pytestmark = pytest.mark.gpu
 
 CASES = [
     base._cfg(401, "bf16", d=128, T=17 * 32, C=32, d_g=512, L=1, B=1, H=1),      # one sequence
-    base._cfg(402, "bf16", d=64, T=16 * 32, C=32, d_g=512, L=3, B=1, H=13),      # a ragged second group of 8 in every layer
+    base._cfg(402, "bf16", d=64, T=16 * 32, C=32, d_g=512, L=3, B=1, H=13),      # 12 groups of 4, the last of a layer with one sequence
     base._cfg(403, "bf16", d=128, T=19 * 32, C=32, d_g=512, L=4, B=2, H=32),     # 32 groups of 8: a workgroup on every compute unit
     base._cfg(404, "bf16", d=64, T=16 * 32, C=32, d_g=512, L=11, B=1, H=19),     # two groups in turn; three a layer, the last ragged, the fourth empty
     base._cfg(405, "bf16", d=128, T=18 * 32, C=32, d_g=512, L=32, B=1, H=9),     # two in turn in every layer, the second with one sequence
@@ -55,6 +55,15 @@ def test_few_sequences(cfg):
     for out in (outs[0], outs[3]):
         for got, r, tol in zip(out, ref, (1, 2, 1, 1)):
             assert np.abs(got.cpu().numpy() - r).max() <= tol * base.SCORE_TOL
+
+
+def test_cases_reach_the_forms_they_claim():
+    assert [base.gate_form(c) for c in CASES] == [(8, 4), (8, 4), (8, 8), (8, 16), (8, 16), (8, 4), (8, 8), (4, 4), (4, 8), (4, 4)]
+
+
+@pytest.mark.parametrize("cfg", [CASES[1], CASES[2], CASES[3], CASES[8], CASES[9]], ids=lambda c: c.name)
+def test_nan_stays_in_its_sequence(cfg):
+    base.test_lstm_gate_nan_stays_in_its_sequence(cfg, 0)
 
 
 @pytest.mark.parametrize("cfg", [CASES[1], CASES[2], CASES[3], CASES[9]], ids=lambda c: c.name)

@@ -738,19 +738,21 @@ def test_chunk_pool(cfg, mode):
 
 def gate_form(cfg):
     """Which workgroups share a group of sequences in the gate: (members, sequences per group), by the rule of the
-    library's dispatch at this device's compute units.  (1, ..) stands for every form on one workgroup.  The fp32-arithmetic
-    gate: "chain" (up to 64 units, few sequences), "one" or "four" sequences per workgroup."""
+    library's dispatch at this device's compute units for a cache of the case's chunks.  (1, ..) stands for every form on
+    one workgroup.  The fp32-arithmetic gate: as the library names its forms."""
     cus = torch.cuda.get_device_properties(0).multi_processor_count
     bh = cfg.B * cfg.kv_heads
     if cfg.dtype == "f32" or cfg.d_g not in (64, 128, 256, 512):
-        return "chain" if cfg.d_g <= 64 and cfg.L * bh <= cus else "four" if cfg.L * ((bh + 3) // 4) >= cus else "one"
+        return kb.kvev_debug_lstm_form(kb.make_shape(cfg), cfg.T // cfg.C)
     if cfg.d_g <= 128:
         return 1, 8
-    groups8, groups16 = cfg.L * ((bh + 7) // 8), cfg.L * ((bh + 15) // 16)
+    groups4, groups8, groups16 = (cfg.L * ((bh + n - 1) // n) for n in (4, 8, 16))
+    if cfg.d_g == 512 and cfg.T // cfg.C >= 16 and 8 * groups16 <= cus:
+        return 8, next((n for n, groups in ((4, groups4), (8, groups8)) if 8 * groups <= cus), 16)
     if cfg.d_g == 512 and bh > 16:
         return 4, 32
     if cfg.d_g == 256 and 4 * groups8 <= cus:
-        return 4, 8
+        return 4, 4 if 4 * groups4 <= cus else 8
     if cfg.d_g == 256 and 2 * groups8 <= cus:
         return 2, 8
     return (2, 16) if cfg.d_g in (256, 512) and 2 * groups16 <= cus else (1, 16)
@@ -762,13 +764,13 @@ LSTM_CASES = [
     _cfg(143, "bf16", d=128, T=1280, C=32, d_g=256, L=2, B=1, H=5),      # 5 sequences per layer: ragged tile
     _cfg(144, "bf16", d=64, T=640, C=32, d_g=64, L=1, B=3, H=7),
     _cfg(145, "bf16", d=128, T=320, C=32, d_g=40),                        # d_g the MFMA tiling does not take
-    _cfg(146, "bf16", d=128, T=768, C=32, d_g=512, L=1, B=1, H=3),        # widest gate: unit tiles one after the other
+    _cfg(146, "bf16", d=128, T=768, C=32, d_g=512, L=1, B=1, H=3),        # widest gate, eight workgroups per 4 sequences
     _cfg(147, "bf16", d=64, T=576, C=16, d_g=128, L=2, B=2, H=9),         # W_hh fully resident on chip
-    _cfg(148, "bf16", d=128, T=800, C=32, d_g=256, L=1, B=2, H=24),       # 3 full groups of 16: six of 8, each on four workgroups
+    _cfg(148, "bf16", d=128, T=800, C=32, d_g=256, L=1, B=2, H=24),       # 12 groups of 4, each on four workgroups
     _cfg(149, "bf16", d=64, T=192, C=32, d_g=256, L=8, B=4, H=64),        # 128 groups of 16: the largest paired launch (a workgroup per compute unit)
     _cfg(150, "bf16", d=64, T=192, C=32, d_g=256, L=26, B=5, H=16),       # 130 groups: one workgroup per group again
     _cfg(152, "bf16", d=128, T=288, C=32, d_g=512, L=2, B=2, H=12),       # widest gate, 24 sequences per layer: four workgroups per 32 sequences, the second block of 16 half empty
-    _cfg(153, "bf16", d=128, T=1024, C=32, d_g=512, L=1, B=2, H=16),      # one full group of 32 on four workgroups, 32 steps
+    _cfg(153, "bf16", d=128, T=1024, C=32, d_g=512, L=1, B=2, H=16),      # 8 groups of 4 on eight workgroups, 32 steps
     _cfg(154, "bf16", d=64, T=256, C=32, d_g=512, L=2, B=5, H=16),        # 80 sequences per layer: the third group of 32 has one block of 16 only
     _cfg(155, "bf16", d=128, T=160, C=32, d_g=512, L=3, B=1, H=16),       # 16 sequences per layer: stays on pairs of workgroups
     # the fp32-arithmetic kernel: rows of W_hh in registers (up to 64, up to 128 wide) or streamed, widths that are no
@@ -825,7 +827,8 @@ def test_lstm_gate(cfg):
 
 NAN_CASES = [
     (_cfg(157, "bf16", d=128, T=256, C=32, d_g=512, L=1, B=1, H=40), 0),     # four workgroups per 32 sequences: h travels with a flag in a bit of its hi terms
-    (_cfg(158, "bf16", d=64, T=256, C=32, d_g=256, L=1, B=1, H=20), 0),      # four workgroups per 8 sequences: a flag in a bit of every first term of four
+    (_cfg(158, "bf16", d=64, T=256, C=32, d_g=256, L=1, B=1, H=20), 0),      # four workgroups per 4 sequences: a flag in a bit of every first term
+    (_cfg(279, "bf16", d=64, T=256, C=32, d_g=256, L=22, B=1, H=9), 0),      # four workgroups per 8 sequences: in a bit of every first term of four
     (_cfg(262, "bf16", d=64, T=160, C=32, d_g=256, L=13, B=1, H=37), 0),     # two workgroups per 8 sequences
     (_cfg(263, "bf16", d=64, T=160, C=32, d_g=256, L=13, B=5, H=16), 0),     # pairs of workgroups at d_g = 256
     (_cfg(159, "bf16", d=128, T=256, C=32, d_g=256, L=1, B=1, H=40), 1),     # the single-kernel form
@@ -961,7 +964,8 @@ def test_lstm_gate_single_kernel_form(cfg):
 
 
 OCT_CASES = [
-    _cfg(171, "bf16", d=128, T=23 * 32, C=32, d_g=256, L=3, B=1, H=13),     # four workgroups per 8 sequences, 13 per layer: ragged
+    _cfg(171, "bf16", d=128, T=23 * 32, C=32, d_g=256, L=3, B=1, H=13),     # four workgroups per 4 sequences, 13 per layer: ragged
+    _cfg(370, "bf16", d=128, T=23 * 32, C=32, d_g=256, L=22, B=1, H=9),     # four workgroups per 8, the second group of a layer with one
     _cfg(172, "bf16", d=64, T=9 * 32, C=32, d_g=256, L=13, B=1, H=37),      # 65 groups: two workgroups per 8 sequences
     _cfg(173, "bf16", d=128, T=1 * 32, C=32, d_g=256, L=1, B=1, H=1),       # one sequence, one step
     _cfg(174, "bf16", d=128, T=2 * 32, C=32, d_g=256, L=2, B=2, H=8),       # two steps: every slot used once
@@ -971,7 +975,7 @@ OCT_CASES = [
 
 @pytest.mark.parametrize("cfg", OCT_CASES, ids=lambda c: c.name)
 def test_lstm_gate_eight_sequences_per_group(cfg, *more):
-    """The forms of the gate that launches of few sequences take at d_g = 256: groups of 8 sequences on two or four
+    """The forms of the gate that launches of few sequences take at d_g = 256: groups of 4 on four, of 8 on four or two
     workgroups, then groups of 16 on two.  One call, then the same range cut into calls that carry the state (with scratch for two steps per launch, so that the
     exchange slots start anew inside a call): the same bits."""
     N = cfg.T // cfg.C
@@ -1115,7 +1119,8 @@ def test_lstm_gate_replaces_h_only_after_hearing_from_all_members(cfg, form):
 
 
 WAIT_CASES = [
-    _cfg(151, "bf16", d=64, T=320, C=32, d_g=256, L=1, B=1, H=5),         # four workgroups per 8 sequences
+    _cfg(151, "bf16", d=64, T=320, C=32, d_g=256, L=1, B=1, H=5),         # four workgroups per 4 sequences
+    _cfg(371, "bf16", d=64, T=128, C=32, d_g=256, L=22, B=1, H=9),        # four workgroups per 8
     _cfg(265, "bf16", d=64, T=128, C=32, d_g=256, L=13, B=1, H=37),       # two workgroups per 8 sequences
     _cfg(266, "bf16", d=128, T=128, C=32, d_g=256, L=13, B=5, H=15),      # pairs of workgroups
     _cfg(267, "bf16", d=64, T=128, C=32, d_g=512, L=2, B=1, H=16),        # pairs at d_g = 512
@@ -1171,7 +1176,8 @@ def test_lstm_pair_wait_expires_cleanly(cfg):
 
 
 PREPARED_CASES = [
-    (_cfg(191, "bf16", d=128, T=384, C=32, d_g=256, L=1, B=1, H=20), 0),     # four workgroups per 8 sequences
+    (_cfg(191, "bf16", d=128, T=384, C=32, d_g=256, L=1, B=1, H=20), 0),     # four workgroups per 4 sequences
+    (_cfg(372, "bf16", d=128, T=224, C=32, d_g=256, L=22, B=1, H=9), 0),    # four workgroups per 8
     (_cfg(268, "bf16", d=64, T=224, C=32, d_g=256, L=13, B=1, H=37), 0),     # two workgroups per 8 sequences
     (_cfg(269, "bf16", d=128, T=224, C=32, d_g=256, L=13, B=5, H=16), 0),    # pairs of workgroups
     (_cfg(192, "bf16", d=64, T=256, C=32, d_g=256, L=26, B=5, H=16), 0),     # one workgroup per group
@@ -1317,8 +1323,8 @@ def test_sigmoids_keep_their_relative_precision(cfg, which):
 
 
 def test_gate_cases_reach_the_forms_they_claim():
-    claims = {148: (4, 8), 149: (2, 16), 150: (1, 16), 151: (4, 8), 152: (4, 32), 155: (2, 16), 156: (4, 32), 157: (4, 32), 158: (4, 8),
-              160: (2, 16), 171: (4, 8), 172: (2, 8), 191: (4, 8), 192: (1, 16), 195: (4, 32), 262: (2, 8), 263: (2, 16), 264: (2, 16),
+    claims = {148: (4, 4), 149: (2, 16), 150: (1, 16), 151: (4, 4), 152: (4, 32), 155: (2, 16), 156: (4, 32), 157: (4, 32), 158: (4, 4), 279: (4, 8),
+              160: (2, 16), 171: (4, 4), 172: (2, 8), 191: (4, 4), 370: (4, 8), 371: (4, 8), 372: (4, 8), 146: (8, 4), 153: (8, 4), 192: (1, 16), 195: (4, 32), 262: (2, 8), 263: (2, 16), 264: (2, 16),
               265: (2, 8), 266: (2, 16), 267: (2, 16), 268: (2, 8), 269: (2, 16), 141: "chain", 142: "chain", 144: (1, 8), 147: (1, 8),
               161: "chain", 162: "one", 163: "one", 164: "four", 165: "four", 166: "four", 194: (1, 8), 196: "chain", 331: (1, 8), 332: (1, 8),
               333: "chain", 334: "chain", 308: "chain", 309: "one", 310: "chain"}
