@@ -552,18 +552,18 @@ __global__ __launch_bounds__(256) void lstm_rec_few_kernel(LstmArgs a, int t0, i
         if (DG == 256) {         // asked again, later, and that answer is taken: see above
             __builtin_amdgcn_sched_barrier(0);
             __builtin_amdgcn_s_sleep(8);
-            if (tt > 0) {
-                ask(nxt, look);
-                // (the first answer is thrown away, but it is asked for: without a use the request would be the compiler's to drop)
-#pragma unroll
-                for (int m = 0; m < kMine; ++m)
-                    if (partner_of(m) < P - 1) asm volatile("" ::"v"(early[m]));
-            }
+            if (tt > 0) ask(nxt, look);
         }
         __builtin_amdgcn_sched_barrier(0);
         if (tt > 1 && member == 0 && wave == kNW - 1) write_util(tt - 2);
         float share = 0.f;
-        if (tt > 0) share = receive(tt, look);
+        if (tt > 0) {
+            share = receive(tt, look);
+            if (DG == 256) {     // (the first answer is thrown away, but asked for: without a use the request would be the compiler's to drop)
+#pragma unroll
+                for (int m = 0; m < kMine; ++m) asm volatile("" ::"v"(early[m]));
+            }
+        }
         lds_barrier();
         if (s_fail) return false;
         products(p_rd, std::integral_constant<int, kKH>{}, std::integral_constant<int, kKP>{});
