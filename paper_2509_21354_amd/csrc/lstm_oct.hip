@@ -10,7 +10,7 @@
 //     same sums share the four units between them.  Half the matrix work, half the nonlinearities and half the exchange
 //     per group, on compute units that were idle;
 //   * P = 4 workgroups of 4 waves where the launch leaves room for them, else 2 of 8 (d_g = 512: 8 of 4): a wave owns 16
-//     units either way;
+//     units either way (smaller launches yet take groups of 4 sequences: lstm_rec_few_kernel, below);
 //   * 8 bytes per lane carry 4 units of one column: |h| <= 1 leaves bit 14 of an fp16 term free (of hi and of lo), and the
 //     first term of every aligned 8-byte word, which is written and read as one, carries a flag there that flips from one
 //     use of a slot to the next.  Two slots by step parity, cleared before the launch: a slot is rewritten two steps
@@ -24,8 +24,9 @@
 // cell, publish, own h to LDS | barrier.  Bounded waits, status word and the layout of weights and projections: as the
 // paired kernel.
 // Measured (the whole gate call, weights prepared): 32 sequences x 128 steps 304 us on pairs per 16 sequences, 233 us in groups of 8 (P =
-// 4; 175 to 205 in lstm_rec_few_kernel's groups of 4, below; about 0.95 us of a step are its own work, the rest is the exchange), 248 us with 16 bytes per lane, a stamp of the
-// step beside every two units, in the flag's place; 512 x 64 183, 145 and 156 us; 1024 x 64 (P = 2) 245, 218 and 219 us.
+// 4; 175 to 205 in groups of 4; about 0.95 us of a step are its own work, the rest is the exchange), 248 us with 16 bytes per
+// lane, a stamp of the step beside every two units, in the flag's place; 512 x 64 183, 145 and 156 us; 1024 x 64 (P = 2) 245, 218
+// and 219 us.
 // Members on one XCD that exchange by plain stores through its L2 took 185 us at the first shape, but publications of that
 // kind were lost under cache pressure (seen in lstm_quad.hip; cause not shown), so all stores write through.
 // d_g = 512: W_hh is 2 MiB as fp16, and what bounds the forms on two or four compute units is its stream out of L2 in every
@@ -33,8 +34,8 @@
 // 4 waves has 512 registers per lane, and matrix instructions take them from the accumulation half.  Where 8 * groups of 8 are
 // more than the compute units, a workgroup takes two groups in turn (SUB = 2): the h of one travels while the other is
 // computed, so nothing is waited for, and each needs one barrier instead of two.  Measured (whole gate call, weights
-// prepared): 32 sequences x 128 steps 1049 -> 325 us, 144 (16 a layer) x 130 1364 -> 414, 256 x 64 564 -> 209, 512 x 64
-// 570 -> 341, 512 (16 a layer) x 64 910 -> 387, 32 x 8 85 -> 45 us.  At d_g = 256 two groups in turn on two workgroups are slower
+// prepared): 32 sequences x 128 steps 1049 -> 325 us (291 in groups of 4), 144 (16 a layer) x 130 1364 -> 414, 256 x 64 564 -> 208,
+// 512 x 64 570 -> 361, 512 (16 a layer) x 64 910 -> 392, 32 x 8 85 -> 45 us.  At d_g = 256 two groups in turn on two workgroups are slower
 // than lstm_rec_pair_kernel (2048 x 128 769 against 690 us: vector work, not the exchange, bounds it there).
 #include "common.hpp"
 #include "kernels.hpp"
